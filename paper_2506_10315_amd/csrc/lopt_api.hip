@@ -288,7 +288,7 @@ void build_plan(const lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d, Plan* 
     T.padN = pad4(N); T.padm = pad4(m); T.padn = pad4(nn);
     T.padH = velo ? pad4(ctx->cfg.lstm_hidden) : 0;
     T.ndim = d[i].ndim;
-    T.vec = (nn % 4 == 0) ? 1 : 0;
+    T.vec = nn % 32 == 0 ? 2 : nn % 4 == 0 ? 1 : 0;
     const int units = (m + kRowUnit - 1) / kRowUnit;
     const int q = (units + kMaxRowTiles - 1) / kMaxRowTiles;
     T.TR = kRowUnit * (q < 1 ? 1 : q) / shrink;   // a multiple of 8: every wavefront of a tile owns whole rows

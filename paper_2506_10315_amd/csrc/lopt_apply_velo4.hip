@@ -10,13 +10,6 @@
 #include "lopt_internal.h"
 #include "lopt_device.h"
 
-#ifndef LOPT_V4_STORE
-#define LOPT_V4_STORE store4s
-#endif
-#ifndef LOPT_V4_STATE_STORE
-#define LOPT_V4_STATE_STORE store4s
-#endif
-
 namespace lopt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -36,7 +29,21 @@ __device__ __forceinline__ float relu1(float x) {
 
 // UPDATE_STATE: the statistics pass left M_1..3 and V as they were; this pass forms the new values (the statistics
 // pass's operations, in its order: the same bits), builds the features from them and writes them back.
-template <bool VEC, bool RAW_RSQ, bool UPDATE_STATE>
+// NT: nontemporal accesses, for rows on the 128-byte grid (each line is touched by one wavefront only). Rows off the grid
+// share their first and last line with the neighbouring tiles, which nontemporal accesses fetch and write twice: there
+// ordinary ones are faster (18 matrices of 2732 columns: 0.587 -> 0.496 ms; on the grid, ViT-B/16 shapes, they cost the
+// next step's statistics pass more than this pass gains).
+template <bool NT>
+__device__ __forceinline__ float4 load4x(const float* __restrict__ row, int col, int n) {
+  return NT ? load4s<true>(row, col, n) : load4<true>(row, col, n);
+}
+template <bool NT>
+__device__ __forceinline__ void store4x(float* __restrict__ row, int col, int n, float4 v) {
+  if (NT) store4s<true>(row, col, n, v);
+  else store4<true>(row, col, n, v);
+}
+
+template <bool NT, bool RAW_RSQ, bool UPDATE_STATE>
 __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
                                                  const StepArgs& A) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -69,8 +76,8 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
     const float* cst = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      rc[k] = load4<VEC>(ws + T.oRC + (size_t)k * T.padn, col, n);
-      cc[k] = load4<VEC>(cst + (size_t)k * T.padn, col, n);
+      rc[k] = load4<true>(ws + T.oRC + (size_t)k * T.padn, col, n);
+      cc[k] = load4<true>(cst + (size_t)k * T.padn, col, n);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -97,12 +104,12 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
 
   for (int r = r0 + wave; r < r1; r += 4) {
     const size_t ro = (size_t)r * n;
-    const float4 g4 = load4s<VEC>(T.g + ro, col, n);
-    const float4 p4 = load4s<VEC>(T.p + ro, col, n);
-    const float4 m1 = load4s<VEC>(M1 + ro, col, n);
-    const float4 m2 = load4s<VEC>(M2 + ro, col, n);
-    const float4 m3 = load4s<VEC>(M3 + ro, col, n);
-    const float4 v4 = load4s<VEC>(Vp + ro, col, n);
+    const float4 g4 = load4x<NT>(T.g + ro, col, n);
+    const float4 p4 = load4x<NT>(T.p + ro, col, n);
+    const float4 m1 = load4x<NT>(M1 + ro, col, n);
+    const float4 m2 = load4x<NT>(M2 + ro, col, n);
+    const float4 m3 = load4x<NT>(M3 + ro, col, n);
+    const float4 v4 = load4x<NT>(Vp + ro, col, n);
     float rr[3], rv[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -145,10 +152,10 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
       h[e] = rowv + colv[e];
     }
     if (UPDATE_STATE) {   // stored while the values are live as features anyway
-      LOPT_V4_STATE_STORE<VEC>(M1 + ro, col, n, make_float4(n1[0], n1[1], n1[2], n1[3]));
-      LOPT_V4_STATE_STORE<VEC>(M2 + ro, col, n, make_float4(n2[0], n2[1], n2[2], n2[3]));
-      LOPT_V4_STATE_STORE<VEC>(M3 + ro, col, n, make_float4(n3[0], n3[1], n3[2], n3[3]));
-      LOPT_V4_STATE_STORE<VEC>(Vp + ro, col, n, make_float4(nv[0], nv[1], nv[2], nv[3]));
+      store4x<NT>(M1 + ro, col, n, make_float4(n1[0], n1[1], n1[2], n1[3]));
+      store4x<NT>(M2 + ro, col, n, make_float4(n2[0], n2[1], n2[2], n2[3]));
+      store4x<NT>(M3 + ro, col, n, make_float4(n3[0], n3[1], n3[2], n3[3]));
+      store4x<NT>(Vp + ro, col, n, make_float4(nv[0], nv[1], nv[2], nv[3]));
     }
     // layer 1: the four elements of the lane are four independent accumulation chains
 #pragma unroll
@@ -179,7 +186,155 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
       const float p = get(p4, e);
       pn[e] = p - lr * (delta + wd * p);
     }
-    LOPT_V4_STORE<VEC>(T.p + ro, col, n, make_float4(pn[0], pn[1], pn[2], pn[3]));
+    store4x<NT>(T.p + ro, col, n, make_float4(pn[0], pn[1], pn[2], pn[3]));
+  }
+}
+
+// Rows that are not 16-byte aligned (n % 4 != 0). A lane owns ONE column and takes four rows of it per trip (the four
+// elements of the MFMA chains are rows instead of columns), so every access is a coalesced dword of a 256-byte row segment
+// and the column factors are one set per lane. The wavefronts of the tile sit on adjacent 64-column segments; where the
+// tile is narrower than three segments they share out its rows as well. The float4 form with four predicated dwords per
+// lane that this replaces touched every cache line four times: 18 tensors of 54 M elements, 2731 columns, 1.82 -> 0.52 ms.
+// Ordinary accesses, not nontemporal ones (0.83 ms): neighbouring segments share their boundary lines.
+template <bool RAW_RSQ, bool UPDATE_STATE>
+__device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
+                                                      const StepArgs& A) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i4 = lane & 3;
+  const int n = T.n, m = T.m;
+  const int c0 = tile.tj * kTileCols;
+  const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
+  const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
+  const int seg = wave / rsplit;
+  if (seg >= nseg) return;
+  const int col = c0 + seg * kWave + lane;
+  const bool col_ok = col < n;
+  const unsigned cc = (unsigned)(col_ok ? col : n - 1);   // lanes past the end compute on the last column and store nothing
+  const float* __restrict__ prep = ws + T.oPrep;
+  const float* __restrict__ W2 = prep + (kVF + 1) * kVH;
+  const float* __restrict__ B2 = W2 + kVH * kVH;
+  const float* __restrict__ W3 = B2 + kVH;
+  const float* __restrict__ B3 = W3 + 2 * kVH;
+  float a1[kVE], a2[kVH], a3[kVH];
+#pragma unroll
+  for (int k = 0; k < kVE; ++k) a1[k] = prep[velo_elem_feat(k) * kVH + i4];
+#pragma unroll
+  for (int k = 0; k < kVH; ++k) {
+    a2[k] = W2[k * kVH + i4];
+    a3[k] = i4 < 2 ? W3[2 * k + i4] : 0.f;
+  }
+  const f32x4 c2 = {B2[0], B2[1], B2[2], B2[3]};
+  const f32x4 c3 = {B3[0], B3[1], 0.f, 0.f};
+  float rc[3];
+  f32x4 colv;
+  {
+    float cv[3];
+    const float* cst = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      rc[k] = ws[T.oRC + (size_t)k * T.padn + cc];
+      cv[k] = cst[(size_t)k * T.padn + cc];
+    }
+#pragma unroll
+    for (int u = 0; u < kVH; ++u) {
+      float a = 0.f;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        a += cv[k] * prep[velo_col_feat(k) * kVH + u];
+        a += rc[k] * prep[velo_col_feat(3 + k) * kVH + u];
+      }
+      colv[u] = a;
+    }
+  }
+  const size_t pN = T.padN;
+  const float* rst = T.st + 4 * pN;
+  const float eps = A.eps_acc, lr = A.lr, wd = A.wd;
+  const float bm1 = A.mom_decay[0], bm2 = A.mom_decay[1], bm3 = A.mom_decay[2], bv = A.rms_decay;
+  const float am1 = 1.0f - bm1, am2 = 1.0f - bm2, am3 = 1.0f - bm3, av = 1.0f - bv;
+  const int r1 = min(tile.ti * T.TR + T.TR, m);
+  for (int r = tile.ti * T.TR + 4 * (wave % rsplit); r < r1; r += 4 * rsplit) {
+    float e_in[4][6];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {   // rows past the tile read its last row and store nothing
+      const size_t ro = (size_t)min(r + e, r1 - 1) * n;
+      e_in[e][0] = T.g[ro + cc];
+      e_in[e][1] = T.p[ro + cc];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) e_in[e][2 + k] = T.st[k * pN + ro + cc];
+    }
+    float x[4][kVE];
+    f32x4 h[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = min(r + e, r1 - 1);
+      const size_t ro = (size_t)row * n;
+      float rr[3], rv[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        rr[k] = ws[T.oRR + (size_t)k * T.padm + row];
+        rv[k] = rst[(size_t)k * T.padm + row];
+      }
+      f32x4 rowv;   // bias + row-constant features (wave-uniform)
+#pragma unroll
+      for (int u = 0; u < kVH; ++u) {
+        float a = prep[kVF * kVH + u];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          a += rv[k] * prep[velo_row_feat(k) * kVH + u];
+          a += rr[k] * prep[velo_row_feat(3 + k) * kVH + u];
+        }
+        rowv[u] = a;
+      }
+      const float g = e_in[e][0];
+      float q1 = e_in[e][2], q2 = e_in[e][3], q3 = e_in[e][4], v = e_in[e][5];
+      if (UPDATE_STATE) {
+        q1 = __builtin_fmaf(bm1, q1, am1 * g);
+        q2 = __builtin_fmaf(bm2, q2, am2 * g);
+        q3 = __builtin_fmaf(bm3, q3, am3 * g);
+        v = __builtin_fmaf(bv, v, av * (g * g));
+        if (r + e < r1 && col_ok) {
+          T.st[ro + cc] = q1;
+          T.st[pN + ro + cc] = q2;
+          T.st[2 * pN + ro + cc] = q3;
+          T.st[3 * pN + ro + cc] = v;
+        }
+      }
+      const float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(v + eps) : rsqrtf(v + eps);
+      const float f0 = rr[0] * rc[0], f1 = rr[1] * rc[1], f2 = rr[2] * rc[2];
+      x[e][0] = g; x[e][1] = e_in[e][1]; x[e][2] = q1; x[e][3] = q2; x[e][4] = q3; x[e][5] = v;
+      x[e][6] = q1 * rs; x[e][7] = q2 * rs; x[e][8] = q3 * rs; x[e][9] = rs;
+      x[e][10] = g * f0; x[e][11] = g * f1; x[e][12] = g * f2;
+      x[e][13] = q1 * f0; x[e][14] = q2 * f1; x[e][15] = q3 * f2;
+      x[e][16] = fminf(fmaxf(g, -0.1f), 0.1f);
+      h[e] = rowv + colv;
+    }
+#pragma unroll
+    for (int k = 0; k < kVE; ++k) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(a1[k], x[e][k], h[e], 0, 0, 0);
+    }
+    f32x4 h2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h2[e] = c2;
+#pragma unroll
+    for (int k = 0; k < kVH; ++k) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h2[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(a2[k], relu1(h[e][k]), h2[e], 0, 0, 0);
+    }
+    f32x4 o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = c3;
+#pragma unroll
+    for (int k = 0; k < kVH; ++k) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(a3[k], relu1(h2[e][k]), o[e], 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float delta = o[e][0] * __expf(o[e][1] * A.exp_mult) * A.step_mult;
+      const float p = e_in[e][1];
+      if (r + e < r1 && col_ok) T.p[(size_t)(r + e) * n + cc] = p - lr * (delta + wd * p);
+    }
   }
 }
 
@@ -189,8 +344,9 @@ __global__ void __launch_bounds__(kBlock, 4) k_apply_velo4(const TensorDev* __re
                                                         StepArgs A) {
   const TileDev tile = tiles[blockIdx.x];
   const TensorDev& T = tensors[tile.tensor];
-  if (T.vec) apply_velo4_tile<true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
-  else apply_velo4_tile<false, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
+  if (T.vec == 2) apply_velo4_tile<true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
+  else if (T.vec) apply_velo4_tile<false, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
+  else apply_velo4_tile_cols<RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
 }
 
 bool apply_velo4_available(const StepArgs& A) { return A.kind == LOPT_VELO && A.H == kVH && A.HP == kVH; }

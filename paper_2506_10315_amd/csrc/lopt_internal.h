@@ -37,7 +37,7 @@ struct TensorDev {
   int m, n;
   uint32_t padN, padm, padn, padH;  // state section strides in floats
   uint32_t ndim;
-  int vec;                          // n % 4 == 0: rows are 16-byte aligned
+  int vec;                          // 0: rows are not 16-byte aligned, 1: they are (n % 4 == 0), 2: 128-byte aligned (n % 32 == 0)
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
   int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2

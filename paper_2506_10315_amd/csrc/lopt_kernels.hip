@@ -135,36 +135,49 @@ template <bool VEC>
 __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                             float (*colred)[kTileCols]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int R = VEC ? 2 : 4;   // rows in flight per wavefront
   const int n = T.n, m = T.m;
-  const int col = tile.tj * kTileCols + 4 * lane;
+  const int c0 = tile.tj * kTileCols;
+  // g of one row: aligned rows, columns 4 lane .. 4 lane + 3 as one float4; other rows, columns lane + 64 e (coalesced dwords)
+  auto row4 = [&](int r) __attribute__((always_inline)) {
+    const float* __restrict__ row = T.g + (size_t)r * n;
+    if (VEC) return load4s<true>(row, c0 + 4 * lane, n);
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = c0 + e * kWave + lane;
+      v[e] = row[min(c, n - 1)];   // columns past the end: a valid address, counted as 0
+      v[e] = c < n ? v[e] : 0.f;
+    }
+    return make_float4(v[0], v[1], v[2], v[3]);
+  };
   const int r0 = tile.ti * T.TR;
   const int r1 = min(r0 + T.TR, m);
   float* __restrict__ rowpart = ws + T.oRowPart + (size_t)tile.tj * m;
-  float c0 = 0.f, c1 = 0.f, c2 = 0.f, c3 = 0.f;
-  int r = r0 + wave;
-  // two rows in flight per wavefront
-  for (; r + 4 < r1; r += 8) {
-    float4 a = load4s<VEC>(T.g + (size_t)r * n, col, n);
-    float4 b = load4s<VEC>(T.g + (size_t)(r + 4) * n, col, n);
-    float ax = a.x * a.x, ay = a.y * a.y, az = a.z * a.z, aw = a.w * a.w;
-    float bx = b.x * b.x, by = b.y * b.y, bz = b.z * b.z, bw = b.w * b.w;
-    c0 += ax; c1 += ay; c2 += az; c3 += aw;
-    c0 += bx; c1 += by; c2 += bz; c3 += bw;
-    float sa = wave_sum((ax + ay) + (az + aw));
-    float sb = wave_sum((bx + by) + (bz + bw));
-    if (lane == 0) { rowpart[r] = sa; rowpart[r + 4] = sb; }
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  for (int r = r0 + wave; r < r1; r += 4 * R) {
+    float4 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = row4(min(r + 4 * i, r1 - 1));   // rows past the tile: its last row, counted as 0
+    float sum[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const float ax = v[i].x * v[i].x, ay = v[i].y * v[i].y, az = v[i].z * v[i].z, aw = v[i].w * v[i].w;
+      const bool in = r + 4 * i < r1;   // wavefront-uniform
+      s0 += in ? ax : 0.f; s1 += in ? ay : 0.f; s2 += in ? az : 0.f; s3 += in ? aw : 0.f;
+      sum[i] = wave_sum((ax + ay) + (az + aw));
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        if (r + 4 * i < r1) rowpart[r + 4 * i] = sum[i];
+    }
   }
-  for (; r < r1; r += 4) {
-    float4 a = load4s<VEC>(T.g + (size_t)r * n, col, n);
-    float ax = a.x * a.x, ay = a.y * a.y, az = a.z * a.z, aw = a.w * a.w;
-    c0 += ax; c1 += ay; c2 += az; c3 += aw;
-    float sa = wave_sum((ax + ay) + (az + aw));
-    if (lane == 0) rowpart[r] = sa;
-  }
-  colred[wave][4 * lane + 0] = c0;
-  colred[wave][4 * lane + 1] = c1;
-  colred[wave][4 * lane + 2] = c2;
-  colred[wave][4 * lane + 3] = c3;
+  const int cl = VEC ? 4 * lane : lane, cs = VEC ? 1 : kWave;
+  colred[wave][cl] = s0;
+  colred[wave][cl + cs] = s1;
+  colred[wave][cl + 2 * cs] = s2;
+  colred[wave][cl + 3 * cs] = s3;
   __syncthreads();
   const int c = tile.tj * kTileCols + threadIdx.x;
   if (c < n) {
@@ -341,42 +354,61 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 // Streaming accesses of this pass: nontemporal loads, ordinary stores (measured: 0.649 ms on the ViT-B/16 set
 // against 0.670 plain/plain, 0.670 plain/nontemporal, 0.680 nontemporal/nontemporal).
 
-// Rows that are not 16-byte aligned (n % 4 != 0; a small share of any list): one column per lane and sweep, four
-// sweeps of 64 columns over the tile, every access a coalesced dword. Kept small in registers on purpose: the
-// kernel's register count is the larger of its two paths, and it decides how many of its workgroups fit beside the
-// apply kernel of another tensor group.
-template <bool WRITE>
+// Rows that are not 16-byte aligned (n % 4 != 0): one column per lane, every access a coalesced dword of a 256-byte row
+// segment, kAccRows rows of loads in flight. The wavefronts of the tile sit on adjacent 64-column segments; where the tile
+// is narrower than three segments they share out its rows as well. RAW_RCP as in the aligned path below.
+// Kept small in registers on purpose: the kernel's register count is the larger of its two paths, and it decides how
+// many of its workgroups fit beside the apply kernel of another tensor group (the float4 path's count, with four rows
+// too). Ordinary loads: neighbouring segments share their boundary lines. 8.3 M elements of 1531 columns: 48 us with one
+// row per trip and nontemporal loads, 41 us.
+constexpr int kAccRows = 4;
+
+template <bool RAW_RCP, bool WRITE>
 __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                            const StepArgs& A, float (&acc)[kNStat]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = T.n, m = T.m;
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
+  const int c0 = tile.tj * kTileCols;
+  const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
+  const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
+  const int seg = wave / rsplit;
+  const int c = c0 + seg * kWave + lane;
+  if (seg >= nseg || c >= n) return;
+  const int r1 = min(tile.ti * T.TR + T.TR, m);
   const size_t pN = T.padN;
   const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
+  const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
   const float eps = A.eps_acc;
-#pragma unroll 1
-  for (int sweep = 0; sweep < kTileCols / kWave; ++sweep) {
-    const int c = tile.tj * kTileCols + sweep * kWave + lane;
-    if (c >= n) break;   // columns only grow with the sweep
-    float rc[3];
+  float rc[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) rc[k] = ws[T.oRC + (size_t)k * T.padn + c];
-#pragma unroll 1
-    for (int r = r0 + wave; r < r1; r += 4) {
-      const size_t ro = (size_t)r * n + c;
-      const float g = __builtin_nontemporal_load(T.g + ro), p = __builtin_nontemporal_load(T.p + ro);
+  for (int k = 0; k < 3; ++k) rc[k] = ws[T.oRC + (size_t)k * T.padn + c];
+  for (int r = tile.ti * T.TR + kAccRows * (wave % rsplit); r < r1; r += kAccRows * rsplit) {
+    float in[kAccRows][6];
+#pragma unroll
+    for (int e = 0; e < kAccRows; ++e) {   // a row past the tile reads the tile's last row and counts for nothing
+      const size_t ro = (size_t)min(r + e, r1 - 1) * n + c;
+      in[e][0] = T.g[ro];
+      in[e][1] = T.p[ro];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) in[e][2 + k] = T.st[k * pN + ro];
+    }
+#pragma unroll
+    for (int e = 0; e < kAccRows; ++e) {
+      if (r + e >= r1) break;   // wavefront-uniform
+      const size_t ro = (size_t)(r + e) * n + c;
+      const float g = in[e][0], p = in[e][1], g2 = g * g;
       // explicit fused multiply-adds: the apply pass may form the same values again (lopt_state_pass), bit for bit
-      const float nm1 = __builtin_fmaf(b1, __builtin_nontemporal_load(T.st + ro), (1.0f - b1) * g);
-      const float nm2 = __builtin_fmaf(b2, __builtin_nontemporal_load(T.st + pN + ro), (1.0f - b2) * g);
-      const float nm3 = __builtin_fmaf(b3, __builtin_nontemporal_load(T.st + 2 * pN + ro), (1.0f - b3) * g);
-      const float nv = __builtin_fmaf(b4, __builtin_nontemporal_load(T.st + 3 * pN + ro), (1.0f - b4) * (g * g));
-      const float rs = rsqrtf(nv + eps);
-      const float f0 = ws[T.oRR + r] * rc[0], f1 = ws[T.oRR + (size_t)T.padm + r] * rc[1];
-      const float f2 = ws[T.oRR + 2 * (size_t)T.padm + r] * rc[2];
+      const float nm1 = __builtin_fmaf(b1, in[e][2], a1 * g);
+      const float nm2 = __builtin_fmaf(b2, in[e][3], a2 * g);
+      const float nm3 = __builtin_fmaf(b3, in[e][4], a3 * g);
+      const float nv = __builtin_fmaf(b4, in[e][5], a4 * g2);
+      const float rs = RAW_RCP ? __builtin_amdgcn_rsqf(nv + eps) : rsqrtf(nv + eps);
+      float f[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) f[k] = ws[T.oRR + (size_t)k * T.padm + r + e] * rc[k];
       const float gc = fminf(fmaxf(g, -0.1f), 0.1f);
       float t;
-      acc[0] += g * g;
+      acc[0] += g2;
       acc[1] += p * p;
       acc[2] += nm1 * nm1;
       acc[3] += nm2 * nm2;
@@ -386,12 +418,12 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
       t = nm2 * rs; acc[7] += t * t;
       t = nm3 * rs; acc[8] += t * t;
       acc[9] += rs * rs;
-      t = g * f0; acc[10] += t * t;
-      t = g * f1; acc[11] += t * t;
-      t = g * f2; acc[12] += t * t;
-      t = nm1 * f0; acc[13] += t * t;
-      t = nm2 * f1; acc[14] += t * t;
-      t = nm3 * f2; acc[15] += t * t;
+      t = g * f[0]; acc[10] += t * t;
+      t = g * f[1]; acc[11] += t * t;
+      t = g * f[2]; acc[12] += t * t;
+      t = nm1 * f[0]; acc[13] += t * t;
+      t = nm2 * f[1]; acc[14] += t * t;
+      t = nm3 * f[2]; acc[15] += t * t;
       acc[16] += gc * gc;
       if (WRITE) {
         T.st[ro] = nm1;
@@ -494,7 +526,7 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
   if (T.vec) accum_tile_vec<RAW_RCP, WRITE>(T, tile, ws, A, acc);
-  else accum_tile<WRITE>(T, tile, ws, A, acc);
+  else accum_tile<RAW_RCP, WRITE>(T, tile, ws, A, acc);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
 }

@@ -53,6 +53,18 @@ def test_unaligned_rows_at_every_sweep_boundary(kind):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("state_pass", ["apply", "stats"])
+def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass):
+    # the width-4 kernel on rows that are not 16-byte aligned: one column per lane, four rows per trip, wavefronts on 64-column
+    # segments that share out the rows of narrow tiles: one, two, three and four segments, heights around the trip of four rows
+    # times four wavefronts; beside them 16-byte aligned rows off and on the 128-byte grid
+    cfg = Hn.make_cfg("velo", lstm_hidden=32, n_bank=8, state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=22)
+    shapes = [(1, 1), (2, 3), (17, 61), (15, 65), (33, 129), (64, 190), (65, 257), (130, 318), (257, 1), (4, 449), (67, 260), (66, 288)]
+    worst = Hn.run_free(Hn.Case(113, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("hidden,lstm_hidden,n_bank", [(3, 33, 5), (4, 512, 256)])
 def test_velo_long_list_takes_the_batched_hypernetwork_head(hidden, lstm_hidden, n_bank):
     # from 1024 tensors on the head of the hypernetwork runs as two batched matrix products and a scatter kernel
