@@ -149,6 +149,7 @@ struct lopt_ctx {
   int HP = 0, F = 0, P = 0;
   float* d_weights = nullptr;      // the uploaded blob
   float* d_tail = nullptr;         // small_fc_lopt: padded W2 b2 W3 b3
+  float* d_pack = nullptr;         // VeLO: the hypernetwork's weights in the layouts its kernels read
   WeightsDev W{};
   // cached plan + device tables: `heap` is library-allocated and grows with the list, `fixed` is the front of the
   // file-scope scratch array (lopt_step_static)
@@ -252,8 +253,8 @@ void build_plan(const lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d, Plan* 
     pl->oBeff = take((uint64_t)kMixJSplit * 4ull * ctx->cfg.lstm_hidden);
     pl->head_batched = n >= (size_t)kHeadBatchMin;
     if (pl->head_batched) {
-      pl->oAlpha = take((uint64_t)n * ctx->cfg.n_bank);
-      pl->oTheta = take((uint64_t)n * (uint64_t)ctx->P);
+      if (!ctx->W.head) pl->oAlpha = take((uint64_t)n * ctx->cfg.n_bank);
+      pl->oTheta = take((uint64_t)n * (uint64_t)(ctx->W.head ? head_ld(ctx->P) : ctx->P));
     }
   }
   // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off): the
@@ -595,6 +596,14 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
     ctx->W.ws = w; w += HL;
     ctx->W.bs = w; w += 1;
     ctx->W.B = w;
+    const bool folds = head_folds((int)HL, (int)K, ctx->P);
+    const size_t lstm_n = (HL + 7) / 8 * (size_t)lstm_k_pad((int)HL) * 32, head_n = folds ? (HL + 1) * (size_t)head_ld(ctx->P) : 0;
+    CREATE_TRY(hipMalloc((void**)&ctx->d_pack, (lstm_n + head_n) * sizeof(float)));
+    ctx->W.lstm = ctx->d_pack;
+    ctx->W.head = folds ? ctx->d_pack + lstm_n : nullptr;
+    launch_velo_pack(ctx->W, (int)HL, (int)K, ctx->P, ctx->d_pack, folds ? ctx->d_pack + lstm_n : nullptr, nullptr);
+    CREATE_TRY(hipGetLastError());
+    CREATE_TRY(hipStreamSynchronize(nullptr));   // steps may come on streams that do not wait for the default one
   }
 #undef CREATE_TRY
   (void)st;
@@ -606,6 +615,7 @@ void lopt_destroy(lopt_ctx* ctx) {
   if (!ctx) return;
   if (ctx->d_weights) (void)hipFree(ctx->d_weights);
   if (ctx->d_tail) (void)hipFree(ctx->d_tail);
+  if (ctx->d_pack) (void)hipFree(ctx->d_pack);
   if (ctx->heap.base) (void)hipFree(ctx->heap.base);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->stage_ev) (void)hipEventDestroy(ctx->stage_ev);

@@ -78,7 +78,15 @@ struct WeightsDev {
   // VeLO
   const float* Wx; const float* Wh; const float* Wg; const float* b; const float* Wa; const float* ba;
   const float* ws; const float* bs; const float* B;
+  const float* lstm;   // [Wx ; Wh] repacked for k_velo_lstm: [ceil(H_L / 8)][lstm_k_pad(H_L)][4 gates x 8 units]
+  const float* head;   // W_a, b_a, B and the step-size head folded into one matrix (null: the bank is too small for it to pay)
 };
+
+// Input slots of the LSTM rounded up to whole octets; row length of the folded head (P columns and the step size's).
+__host__ __device__ inline int lstm_k_pad(int HL) { return kLstmInPad + (HL + 7) / 8 * 8; }
+__host__ __device__ inline int head_ld(int P) { return (P + 1 + 3) / 4 * 4; }
+// The folded head reads (H_L + 1) (P + 1) weights per tensor, the two products H_L K + K P.
+inline bool head_folds(int HL, int K, int P) { return (size_t)HL * P <= (size_t)HL * K + (size_t)K * P; }
 
 struct Launch {
   const TensorDev* tensors;
@@ -103,6 +111,8 @@ void launch_rc_update(const Launch&, const StepArgs&, const WeightsDev&, float* 
 // write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s)
 void launch_accum_stats(const Launch&, const StepArgs&, bool write_state, hipStream_t);
 void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
+// lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
+void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);
 void launch_velo_lstm(const Launch&, const StepArgs&, const WeightsDev&, const float* lstm_u, const float* b_eff,
                       float* h_new, hipStream_t);
 void launch_velo_head(const Launch&, const StepArgs&, const WeightsDev&, const float* h_new, float* alpha,

@@ -667,112 +667,225 @@ void launch_finalize(const Launch& L, const StepArgs& A, const WeightsDev& W, fl
 
 // One LSTM-cell step for all tensors: Z[T, 4 H_L] = [u | h_prev] [Wx ; Wh] is a dense contraction and runs on the
 // matrix cores in fp32 (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32 accumulation). A workgroup owns 32 tensors x
-// 16 hidden units (two 32-column MFMA tiles of 8 units x 4 gates); its four wavefronts split the 48 + H_L input slots
-// and meet in LDS in a fixed order; one thread per (tensor, unit pair) then applies the cell equations.
-// Operands go from global memory straight into the MFMA layout: lane (k-half, t) holds input slot 2p + k-half of tensor
-// t (A operand) and of column (gate, unit) = (lane%32 / 8, u0 + 8 tile + lane%8) (B operand). Loads are unconditional
-// (clamped to a valid row, multiplied by 0 where a slot carries nothing: the padding slots 45..47, slots past H_L,
-// tensors or units past the end), sixteen slot pairs = 48 loads in flight per wavefront: the kernel is bound by the
-// latency of those loads, not by arithmetic.
+// 8 hidden units (one 32-column MFMA tile of 4 gates x 8 units); its eight wavefronts split the 48 + H_L input slots
+// and meet in LDS in a fixed order; one thread per (tensor, unit) then applies the cell equations.
+// The kernel is bound by the latency of its loads (4.6 MB of weights, a few hundred KB of inputs), so every wavefront
+// issues all of them before its first product: the weights are repacked at lopt_create into the order of the tiles,
+// [unit block][input slot][gate, unit], where a slot is one 128-byte line, and eight consecutive slots ("octet") are one
+// float4 of the lane's tensor (its k-half's four slots) and four lines of weights. Default widths: nine octets a wavefront,
+// one trip. One 1000x1000 layer 15.6 -> 9.9 us, 66 tensors 24 -> 11 us, 152 tensors 26 -> 15 us, 2219 tensors 185 -> 91 us
+// (from four wavefronts over 16 units and four gathered 32-byte segments a slot).
 constexpr int kLstmTensors = 32;
-constexpr int kLstmUnits = 16;
-constexpr int kLstmPairsPerTrip = 16;
+constexpr int kLstmWaves = 8;
+constexpr int kLstmOctets = 9;   // octets in flight per wavefront
 typedef float f32x16_l __attribute__((ext_vector_type(16)));
 
-__global__ void __launch_bounds__(kBlock) k_velo_lstm(const TensorDev* __restrict__ tensors, StepArgs A, WeightsDev W,
+// Weights in the order k_velo_lstm reads them: out[ub][k][8 gate + u] for unit 8 ub + u, zero past H_L in units and slots.
+__global__ void __launch_bounds__(kBlock) k_pack_lstm(WeightsDev W, int HL, int k_pad, float* __restrict__ out) {
+  const int ub = blockIdx.x, G = 4 * HL;
+  for (int i = threadIdx.x; i < k_pad * 32; i += kBlock) {
+    const int k = i >> 5, gate = (i >> 3) & 3, unit = 8 * ub + (i & 7);
+    float v = 0.f;
+    if (unit < HL) {
+      const size_t col = (size_t)gate * HL + unit;
+      if (k < kLstmInPad) v = W.Wx[(size_t)k * G + col];
+      else if (k - kLstmInPad < HL) v = W.Wh[(size_t)(k - kLstmInPad) * G + col];
+    }
+    out[((size_t)ub * k_pad + k) * 32 + (i & 31)] = v;
+  }
+}
+
+__global__ void __launch_bounds__(64 * kLstmWaves) k_velo_lstm(const TensorDev* __restrict__ tensors, StepArgs A, WeightsDev W,
                                                       const float* __restrict__ lstm_u, const float* __restrict__ b_eff,
                                                       float* __restrict__ h_new) {
-  __shared__ float part[4][2][32][32];   // [wavefront][column tile][tensor][column]: 32 KB
+  __shared__ float part[kLstmWaves][32][32];   // [wavefront][tensor][column]: 32 KB
   const int HL = A.HL, G = 4 * HL;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int khalf = lane >> 5, l32 = lane & 31;
-  const int t0 = blockIdx.x * kLstmTensors, u0 = blockIdx.y * kLstmUnits;
+  const int t0 = blockIdx.x * kLstmTensors, u0 = blockIdx.y * 8;
+  const int n_oct = lstm_k_pad(HL) / 8;
   // A side: the tensor of this lane (clamped: rows past the list compute on the last tensor and are dropped)
   const int tA = min(t0 + l32, A.n_tensors - 1);
   const TensorDev& T = tensors[tA];
   const float* __restrict__ hsrc = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
   const float* __restrict__ usrc = lstm_u + (size_t)tA * kLstmInPad;
-  // B side: the two columns of this lane
-  const int gate = l32 >> 3;
-  const int ua = min(u0 + (l32 & 7), HL - 1), ub = min(u0 + 8 + (l32 & 7), HL - 1);
-  const size_t cola = (size_t)gate * HL + ua, colb = (size_t)gate * HL + ub;
-
-  f32x16_l acc0, acc1;
+  // B side: this lane's column of the packed weights, its k-half's four slots of an octet
+  const float* __restrict__ wcol = W.lstm + ((size_t)blockIdx.y * (8 * n_oct) + 4 * khalf) * 32 + l32;
+  // bias, cross-tensor term and cell state of this thread's (tensor, unit), ahead of the products
+  const int tt = threadIdx.x >> 3, unit = u0 + (threadIdx.x & 7);
+  const bool cell_ok = tt < kLstmTensors && t0 + tt < A.n_tensors && unit < HL;
+  float be[4] = {0.f, 0.f, 0.f, 0.f}, c_old = 0.f;
+  float* cl = nullptr;
+  if (cell_ok) {
+    const TensorDev& Tt = tensors[t0 + tt];
+    cl = Tt.st + 4 * (size_t)Tt.padN + 3 * (size_t)Tt.padm + 3 * (size_t)Tt.padn + Tt.padH;
+    c_old = cl[unit];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) { acc0[v] = 0.f; acc1[v] = 0.f; }
-  // slot pairs of this wavefront; slots 0..47 are u (45 used), slots 48.. are h_prev; 48 is even, so a pair never straddles
-  const int n_pairs = (kLstmInPad + HL + 1) / 2;
-  const int per_wave = (n_pairs + 3) / 4;
-  const int p_begin = wave * per_wave, p_end = min(p_begin + per_wave, n_pairs);
-  for (int pb = p_begin; pb < p_end; pb += kLstmPairsPerTrip) {
-    float a[kLstmPairsPerTrip], b0[kLstmPairsPerTrip], b1[kLstmPairsPerTrip];
+    for (int g = 0; g < 4; ++g) {
+      const int gc = g * HL + unit;   // bias + cross-tensor term (its four partial sums, in order)
+      be[g] = W.b[gc] + ((b_eff[gc] + b_eff[G + gc]) + (b_eff[2 * G + gc] + b_eff[3 * G + gc]));
+    }
+  }
+  f32x16_l acc;
 #pragma unroll
-    for (int j = 0; j < kLstmPairsPerTrip; ++j) {
-      const int p = pb + j < p_end ? pb + j : p_end - 1;   // a repeated pair is multiplied by 0 below
-      const int k = 2 * p + khalf;
-      const bool isu = 2 * p < kLstmInPad;                  // wave-uniform
-      const int ku = k < LOPT_VELO_LSTM_IN ? k : LOPT_VELO_LSTM_IN - 1;
-      const int kh = k - kLstmInPad;
-      const int khc = kh < 0 ? 0 : kh < HL ? kh : HL - 1;
-      const float keep = (pb + j < p_end && (isu ? k < LOPT_VELO_LSTM_IN : kh < HL)) ? 1.f : 0.f;
-      const float* __restrict__ wrow = isu ? W.Wx + (size_t)ku * G : W.Wh + (size_t)khc * G;
-      a[j] = (isu ? usrc[ku] : hsrc[khc]) * keep;
-      b0[j] = wrow[cola];
-      b1[j] = wrow[colb];
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  const int per_wave = (n_oct + kLstmWaves - 1) / kLstmWaves;
+  const int o_begin = wave * per_wave, o_end = min(o_begin + per_wave, n_oct);
+  for (int ob = o_begin; ob < o_end; ob += kLstmOctets) {
+    float4 a[kLstmOctets];
+    float b[kLstmOctets][4];
+#pragma unroll
+    for (int j = 0; j < kLstmOctets; ++j) {
+      const int o = min(ob + j, o_end - 1);   // octets past the wavefront's share repeat its last one (dropped below)
+      const float4* src = 8 * o < kLstmInPad ? reinterpret_cast<const float4*>(usrc + 8 * o)
+                                             : reinterpret_cast<const float4*>(hsrc + (8 * o - kLstmInPad));
+      // the last octet's upper quad may start at or past H_L: the lower quad is read instead (its weights are zero)
+      const int up = 8 * o - kLstmInPad + 4 < HL ? khalf : 0;
+      a[j] = src[up];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[j][i] = wcol[((size_t)o * 8 + i) * 32];
     }
 #pragma unroll
-    for (int j = 0; j < kLstmPairsPerTrip; ++j) {
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b0[j], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b1[j], acc1, 0, 0, 0);
+    for (int j = 0; j < kLstmOctets; ++j) {
+      if (ob + j >= o_end) break;   // wavefront-uniform
+      float x[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
+      const int kh = 8 * (ob + j) + 4 * khalf - kLstmInPad;   // slots of h past H_L (the blob's padding, the cell) count as 0
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = kh + i < HL ? x[i] : 0.f;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], b[j][i], acc, 0, 0, 0);
+      }
     }
   }
   // accumulator register v of lane (k-half, c) is row 8 (v / 4) + 4 k-half + v % 4, column c
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int row = 8 * (v >> 2) + 4 * khalf + (v & 3);
-    part[wave][0][row][l32] = acc0[v];
-    part[wave][1][row][l32] = acc1[v];
-  }
+  for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * khalf + (v & 3)][l32] = acc[v];
   __syncthreads();
-  {
-    const int tt = threadIdx.x >> 3, uu = threadIdx.x & 7;
-    if (t0 + tt < A.n_tensors) {
-      const TensorDev& Tt = tensors[t0 + tt];
-      float* cl = Tt.st + 4 * (size_t)Tt.padN + 3 * (size_t)Tt.padm + 3 * (size_t)Tt.padn + Tt.padH;
+  if (cell_ok) {
+    float zz[4];
 #pragma unroll
-      for (int tile = 0; tile < 2; ++tile) {
-        const int unit = u0 + 8 * tile + uu;
-        if (unit < HL) {
-          float zz[4];
+    for (int g = 0; g < 4; ++g) {
+      float s[kLstmWaves];
 #pragma unroll
-          for (int g2 = 0; g2 < 4; ++g2) {
-            const int c = g2 * 8 + uu;
-            const int gc = g2 * HL + unit;   // bias + cross-tensor term (its four partial sums, in order)
-            const float be = W.b[gc] + ((b_eff[gc] + b_eff[G + gc]) + (b_eff[2 * G + gc] + b_eff[3 * G + gc]));
-            zz[g2] = be + ((part[0][tile][tt][c] + part[1][tile][tt][c]) + (part[2][tile][tt][c] + part[3][tile][tt][c]));
-          }
-          const float ig = 1.f / (1.f + expf(-zz[0]));
-          const float fg = 1.f / (1.f + expf(-zz[1]));
-          const float gg = tanhf(zz[2]);
-          const float og = 1.f / (1.f + expf(-zz[3]));
-          const float c = fg * cl[unit] + ig * gg;
-          cl[unit] = c;
-          h_new[(size_t)(t0 + tt) * HL + unit] = og * tanhf(c);
-        }
-      }
+      for (int w = 0; w < kLstmWaves; ++w) s[w] = part[w][tt][8 * g + (threadIdx.x & 7)];
+      zz[g] = be[g] + (((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
     }
+    const float ig = 1.f / (1.f + expf(-zz[0]));
+    const float fg = 1.f / (1.f + expf(-zz[1]));
+    const float gg = tanhf(zz[2]);
+    const float og = 1.f / (1.f + expf(-zz[3]));
+    const float c = fg * c_old + ig * gg;
+    cl[unit] = c;
+    h_new[(size_t)(t0 + tt) * HL + unit] = og * tanhf(c);
   }
 }
 
 void launch_velo_lstm(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* lstm_u, const float* b_eff,
                       float* h_new, hipStream_t s) {
   if (L.n_tensors == 0) return;
-  dim3 grid((L.n_tensors + kLstmTensors - 1) / kLstmTensors, (A.HL + kLstmUnits - 1) / kLstmUnits);
+  dim3 grid((L.n_tensors + kLstmTensors - 1) / kLstmTensors, (A.HL + 7) / 8);
   // a sub-list starts at tensor L.tensor0: the kernel indexes tensors, inputs and outputs from there
   StepArgs As = A;
   As.n_tensors = L.n_tensors;
-  hipLaunchKernelGGL(k_velo_lstm, grid, dim3(kBlock), 0, s, L.tensors + L.tensor0, As, W,
+  hipLaunchKernelGGL(k_velo_lstm, grid, dim3(64 * kLstmWaves), 0, s, L.tensors + L.tensor0, As, W,
                      lstm_u + (size_t)L.tensor0 * kLstmInPad, b_eff, h_new + (size_t)L.tensor0 * A.HL);
+}
+
+// ---- the head with its two products folded into one at lopt_create (WeightsDev::head): theta = h (W_a B) + b_a B, with the
+// step-size row (ws, bs) as one more column, [H_L + 1][head_ld(P)], row H_L the constant. Formed in double, stored in fp32.
+__global__ void __launch_bounds__(kBlock) k_pack_head(WeightsDev W, int HL, int K, int P, int ld, float* __restrict__ out) {
+  const int u = blockIdx.x;   // 0 .. H_L
+  for (int p = threadIdx.x; p < ld; p += kBlock) {
+    double a = 0.0;
+    if (p < P)
+#pragma unroll 16
+      for (int q = 0; q < K; ++q) a += (double)(u < HL ? W.Wa[(size_t)u * K + q] : W.ba[q]) * (double)W.B[(size_t)q * P + p];
+    else if (p == P) a = u < HL ? W.ws[u] : W.bs[0];
+    out[(size_t)u * ld + p] = (float)a;
+  }
+}
+
+void launch_velo_pack(const WeightsDev& W, int HL, int K, int P, float* lstm, float* head, hipStream_t s) {
+  hipLaunchKernelGGL(k_pack_lstm, dim3((HL + 7) / 8), dim3(kBlock), 0, s, W, HL, lstm_k_pad(HL), lstm);
+  if (head) hipLaunchKernelGGL(k_pack_head, dim3(HL + 1), dim3(kBlock), 0, s, W, HL, K, P, head_ld(P), head);
+}
+
+// theta[i] of the compact per-tensor MLP (W1[F,H] b1[H] W2[H,H] b2[H] W3[H,2] b3[2]) goes to prep[head_slot(i, ...)], the layout
+// padded to HP; the first layer takes the tensor's feature scales and the direction column of the last layer the step size.
+__device__ __forceinline__ int head_slot(int i, int H, int HP, const float* __restrict__ scale, float lam, float& th) {
+  constexpr int F = LOPT_D_VELO;
+  int o = i;
+  if (o < F * H) { const int f = o / H, u = o - f * H; th *= scale[f]; return f * HP + u; }
+  if ((o -= F * H) < H) return F * HP + o;
+  if ((o -= H) < H * H) { const int a = o / H, u = o - a * H; return (F + 1) * HP + a * HP + u; }
+  if ((o -= H * H) < H) return (F + 1) * HP + HP * HP + o;
+  if ((o -= H) < 2 * H) { if (!(o & 1)) th *= lam; return (F + 1) * HP + HP * HP + HP + o; }   // W3[a][0]: direction
+  o -= 2 * H;
+  if (o == 0) th *= lam;                                                                         // b3[0]
+  return (F + 1) * HP + HP * HP + HP + 2 * HP + o;
+}
+
+// One workgroup per tensor, 16 wavefronts. Wavefront w reduces rows w, w + 16, ... of the folded matrix, a lane four columns
+// as one float4, sixteen rows in flight (bound by their latency: 309 KB at the default widths); partials meet in LDS in a
+// fixed order. Replaces two dependent products (660 KB): 10.3 -> 6.5 us; 152 tensors 14.7 -> 8.4 us.
+constexpr int kHeadWaves = 16;
+__global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_folded(const TensorDev* __restrict__ tensors,
+                                                                      float* __restrict__ ws, StepArgs A, WeightsDev W,
+                                                                      const float* __restrict__ h_new) {
+  extern __shared__ float4 sh4[];   // part[16][256] | h[HL]
+  const TensorDev& T = tensors[blockIdx.x];
+  const int HL = A.HL, H = A.H, HP = A.HP, P = A.P, ld = head_ld(P);
+  float* part = reinterpret_cast<float*>(sh4);
+  float* sh_h = part + kHeadWaves * 256;
+  __shared__ float s_lam;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* hstate = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
+  for (int i = threadIdx.x; i < HL; i += 64 * kHeadWaves) {
+    const float v = h_new[(size_t)blockIdx.x * HL + i];
+    sh_h[i] = v;
+    hstate[i] = v;
+  }
+  float* prep = ws + T.oPrep;
+  const float* scale = ws + T.oScale;
+  if (H != HP) {   // the padding must be zero; written before the values by the barriers below
+    const int prep_n = (LOPT_D_VELO + 1) * HP + HP * HP + HP + 2 * HP + 2;
+    for (int i = threadIdx.x; i < prep_n; i += 64 * kHeadWaves) prep[i] = 0.f;
+  }
+  __syncthreads();
+  // the block with the step-size column comes first: every other block needs its value
+  const int last = P / 256 * 256;
+  for (int blk = 0; blk <= last / 256; ++blk) {
+    const int c0 = blk == 0 ? last : (blk - 1) * 256;
+    const int col = c0 + 4 * lane;
+    const float4* __restrict__ m = reinterpret_cast<const float4*>(W.head + min(col, ld - 4));
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = wave; k0 < HL; k0 += 16 * kHeadWaves) {
+      float4 w[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w[j] = m[(size_t)min(k0 + j * kHeadWaves, HL) * (ld / 4)];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int k = k0 + j * kHeadWaves;
+        const float x = k < HL ? sh_h[min(k, HL - 1)] : 0.f;
+        acc.x += x * w[j].x; acc.y += x * w[j].y; acc.z += x * w[j].z; acc.w += x * w[j].w;
+      }
+    }
+    *reinterpret_cast<float4*>(part + wave * 256 + 4 * lane) = acc;
+    __syncthreads();
+    const int i = c0 + (int)threadIdx.x;
+    float th = 0.f;
+    if (threadIdx.x < 256 && i <= P) {
+      th = W.head[(size_t)HL * ld + i];
+#pragma unroll
+      for (int w = 0; w < kHeadWaves; ++w) th += part[w * 256 + threadIdx.x];
+      if (i == P) s_lam = expf(th);
+    }
+    __syncthreads();   // s_lam; the partials may be overwritten
+    if (threadIdx.x < 256 && i < P) {
+      const int dst = head_slot(i, H, HP, scale, s_lam, th);
+      prep[dst] = th;
+    }
+  }
 }
 
 // Partial matrix-vector product for the hypernetwork head: out[w][c0 + 64 c + lane] = sum over rows
@@ -868,25 +981,19 @@ __global__ void __launch_bounds__(1024) k_velo_head(const TensorDev* __restrict_
   for (int i = threadIdx.x; i < P; i += blockDim.x) {
     float th = 0.f;
     for (int w = 0; w < nw; ++w) th += part[w * W64 + i];
-    // scatter from the compact layout (W1[F,H] b1[H] W2[H,H] b2[H] W3[H,2] b3[2]) to the padded one
-    int o = i, dst;
-    if (o < F * H) { const int f = o / H, u = o - f * H; dst = f * HP + u; th *= scale[f]; }
-    else if ((o -= F * H) < H) dst = F * HP + o;
-    else if ((o -= H) < H * H) { const int a = o / H, u = o - a * H; dst = (F + 1) * HP + a * HP + u; }
-    else if ((o -= H * H) < H) dst = (F + 1) * HP + HP * HP + o;
-    else if ((o -= H) < 2 * H) { dst = (F + 1) * HP + HP * HP + HP + o; if (!(o & 1)) th *= s_lam; }   // W3[a][0]: direction
-    else { o -= 2 * H; dst = (F + 1) * HP + HP * HP + HP + 2 * HP + o; if (o == 0) th *= s_lam; }       // b3[0]
+    const int dst = head_slot(i, H, HP, scale, s_lam, th);   // from the compact layout to the padded one
     prep[dst] = th;
   }
 }
 
-// ---- the head for long tensor lists: alpha = H' W_a + b_a and theta = alpha B as two batched products on the matrix
-// cores (fp32), then one small workgroup per tensor that scatters theta into the prepared layout.
+// ---- the head for long tensor lists as batched products on the matrix cores (fp32), then one small workgroup per tensor
+// that scatters theta into the prepared layout: one product with the folded matrix, or alpha = H' W_a + b_a, theta = alpha B.
 
-// Y[r][c] = bias[c] + sum_k X[r][k] Wm[k][c] with exact fp32 products (v_mfma_f32_32x32x2_f32), the scheme of
-// k_velo_lstm: a workgroup owns 32 rows x 64 columns (two 32-column tiles), its four wavefronts split the k range and
+// Y[r][c] = bias[c] + sum_k X[r][k] Wm[k][c] with exact fp32 products (v_mfma_f32_32x32x2_f32), 
+// a workgroup owns 32 rows x 64 columns (two 32-column tiles), its four wavefronts split the k range and
 // meet in LDS in a fixed order. Lane (k-half, i) holds X[row i][2p + k-half] (A operand) and Wm[2p + k-half][column i] (B
 // operand); loads are unconditional (rows, columns and k clamped, surplus k multiplied by 0).
+constexpr int kMatPairsPerTrip = 16;
 __global__ void __launch_bounds__(kBlock) k_rows_matmul(const float* __restrict__ X, int ldx, int n_rows, int n_in,
                                                         const float* __restrict__ Wm, int ldw, int n_cols,
                                                         const float* __restrict__ bias, float* __restrict__ Y, int ldy) {
@@ -902,10 +1009,10 @@ __global__ void __launch_bounds__(kBlock) k_rows_matmul(const float* __restrict_
   const int n_pairs = (n_in + 1) / 2;
   const int per_wave = (n_pairs + 3) / 4;
   const int p_begin = wave * per_wave, p_end = min(p_begin + per_wave, n_pairs);
-  for (int pb = p_begin; pb < p_end; pb += kLstmPairsPerTrip) {
-    float a[kLstmPairsPerTrip], b0[kLstmPairsPerTrip], b1[kLstmPairsPerTrip];
+  for (int pb = p_begin; pb < p_end; pb += kMatPairsPerTrip) {
+    float a[kMatPairsPerTrip], b0[kMatPairsPerTrip], b1[kMatPairsPerTrip];
 #pragma unroll
-    for (int j = 0; j < kLstmPairsPerTrip; ++j) {
+    for (int j = 0; j < kMatPairsPerTrip; ++j) {
       const int pp = pb + j < p_end ? pb + j : p_end - 1;   // a repeated pair is multiplied by 0 below
       const int k = 2 * pp + khalf;
       const int kc = k < n_in ? k : n_in - 1;
@@ -915,7 +1022,7 @@ __global__ void __launch_bounds__(kBlock) k_rows_matmul(const float* __restrict_
       b1[j] = Wm[(size_t)kc * ldw + cb];
     }
 #pragma unroll
-    for (int j = 0; j < kLstmPairsPerTrip; ++j) {
+    for (int j = 0; j < kMatPairsPerTrip; ++j) {
       acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b0[j], acc0, 0, 0, 0);
       acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b1[j], acc1, 0, 0, 0);
     }
@@ -943,6 +1050,8 @@ __global__ void __launch_bounds__(kBlock) k_rows_matmul(const float* __restrict_
 }
 
 // One workgroup per tensor: new h into the state, step-size multiplier, theta[P] scattered into the prepared layout.
+// FOLDED: the step size's logarithm is column P of theta (rows of head_ld(P)), otherwise it is formed here (rows of P).
+template <bool FOLDED>
 __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                               StepArgs A, WeightsDev W, const float* __restrict__ h_new,
                                                               const float* __restrict__ theta) {
@@ -952,11 +1061,14 @@ __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* _
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float* hstate = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
   const float* __restrict__ hn = h_new + (size_t)blockIdx.x * HL;
+  const float* __restrict__ th_row = theta + (size_t)blockIdx.x * (FOLDED ? head_ld(P) : P);
   for (int i = threadIdx.x; i < HL; i += kBlock) hstate[i] = hn[i];
   float* prep = ws + T.oPrep;
   const int prep_n = (F + 1) * HP + HP * HP + HP + 2 * HP + 2;
   for (int i = threadIdx.x; i < prep_n; i += kBlock) prep[i] = 0.f;   // the padding must be zero
-  if (wave == 0) {
+  if (FOLDED) {
+    if (threadIdx.x == 0) s_lam = expf(th_row[P]);
+  } else if (wave == 0) {
     float a = 0.f;
     for (int i = lane; i < HL; i += kWave) a += hn[i] * W.ws[i];
     a = wave_sum(a);
@@ -964,35 +1076,42 @@ __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* _
   }
   __syncthreads();
   const float* scale = ws + T.oScale;
-  const float* __restrict__ th_row = theta + (size_t)blockIdx.x * P;
   for (int i = threadIdx.x; i < P; i += kBlock) {
     float th = th_row[i];
-    int o = i, dst;
-    if (o < F * H) { const int f = o / H, u = o - f * H; dst = f * HP + u; th *= scale[f]; }
-    else if ((o -= F * H) < H) dst = F * HP + o;
-    else if ((o -= H) < H * H) { const int a = o / H, u = o - a * H; dst = (F + 1) * HP + a * HP + u; }
-    else if ((o -= H * H) < H) dst = (F + 1) * HP + HP * HP + o;
-    else if ((o -= H) < 2 * H) { dst = (F + 1) * HP + HP * HP + HP + o; if (!(o & 1)) th *= s_lam; }   // W3[a][0]: direction
-    else { o -= 2 * H; dst = (F + 1) * HP + HP * HP + HP + 2 * HP + o; if (o == 0) th *= s_lam; }       // b3[0]
+    const int dst = head_slot(i, H, HP, scale, s_lam, th);
     prep[dst] = th;
   }
 }
 
-// alpha / theta: scratch of n_tensors x K and n_tensors x P floats for the batched form, null for lists below
+// theta (and alpha, if the head is not folded): scratch of n_tensors rows for the batched form, null for lists below
 // kHeadBatchMin tensors (one workgroup per tensor then does everything; cheaper in launches, dearer in weight reads).
 void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* h_new, float* alpha,
                       float* theta, hipStream_t s) {
   if (L.n_tensors == 0) return;
-  if (alpha && theta && L.n_tensors >= kHeadBatchMin) {
-    const int T = L.n_tensors;
-    const float* hn = h_new + (size_t)L.tensor0 * A.HL;
+  const int T = L.n_tensors;
+  const float* hn = h_new + (size_t)L.tensor0 * A.HL;
+  const bool batched = theta && T >= kHeadBatchMin;
+  if (W.head) {
+    const int ld = head_ld(A.P);
+    if (batched) {
+      float* th = theta + (size_t)L.tensor0 * ld;
+      hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 1 + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.head,
+                         ld, A.P + 1, W.head + (size_t)A.HL * ld, th, ld);
+      hipLaunchKernelGGL(k_velo_head_scatter<true>, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th);
+    } else {
+      const size_t shmem = (size_t)(((A.HL + 3) & ~3) + kHeadWaves * 256) * sizeof(float);
+      hipLaunchKernelGGL(k_velo_head_folded, dim3(T), dim3(64 * kHeadWaves), shmem, s, L.tensors + L.tensor0, L.ws, A, W, hn);
+    }
+    return;
+  }
+  if (batched) {
     float* al = alpha + (size_t)L.tensor0 * A.K;
     float* th = theta + (size_t)L.tensor0 * A.P;
     hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.K + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.Wa, A.K,
                        A.K, W.ba, al, A.K);
     hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 63) / 64), dim3(kBlock), 0, s, al, A.K, T, A.K, W.B, A.P,
                        A.P, (const float*)nullptr, th, A.P);
-    hipLaunchKernelGGL(k_velo_head_scatter, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th);
+    hipLaunchKernelGGL(k_velo_head_scatter<false>, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th);
     return;
   }
   const int W64 = ((A.K > A.P ? A.K : A.P) + 63) & ~63;
