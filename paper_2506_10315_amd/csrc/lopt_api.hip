@@ -689,7 +689,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   if (st != LOPT_OK) return st;
   const TableStore& tb = ctx->heap;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
-           (int)ctx->plan.rcitems.size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0};
+           (int)ctx->plan.rcitems.size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0};
   StepArgs A = make_args(ctx, 0, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
@@ -750,7 +750,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   // workspace base rounded up to 256 bytes (lopt_state_bytes adds the slack)
   float* ws = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
-           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu};
+           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0};
   const bool profiling = ctx->profiling && !use_static;   // per-pass timing creates events: not on the static path
   StepArgs A = make_args(ctx, step, lr, weight_decay, (int)n);
   const bool mfma_ok = apply_mfma_available(A);
@@ -814,6 +814,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
       S.atiles = L.atiles + at0; S.n_atiles = at1 - at0;
       S.tensor0 = t0; S.n_tensors = t1 - t0;
       S.apply_counter = L.apply_counter + g;
+      S.beside_apply = g > 0;
       return S;
     };
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for

@@ -44,6 +44,32 @@ void launch_fill_zero(const Launch& L, const StepArgs& A, hipStream_t s) {
   }
 }
 
+// ----------------------------------------------------------------------------- sums of partials
+
+// acc + the sum of part[0], part[stride], ... (count terms, 1..B) in double, in index order: B loads issue ahead of the adds,
+// those past the end repeat the last term and are dropped.
+template <int B>
+__device__ __forceinline__ double sum_batch(const float* __restrict__ part, int count, size_t stride, double acc) {
+  float t[B];
+#pragma unroll
+  for (int k = 0; k < B; ++k) t[k] = part[(size_t)min(k, count - 1) * stride];
+#pragma unroll
+  for (int k = 0; k < B; ++k) acc += k < count ? (double)t[k] : 0.0;
+  return acc;
+}
+
+// Sum of part[0], part[stride], ... (count terms) in double, always in index order. Bound by load latency: full batches of
+// 32 loads, then one batch of the power of two that holds the rest.
+__device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
+  double acc = 0.0;
+  for (; count > 32; count -= 32, part += 32 * stride) acc = sum_batch<32>(part, 32, stride, acc);
+  if (count > 16) return sum_batch<32>(part, count, stride, acc);
+  if (count > 8) return sum_batch<16>(part, count, stride, acc);
+  if (count > 4) return sum_batch<8>(part, count, stride, acc);
+  if (count > 1) return sum_batch<4>(part, count, stride, acc);
+  return count == 1 ? acc + (double)part[0] : acc;
+}
+
 // ----------------------------------------------------------------------------- VeLO cross-tensor term
 
 // The cross-tensor input of VeLO's LSTM depends on nothing this step computes (it reads the LSTM outputs h the previous
@@ -85,8 +111,8 @@ __device__ __forceinline__ void mix_hbar_block(const TensorDev* __restrict__ ten
     M.part[(size_t)slice * M.HL + j] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// Workgroup = 64 gate columns (lane = column: coalesced rows of Wg) x one quarter of the units j; its four wavefronts
-// take every fourth unit of the quarter, eight rows in flight each, and meet in LDS in a fixed order. The quarters
+// Workgroup = 64 gate columns (lane = column: coalesced rows of Wg) x one quarter of the units j; its wavefronts
+// take the units of the quarter in turn, eight rows in flight each, and meet in LDS in a fixed order. The quarters
 // are added up (with the bias b) by k_velo_lstm, again in a fixed order.
 __device__ __forceinline__ void mix_bias_block(const MixArgs& M, int blk, float* hbar, float (*red)[kWave]) {
   const int HL = M.HL, G = 4 * HL;
@@ -94,27 +120,27 @@ __device__ __forceinline__ void mix_bias_block(const MixArgs& M, int blk, float*
   const int colblk = blk % n_colblk, quarter = blk / n_colblk;
   const int jq = (HL + kMixJSplit - 1) / kMixJSplit;
   const int j0 = quarter * jq, j1 = min(j0 + jq, HL);
-  for (int j = j0 + (int)threadIdx.x; j < j1; j += kBlock) {
-    double a = 0.0;
-    for (int s = 0; s < M.n_slices; ++s) a += (double)M.part[(size_t)s * HL + j];
-    hbar[j - j0] = (float)(a / (double)M.n_tensors);
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int col = min(colblk * kWave + lane, G - 1);
   const float* __restrict__ wg = M.Wg + col;
+  for (int j = j0 + (int)threadIdx.x; j < j1; j += (int)blockDim.x)
+    hbar[j - j0] = (float)(strided_sum(M.part + j, M.n_slices, (size_t)HL) / (double)M.n_tensors);
+  __syncthreads();
   float a = 0.f;
-  for (int j = j0 + wave; j < j1; j += 32) {
+  for (int j = j0 + wave; j < j1; j += 8 * nw) {
     float w[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = wg[(size_t)min(j + 4 * k, j1 - 1) * G];
+    for (int k = 0; k < 8; ++k) w[k] = wg[(size_t)min(j + nw * k, j1 - 1) * G];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a += j + 4 * k < j1 ? hbar[j + 4 * k - j0] * w[k] : 0.f;
+    for (int k = 0; k < 8; ++k) a += j + nw * k < j1 ? hbar[j + nw * k - j0] * w[k] : 0.f;
   }
   red[wave][lane] = a;
   __syncthreads();
-  if (wave == 0 && colblk * kWave + lane < G)
-    M.b_eff[(size_t)quarter * G + col] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  if (wave == 0 && colblk * kWave + lane < G) {
+    float s = 0.f;
+    for (int w = 0; w < nw; ++w) s += red[w][lane];
+    M.b_eff[(size_t)quarter * G + col] = s;
+  }
 }
 
 static MixArgs make_mix(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff) {
@@ -210,14 +236,16 @@ void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W,
 
 // ----------------------------------------------------------------------------- rc_update
 
-// Block-wide sums of NV values per thread; thread 0 of the block gets them in out[].
+// Sums over the workgroup's first four wavefronts (256 threads) of NV values per thread, to out[0..NV).
 template <int NV>
 __device__ __forceinline__ void block_sum(float (&v)[NV], float (*red)[4], float* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (wave < 4) {
 #pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    float s = wave_sum(v[q]);
-    if (lane == 0) red[q][wave] = s;
+    for (int q = 0; q < NV; ++q) {
+      float s = wave_sum(v[q]);
+      if (lane == 0) red[q][wave] = s;
+    }
   }
   __syncthreads();
   if (threadIdx.x < NV) {
@@ -226,41 +254,25 @@ __device__ __forceinline__ void block_sum(float (&v)[NV], float (*red)[4], float
   }
 }
 
-// Sum of part[0], part[stride], ... (count terms) in double, always in index order. The loads of a batch issue
-// ahead of the adds: batches of 32 while that many terms are left (the loop is bound by load latency), then 8.
-__device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
-  double acc = 0.0;
-  int j = 0;
-  for (; j + 32 <= count; j += 32) {
-    float t[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) t[k] = part[(size_t)(j + k) * stride];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) acc += (double)t[k];
-  }
-#pragma unroll 8
-  for (; j < count; ++j) acc += (double)part[(size_t)j * stride];
-  return acc;
-}
-
-// The same sum formed by the whole workgroup (for one row or column at a time): thread t adds the terms t, t + 256, ...
-// in index order, then a fixed tree over the 256 threads. Every thread gets the result. For tensors of extreme aspect
+// The same sum formed by the whole workgroup (for one row or column at a time): thread t adds every blockDim-th term from t on
+// in index order, then a fixed tree over the threads. Every thread gets the result. For tensors of extreme aspect
 // ratio (a 1 x 2^28 vector has a million column tiles): one lane summing them all would take milliseconds.
 __device__ __forceinline__ double strided_sum_coop(const float* __restrict__ part, int count, size_t stride, double* tree) {
   double a = 0.0;
+  const int nt = blockDim.x;
   int j = threadIdx.x;
-  for (; j + 7 * kBlock < count; j += 8 * kBlock) {
+  for (; j + 7 * nt < count; j += 8 * nt) {
     float t[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) t[k] = part[(size_t)(j + k * kBlock) * stride];
+    for (int k = 0; k < 8; ++k) t[k] = part[(size_t)(j + k * nt) * stride];
 #pragma unroll
     for (int k = 0; k < 8; ++k) a += (double)t[k];
   }
-  for (; j < count; j += kBlock) a += (double)part[(size_t)j * stride];
+  for (; j < count; j += nt) a += (double)part[(size_t)j * stride];
   __syncthreads();   // the previous use of the tree is over
   tree[threadIdx.x] = a;
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
+  for (int w = nt / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) tree[threadIdx.x] += tree[threadIdx.x + w];
     __syncthreads();
   }
@@ -271,20 +283,25 @@ __device__ __forceinline__ double strided_sum_coop(const float* __restrict__ par
 // more than 512 in all (decided by the shapes alone, so a given tensor list always takes the same path).
 __device__ __forceinline__ bool rc_sum_coop(int count, int valid) { return count > 512 && count >= 64 * valid; }
 
-__global__ void __launch_bounds__(kBlock) k_rc_update(const TensorDev* __restrict__ tensors,
+// Workgroup = a block of 256 rows (or columns) of one tensor; the first 256 threads finish one row each. On short lists it
+// has 1024 threads, which sum each row's partials as four interleaved quarters that meet in LDS in a fixed order: the
+// kernel is a chain of load latencies (125 partials a column, 1000x1000: 7.2 -> 5.5 us with one batch of loads, not eight).
+constexpr int kRcMaxThreads = 4 * kBlock;
+__global__ void __launch_bounds__(kRcMaxThreads) k_rc_update(const TensorDev* __restrict__ tensors,
                                                       const RcItemDev* __restrict__ items, float* __restrict__ ws,
                                                       StepArgs A, int n_items, MixArgs M) {
   __shared__ float red[9][4];
-  __shared__ double tree[kBlock];
+  __shared__ double tree[kRcMaxThreads];
   if ((int)blockIdx.x >= n_items) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
     __shared__ float hbar[1024];
-    __shared__ float mred[4][kWave];
+    __shared__ float mred[kRcMaxThreads / kWave][kWave];
     mix_bias_block(M, (int)blockIdx.x - n_items, hbar, mred);
     return;
   }
   const RcItemDev it = items[blockIdx.x];
   const TensorDev& T = tensors[it.tensor];
-  const int idx = it.blk * kBlock + threadIdx.x;
+  const int i = threadIdx.x & (kBlock - 1), quarter = threadIdx.x / kBlock, nq = blockDim.x / kBlock;
+  const int idx = it.blk * kBlock + i;
   float v[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) v[q] = 0.f;
@@ -292,45 +309,42 @@ __global__ void __launch_bounds__(kBlock) k_rc_update(const TensorDev* __restric
   const int dim = it.is_col ? T.n : T.m, count = it.is_col ? T.nrt : T.nct;
   const int valid = min(kBlock, dim - it.blk * kBlock);
   const float* __restrict__ pbase = ws + (it.is_col ? T.oColPart : T.oRowPart) + (size_t)it.blk * kBlock;
+  // the three accumulators of this row or column, ahead of the sums
+  const size_t pd = it.is_col ? T.padn : T.padm;
+  float* acc3 = st + 4 * (size_t)T.padN + (it.is_col ? 3 * (size_t)T.padm : 0) + idx;
+  float* inv3 = ws + (it.is_col ? T.oRC : T.oRR) + idx;
+  const bool mine = quarter == 0 && idx < dim;
+  float old[3] = {0.f, 0.f, 0.f};
+  if (mine)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) old[k] = acc3[(size_t)k * pd];
   double acc = 0.0;
   if (rc_sum_coop(count, valid)) {   // workgroup-uniform
-    for (int i = 0; i < valid; ++i) {
-      const double v1 = strided_sum_coop(pbase + i, count, (size_t)dim, tree);
-      if ((int)threadIdx.x == i) acc = v1;
-    }
-  } else if (idx < dim) {
-    acc = strided_sum(pbase + threadIdx.x, count, (size_t)dim);
-  }
-  if (!it.is_col) {
-    if (idx < T.m) {
-      const float R = (float)(acc / (double)T.n);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        float* rk = st + 4 * (size_t)T.padN + (size_t)k * T.padm;
-        const float b = A.fac_decay[k];
-        const float r = b * rk[idx] + (1.0f - b) * R;
-        rk[idx] = r;
-        const float rr = rsqrtf(r + A.eps_acc);
-        ws[T.oRR + (size_t)k * T.padm + idx] = rr;
-        v[k] = r;
-        v[3 + k] = r * r;
-        v[6 + k] = rr * rr;
-      }
+    for (int r = 0; r < valid; ++r) {
+      const double v1 = strided_sum_coop(pbase + r, count, (size_t)dim, tree);
+      if (i == r) acc = v1;
     }
   } else {
-    if (idx < T.n) {
-      const float C = (float)(acc / (double)T.m);
+    if (idx < dim && quarter < count)
+      acc = strided_sum(pbase + i + (size_t)quarter * dim, (count - quarter + nq - 1) / nq, (size_t)nq * dim);
+    if (count > 1 && nq > 1) {   // workgroup-uniform
+      tree[threadIdx.x] = acc;
+      __syncthreads();
+      if (quarter == 0) acc = (tree[i] + tree[kBlock + i]) + (tree[2 * kBlock + i] + tree[3 * kBlock + i]);
+    }
+  }
+  if (mine) {
+    const float mean = (float)(acc / (double)(it.is_col ? T.m : T.n));
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        float* ck = st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + (size_t)k * T.padn;
-        const float b = A.fac_decay[k];
-        const float c = b * ck[idx] + (1.0f - b) * C;
-        ck[idx] = c;
-        const float rc = rsqrtf(c + A.eps_acc);
-        ws[T.oRC + (size_t)k * T.padn + idx] = rc;
-        v[3 + k] = c * c;
-        v[6 + k] = rc * rc;
-      }
+    for (int k = 0; k < 3; ++k) {
+      const float b = A.fac_decay[k];
+      const float r = b * old[k] + (1.0f - b) * mean;
+      acc3[(size_t)k * pd] = r;
+      const float rr = rsqrtf(r + A.eps_acc);
+      inv3[(size_t)k * pd] = rr;
+      v[k] = r;   // (the columns' plain sum is not used)
+      v[3 + k] = r * r;
+      v[6 + k] = rr * rr;
     }
   }
   const int slot = it.is_col ? T.nrblk + it.blk : it.blk;
@@ -342,7 +356,10 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
   if (L.n_rcitems == 0) return;
   const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
   const int extra = M.n_slices ? kMixJSplit * ((4 * M.HL + kWave - 1) / kWave) : 0;
-  hipLaunchKernelGGL(k_rc_update, dim3(L.n_rcitems + extra), dim3(kBlock), 0, s, L.tensors, L.rcitems, L.ws, A,
+  // The wide form shortens the chain of loads; on longer lists its workgroups no longer all fit on the chip at once and its
+  // idle wavefronts cost more than that (2219 tensors: 46 us narrow, 154 us wide).
+  const int threads = L.n_rcitems + extra <= 512 ? kRcMaxThreads : kBlock;
+  hipLaunchKernelGGL(k_rc_update, dim3(L.n_rcitems + extra), dim3(threads), 0, s, L.tensors, L.rcitems, L.ws, A,
                      L.n_rcitems, M);
 }
 
@@ -546,12 +563,16 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, bool write_state, hi
 // ----------------------------------------------------------------------------- finalize
 
 // One workgroup per tensor. Reduces every partial in a fixed order (double accumulation),
-// then writes s_f, the per-feature scale factors and the prepared first layer.
-__global__ void __launch_bounds__(kBlock) k_finalize(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
+// then writes s_f, the per-feature scale factors and the prepared first layer. The 32 sums (17 statistics over the tiles,
+// 9 over the row blocks, 6 over the column blocks) are one column of threads each, cut into blockDim / 32 interleaved
+// segments: the kernel is a chain of load latencies, and this way it is one batch of loads for up to 1024 tiles
+// (1000x1000: 7.9 -> 4.8 us from eight segments and three such phases; six tensors of 0.3 M elements 5.2 -> 4.9 us).
+constexpr int kFinSegs = 32;
+__global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                      StepArgs A, WeightsDev W, float* __restrict__ lstm_u, int tensor0,
                                                      int* __restrict__ apply_counter) {
-  __shared__ double part[8][32];
-  __shared__ double tot[48];
+  __shared__ double part[kFinSegs][32];
+  __shared__ double tot[32];
   __shared__ float s_stats[32], s_scale[32], s_tfeat[LOPT_N_TIME], s_lfeat[LOPT_N_LOSS];
   const int ti = tensor0 + (int)blockIdx.x;
   const TensorDev& T = tensors[ti];
@@ -568,38 +589,24 @@ __global__ void __launch_bounds__(kBlock) k_finalize(const TensorDev* __restrict
     const double psi = copysign(log1p(fabs(l)), l);
     s_lfeat[threadIdx.x - 96] = (float)tanh(psi / xs[threadIdx.x - 96]);
   }
-  const int q = threadIdx.x & 31, seg = threadIdx.x >> 5;
-  const int ntiles = T.nrt * T.nct;
-  // per-element statistics: 17 sums over the tiles
-  double a = 0.0;
-  if (q < kNStat && seg < ntiles)   // thread (seg, q): tiles seg, seg + 8, ...
-    a = strided_sum(ws + T.oStatPart + q + (size_t)seg * kStatStride, (ntiles - seg + 7) / 8, (size_t)8 * kStatStride);
-  part[seg][q] = a;
+  const int q = threadIdx.x & 31, seg = threadIdx.x >> 5, n_seg = blockDim.x >> 5;
+  // tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25 sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps)
+  {
+    const float* base;
+    int count, stride;
+    if (q < kNStat) { base = ws + T.oStatPart + q; count = T.nrt * T.nct; stride = kStatStride; }
+    else if (q < 26) { base = ws + T.oRcPart + (q - kNStat); count = T.nrblk; stride = kRcStride; }
+    else { base = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3); count = T.ncblk; stride = kRcStride; }
+    double a = 0.0;
+    if (seg < count)   // thread (seg, q): terms seg, seg + n_seg, ...
+      a = strided_sum(base + (size_t)seg * stride, (count - seg + n_seg - 1) / n_seg, (size_t)n_seg * stride);
+    part[seg][q] = a;
+  }
   __syncthreads();
   if (threadIdx.x < 32) {
     double s = 0.0;
-    for (int k = 0; k < 8; ++k) s += part[k][q];
+    for (int k = 0; k < n_seg; ++k) s += part[k][q];
     tot[q] = s;
-  }
-  __syncthreads();
-  // row partials (9 sums over the row blocks) then column partials (slots 3..8 used)
-  a = 0.0;
-  if (q < 9) {
-    const float* rp = ws + T.oRcPart + q;
-#pragma unroll 4
-    for (int i = seg; i < T.nrblk; i += 8) a += (double)rp[(size_t)i * kRcStride];
-  } else if (q >= 16 && q < 25) {
-    const float* cp = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 16);
-#pragma unroll 4
-    for (int i = seg; i < T.ncblk; i += 8) a += (double)cp[(size_t)i * kRcStride];
-  }
-  part[seg][q] = a;
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    double s = 0.0;
-    for (int k = 0; k < 8; ++k) s += part[k][q];
-    if (q < 9) tot[17 + q] = s;                    // 17..19 sum r, 20..22 sum r^2, 23..25 sum 1/(r+eps)
-    else if (q >= 19 && q < 25) tot[26 + (q - 19)] = s;  // 26..28 sum c^2, 29..31 sum 1/(c+eps)
   }
   __syncthreads();
   if (threadIdx.x < 32) {
@@ -631,11 +638,11 @@ __global__ void __launch_bounds__(kBlock) k_finalize(const TensorDev* __restrict
     // the un-normalized time features only shift the bias.
     const int H = A.H, HP = A.HP;
     float* prep = ws + T.oPrep;
-    for (int i = threadIdx.x; i < LOPT_N_ELEM_FEATS * HP; i += kBlock) {
+    for (int i = threadIdx.x; i < LOPT_N_ELEM_FEATS * HP; i += (int)blockDim.x) {
       const int f = i / HP, u = i - f * HP;
       prep[i] = u < H ? W.mlp[f * H + u] * s_scale[f] : 0.f;
     }
-    for (int u = threadIdx.x; u < HP; u += kBlock) {
+    for (int u = threadIdx.x; u < HP; u += (int)blockDim.x) {
       float b = 0.f;
       if (u < H) {
         b = W.mlp[LOPT_D_SMALL_FC * H + u];
@@ -659,7 +666,10 @@ __global__ void __launch_bounds__(kBlock) k_finalize(const TensorDev* __restrict
 
 void launch_finalize(const Launch& L, const StepArgs& A, const WeightsDev& W, float* lstm_u, hipStream_t s) {
   if (L.n_tensors == 0) return;
-  hipLaunchKernelGGL(k_finalize, dim3(L.n_tensors), dim3(kBlock), 0, s, L.tensors, L.ws, A, W, lstm_u, L.tensor0,
+  // long lists have more workgroups than the chip holds at once: there small ones win; beside the apply pass of another
+  // tensor group only small ones find room (eight groups of 388 tensors: 18 us a launch, 53 us with 1024 threads)
+  const int threads = L.n_tensors <= 512 && !L.beside_apply ? 32 * kFinSegs : kBlock;
+  hipLaunchKernelGGL(k_finalize, dim3(L.n_tensors), dim3(threads), 0, s, L.tensors, L.ws, A, W, lstm_u, L.tensor0,
                      L.apply_counter);
 }
 
