@@ -67,8 +67,8 @@ typedef enum {
 
 typedef enum { LOPT_SMALL_FC = 0, LOPT_VELO = 1 } lopt_kind;
 
-/* Apply kernel for small_fc_lopt with hidden width 32 (other widths and VeLO have one kernel each; VeLO honours
- * LOPT_APPLY_VALU). None changes what is computed beyond rounding. */
+/* Apply kernel for small_fc_lopt with hidden width 17..32 (narrower widths run on the fp32 matrix cores, VeLO has one
+ * kernel per width; both honour LOPT_APPLY_VALU). None changes what is computed beyond rounding. */
 typedef enum {
   LOPT_APPLY_AUTO = 0,      /* = LOPT_APPLY_MFMA_F16S */
   LOPT_APPLY_VALU = 1,      /* fp32 vector ALU */
@@ -76,8 +76,8 @@ typedef enum {
   LOPT_APPLY_MFMA_F16S = 3  /* matrix cores on fp16 hi+lo operand pairs, fp32 accumulate; column strips, software-pipelined */
 } lopt_apply_kernel;
 
-/* Which pass writes the new momentum / second-moment accumulators M_1..3, V when the apply kernel is one of the two
- * default ones: LOPT_APPLY_MFMA_F16S (small_fc_lopt, hidden 32) or the width-4 VeLO kernel. Every other kernel
+/* Which pass writes the new momentum / second-moment accumulators M_1..3, V when the apply kernel is one of the
+ * default ones: LOPT_APPLY_MFMA_F16S, the one for small_fc_lopt of width 16 or less, or the width-4 VeLO kernel. Every other kernel
  * combination writes them in the statistics pass. The values are the same bit for bit either way: both passes form
  * them with the same fp32 operations from the same inputs. */
 typedef enum {

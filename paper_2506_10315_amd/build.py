@@ -21,6 +21,7 @@ UNITS = [
     ("lopt_apply_mfma.hip", "apply_mfma", []),
     ("lopt_apply_f16s.hip", "apply_f16s", []),
     ("lopt_apply_velo4.hip", "apply_velo4", []),
+    ("lopt_apply_fc4x.hip", "apply_fc4x", []),
 ]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

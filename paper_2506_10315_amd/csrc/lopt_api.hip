@@ -759,16 +759,18 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   // 2^30 - 255 or more columns breaks (it takes the fp32 kernel)
   bool strip_ok = mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
-  // With the two default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
+  // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
   // statistics pass only reads them: 24 + 44 instead of 40 + 28 bytes per element (configuration field state_pass).
   // The read-only statistics stream runs at 83 % of the HBM rate against 67 % for the read-write one; the strip-form
   // kernel is bound by instruction issue and takes the extra stores in its stride, the VeLO kernel is HBM-bound and
   // gives part of the gain back.
   const bool velo4_ok = ctx->cfg.kind == LOPT_VELO && ctx->apply_variant != LOPT_APPLY_VALU && apply_velo4_available(A);
-  const bool state_in_apply = (strip_ok || velo4_ok) && ctx->state_in_apply;
+  const bool fc4x_ok = ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
+  const bool state_in_apply = (strip_ok || fc4x_ok || velo4_ok) && ctx->state_in_apply;
   auto launch_apply = [&](const Launch& La) {
     if (strip_ok) launch_apply_f16s(La, A, ctx->W, state_in_apply, stream);
     else if (mfma_ok && ctx->apply_variant != LOPT_APPLY_VALU) launch_apply_mfma(La, A, ctx->W, stream);
+    else if (fc4x_ok) launch_apply_fc4x(La, A, ctx->W, state_in_apply, stream);
     else if (ctx->cfg.kind == LOPT_SMALL_FC) launch_apply_small_fc(La, A, ctx->W, stream);
     else if (velo4_ok) launch_apply_velo4(La, A, state_in_apply, stream);
     else launch_apply_velo(La, A, ctx->W, stream);

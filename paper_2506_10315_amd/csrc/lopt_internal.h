@@ -122,6 +122,8 @@ void launch_apply_small_fc(const Launch&, const StepArgs&, const WeightsDev&, hi
 void launch_apply_velo(const Launch&, const StepArgs&, const WeightsDev&, hipStream_t);
 bool apply_mfma_available(const StepArgs&);
 void launch_apply_mfma(const Launch&, const StepArgs&, const WeightsDev&, hipStream_t);
+bool apply_fc4x_available(const StepArgs&);
+void launch_apply_fc4x(const Launch&, const StepArgs&, const WeightsDev&, bool update_state, hipStream_t);
 bool apply_velo4_available(const StepArgs&);
 void launch_apply_velo4(const Launch&, const StepArgs&, bool update_state, hipStream_t);
 void launch_apply_f16s(const Launch&, const StepArgs&, const WeightsDev&, bool update_state, hipStream_t);

@@ -65,6 +65,18 @@ def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass)
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
+def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
+    # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of up to 128 rows x 128 columns,
+    # 64 columns a wavefront: one segment, two segments, ragged second tiles, rows off and on the 16- and 128-byte grids,
+    # heights around one row per wavefront and the tile; the accumulators written in either pass
+    cfg = Hn.make_cfg("small_fc_lopt", hidden=hidden, state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=30 + hidden)
+    shapes = [(1, 1), (3, 15), (5, 17), (2, 63), (129, 64), (17, 65), (16, 127), (260, 128), (9, 129), (31, 193), (7, 256), (70, 300)]
+    worst = Hn.run_free(Hn.Case(114, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("hidden,lstm_hidden,n_bank", [(3, 33, 5), (4, 512, 256)])
 def test_velo_long_list_takes_the_batched_hypernetwork_head(hidden, lstm_hidden, n_bank):
     # from 1024 tensors on the head of the hypernetwork runs as two batched matrix products and a scatter kernel
