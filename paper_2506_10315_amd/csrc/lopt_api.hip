@@ -281,6 +281,16 @@ void build_plan(const lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d, Plan* 
     std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
+  // Short lists: the smallest even apply-tile height at which every tile has a workgroup slot of its own (two per CU), if
+  // that is at most 32 rows: the launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the
+  // graded heights below gave 650 tiles and a second, nearly empty round).
+  int ar_short = 0;
+  for (int ar : {2, 4, 6, 8, 12, 16, 20, 24, 32}) {
+    uint64_t tiles = 0;
+    for (size_t i = 0; i < n; ++i)
+      tiles += (uint64_t)((d[i].rows + ar - 1) / ar) * (uint64_t)((d[i].cols + kApplyCols - 1) / kApplyCols);
+    if (tiles <= 2ull * ctx->n_cu) { ar_short = ar; break; }
+  }
   for (size_t i = 0; i < n; ++i) {
     TensorDev& T = pl->tensors[i];
     const int m = (int)d[i].rows, nn = (int)d[i].cols;
@@ -322,6 +332,7 @@ void build_plan(const lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d, Plan* 
       if (pos * 100 >= gt * 88) AR /= 4;
       else if (pos * 100 >= gt * 70) AR /= 2;
       if (AR < 8) AR = 8;
+      if (ar_short) AR = ar_short;
       const int rows = m - ar0 < AR ? m - ar0 : AR;
       for (int ac0 = 0; ac0 < nn; ac0 += kApplyCols) pl->atiles.push_back(ApplyTileDev{(int)i, ar0, ac0, rows});
       ar0 += rows;
@@ -749,8 +760,6 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   if ((st = upload_tables(ctx, tb, stream)) != LOPT_OK) return st;
   // workspace base rounded up to 256 bytes (lopt_state_bytes adds the slack)
   float* ws = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
-  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
-           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0};
   const bool profiling = ctx->profiling && !use_static;   // per-pass timing creates events: not on the static path
   StepArgs A = make_args(ctx, step, lr, weight_decay, (int)n);
   const bool mfma_ok = apply_mfma_available(A);
@@ -759,6 +768,8 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   // 2^30 - 255 or more columns breaks (it takes the fp32 kernel)
   bool strip_ok = mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
+  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
+           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0};
   // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
   // statistics pass only reads them: 24 + 44 instead of 40 + 28 bytes per element (configuration field state_pass).
   // The read-only statistics stream runs at 83 % of the HBM rate against 67 % for the read-write one; the strip-form

@@ -61,6 +61,8 @@ namespace {
 
 constexpr int kStripCols = 32;
 constexpr int kRowSlack = 16;   // rows of zeros after the tile in the LDS row tables (read by the pipeline's run-out)
+constexpr int kRowPre = 2;      // rows per thread whose factors are loaded ahead of the tile's set-up
+constexpr int kRowTrip = 4;     // and per trip for the rest of a tall tile
 
 #ifndef LOPT_F16S_NSETS
 #define LOPT_F16S_NSETS 2
@@ -242,6 +244,10 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   __shared__ int s_tile;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
+  // the first tile is the workgroup's number (the launch has no more workgroups than tiles); its records are on their way
+  // while the weights are packed
+  ApplyTileDev at = atiles[blockIdx.x];
+  const TensorDev* Tp = &tensors[at.tensor];
 
   // ---- what does not depend on the tile: W3 table, packed weights, scalars
   if (threadIdx.x < 16) {
@@ -286,82 +292,18 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   C.b_one_lo = pk8(half ? 0u : one2, 0u, 0u, 0u);
   C.b_one_hi = pk8(half ? one2 : 0u, 0u, 0u, 0u);
 
-  // ---- tiles are handed out through a counter: a workgroup takes the next one when it is done with its last,
+  // ---- the next tiles are handed out through a counter: a workgroup takes the next one when it is done with its last,
   // so the launch is as many workgroups as fit on the chip and ends without a ragged last round
   for (;;) {
-  if (threadIdx.x == 0) s_tile = atomicAdd(next_tile, 1);
-  __syncthreads();   // also: every wavefront is done with the previous tile's LDS tables
-  const int tile_id = s_tile;
-  if (tile_id >= n_atiles) break;
-  const ApplyTileDev at = atiles[tile_id];
-  const TensorDev& T = tensors[at.tensor];
+  int next_id = 0;
+  if (threadIdx.x == 0) next_id = (int)gridDim.x + atomicAdd(next_tile, 1);   // the answer is needed at the end of this tile
+  const TensorDev& T = *Tp;
   const int n = T.n, m = T.m;
   const float* __restrict__ prep = ws + T.oPrep;  // W1s[28][32] (normalization folded in), b1'[32]
   const int col = at.c0 + wave * kStripCols + l32;
   const bool col_ok = col < n;
   const int r0 = at.r0, r1 = at.r0 + at.rows;
   const float* __restrict__ rst = T.st + 4 * (size_t)T.padN;   // r_k[3][padm] then c_k[3][padn]
-  {
-    const int t = threadIdx.x;
-    if (t < 192) {
-      L.w1row[t >> 5][t & 31] = prep[row_feat(t >> 5) * kH + (t & 31)];
-      L.w1col[t >> 5][t & 31] = prep[col_feat(t >> 5) * kH + (t & 31)];
-    } else if (t < 224) L.b1[t - 192] = prep[kNF * kH + (t - 192)];
-  }
-#pragma unroll
-  for (int i = 0; i < 10; ++i) C.sc[i] = ws[T.oScale + i];
-  __syncthreads();   // w1row, w1col, b1
-  // ---- column part of layer 1's C operand for this lane's column: units unit_of(v, half), v = 0..15
-  {
-    float cf[6];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      cf[k] = col_ok ? rst[3 * (size_t)T.padm + (size_t)k * T.padn + col] : 0.f;
-      cf[3 + k] = col_ok ? ws[T.oRC + (size_t)k * T.padn + col] : 0.f;
-      C.fg[k] = cf[3 + k] * ws[T.oScale + 10 + k];
-      C.fm[k] = cf[3 + k] * ws[T.oScale + 25 + k];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int f = 0; f < 6; ++f) {
-        const float4 w = *reinterpret_cast<const float4*>(&L.w1col[f][8 * q + 4 * half]);
-        a.x += cf[f] * w.x; a.y += cf[f] * w.y; a.z += cf[f] * w.z; a.w += cf[f] * w.w;
-      }
-      C.colc[4 * q] = a.x; C.colc[4 * q + 1] = a.y; C.colc[4 * q + 2] = a.z; C.colc[4 * q + 3] = a.w;
-    }
-  }
-  // ---- row part of the tile's rows -> LDS (thread: unit t & 31, rows (t >> 5), +8, ...); rows past the tile
-  // hold zeros: the injection MFMA multiplies them by 0, and the pipeline's run-out rounds read them
-  {
-    const int u = threadIdx.x & 31;
-    float w1r[6];
-#pragma unroll
-    for (int f = 0; f < 6; ++f) w1r[f] = L.w1row[f][u];
-    const float b1u = L.b1[u];
-    for (int lrow = threadIdx.x >> 5; lrow < at.rows + kRowSlack; lrow += kBlock / 32) {
-      const int row = r0 + lrow;
-      unsigned pk = 0u;
-      float4 rs4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (row < r1) {
-        float rb = b1u;
-        float rr[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          rr[k] = ws[T.oRR + (size_t)k * T.padm + row];
-          rb += rst[(size_t)k * T.padm + row] * w1r[k];
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k) rb += rr[k] * w1r[3 + k];
-        pk = split1(rb);
-        rs4 = make_float4(rr[0], rr[1], rr[2], 0.f);
-      }
-      L.rowinj[lrow][u] = pk;
-      if (u == 0) L.rowrs[lrow] = rs4;
-    }
-  }
-  __syncthreads();
 
   // ---- streaming: lanes of the lower half read row q, lanes of the upper half row q + 1 (q - r0 even,
   // wave-uniform). Loads are unconditional: a column past the end reads the last column, the upper half of a
@@ -384,6 +326,97 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     const int qc = in_tile ? q : r1 - 1;
     return load_elem(S, (size_t)qc * (size_t)n + c0, in_tile && qc + 1 < m ? voff_pair : colc_);
   };
+
+  // ---- the loads of the set-up leave before the first wait for one: the prepared first layer, the scales, this lane's
+  // column, the first rows' factors (thread: unit t & 31, rows (t >> 5), +8, ...). A short list's launch is little else than
+  // this chain of latencies (toy list of three tensors 13.7 -> 12.1 us, 1000x1000 29.0 -> 27.1 us with the equal tiles of the planner).
+  const int su = threadIdx.x & 31, srow = threadIdx.x >> 5;
+  float wr = 0.f, wc = 0.f, bb = 0.f;
+  if (srow < 6) {
+    wr = prep[row_feat(srow) * kH + su];
+    wc = prep[col_feat(srow) * kH + su];
+  } else if (srow == 6) bb = prep[kNF * kH + su];
+  float cf[6];
+  const int colx = col_ok ? col : n - 1;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cf[k] = rst[3 * (size_t)T.padm + (size_t)k * T.padn + colx];
+    cf[3 + k] = ws[T.oRC + (size_t)k * T.padn + colx];
+  }
+  float rrow[kRowPre][6];
+#pragma unroll
+  for (int i = 0; i < kRowPre; ++i) {
+    const int row = min(r0 + srow + 8 * i, r1 - 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      rrow[i][k] = rst[(size_t)k * T.padm + row];
+      rrow[i][3 + k] = ws[T.oRR + (size_t)k * T.padm + row];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 10; ++i) C.sc[i] = ws[T.oScale + i];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    C.fg[k] = cf[3 + k] * ws[T.oScale + 10 + k];
+    C.fm[k] = cf[3 + k] * ws[T.oScale + 25 + k];
+  }
+  if (srow < 6) {
+    L.w1row[srow][su] = wr;
+    L.w1col[srow][su] = wc;
+  } else if (srow == 6) L.b1[su] = bb;
+  __syncthreads();   // w1row, w1col, b1
+  // ---- column part of layer 1's C operand for this lane's column: units unit_of(v, half), v = 0..15
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      const float4 w = *reinterpret_cast<const float4*>(&L.w1col[f][8 * q + 4 * half]);
+      a.x += cf[f] * w.x; a.y += cf[f] * w.y; a.z += cf[f] * w.z; a.w += cf[f] * w.w;
+    }
+    C.colc[4 * q] = a.x; C.colc[4 * q + 1] = a.y; C.colc[4 * q + 2] = a.z; C.colc[4 * q + 3] = a.w;
+  }
+  // ---- row part of the tile's rows -> LDS; rows past the tile hold zeros: the injection MFMA multiplies them by 0, and
+  // the pipeline's run-out rounds read them
+  {
+    float w1r[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) w1r[f] = L.w1row[f][su];
+    const float b1u = L.b1[su];
+    auto put_row = [&](int lrow, const float (&x)[6]) __attribute__((always_inline)) {
+      const bool in = r0 + lrow < r1;
+      float rb = b1u;
+#pragma unroll
+      for (int f = 0; f < 6; ++f) rb += x[f] * w1r[f];
+      L.rowinj[lrow][su] = in ? split1(rb) : 0u;
+      if (su == 0) L.rowrs[lrow] = in ? make_float4(x[3], x[4], x[5], 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    const int n_rows = at.rows + kRowSlack;
+#pragma unroll
+    for (int i = 0; i < kRowPre; ++i)
+      if (srow + 8 * i < n_rows) put_row(srow + 8 * i, rrow[i]);
+    for (int lrow = srow + 8 * kRowPre; lrow < n_rows; lrow += 8 * kRowTrip) {
+      float x[kRowTrip][6];   // kRowTrip rows of loads in flight
+#pragma unroll
+      for (int i = 0; i < kRowTrip; ++i) {
+        const int row = min(r0 + lrow + 8 * i, r1 - 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          x[i][k] = rst[(size_t)k * T.padm + row];
+          x[i][3 + k] = ws[T.oRR + (size_t)k * T.padm + row];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kRowTrip; ++i)
+        if (lrow + 8 * i < n_rows) put_row(lrow + 8 * i, x[i]);
+    }
+  }
+  // the first rounds of the streams: round k (rows r0 + 2k, +1) goes through register set k % kSets. Not earlier: with them
+  // in flight the set-up above needs more registers than leave room for a statistics workgroup on the CU (216)
+  Elem es[kSets];
+#pragma unroll
+  for (int s = 0; s < kSets; ++s) es[s] = fetch(r0 + 2 * s);
+  __syncthreads();
 
   // One step of the pipeline. On entry: h2a/h2b/p_e belong to the round of rows qe, qe+1 (layer 3 and update
   // pending, if DO_E), `f` holds the swapped features of the round at qe + 2 (its layer 1 pending) and `e` the
@@ -510,11 +543,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     LOPT_SB();
   };
 
-  // ---- prologue: features of the first round with nothing to hide behind, then one step without layer 3.
-  // Round k (rows r0 + 2k, +1) streams through register set k % kSets.
-  Elem es[kSets];
-#pragma unroll
-  for (int s = 0; s < kSets; ++s) es[s] = fetch(r0 + 2 * s);
+  // ---- prologue: features of the first round with nothing to hide behind, then one step without layer 3
   {
     const float4 rr4 = L.rowrs[half];
     FeatTmp t;
@@ -533,6 +562,14 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     for (int s = 0; s < kSets; ++s)   // update rows q + 2s, +1 (nothing is stored past the tile); features of round +2
       step(std::true_type{}, es[(s + 2) % kSets], q + 2 * s);
   }
+
+  if (threadIdx.x == 0) s_tile = next_id;
+  __syncthreads();   // also: every wavefront is done with this tile's LDS tables
+  const int tile_id = s_tile;
+  if (tile_id >= n_atiles) break;
+  at = atiles[tile_id];
+  Tp = &tensors[at.tensor];
+  __syncthreads();   // s_tile has been read
   }   // tile loop
 }
 
