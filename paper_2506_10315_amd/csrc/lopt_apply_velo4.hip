@@ -65,10 +65,9 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
   const f32x4 c2 = {B2[0], B2[1], B2[2], B2[3]};
   const f32x4 c3 = {B3[0], B3[1], 0.f, 0.f};
 
-  const int n = T.n, m = T.m;
-  const int col = tile.tj * kTileCols + 4 * lane;
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
+  const int n = T.n;
+  const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(wave));
+  const int col = w.tj * kTileCols + 4 * lane;
   float4 rc[3];
   f32x4 colv[4];   // per column of this lane: sum over the 6 column-constant features, for the 4 hidden units
   {
@@ -102,7 +101,8 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
   const float bm1 = A.mom_decay[0], bm2 = A.mom_decay[1], bm3 = A.mom_decay[2], bv = A.rms_decay;
   const float am1 = 1.0f - bm1, am2 = 1.0f - bm2, am3 = 1.0f - bm3, av = 1.0f - bv;
 
-  for (int r = r0 + wave; r < r1; r += 4) {
+  for (int i = 0; i < w.cnt; ++i) {
+    const int r = walk_row(w, i);
     const size_t ro = (size_t)r * n;
     const float4 g4 = load4x<NT>(T.g + ro, col, n);
     const float4 p4 = load4x<NT>(T.p + ro, col, n);

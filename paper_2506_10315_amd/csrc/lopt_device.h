@@ -89,6 +89,33 @@ __device__ __forceinline__ void store4s(float* __restrict__ row, int col, int n,
   if (col + 3 < n) __builtin_nontemporal_store(v.w, row + col + 3);
 }
 
+// The rows and the 256-column segment of a tile that one of the workgroup's four wavefronts streams (for passes that may cut
+// the elements in any way). Workgroups advance through their rows more or less in step, and tiles of power-of-two pitch
+// then keep meeting on the same few of the 128 memory channels (4 KB interleave: rows 512 KB apart share one). Where the
+// row is a multiple of 4 KB the walk is changed, by what measured best (VeLO step, four tensors of 16.8 M elements):
+//   up to 12 KB  the four workgroups of a group of four adjacent tiles cut their common rows into quarters and every wavefront
+//                takes a segment of its own, so that a row access of the workgroup is 4 KB contiguous
+//                (1024 columns 1.009 -> 0.907 ms, 2048 1.161 -> 0.894, 3072 0.915 -> 0.890)
+//   longer       every fourth row, as for other rows, but starting at a place that differs from tile to tile
+//                (4096 columns 0.932 -> 0.887 ms, 6144 0.934 -> 0.882, 8192 0.875 -> 0.867; the first form: 0.945, 0.928, 1.10)
+// Other rows measured the same or up to 4 % slower with either, and keep the plain walk.
+struct RowWalk { int tj, base, cnt, rot, step; };
+__device__ __forceinline__ RowWalk row_walk(const TensorDev& T, const TileDev& tile, int wave) {
+  const int r0 = tile.ti * T.TR;
+  const bool pitch = (T.n & 1023) == 0;
+  if (pitch && T.n <= 3072) {   // n % 1024 == 0: every group of four tiles is complete
+    const int quarter = T.TR / 4, b = r0 + (tile.tj & 3) * quarter;   // TR is a multiple of 8
+    return RowWalk{(tile.tj & ~3) + wave, b, min(quarter, T.m - b), 0, 1};
+  }
+  const int cnt = (min(T.TR, T.m - r0) - wave + 3) >> 2;   // rows r0 + wave + 4 i
+  return RowWalk{tile.tj, r0 + wave, cnt, pitch && cnt > 0 ? tile.ti * 7 % cnt : 0, 4};
+}
+__device__ __forceinline__ int walk_row(const RowWalk& w, int i) {   // 0 <= i < cnt (cnt <= 0: no rows)
+  int k = i + w.rot;
+  k = k >= w.cnt ? k - w.cnt : k;
+  return w.base + w.step * k;
+}
+
 __device__ __forceinline__ float get(const float4& v, int i) {
   return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }

@@ -465,12 +465,11 @@ typedef f32x4v __attribute__((address_space(1)))* gv4;
 template <bool RAW_RCP, bool WRITE>
 __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                const StepArgs& A, float (&acc)[kNStat]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = T.n, m = T.m;
-  const int col = tile.tj * kTileCols + 4 * lane;
+  const int lane = threadIdx.x & 63;
+  const int n = T.n;
+  const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const int col = w.tj * kTileCols + 4 * lane;
   if (col >= n) return;
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
   float rc2[3][4];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -482,7 +481,8 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
   const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
   const float eps = A.eps_acc;
   const float clip2 = 0.1f * 0.1f;
-  for (int r = r0 + wave; r < r1; r += 4) {
+  for (int i = 0; i < w.cnt; ++i) {
+    const int r = walk_row(w, i);
     const size_t ro = (size_t)r * n + col;   // a multiple of 4: every section starts 16-byte aligned
     const f32x4v g4 = __builtin_nontemporal_load((gcv4)(T.g + ro));
     const f32x4v p4 = __builtin_nontemporal_load((gcv4)(T.p + ro));
