@@ -85,8 +85,9 @@ struct WeightsDev {
 // Input slots of the LSTM rounded up to whole octets; row length of the folded head (P columns and the step size's).
 __host__ __device__ inline int lstm_k_pad(int HL) { return kLstmInPad + (HL + 7) / 8 * 8; }
 __host__ __device__ inline int head_ld(int P) { return (P + 1 + 3) / 4 * 4; }
-// The folded head reads (H_L + 1) (P + 1) weights per tensor, the two products H_L K + K P.
-inline bool head_folds(int HL, int K, int P) { return (size_t)HL * P <= (size_t)HL * K + (size_t)K * P; }
+// The folded head reads (H_L + 1) (P + 1) weights per tensor, the two products H_L K + K P. (K >= 4: the folded form's scratch
+// row, P + 1 rounded up, is then never longer than the K + P floats of the other.)
+inline bool head_folds(int HL, int K, int P) { return K >= 4 && (size_t)HL * P <= (size_t)HL * K + (size_t)K * P; }
 
 struct Launch {
   const TensorDev* tensors;

@@ -65,6 +65,35 @@ def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass)
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("velo", "apply"), ("velo", "stats")])
+def test_rows_of_a_multiple_of_4_kb(kind, state_pass):
+    # widths that are a multiple of 1024 are walked by groups of four tiles (up to 3072 columns) or from a start that differs
+    # from tile to tile (beyond): heights below, at and above a tile and its quarters; 1280 columns keep the plain walk
+    cfg = Hn.make_cfg(kind, state_pass=state_pass) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8,
+                                                                                             state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=24)
+    shapes = [(70, 1024), (1, 1024), (9, 2048), (64, 2048), (131, 3072), (3, 3072), (67, 4096), (2, 5120), (150, 4096), (66, 1280)]
+    worst = Hn.run_free(Hn.Case(115, _specs(shapes), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("hidden,lstm_hidden,n_bank,count", [(3, 37, 64, 7), (7, 64, 128, 33), (4, 5, 300, 3), (8, 200, 400, 40),
+                                                             (7, 64, 128, 1030)])
+def test_velo_folded_head_and_lstm_octets(hidden, lstm_hidden, n_bank, count):
+    # banks large enough for the head's two products to be folded into one matrix: padded widths, more than 256 columns (the
+    # step-size column in a second block), LSTM widths off the octet and unit grids, tensor counts around a block of 32, and
+    # the batched form. Tensors have at least 8 elements: the statistic of M_i / sqrt(V) of a single element carries the
+    # relative rounding error of beta M + (1 - beta) g, 2^-24 (|beta M| + |(1 - beta) g|) / |their sum|, which has no bound
+    # when the two nearly cancel (a one-element tensor of this seed: factor 1005, 2.4e-5); in a mean over 8 the other terms
+    # keep the sum's size.
+    cfg = Hn.make_cfg("velo", hidden=hidden, lstm_hidden=lstm_hidden, n_bank=n_bank)
+    w = Hn.random_weights(cfg, seed=40 + lstm_hidden)
+    r = np.random.default_rng(78)
+    shapes = [(7, 13), (33, 20)] + [(int(r.integers(8, 60)),) for _ in range(count - 2)]
+    worst = Hn.run_free(Hn.Case(116, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
 def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
     # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of up to 128 rows x 128 columns,
