@@ -147,9 +147,8 @@ struct lopt_ctx {
   int device = 0;
   int n_cu = 256;
   int HP = 0, F = 0, P = 0;
-  float* d_weights = nullptr;      // the uploaded blob
+  float* d_weights = nullptr;      // the uploaded blob; VeLO: behind it the hypernetwork's repacked weights
   float* d_tail = nullptr;         // small_fc_lopt: padded W2 b2 W3 b3
-  float* d_pack = nullptr;         // VeLO: the hypernetwork's weights in the layouts its kernels read
   WeightsDev W{};
   // cached plan + device tables: `heap` is library-allocated and grows with the list, `fixed` is the front of the
   // file-scope scratch array (lopt_step_static)
@@ -550,7 +549,14 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
   } while (0)
   CREATE_TRY(hipGetDevice(&ctx->device));
   CREATE_TRY(hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
-  CREATE_TRY(hipMalloc((void**)&ctx->d_weights, n_weights * sizeof(float)));
+  // one allocation: the uploaded blob, then (VeLO) the hypernetwork's weights in the layouts its kernels read
+  const bool folds = cfg->kind == LOPT_VELO && head_folds((int)cfg->lstm_hidden, (int)cfg->n_bank, ctx->P);
+  size_t lstm_n = 0, head_n = 0;
+  if (cfg->kind == LOPT_VELO) {
+    lstm_n = (cfg->lstm_hidden + 7) / 8 * (size_t)lstm_k_pad((int)cfg->lstm_hidden) * 32;
+    head_n = folds ? (cfg->lstm_hidden + 1) * (size_t)head_ld(ctx->P) : 0;
+  }
+  CREATE_TRY(hipMalloc((void**)&ctx->d_weights, (align64(n_weights) + lstm_n + head_n) * sizeof(float)));
   CREATE_TRY(hipMemcpy(ctx->d_weights, weights_host, n_weights * sizeof(float), hipMemcpyHostToDevice));
   CREATE_TRY(hipEventCreateWithFlags(&ctx->stage_ev, hipEventDisableTiming));
   CREATE_TRY(hipHostMalloc(&ctx->h_stage, kStageInitBytes, hipHostMallocDefault));
@@ -612,12 +618,10 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
     ctx->W.ws = w; w += HL;
     ctx->W.bs = w; w += 1;
     ctx->W.B = w;
-    const bool folds = head_folds((int)HL, (int)K, ctx->P);
-    const size_t lstm_n = (HL + 7) / 8 * (size_t)lstm_k_pad((int)HL) * 32, head_n = folds ? (HL + 1) * (size_t)head_ld(ctx->P) : 0;
-    CREATE_TRY(hipMalloc((void**)&ctx->d_pack, (lstm_n + head_n) * sizeof(float)));
-    ctx->W.lstm = ctx->d_pack;
-    ctx->W.head = folds ? ctx->d_pack + lstm_n : nullptr;
-    launch_velo_pack(ctx->W, (int)HL, (int)K, ctx->P, ctx->d_pack, folds ? ctx->d_pack + lstm_n : nullptr, nullptr);
+    float* pack = ctx->d_weights + align64(n_weights);
+    ctx->W.lstm = pack;
+    ctx->W.head = folds ? pack + lstm_n : nullptr;
+    launch_velo_pack(ctx->W, (int)HL, (int)K, ctx->P, pack, folds ? pack + lstm_n : nullptr, nullptr);
     CREATE_TRY(hipGetLastError());
     CREATE_TRY(hipStreamSynchronize(nullptr));   // steps may come on streams that do not wait for the default one
   }
@@ -631,7 +635,6 @@ void lopt_destroy(lopt_ctx* ctx) {
   if (!ctx) return;
   if (ctx->d_weights) (void)hipFree(ctx->d_weights);
   if (ctx->d_tail) (void)hipFree(ctx->d_tail);
-  if (ctx->d_pack) (void)hipFree(ctx->d_pack);
   if (ctx->heap.base) (void)hipFree(ctx->heap.base);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->stage_ev) (void)hipEventDestroy(ctx->stage_ev);

@@ -708,6 +708,7 @@ typedef float f32x16_l __attribute__((ext_vector_type(16)));
 // Weights in the order k_velo_lstm reads them: out[ub][k][8 gate + u] for unit 8 ub + u, zero past H_L in units and slots.
 __global__ void __launch_bounds__(kBlock) k_pack_lstm(WeightsDev W, int HL, int k_pad, float* __restrict__ out) {
   const int ub = blockIdx.x, G = 4 * HL;
+#pragma unroll 8
   for (int i = threadIdx.x; i < k_pad * 32; i += kBlock) {
     const int k = i >> 5, gate = (i >> 3) & 3, unit = 8 * ub + (i & 7);
     float v = 0.f;
@@ -819,13 +820,21 @@ void launch_velo_lstm(const Launch& L, const StepArgs& A, const WeightsDev& W, c
 // ---- the head with its two products folded into one at lopt_create (WeightsDev::head): theta = h (W_a B) + b_a B, with the
 // step-size row (ws, bs) as one more column, [H_L + 1][head_ld(P)], row H_L the constant. Formed in double, stored in fp32.
 __global__ void __launch_bounds__(kBlock) k_pack_head(WeightsDev W, int HL, int K, int P, int ld, float* __restrict__ out) {
-  const int u = blockIdx.x;   // 0 .. H_L
+  __shared__ float row[1024];   // this unit's coefficients of the bank's K <= 1024 rows
+  const int u = blockIdx.x;     // 0 .. H_L
+  for (int q = threadIdx.x; q < K; q += kBlock) row[q] = u < HL ? W.Wa[(size_t)u * K + q] : W.ba[q];
+  __syncthreads();
   for (int p = threadIdx.x; p < ld; p += kBlock) {
     double a = 0.0;
-    if (p < P)
-#pragma unroll 16
-      for (int q = 0; q < K; ++q) a += (double)(u < HL ? W.Wa[(size_t)u * K + q] : W.ba[q]) * (double)W.B[(size_t)q * P + p];
-    else if (p == P) a = u < HL ? W.ws[u] : W.bs[0];
+    if (p < P) {
+      for (int q0 = 0; q0 < K; q0 += 32) {   // 32 loads in flight
+        float t[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) t[k] = W.B[(size_t)min(q0 + k, K - 1) * P + p];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) a += q0 + k < K ? (double)row[q0 + k] * (double)t[k] : 0.0;
+      }
+    } else if (p == P) a = u < HL ? W.ws[u] : W.bs[0];
     out[(size_t)u * ld + p] = (float)a;
   }
 }
