@@ -1,5 +1,5 @@
-// Host side of the C boundary declared in include/lopt.h: argument validation, the planner that
-// turns a tensor list into the device tables the kernels walk, and the launch sequence of a step.
+// Host side of the C boundary declared in include/lopt.h: argument validation, the upload of the device tables that the
+// planner (lopt_plan.h) makes of a tensor list, and the launch sequence of a step.
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -10,15 +10,13 @@
 #include <string>
 #include <vector>
 
-#include "lopt_internal.h"
+#include "lopt_plan.h"
 
 using namespace lopt;
 
 namespace {
 
 thread_local std::string g_last_error;
-
-constexpr int kMaxGroups = 16;
 
 // ---- fixed scratch of lopt_step_static: device tables followed by the workspace. One copy per GPU, at an address
 // of its own on each; host code reaches it only through the pointer hipGetSymbolAddress returns for the current
@@ -31,9 +29,6 @@ std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices];        // per device: address of `scratch` there (null until a context is created on it)
 uint64_t g_scratch_owner[kMaxDevices];   // per device: id of the context whose tables the array holds (0 = none)
 std::atomic<uint64_t> g_next_ctx_id{1};
-
-inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
-inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
 
 int padded_hidden(int H) {
   for (int hp : {4, 8, 16, 32})
@@ -123,23 +118,6 @@ std::vector<float> equilibrate_small_fc(const float* w, int H) {
   return out;
 }
 
-struct Plan {
-  std::vector<lopt_tensor_desc> descs;
-  std::vector<TensorDev> tensors;   // pointers filled per call
-  std::vector<TileDev> tiles;
-  std::vector<RcItemDev> rcitems;
-  std::vector<ApplyTileDev> atiles;   // tiles of the strip-form apply kernel
-  std::vector<int> atile0;            // first apply tile of every tensor
-  uint64_t total_elems = 0;
-  std::vector<size_t> state_bytes;
-  uint64_t oLstmU = 0, oHNew = 0;   // VeLO scratch (floats)
-  uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
-  uint64_t oAlpha = 0, oTheta = 0;   // VeLO, long lists: bank coefficients [T][K] and per-tensor MLPs [T][P]
-  bool head_batched = false;
-  uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the strip-form apply kernel
-  uint64_t ws_floats = 0;
-};
-
 }  // namespace
 
 struct lopt_ctx {
@@ -147,6 +125,7 @@ struct lopt_ctx {
   int device = 0;
   int n_cu = 256;
   int HP = 0, F = 0, P = 0;
+  PlanOptions opts;                // what of this context the planner reads
   float* d_weights = nullptr;      // the uploaded blob; VeLO: behind it the hypernetwork's repacked weights
   float* d_tail = nullptr;         // small_fc_lopt: padded W2 b2 W3 b3
   WeightsDev W{};
@@ -167,7 +146,6 @@ struct lopt_ctx {
   int apply_variant = 0;           // lopt_apply_kernel (configuration field, else LOPT_APPLY in the environment at create)
   // Group pipeline (small_fc_lopt, strip-form apply): the tensor list is cut into groups; the HBM-bound passes of
   // group g+1 run on `aux_stream` while the compute-bound apply pass of group g runs on the caller's stream.
-  int groups_override = 0;         // configuration field, else LOPT_GROUPS in the environment at create (0 = choose by size)
   hipStream_t aux_stream = nullptr;
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_start, ev_pre;   // per group: "previous group's passes are enqueued" / "this group's passes are done"
@@ -210,163 +188,10 @@ lopt_status check_descs(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d) {
   return LOPT_OK;
 }
 
-// Number of tensor groups of the two-stream pipeline for a list of `total` elements (0 override = by size). A group more costs
-// two launches, two waits across streams and one more drain of both kernels, about 40 us. Measured, ms a step with
-// G = 1 / 2 / 3 / 4 / 5 / 8: 20 M elements 0.370 / 0.389 / 0.410 / 0.439 / 0.458 / 0.583; 40 M 0.752 / 0.766 / 0.807 / 0.851 /
-// 0.853 / 1.020; 87 M 1.57 / 1.53 / 1.54 / 1.55 / 1.64 / 1.78; 150 M 2.78 / 2.70 / 2.70 / 2.72 / 2.73 / 2.86; 355 M 6.36 / 6.14 /
-// 6.07 / 6.02 / 6.02 / 6.08.
-int planned_groups(int override_g, uint64_t total, size_t n) {
-  int G = override_g;
-  if (!G) G = total >= (1024u << 20) ? 8 : total >= (256u << 20) ? 4 : total >= (128u << 20) ? 3 : total >= (64u << 20) ? 2 : 1;
-  if ((size_t)G > n) G = (int)n;
-  return G < 1 ? 1 : G;
-}
-
-// Contiguous tensor ranges [bound[g], bound[g+1]) of about equal element count.
-void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t total, int* bound) {
-  uint64_t cum = 0;
-  int g = 1;
-  bound[0] = 0;
-  for (size_t i = 0; i < n && g < G; ++i) {
-    cum += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-    if (cum * (uint64_t)G >= total * (uint64_t)g && (int)i + 1 > bound[g - 1]) bound[g++] = (int)i + 1;
-  }
-  while (g <= G) bound[g++] = (int)n;
-}
-
-// Lay out tiles, row/column blocks and workspace regions for a tensor list.
-void build_plan(const lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d, Plan* pl) {
-  pl->descs.assign(d, d + n);
-  pl->tensors.assign(n, TensorDev{});
-  pl->tiles.clear();
-  pl->rcitems.clear();
-  pl->atiles.clear();
-  pl->atile0.assign(n, 0);
-  pl->total_elems = 0;
-  pl->state_bytes.assign(n, 0);
-  const bool velo = ctx->cfg.kind == LOPT_VELO;
-  const int HP = ctx->HP;
-  const uint64_t prep_floats = (uint64_t)(LOPT_D_VELO + 1) * HP + (uint64_t)HP * HP + HP + 2 * HP + 2;
-  uint64_t off = 0;
-  auto take = [&](uint64_t nfloats) { uint64_t o = off; off = align64(off + nfloats); return o; };
-  pl->oCounters = take(kMaxGroups);
-  if (velo) {
-    pl->oLstmU = take((uint64_t)n * kLstmInPad);
-    pl->oHNew = take((uint64_t)n * ctx->cfg.lstm_hidden);
-    pl->oHbarPart = take((uint64_t)kMixSlices * ctx->cfg.lstm_hidden);
-    pl->oBeff = take((uint64_t)kMixJSplit * 4ull * ctx->cfg.lstm_hidden);
-    pl->head_batched = n >= (size_t)kHeadBatchMin;
-    if (pl->head_batched) {
-      if (!ctx->W.head) pl->oAlpha = take((uint64_t)n * ctx->cfg.n_bank);
-      pl->oTheta = take((uint64_t)n * (uint64_t)(ctx->W.head ? head_ld(ctx->P) : ctx->P));
-    }
-  }
-  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off): the
-  // strip apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
-  // while the final workgroups finish (a 128-row tile is about 90 us of work, a 32-row tile a quarter of that).
-  uint64_t total = 0;
-  for (size_t i = 0; i < n; ++i) total += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-  const int G_plan = ctx->cfg.kind == LOPT_SMALL_FC ? planned_groups(ctx->groups_override, total, n) : 1;
-  int gbound[kMaxGroups + 1];
-  group_bounds(d, n, G_plan, total, gbound);
-  std::vector<uint64_t> gtotal(G_plan, 0), gbefore(n, 0);
-  for (int g = 0; g < G_plan; ++g)
-    for (int i = gbound[g]; i < gbound[g + 1]; ++i) {
-      gbefore[i] = gtotal[g];
-      gtotal[g] += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-    }
-  std::vector<int> group_of(n, 0);
-  for (int g = 0; g < G_plan; ++g)
-    for (int i = gbound[g]; i < gbound[g + 1]; ++i) group_of[i] = g;
-  // Small parameter sets: with the standard 64-row tiles there may be fewer tiles than the chip has workgroup
-  // slots (256 CUs x 2..8), so the tile height is halved until the list yields about 2048 tiles or reaches 8 rows.
-  uint64_t std_tiles = 0;
-  for (size_t i = 0; i < n; ++i)
-    std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
-  int shrink = 1;
-  while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
-  // Short lists: the smallest even apply-tile height at which every tile has a workgroup slot of its own (two per CU), if
-  // that is at most 32 rows: the launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the
-  // graded heights below gave 650 tiles and a second, nearly empty round).
-  int ar_short = 0;
-  for (int ar : {2, 4, 6, 8, 12, 16, 20, 24, 32}) {
-    uint64_t tiles = 0;
-    for (size_t i = 0; i < n; ++i)
-      tiles += (uint64_t)((d[i].rows + ar - 1) / ar) * (uint64_t)((d[i].cols + kApplyCols - 1) / kApplyCols);
-    if (tiles <= 2ull * ctx->n_cu) { ar_short = ar; break; }
-  }
-  for (size_t i = 0; i < n; ++i) {
-    TensorDev& T = pl->tensors[i];
-    const int m = (int)d[i].rows, nn = (int)d[i].cols;
-    const uint64_t N = (uint64_t)m * nn;
-    T.m = m; T.n = nn;
-    T.padN = pad4(N); T.padm = pad4(m); T.padn = pad4(nn);
-    T.padH = velo ? pad4(ctx->cfg.lstm_hidden) : 0;
-    T.ndim = d[i].ndim;
-    T.vec = nn % 32 == 0 ? 2 : nn % 4 == 0 ? 1 : 0;
-    const int units = (m + kRowUnit - 1) / kRowUnit;
-    const int q = (units + kMaxRowTiles - 1) / kMaxRowTiles;
-    T.TR = kRowUnit * (q < 1 ? 1 : q) / shrink;   // a multiple of 8: every wavefront of a tile owns whole rows
-    // ... but never more than kMaxRowTiles row tiles per tensor (the second-stage reductions loop over them; a small
-    // list, whose tiles were made shorter above, may have `shrink` times as many) ...
-    const int max_rt = kMaxRowTiles * shrink;
-    const int min_tr = ((m + max_rt - 1) / max_rt + 7) & ~7;
-    if (T.TR < min_tr) T.TR = min_tr;
-    // ... unless that makes a tile taller than kMaxTileRows: a lane sums a quarter of the tile's rows in fp32
-    // (four values per row), and such a partial sum must stay at about a thousand terms. Tensors of more than
-    // kMaxRowTiles * kMaxTileRows rows get more row tiles instead.
-    if (T.TR > kMaxTileRows) T.TR = kMaxTileRows;
-    T.nrt = (m + T.TR - 1) / T.TR;
-    T.nct = (nn + kTileCols - 1) / kTileCols;
-    T.tile0 = (int)pl->tiles.size();
-    for (int ti = 0; ti < T.nrt; ++ti)
-      for (int tj = 0; tj < T.nct; ++tj) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
-    T.nrblk = (m + kBlock - 1) / kBlock;
-    T.ncblk = (nn + kBlock - 1) / kBlock;
-    T.rc0 = (int)pl->rcitems.size();
-    for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
-    for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
-    // apply tiles: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
-    pl->atile0[i] = (int)pl->atiles.size();
-    pl->total_elems += N;
-    for (int ar0 = 0; ar0 < m;) {
-      // position of this row block inside its group: full height for the first 70 %, half to 88 %, a quarter after
-      const uint64_t pos = gbefore[i] + (uint64_t)ar0 * (uint64_t)nn, gt = gtotal[group_of[i]];
-      int AR = kApplyRows / shrink;
-      if (pos * 100 >= gt * 88) AR /= 4;
-      else if (pos * 100 >= gt * 70) AR /= 2;
-      if (AR < 8) AR = 8;
-      if (ar_short) AR = ar_short;
-      const int rows = m - ar0 < AR ? m - ar0 : AR;
-      for (int ac0 = 0; ac0 < nn; ac0 += kApplyCols) pl->atiles.push_back(ApplyTileDev{(int)i, ar0, ac0, rows});
-      ar0 += rows;
-    }
-    T.oRowPart = take((uint64_t)T.nct * m);
-    T.oColPart = take((uint64_t)T.nrt * nn);
-    T.oRR = take(3ull * T.padm);
-    T.oRC = take(3ull * T.padn);
-    T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);
-    T.oStatPart = take((uint64_t)T.nrt * T.nct * kStatStride);
-    T.oStats = take(kStatsPerTensor);
-    T.oScale = take(kStatsPerTensor);
-    T.oPrep = take(prep_floats);
-    pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
-  }
-  pl->ws_floats = off;
-}
-
-bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {
-  if (pl.descs.size() != n) return false;
-  for (size_t i = 0; i < n; ++i)
-    if (pl.descs[i].ndim != d[i].ndim || pl.descs[i].rows != d[i].rows || pl.descs[i].cols != d[i].cols)
-      return false;
-  return true;
-}
-
 lopt_status ensure_plan(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d) {
   if (ctx->plan_valid && same_descs(ctx->plan, n, d)) return LOPT_OK;
   try {
-    build_plan(ctx, n, d, &ctx->plan);
+    build_plan(ctx->opts, n, d, &ctx->plan);
   } catch (const std::bad_alloc&) {
     ctx->plan_valid = false;
     return fail(ctx, LOPT_ENOMEM, "out of host memory while planning");
@@ -374,11 +199,6 @@ lopt_status ensure_plan(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d) {
   ctx->plan_valid = true;
   for (TableStore* st : {&ctx->heap, &ctx->fixed}) st->static_uploaded = st->tensors_uploaded = false;
   return LOPT_OK;
-}
-
-size_t table_bytes(const Plan& pl) {
-  return align64(pl.tensors.size() * sizeof(TensorDev)) + align64(pl.tiles.size() * sizeof(TileDev)) +
-         align64(pl.rcitems.size() * sizeof(RcItemDev)) + align64(pl.atiles.size() * sizeof(ApplyTileDev));
 }
 
 // Make sure the device tables of `st` hold the current plan and pointers. A growable store and the pinned staging
@@ -531,7 +351,6 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
   ctx->cfg = *cfg;
   ctx->apply_variant = apply_variant;
   ctx->state_in_apply = state_pass != LOPT_STATE_IN_STATS;
-  ctx->groups_override = groups_override;
   const int H = (int)cfg->hidden;
   ctx->HP = padded_hidden(H);
   ctx->F = cfg->kind == LOPT_SMALL_FC ? LOPT_N_ELEM_FEATS : LOPT_D_VELO;
@@ -551,6 +370,14 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
   CREATE_TRY(hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
   // one allocation: the uploaded blob, then (VeLO) the hypernetwork's weights in the layouts its kernels read
   const bool folds = cfg->kind == LOPT_VELO && head_folds((int)cfg->lstm_hidden, (int)cfg->n_bank, ctx->P);
+  ctx->opts.kind = (int)cfg->kind;
+  ctx->opts.HP = ctx->HP;
+  ctx->opts.P = ctx->P;
+  ctx->opts.lstm_hidden = (int)cfg->lstm_hidden;
+  ctx->opts.n_bank = (int)cfg->n_bank;
+  ctx->opts.head_folded = folds;
+  ctx->opts.groups_override = groups_override;
+  ctx->opts.n_cu = ctx->n_cu;
   size_t lstm_n = 0, head_n = 0;
   if (cfg->kind == LOPT_VELO) {
     lstm_n = (cfg->lstm_hidden + 7) / 8 * (size_t)lstm_k_pad((int)cfg->lstm_hidden) * 32;
@@ -656,7 +483,7 @@ lopt_status lopt_state_bytes(const lopt_ctx* cctx, size_t n, const lopt_tensor_d
   const Plan* pl = &tmp;
   if (ctx->plan_valid && same_descs(ctx->plan, n, descs)) pl = &ctx->plan;
   else {
-    try { build_plan(ctx, n, descs, &tmp); } catch (const std::bad_alloc&) { return fail(ctx, LOPT_ENOMEM, "out of host memory while planning"); }
+    try { build_plan(ctx->opts, n, descs, &tmp); } catch (const std::bad_alloc&) { return fail(ctx, LOPT_ENOMEM, "out of host memory while planning"); }
   }
   if (per_tensor) for (size_t i = 0; i < n; ++i) per_tensor[i] = pl->state_bytes[i];
   if (workspace_bytes) *workspace_bytes = (size_t)(pl->ws_floats * sizeof(float)) + 256;
@@ -673,7 +500,7 @@ lopt_status lopt_stats_offsets(const lopt_ctx* cctx, size_t n, const lopt_tensor
   const Plan* pl = &tmp;
   if (ctx->plan_valid && same_descs(ctx->plan, n, descs)) pl = &ctx->plan;
   else {
-    try { build_plan(ctx, n, descs, &tmp); } catch (const std::bad_alloc&) { return fail(ctx, LOPT_ENOMEM, "out of host memory while planning"); }
+    try { build_plan(ctx->opts, n, descs, &tmp); } catch (const std::bad_alloc&) { return fail(ctx, LOPT_ENOMEM, "out of host memory while planning"); }
   }
   for (size_t i = 0; i < n; ++i) offsets[i] = (size_t)pl->tensors[i].oStats * sizeof(float);
   return LOPT_OK;
@@ -799,8 +626,8 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   int G = 1;
   const bool velo = ctx->cfg.kind == LOPT_VELO;
   if (ctx->aux_stream && !profiling) {
-    if (strip_ok) G = planned_groups(ctx->groups_override, pl.total_elems, n);
-    else if (velo && ctx->groups_override) G = planned_groups(ctx->groups_override, pl.total_elems, n);
+    if (strip_ok) G = planned_groups(ctx->opts.groups_override, pl.total_elems, n);
+    else if (velo && ctx->opts.groups_override) G = planned_groups(ctx->opts.groups_override, pl.total_elems, n);
   }
   // From here on kernels are in flight: a HIP error leaves params and state partly updated. The context is marked
   // failed, and the second stream (if it was forked) is joined back so that the caller's stream semantics hold.

@@ -1,0 +1,200 @@
+// The planner: turns a tensor list into the tables the kernels walk and lays out the workspace. Plain host C++, no HIP calls.
+#pragma once
+
+#include <vector>
+
+#include "lopt_internal.h"
+
+namespace lopt {
+
+constexpr int kMaxGroups = 16;
+
+inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
+inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
+
+// What the planner has to know of a context.
+struct PlanOptions {
+  int kind = LOPT_SMALL_FC;      // lopt_kind
+  int HP = 0, P = 0;             // padded MLP width; VeLO: floats per per-tensor MLP
+  int lstm_hidden = 0, n_bank = 0;
+  bool head_folded = false;      // VeLO: the hypernetwork head is one folded matrix (WeightsDev::head)
+  int groups_override = 0;       // tensor groups of the two-stream pipeline (0 = choose by size)
+  int n_cu = 256;
+};
+
+struct Plan {
+  std::vector<lopt_tensor_desc> descs;
+  std::vector<TensorDev> tensors;   // pointers filled per call
+  std::vector<TileDev> tiles;
+  std::vector<RcItemDev> rcitems;
+  std::vector<ApplyTileDev> atiles;   // tiles of the strip-form apply kernel
+  std::vector<int> atile0;            // first apply tile of every tensor
+  uint64_t total_elems = 0;
+  std::vector<size_t> state_bytes;
+  uint64_t oLstmU = 0, oHNew = 0;   // VeLO scratch (floats)
+  uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
+  uint64_t oAlpha = 0, oTheta = 0;   // VeLO, long lists: bank coefficients [T][K] and per-tensor MLPs [T][P]
+  bool head_batched = false;
+  uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the strip-form apply kernel
+  uint64_t ws_floats = 0;
+};
+
+// Number of tensor groups of the two-stream pipeline for a list of `total` elements (0 override = by size). A group more costs
+// two launches, two waits across streams and one more drain of both kernels, about 40 us. Measured, ms a step with
+// G = 1 / 2 / 3 / 4 / 5 / 8: 20 M elements 0.370 / 0.389 / 0.410 / 0.439 / 0.458 / 0.583; 40 M 0.752 / 0.766 / 0.807 / 0.851 /
+// 0.853 / 1.020; 87 M 1.57 / 1.53 / 1.54 / 1.55 / 1.64 / 1.78; 150 M 2.78 / 2.70 / 2.70 / 2.72 / 2.73 / 2.86; 355 M 6.36 / 6.14 /
+// 6.07 / 6.02 / 6.02 / 6.08.
+inline int planned_groups(int override_g, uint64_t total, size_t n) {
+  int G = override_g;
+  if (!G) G = total >= (1024u << 20) ? 8 : total >= (256u << 20) ? 4 : total >= (128u << 20) ? 3 : total >= (64u << 20) ? 2 : 1;
+  if ((size_t)G > n) G = (int)n;
+  return G < 1 ? 1 : G;
+}
+
+// Contiguous tensor ranges [bound[g], bound[g+1]) of about equal element count.
+inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t total, int* bound) {
+  uint64_t cum = 0;
+  int g = 1;
+  bound[0] = 0;
+  for (size_t i = 0; i < n && g < G; ++i) {
+    cum += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
+    if (cum * (uint64_t)G >= total * (uint64_t)g && (int)i + 1 > bound[g - 1]) bound[g++] = (int)i + 1;
+  }
+  while (g <= G) bound[g++] = (int)n;
+}
+
+// Lay out tiles, row/column blocks and workspace regions for a tensor list.
+inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d, Plan* pl) {
+  pl->descs.assign(d, d + n);
+  pl->tensors.assign(n, TensorDev{});
+  pl->tiles.clear();
+  pl->rcitems.clear();
+  pl->atiles.clear();
+  pl->atile0.assign(n, 0);
+  pl->total_elems = 0;
+  pl->state_bytes.assign(n, 0);
+  const bool velo = o.kind == LOPT_VELO;
+  const int HP = o.HP;
+  const uint64_t prep_floats = (uint64_t)(LOPT_D_VELO + 1) * HP + (uint64_t)HP * HP + HP + 2 * HP + 2;
+  uint64_t off = 0;
+  auto take = [&](uint64_t nfloats) { uint64_t at = off; off = align64(off + nfloats); return at; };
+  pl->oCounters = take(kMaxGroups);
+  if (velo) {
+    pl->oLstmU = take((uint64_t)n * kLstmInPad);
+    pl->oHNew = take((uint64_t)n * o.lstm_hidden);
+    pl->oHbarPart = take((uint64_t)kMixSlices * o.lstm_hidden);
+    pl->oBeff = take((uint64_t)kMixJSplit * 4ull * o.lstm_hidden);
+    pl->head_batched = n >= (size_t)kHeadBatchMin;
+    if (pl->head_batched) {
+      if (!o.head_folded) pl->oAlpha = take((uint64_t)n * o.n_bank);
+      pl->oTheta = take((uint64_t)n * (uint64_t)(o.head_folded ? head_ld(o.P) : o.P));
+    }
+  }
+  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off): the
+  // strip apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
+  // while the final workgroups finish (a 128-row tile is about 90 us of work, a 32-row tile a quarter of that).
+  uint64_t total = 0;
+  for (size_t i = 0; i < n; ++i) total += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
+  const int G_plan = o.kind == LOPT_SMALL_FC ? planned_groups(o.groups_override, total, n) : 1;
+  int gbound[kMaxGroups + 1];
+  group_bounds(d, n, G_plan, total, gbound);
+  std::vector<uint64_t> gtotal(G_plan, 0), gbefore(n, 0);
+  for (int g = 0; g < G_plan; ++g)
+    for (int i = gbound[g]; i < gbound[g + 1]; ++i) {
+      gbefore[i] = gtotal[g];
+      gtotal[g] += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
+    }
+  std::vector<int> group_of(n, 0);
+  for (int g = 0; g < G_plan; ++g)
+    for (int i = gbound[g]; i < gbound[g + 1]; ++i) group_of[i] = g;
+  // Small parameter sets: with the standard 64-row tiles there may be fewer tiles than the chip has workgroup
+  // slots (256 CUs x 2..8), so the tile height is halved until the list yields about 2048 tiles or reaches 8 rows.
+  uint64_t std_tiles = 0;
+  for (size_t i = 0; i < n; ++i)
+    std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
+  int shrink = 1;
+  while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
+  // Short lists: the smallest even apply-tile height at which every tile has a workgroup slot of its own (two per CU), if
+  // that is at most 32 rows: the launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the
+  // graded heights below gave 650 tiles and a second, nearly empty round).
+  int ar_short = 0;
+  for (int ar : {2, 4, 6, 8, 12, 16, 20, 24, 32}) {
+    uint64_t tiles = 0;
+    for (size_t i = 0; i < n; ++i)
+      tiles += (uint64_t)((d[i].rows + ar - 1) / ar) * (uint64_t)((d[i].cols + kApplyCols - 1) / kApplyCols);
+    if (tiles <= 2ull * o.n_cu) { ar_short = ar; break; }
+  }
+  for (size_t i = 0; i < n; ++i) {
+    TensorDev& T = pl->tensors[i];
+    const int m = (int)d[i].rows, nn = (int)d[i].cols;
+    const uint64_t N = (uint64_t)m * nn;
+    T.m = m; T.n = nn;
+    T.padN = pad4(N); T.padm = pad4(m); T.padn = pad4(nn);
+    T.padH = velo ? pad4(o.lstm_hidden) : 0;
+    T.ndim = d[i].ndim;
+    T.vec = nn % 32 == 0 ? 2 : nn % 4 == 0 ? 1 : 0;
+    const int units = (m + kRowUnit - 1) / kRowUnit;
+    const int q = (units + kMaxRowTiles - 1) / kMaxRowTiles;
+    T.TR = kRowUnit * (q < 1 ? 1 : q) / shrink;   // a multiple of 8: every wavefront of a tile owns whole rows
+    // ... but never more than kMaxRowTiles row tiles per tensor (the second-stage reductions loop over them; a small
+    // list, whose tiles were made shorter above, may have `shrink` times as many) ...
+    const int max_rt = kMaxRowTiles * shrink;
+    const int min_tr = ((m + max_rt - 1) / max_rt + 7) & ~7;
+    if (T.TR < min_tr) T.TR = min_tr;
+    // ... unless that makes a tile taller than kMaxTileRows: a lane sums a quarter of the tile's rows in fp32
+    // (four values per row), and such a partial sum must stay at about a thousand terms. Tensors of more than
+    // kMaxRowTiles * kMaxTileRows rows get more row tiles instead.
+    if (T.TR > kMaxTileRows) T.TR = kMaxTileRows;
+    T.nrt = (m + T.TR - 1) / T.TR;
+    T.nct = (nn + kTileCols - 1) / kTileCols;
+    T.tile0 = (int)pl->tiles.size();
+    for (int ti = 0; ti < T.nrt; ++ti)
+      for (int tj = 0; tj < T.nct; ++tj) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
+    T.nrblk = (m + kBlock - 1) / kBlock;
+    T.ncblk = (nn + kBlock - 1) / kBlock;
+    T.rc0 = (int)pl->rcitems.size();
+    for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
+    for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
+    // apply tiles: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
+    pl->atile0[i] = (int)pl->atiles.size();
+    pl->total_elems += N;
+    for (int ar0 = 0; ar0 < m;) {
+      // position of this row block inside its group: full height for the first 70 %, half to 88 %, a quarter after
+      const uint64_t pos = gbefore[i] + (uint64_t)ar0 * (uint64_t)nn, gt = gtotal[group_of[i]];
+      int AR = kApplyRows / shrink;
+      if (pos * 100 >= gt * 88) AR /= 4;
+      else if (pos * 100 >= gt * 70) AR /= 2;
+      if (AR < 8) AR = 8;
+      if (ar_short) AR = ar_short;
+      const int rows = m - ar0 < AR ? m - ar0 : AR;
+      for (int ac0 = 0; ac0 < nn; ac0 += kApplyCols) pl->atiles.push_back(ApplyTileDev{(int)i, ar0, ac0, rows});
+      ar0 += rows;
+    }
+    T.oRowPart = take((uint64_t)T.nct * m);
+    T.oColPart = take((uint64_t)T.nrt * nn);
+    T.oRR = take(3ull * T.padm);
+    T.oRC = take(3ull * T.padn);
+    T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);
+    T.oStatPart = take((uint64_t)T.nrt * T.nct * kStatStride);
+    T.oStats = take(kStatsPerTensor);
+    T.oScale = take(kStatsPerTensor);
+    T.oPrep = take(prep_floats);
+    pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
+  }
+  pl->ws_floats = off;
+}
+
+inline bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {
+  if (pl.descs.size() != n) return false;
+  for (size_t i = 0; i < n; ++i)
+    if (pl.descs[i].ndim != d[i].ndim || pl.descs[i].rows != d[i].rows || pl.descs[i].cols != d[i].cols)
+      return false;
+  return true;
+}
+
+inline size_t table_bytes(const Plan& pl) {
+  return align64(pl.tensors.size() * sizeof(TensorDev)) + align64(pl.tiles.size() * sizeof(TileDev)) +
+         align64(pl.rcitems.size() * sizeof(RcItemDev)) + align64(pl.atiles.size() * sizeof(ApplyTileDev));
+}
+
+}  // namespace lopt
