@@ -600,8 +600,11 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool mfma_ok = apply_mfma_available(A);
   // the strip-form kernel addresses a row pair with 32-bit byte offsets from the tile's first column: 4 (127 + cols)
   // must stay below the range of its store descriptors (2^32 - 512), which only a tensor of two or more rows and
-  // 2^30 - 255 or more columns breaks (it takes the fp32 kernel)
-  bool strip_ok = mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
+  // 2^30 - 255 or more columns breaks (it takes the fp32 kernel).
+  // The row counters of the strip and of the narrow-width kernel are signed and run up to 20 rows past a tile (unsigned ones cost
+  // four registers in the first and 0.7 % in the second): tensors of more than 2^31 - 64 rows go to the kernels below them.
+  const bool rows_ok = pl.max_rows <= 0x7fffffff - 63;
+  bool strip_ok = rows_ok && mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
            tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0};
@@ -611,7 +614,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   // kernel is bound by instruction issue and takes the extra stores in its stride, the VeLO kernel is HBM-bound and
   // gives part of the gain back.
   const bool velo4_ok = ctx->cfg.kind == LOPT_VELO && ctx->apply_variant != LOPT_APPLY_VALU && apply_velo4_available(A);
-  const bool fc4x_ok = ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
+  const bool fc4x_ok = rows_ok && ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
   const bool state_in_apply = (strip_ok || fc4x_ok || velo4_ok) && ctx->state_in_apply;
   auto launch_apply = [&](const Launch& La) {
     if (strip_ok) launch_apply_f16s(La, A, ctx->W, state_in_apply, stream);

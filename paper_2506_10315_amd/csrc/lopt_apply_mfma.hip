@@ -35,7 +35,7 @@ __device__ __forceinline__ void apply_mfma_tile(const TensorDev& T, const TileDe
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
   const float* __restrict__ prep = ws + T.oPrep;  // W1s[28][32] (normalization folded in), b1'[32]
-  const int n = T.n, m = T.m;
+  const int n = T.n;
 
   apply_tile_setup(T, tile, ws, prep, tail, L);
 
@@ -53,21 +53,20 @@ __device__ __forceinline__ void apply_mfma_tile(const TensorDev& T, const TileDe
   const float b3d = tail[kH * kH + kH + 2 * kH], b3m = tail[kH * kH + kH + 2 * kH + 1];
 
   const int col = tile.tj * kTileCols + 4 * lane;
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
+  const auto [r0, r1] = tile_rows(T, tile);
   float4 rc[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) rc[k] = load4<VEC>(ws + T.oRC + (size_t)k * T.padn, col, n);
   const float* rst = T.st + 4 * (size_t)T.padN;
   const float eps = A.eps_acc, lr = A.lr, wd = A.wd;
 
-  int r = r0 + wave;
+  unsigned r = r0 + wave;
   float4 cur[6];
-  if (r < r1) load_row<VEC>(T, (size_t)r * n, col, n, cur);
+  if (r < r1) load_row<VEC>(T, (size_t)r * (unsigned)n, col, n, cur);
   for (; r < r1; r += 4) {
-    const size_t ro = (size_t)r * n;
+    const size_t ro = (size_t)r * (unsigned)n;
     float4 nxt[6];
-    if (r + 4 < r1) load_row<VEC>(T, (size_t)(r + 4) * n, col, n, nxt);   // next row in flight during the MLP
+    if (r + 4 < r1) load_row<VEC>(T, (size_t)(r + 4) * (unsigned)n, col, n, nxt);   // next row in flight during the MLP
     float rr[3], rv[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {

@@ -22,10 +22,9 @@ __device__ __forceinline__ void apply_tile(const TensorDev& T, const TileDev& ti
   const float* __restrict__ W3 = reinterpret_cast<const float*>(B2 + H4);          // [HP][2]
   const float* __restrict__ B3 = W3 + 2 * HP;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = T.n, m = T.m;
+  const int n = T.n;
   const int col = tile.tj * kTileCols + 4 * lane;
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
+  const auto [r0, r1] = tile_rows(T, tile);
   float4 rc[3], cc[3];
   const float* cst = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm;
 #pragma unroll
@@ -40,8 +39,8 @@ __device__ __forceinline__ void apply_tile(const TensorDev& T, const TileDev& ti
   const float* rst = T.st + 4 * (size_t)T.padN;
   const float eps = A.eps_acc;
   const float lr = A.lr, wd = A.wd;
-  for (int r = r0 + wave; r < r1; r += 4) {
-    const size_t ro = (size_t)r * n;
+  for (unsigned r = r0 + wave; r < r1; r += 4) {
+    const size_t ro = (size_t)r * (unsigned)n;
     const float4 g4 = load4s<VEC>(T.g + ro, col, n);
     const float4 p4 = load4s<VEC>(T.p + ro, col, n);
     const float4 m1 = load4s<VEC>(M1 + ro, col, n);

@@ -201,7 +201,7 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
                                                       const StepArgs& A) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i4 = lane & 3;
-  const int n = T.n, m = T.m;
+  const int n = T.n;
   const int c0 = tile.tj * kTileCols;
   const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
   const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
@@ -251,12 +251,12 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
   const float eps = A.eps_acc, lr = A.lr, wd = A.wd;
   const float bm1 = A.mom_decay[0], bm2 = A.mom_decay[1], bm3 = A.mom_decay[2], bv = A.rms_decay;
   const float am1 = 1.0f - bm1, am2 = 1.0f - bm2, am3 = 1.0f - bm3, av = 1.0f - bv;
-  const int r1 = min(tile.ti * T.TR + T.TR, m);
-  for (int r = tile.ti * T.TR + 4 * (wave % rsplit); r < r1; r += 4 * rsplit) {
+  const auto [r0, r1] = tile_rows(T, tile);
+  for (unsigned r = r0 + 4 * (wave % rsplit); r < r1; r += 4 * rsplit) {
     float e_in[4][6];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {   // rows past the tile read its last row and store nothing
-      const size_t ro = (size_t)min(r + e, r1 - 1) * n;
+      const size_t ro = (size_t)min(r + e, r1 - 1) * (unsigned)n;
       e_in[e][0] = T.g[ro + cc];
       e_in[e][1] = T.p[ro + cc];
 #pragma unroll
@@ -266,8 +266,8 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
     f32x4 h[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int row = min(r + e, r1 - 1);
-      const size_t ro = (size_t)row * n;
+      const unsigned row = min(r + e, r1 - 1);
+      const size_t ro = (size_t)row * (unsigned)n;
       float rr[3], rv[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -333,7 +333,7 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
     for (int e = 0; e < 4; ++e) {
       const float delta = o[e][0] * __expf(o[e][1] * A.exp_mult) * A.step_mult;
       const float p = e_in[e][1];
-      if (r + e < r1 && col_ok) T.p[(size_t)(r + e) * n + cc] = p - lr * (delta + wd * p);
+      if (r + e < r1 && col_ok) T.p[(size_t)(r + e) * (unsigned)n + cc] = p - lr * (delta + wd * p);
     }
   }
 }

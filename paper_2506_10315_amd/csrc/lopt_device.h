@@ -89,6 +89,14 @@ __device__ __forceinline__ void store4s(float* __restrict__ row, int col, int n,
   if (col + 3 < n) __builtin_nontemporal_store(v.w, row + col + 3);
 }
 
+// Rows [r0, r1) of a statistics tile. Row counters are unsigned wherever a loop steps past its end or clamps a row ahead of it:
+// a tensor may have 2^31 - 1 rows, and such a counter runs up to TR + 16 further.
+struct TileRows { unsigned r0, r1; };
+__device__ __forceinline__ TileRows tile_rows(const TensorDev& T, const TileDev& tile) {
+  const unsigned r0 = (unsigned)tile.ti * (unsigned)T.TR;
+  return TileRows{r0, min(r0 + (unsigned)T.TR, (unsigned)T.m)};
+}
+
 // The rows and the 256-column segment of a tile that one of the workgroup's four wavefronts streams (for passes that may cut
 // the elements in any way). Workgroups advance through their rows more or less in step, and tiles of power-of-two pitch
 // then keep meeting on the same few of the 128 memory channels (4 KB interleave: rows 512 KB apart share one). Where the

@@ -165,8 +165,8 @@ __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& t
   const int n = T.n, m = T.m;
   const int c0 = tile.tj * kTileCols;
   // g of one row: aligned rows, columns 4 lane .. 4 lane + 3 as one float4; other rows, columns lane + 64 e (coalesced dwords)
-  auto row4 = [&](int r) __attribute__((always_inline)) {
-    const float* __restrict__ row = T.g + (size_t)r * n;
+  auto row4 = [&](unsigned r) __attribute__((always_inline)) {
+    const float* __restrict__ row = T.g + (size_t)r * (unsigned)n;
     if (VEC) return load4s<true>(row, c0 + 4 * lane, n);
     float v[4];
 #pragma unroll
@@ -177,11 +177,10 @@ __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& t
     }
     return make_float4(v[0], v[1], v[2], v[3]);
   };
-  const int r0 = tile.ti * T.TR;
-  const int r1 = min(r0 + T.TR, m);
+  const auto [r0, r1] = tile_rows(T, tile);
   float* __restrict__ rowpart = ws + T.oRowPart + (size_t)tile.tj * m;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  for (int r = r0 + wave; r < r1; r += 4 * R) {
+  for (unsigned r = r0 + wave; r < r1; r += 4 * R) {
     float4 v[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) v[i] = row4(min(r + 4 * i, r1 - 1));   // rows past the tile: its last row, counted as 0
@@ -384,14 +383,14 @@ template <bool RAW_RCP, bool WRITE>
 __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                            const StepArgs& A, float (&acc)[kNStat]) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = T.n, m = T.m;
+  const int n = T.n;
   const int c0 = tile.tj * kTileCols;
   const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
   const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
   const int seg = wave / rsplit;
   const int c = c0 + seg * kWave + lane;
   if (seg >= nseg || c >= n) return;
-  const int r1 = min(tile.ti * T.TR + T.TR, m);
+  const auto [r0, r1] = tile_rows(T, tile);
   const size_t pN = T.padN;
   const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
   const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
@@ -399,11 +398,11 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
   float rc[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) rc[k] = ws[T.oRC + (size_t)k * T.padn + c];
-  for (int r = tile.ti * T.TR + kAccRows * (wave % rsplit); r < r1; r += kAccRows * rsplit) {
+  for (unsigned r = r0 + kAccRows * (wave % rsplit); r < r1; r += kAccRows * rsplit) {
     float in[kAccRows][6];
 #pragma unroll
     for (int e = 0; e < kAccRows; ++e) {   // a row past the tile reads the tile's last row and counts for nothing
-      const size_t ro = (size_t)min(r + e, r1 - 1) * n + c;
+      const size_t ro = (size_t)min(r + e, r1 - 1) * (unsigned)n + c;
       in[e][0] = T.g[ro];
       in[e][1] = T.p[ro];
 #pragma unroll
@@ -412,7 +411,7 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
 #pragma unroll
     for (int e = 0; e < kAccRows; ++e) {
       if (r + e >= r1) break;   // wavefront-uniform
-      const size_t ro = (size_t)(r + e) * n + c;
+      const size_t ro = (size_t)(r + e) * (unsigned)n + c;
       const float g = in[e][0], p = in[e][1], g2 = g * g;
       // explicit fused multiply-adds: the apply pass may form the same values again (lopt_state_pass), bit for bit
       const float nm1 = __builtin_fmaf(b1, in[e][2], a1 * g);

@@ -11,6 +11,7 @@ constexpr int kMaxGroups = 16;
 
 inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
 inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
+inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }   // a up to 2^31 - 1: a + b - 1 does not fit an int
 
 // What the planner has to know of a context.
 struct PlanOptions {
@@ -30,6 +31,7 @@ struct Plan {
   std::vector<ApplyTileDev> atiles;   // tiles of the strip-form apply kernel
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
+  int64_t max_rows = 0;               // of any tensor
   std::vector<size_t> state_bytes;
   uint64_t oLstmU = 0, oHNew = 0;   // VeLO scratch (floats)
   uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
@@ -72,6 +74,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   pl->atiles.clear();
   pl->atile0.assign(n, 0);
   pl->total_elems = 0;
+  pl->max_rows = 0;
   pl->state_bytes.assign(n, 0);
   const bool velo = o.kind == LOPT_VELO;
   const int HP = o.HP;
@@ -133,31 +136,32 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.padH = velo ? pad4(o.lstm_hidden) : 0;
     T.ndim = d[i].ndim;
     T.vec = nn % 32 == 0 ? 2 : nn % 4 == 0 ? 1 : 0;
-    const int units = (m + kRowUnit - 1) / kRowUnit;
-    const int q = (units + kMaxRowTiles - 1) / kMaxRowTiles;
+    const int units = ceil_div(m, kRowUnit);
+    const int q = ceil_div(units, kMaxRowTiles);
     T.TR = kRowUnit * (q < 1 ? 1 : q) / shrink;   // a multiple of 8: every wavefront of a tile owns whole rows
     // ... but never more than kMaxRowTiles row tiles per tensor (the second-stage reductions loop over them; a small
     // list, whose tiles were made shorter above, may have `shrink` times as many) ...
     const int max_rt = kMaxRowTiles * shrink;
-    const int min_tr = ((m + max_rt - 1) / max_rt + 7) & ~7;
+    const int min_tr = (ceil_div(m, max_rt) + 7) & ~7;
     if (T.TR < min_tr) T.TR = min_tr;
     // ... unless that makes a tile taller than kMaxTileRows: a lane sums a quarter of the tile's rows in fp32
     // (four values per row), and such a partial sum must stay at about a thousand terms. Tensors of more than
     // kMaxRowTiles * kMaxTileRows rows get more row tiles instead.
     if (T.TR > kMaxTileRows) T.TR = kMaxTileRows;
-    T.nrt = (m + T.TR - 1) / T.TR;
-    T.nct = (nn + kTileCols - 1) / kTileCols;
+    T.nrt = ceil_div(m, T.TR);
+    T.nct = ceil_div(nn, kTileCols);
     T.tile0 = (int)pl->tiles.size();
     for (int ti = 0; ti < T.nrt; ++ti)
       for (int tj = 0; tj < T.nct; ++tj) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
-    T.nrblk = (m + kBlock - 1) / kBlock;
-    T.ncblk = (nn + kBlock - 1) / kBlock;
+    T.nrblk = ceil_div(m, kBlock);
+    T.ncblk = ceil_div(nn, kBlock);
     T.rc0 = (int)pl->rcitems.size();
     for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
     for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
     // apply tiles: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
     pl->atile0[i] = (int)pl->atiles.size();
     pl->total_elems += N;
+    if (m > pl->max_rows) pl->max_rows = m;
     for (int ar0 = 0; ar0 < m;) {
       // position of this row block inside its group: full height for the first 70 %, half to 88 %, a quarter after
       const uint64_t pos = gbefore[i] + (uint64_t)ar0 * (uint64_t)nn, gt = gtotal[group_of[i]];
@@ -167,7 +171,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       if (AR < 8) AR = 8;
       if (ar_short) AR = ar_short;
       const int rows = m - ar0 < AR ? m - ar0 : AR;
-      for (int ac0 = 0; ac0 < nn; ac0 += kApplyCols) pl->atiles.push_back(ApplyTileDev{(int)i, ar0, ac0, rows});
+      for (int64_t ac0 = 0; ac0 < nn; ac0 += kApplyCols) pl->atiles.push_back(ApplyTileDev{(int)i, ar0, (int)ac0, rows});
       ar0 += rows;
     }
     T.oRowPart = take((uint64_t)T.nct * m);

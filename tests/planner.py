@@ -1,0 +1,32 @@
+"""The library's planner (csrc/lopt_plan.h) on the CPU: which tiles, blocks and workspace a tensor list gets."""
+from __future__ import annotations
+
+import functools
+import json
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+N_CU = 256   # compute units of an MI355X
+
+
+@functools.lru_cache(maxsize=None)
+def _probe():
+    out = os.path.join(tempfile.mkdtemp(prefix="lopt_planner_"), "probe")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2506_10315_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "planner_probe.cpp"), "-o", out], check=True, capture_output=True, text=True)
+    return out
+
+
+def plan(shapes, kind="small_fc_lopt", hidden=None, lstm_hidden=512, n_bank=256, groups=0):
+    """The plan of a list of (rows, cols)."""
+    h = hidden if hidden is not None else 32 if kind == "small_fc_lopt" else 4
+    hp = next(x for x in (4, 8, 16, 32) if h <= x)
+    p = 29 * h + h + h * h + h + 2 * h + 2
+    folded = n_bank >= 4 and lstm_hidden * p <= lstm_hidden * n_bank + n_bank * p
+    args = [int(kind == "velo"), hp, p, lstm_hidden, n_bank, int(folded), groups, N_CU]
+    r = subprocess.run([_probe(), *map(str, args)], input="\n".join(f"{m} {n}" for m, n in shapes), capture_output=True,
+                       text=True, check=True)
+    return json.loads(r.stdout)

@@ -1,0 +1,46 @@
+// Prints what the planner makes of a tensor list, one JSON object: built and run on the CPU by tests/planner.py.
+// Arguments: kind hidden_padded P lstm_hidden n_bank head_folded groups n_cu; standard input: "rows cols" per tensor.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+
+#include "lopt_plan.h"
+
+int main(int argc, char** argv) {
+  if (argc != 9) return 2;
+  lopt::PlanOptions o;
+  o.kind = atoi(argv[1]);
+  o.HP = atoi(argv[2]);
+  o.P = atoi(argv[3]);
+  o.lstm_hidden = atoi(argv[4]);
+  o.n_bank = atoi(argv[5]);
+  o.head_folded = atoi(argv[6]) != 0;
+  o.groups_override = atoi(argv[7]);
+  o.n_cu = atoi(argv[8]);
+  std::vector<lopt_tensor_desc> d;
+  long long m, n;
+  while (scanf("%lld %lld", &m, &n) == 2) {
+    lopt_tensor_desc x{};
+    x.ndim = 2; x.rows = m; x.cols = n;
+    d.push_back(x);
+  }
+  lopt::Plan pl;
+  lopt::build_plan(o, d.size(), d.data(), &pl);
+  std::map<int, long long> heights;
+  for (const auto& t : pl.atiles) heights[t.rows]++;
+  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_atiles\": %zu, \"atile_rows\": {",
+         (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.atiles.size());
+  const char* sep = "";
+  for (const auto& h : heights) { printf("%s\"%d\": %lld", sep, h.first, h.second); sep = ", "; }
+  printf("}, \"tensors\": [");
+  for (size_t i = 0; i < d.size(); ++i) {
+    const lopt::TensorDev& T = pl.tensors[i];
+    printf("%s{\"TR\": %d, \"nrt\": %d, \"nct\": %d, \"nrblk\": %d, \"ncblk\": %d, \"state_bytes\": %zu, "
+           "\"regions\": [%llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu]}", i ? ", " : "", T.TR, T.nrt, T.nct, T.nrblk, T.ncblk,
+           pl.state_bytes[i], (unsigned long long)T.oRowPart, (unsigned long long)T.oColPart, (unsigned long long)T.oRR,
+           (unsigned long long)T.oRC, (unsigned long long)T.oRcPart, (unsigned long long)T.oStatPart, (unsigned long long)T.oStats,
+           (unsigned long long)T.oScale, (unsigned long long)T.oPrep);
+  }
+  printf("]}\n");
+  return 0;
+}

@@ -85,7 +85,7 @@ def test_config5_llama_1p3b_velo_full_size(capsys):
     _progress(capsys)(f"config 5 worst: {worst}")
 
 
-def _periodic_tensor_case(kind, reps_r, reps_c, say, tag, pr=4, pc=4):
+def _periodic_tensor_case(kind, reps_r, reps_c, say, tag, pr=4, pc=4, hidden=None):
     """One tensor of (pr reps_r) x (pc reps_c) elements whose parameters and gradients tile a pr x pc base pattern: every
     row mean, column mean and whole-tensor mean is that of the base pattern, so the oracle's result for the pr x pc
     tensor, tiled, is the expected value of EVERY element (all of them are compared, on the device). Two steps: the
@@ -95,9 +95,9 @@ def _periodic_tensor_case(kind, reps_r, reps_c, say, tag, pr=4, pc=4):
     from oracle import lopt_oracle as O
     dev = "cuda:0"
     rows, cols = pr * reps_r, pc * reps_c
-    cfg = Hn.make_cfg(kind)
+    cfg = Hn.make_cfg(kind, hidden=hidden)
     ocfg = Hn.oracle_config_from(cfg)
-    w = W.small_fc_weights(0, 32) if kind == "small_fc_lopt" else W.velo_weights(0)
+    w = W.small_fc_weights(0, int(cfg.hidden)) if kind == "small_fc_lopt" else W.velo_weights(0)
     rng = np.random.default_rng([20250610, 900, 0 if kind == "small_fc_lopt" else 1])
     p_base = (rng.standard_normal((pr, pc)) * 0.02).astype(np.float32)
     g_base = [(rng.standard_normal((pr, pc)) * 1e-3).astype(np.float32) for _ in range(2)]
@@ -140,7 +140,7 @@ def _periodic_tensor_case(kind, reps_r, reps_c, say, tag, pr=4, pc=4):
         say(f"{tag} {kind}: step {t}")
         opt.step([p], [g], lr=lr, weight_decay=wd, step=t)
         torch.cuda.synchronize()
-        p_ora = O.tensor_step(p_ora, g_base[t], st, w, ocfg, t, lr, wd, ndim=2)
+        p_ora = O.tensor_step(p_ora, g_base[t], st, w, ocfg, t, lr, wd, ndim=1 if rows == 1 else 2)   # leading ones are squeezed
         e = tiled_err(p, p_ora)
         assert e <= Hn.TOL_PARAM, f"step {t}: parameter rel err {e:.3e}"
         sv = opt.state_views(0)
@@ -185,6 +185,18 @@ def test_maximum_size_tensor_with_unaligned_rows(kind, capsys):
     # 32768 x 65535 = 2,147,450,880 elements, rows of 65535 floats (not a multiple of 4): the scalar-access
     # instantiations of every pass at byte offsets beyond 2^32; base pattern 4 x 3
     _periodic_tensor_case(kind, 8192, 21845, _progress(capsys), "maximum size, unaligned rows", pr=4, pc=3)
+
+
+@pytest.mark.parametrize("kind,hidden,rows,cols", [("small_fc_lopt", 32, 2 ** 31 - 2, 1), ("small_fc_lopt", 32, 2 ** 31 - 64, 1),
+                                                   ("small_fc_lopt", 16, 2 ** 31 - 64, 1), ("velo", 4, 2 ** 31 - 2, 1),
+                                                   ("small_fc_lopt", 32, 1, 2 ** 31 - 2), ("velo", 4, 1, 2 ** 31 - 2)])
+def test_row_and_column_counts_next_to_2_to_31(kind, hidden, rows, cols, capsys):
+    # the row loops of every pass step and clamp up to a tile's height past the last row, block counts are rounded up: neither
+    # fits 32 signed bits here (the boundary admits 2^31 - 1, which is prime; the base pattern has two rows or six columns).
+    # 2^31 - 64 rows are the most that the strip kernel and that of widths up to 16 take; taller tensors run on the fp32
+    # matrix kernel and the vector-ALU kernel (one lane in 64 at work here: the latter would need a minute a step).
+    pr, pc = (2, 1) if cols == 1 else (1, 6)
+    _periodic_tensor_case(kind, rows // pr, cols // pc, _progress(capsys), f"{rows} x {cols}", pr=pr, pc=pc, hidden=hidden)
 
 
 VIT_LONG_RUN = ["cls_token", "pos_embed", "patch_embed.bias", "blocks.5.norm1.weight", "blocks.5.attn.qkv.bias",
