@@ -46,28 +46,36 @@ void launch_fill_zero(const Launch& L, const StepArgs& A, hipStream_t s) {
 
 // ----------------------------------------------------------------------------- sums of partials
 
-// acc + the sum of part[0], part[stride], ... (count terms, 1..B) in double, in index order: B loads issue ahead of the adds,
-// those past the end repeat the last term and are dropped.
-template <int B>
-__device__ __forceinline__ double sum_batch(const float* __restrict__ part, int count, size_t stride, double acc) {
+// Adds part[0], part[stride], ... (count terms, 1..B) in double, in index order, term k to acc[k % NS]: B loads issue ahead of
+// the adds, those past the end repeat the last term and are dropped.
+template <int B, int NS>
+__device__ __forceinline__ void sum_batch(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
   float t[B];
 #pragma unroll
   for (int k = 0; k < B; ++k) t[k] = part[(size_t)min(k, count - 1) * stride];
 #pragma unroll
-  for (int k = 0; k < B; ++k) acc += k < count ? (double)t[k] : 0.0;
-  return acc;
+  for (int k = 0; k < B; ++k) acc[k % NS] += k < count ? (double)t[k] : 0.0;
 }
 
-// Sum of part[0], part[stride], ... (count terms) in double, always in index order. Bound by load latency: full batches of
-// 32 loads, then one batch of the power of two that holds the rest.
+// Sums of part[0], part[stride], ... (count terms) in double, always in index order, as NS interleaved sums. Bound by load
+// latency: full batches of 32 loads, then one batch of the power of two that holds the rest.
+template <int NS>
+__device__ __forceinline__ void strided_sums(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
+  static_assert(NS == 1 || NS == 4, "every batch holds whole rounds of the NS sums");
+#pragma unroll
+  for (int k = 0; k < NS; ++k) acc[k] = 0.0;
+  for (; count > 32; count -= 32, part += 32 * stride) sum_batch<32>(part, 32, stride, acc);
+  if (count > 16) sum_batch<32>(part, count, stride, acc);
+  else if (count > 8) sum_batch<16>(part, count, stride, acc);
+  else if (count > 4) sum_batch<8>(part, count, stride, acc);
+  else if (count > 1) sum_batch<4>(part, count, stride, acc);
+  else if (count == 1) acc[0] += (double)part[0];
+}
+
 __device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
-  double acc = 0.0;
-  for (; count > 32; count -= 32, part += 32 * stride) acc = sum_batch<32>(part, 32, stride, acc);
-  if (count > 16) return sum_batch<32>(part, count, stride, acc);
-  if (count > 8) return sum_batch<16>(part, count, stride, acc);
-  if (count > 4) return sum_batch<8>(part, count, stride, acc);
-  if (count > 1) return sum_batch<4>(part, count, stride, acc);
-  return count == 1 ? acc + (double)part[0] : acc;
+  double acc[1];
+  strided_sums(part, count, stride, acc);
+  return acc[0];
 }
 
 // ----------------------------------------------------------------------------- VeLO cross-tensor term
@@ -578,10 +586,13 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, bool write_state, hi
 
 // One workgroup per tensor. Reduces every partial in a fixed order (double accumulation),
 // then writes s_f, the per-feature scale factors and the prepared first layer. The 32 sums (17 statistics over the tiles,
-// 9 over the row blocks, 6 over the column blocks) are one column of threads each, cut into blockDim / 32 interleaved
+// 9 over the row blocks, 6 over the column blocks) are one column of threads each, cut into 32 interleaved
 // segments: the kernel is a chain of load latencies, and this way it is one batch of loads for up to 1024 tiles
 // (1000x1000: 7.9 -> 4.8 us from eight segments and three such phases; six tensors of 0.3 M elements 5.2 -> 4.9 us).
+// A workgroup of 256 threads forms four segments per thread: the order of summation does not depend on the launch.
 constexpr int kFinSegs = 32;
+constexpr int kFinPerThread = kFinSegs / (kBlock / 32);
+static_assert(kFinPerThread == 4, "a narrow workgroup takes four segments per thread");
 __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                      StepArgs A, WeightsDev W, float* __restrict__ lstm_u, int tensor0,
                                                      int* __restrict__ apply_counter) {
@@ -611,15 +622,22 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
     if (q < kNStat) { base = ws + T.oStatPart + q; count = T.nrt * T.nct; stride = kStatStride; }
     else if (q < 26) { base = ws + T.oRcPart + (q - kNStat); count = T.nrblk; stride = kRcStride; }
     else { base = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3); count = T.ncblk; stride = kRcStride; }
-    double a = 0.0;
-    if (seg < count)   // thread (seg, q): terms seg, seg + n_seg, ...
-      a = strided_sum(base + (size_t)seg * stride, (count - seg + n_seg - 1) / n_seg, (size_t)n_seg * stride);
-    part[seg][q] = a;
+    // thread (seg, q): terms seg, seg + n_seg, ..., which are those of the segments seg, seg + n_seg, ... < 32 in turn
+    const int mine = seg < count ? (count - seg + n_seg - 1) / n_seg : 0;
+    base += (size_t)seg * stride;
+    if (n_seg == kFinSegs) {
+      part[seg][q] = strided_sum(base, mine, (size_t)kFinSegs * stride);
+    } else {
+      double a[kFinPerThread];
+      strided_sums(base, mine, (size_t)n_seg * stride, a);
+#pragma unroll
+      for (int k = 0; k < kFinPerThread; ++k) part[seg + n_seg * k][q] = a[k];
+    }
   }
   __syncthreads();
   if (threadIdx.x < 32) {
     double s = 0.0;
-    for (int k = 0; k < n_seg; ++k) s += part[k][q];
+    for (int k = 0; k < kFinSegs; ++k) s += part[k][q];
     tot[q] = s;
   }
   __syncthreads();

@@ -122,6 +122,32 @@ def test_group_pipeline_is_bit_identical_to_one_stream(groups, monkeypatch):
 
 
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_statistics_do_not_depend_on_the_group_a_tensor_falls_in(kind):
+    # Two equal tensors, one per tensor group, with per-tile sums of g^2 (256 tiles of 8 rows) whose total depends on the order
+    # of a double summation in the last bit of the float result: 1 and 2^-24 meet a tie between two floats, 31 tiles of 2^-54
+    # (every eighth) vanish one by one beside the 1 and break the tie when eight of them are added up first.
+    import torch
+    import paper_2506_10315_amd as P
+    cfg = Hn.make_cfg(kind, groups=2) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8, groups=2)
+    rows, cols = 2048, 256
+    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, 0), [(rows, cols)] * 2)
+    g = torch.zeros(rows, cols)
+    g[0, 0], g[8, 0] = 1.0, 2.0 ** -12
+    g[64::64, 0] = 2.0 ** -27
+    gen = torch.Generator().manual_seed(1)
+    p0 = torch.randn(rows, cols, generator=gen) * 0.02
+    p = [p0.to("cuda:0") for _ in range(2)]
+    opt.step(p, [g.to("cuda:0") for _ in range(2)], lr=0.7, step=0, loss=1.0)
+    torch.cuda.synchronize()
+    a, b = (x.cpu().numpy() for x in opt.stats())
+    assert a[0] in (np.float32(2.0 ** -19), np.nextafter(np.float32(2.0 ** -19), np.float32(1)))
+    assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    assert torch.equal(p[0].view(torch.int32), p[1].view(torch.int32))
+    assert torch.equal(opt.state[0].view(torch.int32), opt.state[1].view(torch.int32))
+    opt.close()
+
+
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_per_pass_timing_changes_no_result_and_names_every_pass(kind, monkeypatch):
     # With lopt_profile_enable the step runs pass after pass on one stream with events in between (no tensor groups);
     # results must be bit-identical to the default launch plan, here forced to three groups.
