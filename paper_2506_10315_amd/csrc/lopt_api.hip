@@ -1,6 +1,7 @@
 // Host side of the C boundary declared in include/lopt.h: argument validation, the upload of the device tables that the
 // planner (lopt_plan.h) makes of a tensor list, and the launch sequence of a step.
 #include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -58,6 +59,16 @@ bool config_ok(const lopt_config* c, std::string* why) {
     if (c->n_bank < 1 || c->n_bank > 1024) return bad("config.n_bank must be in [1, 1024]");
   }
   return true;
+}
+
+// The folded head holds W_a B, which finite weights may take out of the fp32 range although h W_a and (h W_a) B stay in it (an
+// infinity there is also a NaN wherever h is 0). Every entry and, as |h| < 1, every partial sum of h (W_a B) + b_a B is at
+// most the bound below; weights beyond it keep the two products.
+bool head_fold_in_range(const float* Wa_ba, const float* B, size_t HL, size_t K, size_t P) {
+  float a = 0.f, b = 0.f;
+  for (size_t i = 0; i < (HL + 1) * K; ++i) a = std::fmax(a, std::fabs(Wa_ba[i]));
+  for (size_t i = 0; i < K * P; ++i) b = std::fmax(b, std::fabs(B[i]));
+  return (double)a * (double)b * (double)((HL + 1) * K) <= (double)FLT_MAX;
 }
 
 // Device copy of the plan's tables and what it currently holds.
@@ -369,7 +380,12 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
   CREATE_TRY(hipGetDevice(&ctx->device));
   CREATE_TRY(hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
   // one allocation: the uploaded blob, then (VeLO) the hypernetwork's weights in the layouts its kernels read
-  const bool folds = cfg->kind == LOPT_VELO && head_folds((int)cfg->lstm_hidden, (int)cfg->n_bank, ctx->P);
+  bool folds = false;
+  if (cfg->kind == LOPT_VELO) {
+    const size_t HL = cfg->lstm_hidden, K = cfg->n_bank;
+    const float* Wa = weights_host + (LOPT_VELO_LSTM_IN + 2 * HL + 1) * 4 * HL;   // Wx Wh Wg b before it
+    folds = head_folds((int)HL, (int)K, ctx->P) && head_fold_in_range(Wa, Wa + (HL + 1) * K + HL + 1, HL, K, (size_t)ctx->P);
+  }
   ctx->opts.kind = (int)cfg->kind;
   ctx->opts.HP = ctx->HP;
   ctx->opts.P = ctx->P;

@@ -94,6 +94,40 @@ def test_velo_folded_head_and_lstm_octets(hidden, lstm_hidden, n_bank, count):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+def _velo_weight_views(w, cfg):
+    """The sections of a VeLO weight blob (include/lopt.h) as views of `w`."""
+    HL, K, h = int(cfg.lstm_hidden), int(cfg.n_bank), int(cfg.hidden)
+    P_ = 29 * h + h + h * h + h + 2 * h + 2
+    out, o = {}, 0
+    for name, shape in (("Wx", (48, 4, HL)), ("Wh", (HL, 4, HL)), ("Wg", (HL, 4, HL)), ("b", (4, HL)), ("Wa", (HL, K)), ("ba", (K,)),
+                        ("ws", (HL,)), ("bs", (1,)), ("B", (K, P_))):
+        n = int(np.prod(shape))
+        out[name] = w[o:o + n].reshape(shape)
+        o += n
+    assert o == w.size
+    return out
+
+
+@pytest.mark.parametrize("count", [3, 1030])
+def test_velo_bank_products_beyond_the_fp32_range(count):
+    # finite weights whose product W_a B is not: a unit whose output is exactly 0 (its candidate gate has no weights) with
+    # coefficients of 1e30 beside a bank of 1e10; h W_a and (h W_a) B stay of ordinary size
+    cfg = Hn.make_cfg("velo", lstm_hidden=64, n_bank=128)
+    w = Hn.random_weights(cfg, seed=50)
+    v = _velo_weight_views(w, cfg)
+    for name in ("Wx", "Wh", "Wg"):
+        v[name][:, 2, 5] = 0.0
+    v["b"][2, 5] = 0.0
+    v["Wa"][:] *= 1e-10
+    v["ba"][:] *= 1e-10
+    v["B"][:] *= 1e10
+    v["Wa"][5] = np.where(np.arange(128) % 3 == 0, -1e30, 1e30)
+    r = np.random.default_rng(79)
+    shapes = [(7, 13), (33, 20)] + [(int(r.integers(8, 60)),) for _ in range(count - 2)]
+    worst = Hn.run_free(Hn.Case(117, _specs(shapes), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
 def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
     # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of up to 128 rows x 128 columns,
