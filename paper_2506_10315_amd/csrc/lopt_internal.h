@@ -79,7 +79,7 @@ struct WeightsDev {
   const float* Wx; const float* Wh; const float* Wg; const float* b; const float* Wa; const float* ba;
   const float* ws; const float* bs; const float* B;
   const float* lstm;   // [Wx ; Wh] repacked for k_velo_lstm: [ceil(H_L / 8)][lstm_k_pad(H_L)][4 gates x 8 units]
-  const float* head;   // W_a, b_a, B and the step-size head folded into one matrix (null: the bank is too small for it to pay)
+  const float* head;   // W_a, b_a, B and the step-size head folded into one matrix (null: two products, see head_folds)
 };
 
 // Input slots of the LSTM rounded up to whole octets; row length of the folded head (P columns and the step size's).

@@ -878,7 +878,10 @@ __device__ __forceinline__ int head_slot(int i, int H, int HP, const float* __re
 
 // One workgroup per tensor, 16 wavefronts. Wavefront w reduces rows w, w + 16, ... of the folded matrix, a lane four columns
 // as one float4, sixteen rows in flight (bound by their latency: 309 KB at the default widths); partials meet in LDS in a
-// fixed order. Replaces two dependent products (660 KB): 10.3 -> 6.5 us; 152 tensors 14.7 -> 8.4 us.
+// fixed order. Replaces two dependent products (660 KB): 10.3 -> 6.5 us; 152 tensors 14.7 -> 8.4 us. Eight sums per lane
+// and column and a tree behind them, not one chain: the step size's logarithm is a column too, and its absolute error is the
+// relative error of the whole update (rms error of 512 random terms: 8.9e-8 in chains of 32 and 16, 5.9e-8 as 64 chains of
+// eight and a tree, 5.7e-8 this way).
 constexpr int kHeadWaves = 16;
 __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_folded(const TensorDev* __restrict__ tensors,
                                                                       float* __restrict__ ws, StepArgs A, WeightsDev W,
@@ -909,7 +912,9 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_folded(const Tens
     const int c0 = blk == 0 ? last : (blk - 1) * 256;
     const int col = c0 + 4 * lane;
     const float4* __restrict__ m = reinterpret_cast<const float4*>(W.head + min(col, ld - 4));
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int k0 = wave; k0 < HL; k0 += 16 * kHeadWaves) {
       float4 w[16];
 #pragma unroll
@@ -918,17 +923,29 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_folded(const Tens
       for (int j = 0; j < 16; ++j) {
         const int k = k0 + j * kHeadWaves;
         const float x = k < HL ? sh_h[min(k, HL - 1)] : 0.f;
-        acc.x += x * w[j].x; acc.y += x * w[j].y; acc.z += x * w[j].z; acc.w += x * w[j].w;
+        float4& a = acc[j & 7];
+        a.x += x * w[j].x; a.y += x * w[j].y; a.z += x * w[j].z; a.w += x * w[j].w;
       }
     }
-    *reinterpret_cast<float4*>(part + wave * 256 + 4 * lane) = acc;
+#pragma unroll
+    for (int step = 1; step < 8; step *= 2)
+#pragma unroll
+      for (int q = 0; q < 8; q += 2 * step) {
+        acc[q].x += acc[q + step].x; acc[q].y += acc[q + step].y; acc[q].z += acc[q + step].z; acc[q].w += acc[q + step].w;
+      }
+    *reinterpret_cast<float4*>(part + wave * 256 + 4 * lane) = acc[0];
     __syncthreads();
     const int i = c0 + (int)threadIdx.x;
     float th = 0.f;
     if (threadIdx.x < 256 && i <= P) {
-      th = W.head[(size_t)HL * ld + i];
+      float s[kHeadWaves];
 #pragma unroll
-      for (int w = 0; w < kHeadWaves; ++w) th += part[w * 256 + threadIdx.x];
+      for (int w = 0; w < kHeadWaves; ++w) s[w] = part[w * 256 + threadIdx.x];
+#pragma unroll
+      for (int step = 1; step < kHeadWaves; step *= 2)
+#pragma unroll
+        for (int w = 0; w < kHeadWaves; w += 2 * step) s[w] += s[w + step];
+      th = W.head[(size_t)HL * ld + i] + s[0];
       if (i == P) s_lam = expf(th);
     }
     __syncthreads();   // s_lam; the partials may be overwritten
@@ -1100,26 +1117,23 @@ __global__ void __launch_bounds__(kBlock) k_rows_matmul(const float* __restrict_
   }
 }
 
-// One workgroup per tensor: new h into the state, step-size multiplier, theta[P] scattered into the prepared layout.
-// FOLDED: the step size's logarithm is column P of theta (rows of head_ld(P)), otherwise it is formed here (rows of P).
-template <bool FOLDED>
+// One workgroup per tensor: new h into the state, step-size multiplier, theta[P] (rows of ld) scattered into the prepared layout.
+// The step size's logarithm is formed here (eight terms a lane and a tree): as a column of the product it would be chains of 128.
 __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                               StepArgs A, WeightsDev W, const float* __restrict__ h_new,
-                                                              const float* __restrict__ theta) {
+                                                              const float* __restrict__ theta, int ld) {
   __shared__ float s_lam;
   const TensorDev& T = tensors[blockIdx.x];
   const int HL = A.HL, H = A.H, HP = A.HP, F = LOPT_D_VELO, P = A.P;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float* hstate = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
   const float* __restrict__ hn = h_new + (size_t)blockIdx.x * HL;
-  const float* __restrict__ th_row = theta + (size_t)blockIdx.x * (FOLDED ? head_ld(P) : P);
+  const float* __restrict__ th_row = theta + (size_t)blockIdx.x * ld;
   for (int i = threadIdx.x; i < HL; i += kBlock) hstate[i] = hn[i];
   float* prep = ws + T.oPrep;
   const int prep_n = (F + 1) * HP + HP * HP + HP + 2 * HP + 2;
   for (int i = threadIdx.x; i < prep_n; i += kBlock) prep[i] = 0.f;   // the padding must be zero
-  if (FOLDED) {
-    if (threadIdx.x == 0) s_lam = expf(th_row[P]);
-  } else if (wave == 0) {
+  if (wave == 0) {
     float a = 0.f;
     for (int i = lane; i < HL; i += kWave) a += hn[i] * W.ws[i];
     a = wave_sum(a);
@@ -1146,9 +1160,9 @@ void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, c
     const int ld = head_ld(A.P);
     if (batched) {
       float* th = theta + (size_t)L.tensor0 * ld;
-      hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 1 + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.head,
-                         ld, A.P + 1, W.head + (size_t)A.HL * ld, th, ld);
-      hipLaunchKernelGGL(k_velo_head_scatter<true>, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th);
+      hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.head,
+                         ld, A.P, W.head + (size_t)A.HL * ld, th, ld);
+      hipLaunchKernelGGL(k_velo_head_scatter, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th, ld);
     } else {
       const size_t shmem = (size_t)(((A.HL + 3) & ~3) + kHeadWaves * 256) * sizeof(float);
       hipLaunchKernelGGL(k_velo_head_folded, dim3(T), dim3(64 * kHeadWaves), shmem, s, L.tensors + L.tensor0, L.ws, A, W, hn);
@@ -1162,7 +1176,7 @@ void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, c
                        A.K, W.ba, al, A.K);
     hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 63) / 64), dim3(kBlock), 0, s, al, A.K, T, A.K, W.B, A.P,
                        A.P, (const float*)nullptr, th, A.P);
-    hipLaunchKernelGGL(k_velo_head_scatter<false>, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th);
+    hipLaunchKernelGGL(k_velo_head_scatter, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th, A.P);
     return;
   }
   const int W64 = ((A.K > A.P ? A.K : A.P) + 63) & ~63;

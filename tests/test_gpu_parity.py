@@ -128,6 +128,36 @@ def test_velo_bank_products_beyond_the_fp32_range(count):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("count", [3, 1030])
+def test_velo_step_size_is_summed_with_few_roundings(count):
+    # ln(lambda) = h . ws over 512 equal terms of about 0.12, whose long serial sums round the same way again and again (the
+    # chosen ws: 12 units of 2^-24 after 32 + 16 terms, 20 after 128 + 4; 0.4 from eight terms a lane and a tree, in any of
+    # the three floats next to tanh(1)). One rounding for the products and up to three for eight terms a lane are admitted,
+    # the tree is exact; 8 units for expf, the MLP's output layer and the update. W_a and B make the direction exactly 1.
+    import torch
+    import paper_2506_10315_amd as P
+    cfg = Hn.make_cfg("velo")
+    w = np.zeros(P.weights_count(cfg), np.float32)
+    v = _velo_weight_views(w, cfg)
+    v["b"][:] = 20.0                       # saturated gates: c = 1, h = tanh(1) in every unit
+    v["ba"][0] = 1.0
+    v["B"][0, -2] = 1.0                    # b3, direction
+    v["ws"][:] = 0.15736201
+    shapes = [(8, 16)] * count
+    opt = P.LearnedOptimizer(cfg, w, shapes)
+    p = [torch.zeros(s, device="cuda:0") for s in shapes]
+    g = [torch.full(s, 1e-3, device="cuda:0") for s in shapes]
+    opt.step(p, g, lr=1.0, step=0, loss=1.0)
+    torch.cuda.synchronize()
+    for i in (0, count - 1):
+        h = opt.state_views(i)["h"].cpu().numpy().astype(np.float64)
+        ln = float(h @ v["ws"].astype(np.float64))
+        assert 61.0 < ln < 62.0
+        lam = -p[i].cpu().numpy().astype(np.float64) / float(np.float32(cfg.step_mult))
+        assert np.max(np.abs(lam / np.exp(ln) - 1.0)) <= (4 * ln + 8) * 2.0 ** -24
+    opt.close()
+
+
 @pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
 def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
     # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of up to 128 rows x 128 columns,
