@@ -392,6 +392,9 @@ lopt_status lopt_create(const lopt_config* cfg, const float* weights_host, size_
   ctx->opts.lstm_hidden = (int)cfg->lstm_hidden;
   ctx->opts.n_bank = (int)cfg->n_bank;
   ctx->opts.head_folded = folds;
+  if (cfg->kind == LOPT_SMALL_FC && ctx->HP <= 16 && apply_variant != LOPT_APPLY_VALU) ctx->opts.apply = ApplyTiles::Narrow;
+  if (cfg->kind == LOPT_SMALL_FC && ctx->HP == 32 && (apply_variant == LOPT_APPLY_AUTO || apply_variant == LOPT_APPLY_MFMA_F16S))
+    ctx->opts.apply = ApplyTiles::Strip;
   ctx->opts.groups_override = groups_override;
   ctx->opts.n_cu = ctx->n_cu;
   size_t lstm_n = 0, head_n = 0;

@@ -13,12 +13,16 @@ inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
 inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }   // a up to 2^31 - 1: a + b - 1 does not fit an int
 
+// The apply kernels that take their work from the table of apply tiles (the others walk the statistics tiles).
+enum class ApplyTiles { None, Strip, Narrow };   // k_apply_f16s; k_apply_fc4x
+
 // What the planner has to know of a context.
 struct PlanOptions {
   int kind = LOPT_SMALL_FC;      // lopt_kind
   int HP = 0, P = 0;             // padded MLP width; VeLO: floats per per-tensor MLP
   int lstm_hidden = 0, n_bank = 0;
   bool head_folded = false;      // VeLO: the hypernetwork head is one folded matrix (WeightsDev::head)
+  ApplyTiles apply = ApplyTiles::None;
   int groups_override = 0;       // tensor groups of the two-stream pipeline (0 = choose by size)
   int n_cu = 256;
 };
@@ -28,7 +32,7 @@ struct Plan {
   std::vector<TensorDev> tensors;   // pointers filled per call
   std::vector<TileDev> tiles;
   std::vector<RcItemDev> rcitems;
-  std::vector<ApplyTileDev> atiles;   // tiles of the strip-form apply kernel
+  std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
   int64_t max_rows = 0;               // of any tensor
@@ -37,7 +41,7 @@ struct Plan {
   uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
   uint64_t oAlpha = 0, oTheta = 0;   // VeLO, long lists: bank coefficients [T][K] and per-tensor MLPs [T][P]
   bool head_batched = false;
-  uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the strip-form apply kernel
+  uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the apply kernel
   uint64_t ws_floats = 0;
 };
 
@@ -158,11 +162,11 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.rc0 = (int)pl->rcitems.size();
     for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
     for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
-    // apply tiles: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
+    // apply tiles, for the kernels that read them: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
     pl->atile0[i] = (int)pl->atiles.size();
     pl->total_elems += N;
     if (m > pl->max_rows) pl->max_rows = m;
-    for (int ar0 = 0; ar0 < m;) {
+    for (int ar0 = 0; o.apply != ApplyTiles::None && ar0 < m;) {
       // position of this row block inside its group: full height for the first 70 %, half to 88 %, a quarter after
       const uint64_t pos = gbefore[i] + (uint64_t)ar0 * (uint64_t)nn, gt = gtotal[group_of[i]];
       int AR = kApplyRows / shrink;

@@ -21,12 +21,13 @@ def _probe():
 
 
 def plan(shapes, kind="small_fc_lopt", hidden=None, lstm_hidden=512, n_bank=256, groups=0):
-    """The plan of a list of (rows, cols)."""
+    """The plan of a list of (rows, cols) with the default apply kernels."""
     h = hidden if hidden is not None else 32 if kind == "small_fc_lopt" else 4
     hp = next(x for x in (4, 8, 16, 32) if h <= x)
     p = 29 * h + h + h * h + h + 2 * h + 2
     folded = n_bank >= 4 and lstm_hidden * p <= lstm_hidden * n_bank + n_bank * p
-    args = [int(kind == "velo"), hp, p, lstm_hidden, n_bank, int(folded), groups, N_CU]
+    args = [int(kind == "velo"), hp, p, lstm_hidden, n_bank, int(folded), groups, N_CU,
+            0 if kind == "velo" else 1 if hp == 32 else 2]
     r = subprocess.run([_probe(), *map(str, args)], input="\n".join(f"{m} {n}" for m, n in shapes), capture_output=True,
                        text=True, check=True)
     return json.loads(r.stdout)

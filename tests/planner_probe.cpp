@@ -1,13 +1,14 @@
 // Prints what the planner makes of a tensor list, one JSON object: built and run on the CPU by tests/planner.py.
-// Arguments: kind hidden_padded P lstm_hidden n_bank head_folded groups n_cu; standard input: "rows cols" per tensor.
+// Arguments: kind hidden_padded P lstm_hidden n_bank head_folded groups n_cu apply (0 none, 1 strip, 2 narrow); standard input: "rows cols" per tensor.
 #include <cstdio>
 #include <cstdlib>
-#include <map>
+#include <utility>
+#include <vector>
 
 #include "lopt_plan.h"
 
 int main(int argc, char** argv) {
-  if (argc != 9) return 2;
+  if (argc != 10) return 2;
   lopt::PlanOptions o;
   o.kind = atoi(argv[1]);
   o.HP = atoi(argv[2]);
@@ -17,6 +18,7 @@ int main(int argc, char** argv) {
   o.head_folded = atoi(argv[6]) != 0;
   o.groups_override = atoi(argv[7]);
   o.n_cu = atoi(argv[8]);
+  o.apply = (lopt::ApplyTiles)atoi(argv[9]);
   std::vector<lopt_tensor_desc> d;
   long long m, n;
   while (scanf("%lld %lld", &m, &n) == 2) {
@@ -26,13 +28,16 @@ int main(int argc, char** argv) {
   }
   lopt::Plan pl;
   lopt::build_plan(o, d.size(), d.data(), &pl);
-  std::map<int, long long> heights;
-  for (const auto& t : pl.atiles) heights[t.rows]++;
-  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_atiles\": %zu, \"atile_rows\": {",
+  std::vector<std::pair<int, long long>> runs;   // heights of the apply tiles in table order, run by run
+  for (const auto& t : pl.atiles) {
+    if (runs.empty() || runs.back().first != t.rows) runs.push_back({t.rows, 0});
+    runs.back().second++;
+  }
+  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_atiles\": %zu, \"atile_runs\": [",
          (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.atiles.size());
   const char* sep = "";
-  for (const auto& h : heights) { printf("%s\"%d\": %lld", sep, h.first, h.second); sep = ", "; }
-  printf("}, \"tensors\": [");
+  for (const auto& h : runs) { printf("%s[%d, %lld]", sep, h.first, h.second); sep = ", "; }
+  printf("], \"tensors\": [");
   for (size_t i = 0; i < d.size(); ++i) {
     const lopt::TensorDev& T = pl.tensors[i];
     printf("%s{\"TR\": %d, \"nrt\": %d, \"nct\": %d, \"nrblk\": %d, \"ncblk\": %d, \"state_bytes\": %zu, "

@@ -22,3 +22,11 @@ def test_block_counts_at_the_size_limit(rows, cols):
         assert at[k] + s <= at[k + 1]
     assert at[-1] < r["ws_floats"] < 2 ** 36
     assert t["state_bytes"] == 4 * (4 * pad4(rows * cols) + 3 * pad4(rows) + 3 * pad4(cols))
+
+
+def test_only_the_kernels_that_read_apply_tiles_get_them():
+    # VeLO's kernels walk the statistics tiles: no table of apply tiles to upload or to count against lopt_step_static's array
+    shapes = [(5504, 2048)] * 4 + [(1, 300)] * 50
+    velo, fc = plan(shapes, kind="velo"), plan(shapes)
+    assert velo["n_atiles"] == 0 and fc["n_atiles"] > 0
+    assert fc["table_bytes"] - velo["table_bytes"] >= 16 * fc["n_atiles"]
