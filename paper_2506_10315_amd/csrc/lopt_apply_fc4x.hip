@@ -24,12 +24,6 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Rows of loads in flight per wavefront, wavefronts per SIMD. Width 16 is bound by its instructions: occupancy is worth more than
-// prefetch there (four rows and three wavefronts 198 us a step, two and four 196, one and four 192, one and five 191 with
-// 14 spilled registers; 9.5 M elements).
-constexpr int trip_rows(int HP) { return HP == 16 ? 1 : 4; }
-constexpr int waves_per_simd(int HP) { return HP == 8 ? 3 : 4; }
-
 template <int HP>
 struct Fc4Lds {
   f32x4 rowv[kApplyRows][HP / 4];         // bias (time features folded in) + row-constant features, first layer
@@ -225,7 +219,7 @@ struct Mlp<16> {
 template <int HP, bool NT, bool RAW_RSQ, bool UPDATE_STATE>
 __device__ __forceinline__ void apply_fc4x_tile(const TensorDev& T, const ApplyTileDev& tile, const float* __restrict__ ws,
                                                 const StepArgs& A, const float* __restrict__ tail, Fc4Lds<HP>& L) {
-  constexpr int kTrip = trip_rows(HP);
+  constexpr int kTrip = narrow_trip_rows(HP);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = T.n;
   const int rsplit = n - tile.c0 > kWave ? 2 : 4;          // wavefronts that share a 64-column segment's rows
@@ -314,10 +308,10 @@ __device__ __forceinline__ void apply_fc4x_tile(const TensorDev& T, const ApplyT
 // Persistent workgroups: the first tile is the workgroup's number, the next ones come from a counter (k_finalize cleared
 // it); the table's last tiles are shorter, so that a launch does not end on a nearly empty last round.
 template <int HP, bool RAW_RSQ, bool UPDATE_STATE>
-__global__ void __launch_bounds__(kBlock, waves_per_simd(HP)) k_apply_fc4x(const TensorDev* __restrict__ tensors,
-                                                                        const ApplyTileDev* __restrict__ atiles, int n_atiles,
-                                                                        int* __restrict__ next_tile, float* __restrict__ ws,
-                                                                        StepArgs A, const float* __restrict__ tail) {
+__global__ void __launch_bounds__(kBlock, narrow_waves_per_simd(HP)) k_apply_fc4x(const TensorDev* __restrict__ tensors,
+                                                                               const ApplyTileDev* __restrict__ atiles, int n_atiles,
+                                                                               int* __restrict__ next_tile, float* __restrict__ ws,
+                                                                               StepArgs A, const float* __restrict__ tail) {
   __shared__ Fc4Lds<HP> L;
   __shared__ int s_tile;
   for (int tile_id = blockIdx.x; tile_id < n_atiles; tile_id = s_tile) {   // workgroup-uniform
@@ -339,7 +333,7 @@ void launch_apply_fc4x(const Launch& L, const StepArgs& A, const WeightsDev& W, 
   // v_rsq_f32 treats inputs below the smallest normal float as zero; with eps_acc that small the kernel takes the library
   // reciprocal square root (which rescales such inputs) instead of the bare instruction
   const bool raw = A.eps_acc >= 1e-30f;
-  const int resident = L.resident_wgs / 2 * waves_per_simd(A.HP);   // (resident_wgs counts two workgroups per CU)
+  const int resident = L.resident_wgs / 2 * narrow_waves_per_simd(A.HP);   // (resident_wgs counts two workgroups per CU)
   const int grid = L.n_atiles < resident ? L.n_atiles : resident;
 #define LOPT_LAUNCH_FC4X(HP, R, U)                                                                                    \
   hipLaunchKernelGGL((k_apply_fc4x<HP, R, U>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,       \

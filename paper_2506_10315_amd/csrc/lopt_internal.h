@@ -28,6 +28,11 @@ constexpr int kMixJSplit = 4;     // the LSTM units are cut into this many range
 #endif
 constexpr int kApplyRows = LOPT_APPLY_ROWS;   // tile of the strip-form apply kernel: up to this many rows x 128 columns
 constexpr int kApplyCols = 128;
+// small_fc_lopt of padded width 4, 8 or 16 (k_apply_fc4x): rows of loads in flight per wavefront, wavefronts per SIMD (which is
+// workgroups per CU). Width 16 is bound by its instructions: occupancy is worth more than prefetch there (four rows and three
+// wavefronts 198 us a step, two and four 196, one and four 192, one and five 191 with 14 spilled registers; 9.5 M elements).
+constexpr int narrow_trip_rows(int HP) { return HP == 16 ? 1 : 4; }
+constexpr int narrow_waves_per_simd(int HP) { return HP == 8 ? 3 : 4; }
 
 // Per-tensor record in device memory. Offsets o* are in floats from the workspace base.
 struct TensorDev {

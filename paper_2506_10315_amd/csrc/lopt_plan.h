@@ -97,12 +97,12 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       pl->oTheta = take((uint64_t)n * (uint64_t)(o.head_folded ? head_ld(o.P) : o.P));
     }
   }
-  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off): the
-  // strip apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
+  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off, as it is for
+  // every kernel but the strip one): the apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
   // while the final workgroups finish (a 128-row tile is about 90 us of work, a 32-row tile a quarter of that).
   uint64_t total = 0;
   for (size_t i = 0; i < n; ++i) total += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-  const int G_plan = o.kind == LOPT_SMALL_FC ? planned_groups(o.groups_override, total, n) : 1;
+  const int G_plan = o.apply == ApplyTiles::Strip ? planned_groups(o.groups_override, total, n) : 1;
   int gbound[kMaxGroups + 1];
   group_bounds(d, n, G_plan, total, gbound);
   std::vector<uint64_t> gtotal(G_plan, 0), gbefore(n, 0);
@@ -121,16 +121,23 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
-  // Short lists: the smallest even apply-tile height at which every tile has a workgroup slot of its own (two per CU), if
-  // that is at most 32 rows: the launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the
-  // graded heights below gave 650 tiles and a second, nearly empty round).
+  // Short lists: the smallest even apply-tile height at which every CU gets at most two tiles, if that is at most 32 rows: the
+  // launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the graded heights below gave 650
+  // tiles and a second, nearly empty round). The strip kernel has two workgroups per CU. The narrow one has three or four, and
+  // as many tiles are its second choice (1700x1400, width 4: 63.6 us a step with graded heights, 59.5 this way; 1000x1000: 39.6
+  // with two tiles per CU, 44.2 with four); its wavefronts take narrow_trip_rows at a time, two to a column segment, and
+  // a tile is at least that high (toy list of three tensors, width 4: 25.2 us with tiles of two rows, 23.5 with eight).
+  const bool narrow = o.apply == ApplyTiles::Narrow;
   int ar_short = 0;
-  for (int ar : {2, 4, 6, 8, 12, 16, 20, 24, 32}) {
-    uint64_t tiles = 0;
-    for (size_t i = 0; i < n; ++i)
-      tiles += (uint64_t)((d[i].rows + ar - 1) / ar) * (uint64_t)((d[i].cols + kApplyCols - 1) / kApplyCols);
-    if (tiles <= 2ull * o.n_cu) { ar_short = ar; break; }
-  }
+  for (int per_cu : {2, narrow ? narrow_waves_per_simd(HP) : 2})
+    for (int ar : {2, 4, 6, 8, 12, 16, 20, 24, 32}) {
+      if (ar_short || o.apply == ApplyTiles::None || (narrow && ar < 2 * narrow_trip_rows(HP))) continue;
+      const uint64_t most = (uint64_t)per_cu * o.n_cu;
+      uint64_t tiles = 0;
+      for (size_t i = 0; i < n && tiles <= most; ++i)
+        tiles += (uint64_t)((d[i].rows + ar - 1) / ar) * (uint64_t)((d[i].cols + kApplyCols - 1) / kApplyCols);
+      if (tiles <= most) ar_short = ar;
+    }
   for (size_t i = 0; i < n; ++i) {
     TensorDev& T = pl->tensors[i];
     const int m = (int)d[i].rows, nn = (int)d[i].cols;

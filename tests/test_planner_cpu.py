@@ -30,3 +30,27 @@ def test_only_the_kernels_that_read_apply_tiles_get_them():
     velo, fc = plan(shapes, kind="velo"), plan(shapes)
     assert velo["n_atiles"] == 0 and fc["n_atiles"] > 0
     assert fc["table_bytes"] - velo["table_bytes"] >= 16 * fc["n_atiles"]
+
+
+@pytest.mark.parametrize("hidden,groups", [(32, 3), (16, 1), (8, 1), (4, 1)])
+def test_apply_tiles_shorten_once_per_launch(hidden, groups):
+    # 134 M elements: three tensor groups, but only the strip kernel (width 32) is launched once per group; every launch has
+    # tiles of full height, then half, then a quarter
+    runs = [h for h, _ in plan([(8192, 4096)] * 4, hidden=hidden)["atile_runs"]]
+    assert runs == [128, 64, 32] * groups
+
+
+@pytest.mark.parametrize("hidden,per_cu,least", [(32, 2, 2), (16, 4, 2), (8, 3, 8), (4, 4, 8)])
+@pytest.mark.parametrize("shapes", [[(256, 256), (1, 256), (64, 256)], [(1000, 1000)], [(1700, 1400)], [(40, 30)]])
+def test_short_lists_are_one_round_of_equal_tiles(hidden, per_cu, least, shapes):
+    # two tiles per CU if 32 rows suffice, otherwise as many as the kernel has workgroups there (otherwise graded heights); no
+    # tile lower than one trip of the two wavefronts that share a column segment
+    r = plan(shapes, hidden=hidden)
+    tiles = lambda ar: sum(-(-m // ar) * -(-n // 128) for m, n in shapes)
+    heights = [ar for ar in (2, 4, 6, 8, 12, 16, 20, 24, 32) if ar >= least]
+    want = [ar for k in (2, per_cu) for ar in heights if tiles(ar) <= 256 * k]
+    if not want:
+        assert hidden == 32 and shapes == [(1700, 1400)]   # 594 tiles of 32 rows
+        return
+    top = max(h for h, _ in r["atile_runs"])
+    assert top == min(want[0], max(m for m, _ in shapes)) and r["n_atiles"] == tiles(want[0])
