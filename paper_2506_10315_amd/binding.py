@@ -138,6 +138,7 @@ class LearnedOptimizer:
         self.state = [torch.empty(b // 4, dtype=torch.float32, device=self.device) for b in self.state_bytes]
         self.workspace = torch.empty(max(self.workspace_bytes // 4, 64), dtype=torch.float32, device=self.device)
         self._state_ptrs = (C.c_void_p * max(self.n, 1))(*[t.data_ptr() for t in self.state])
+        self._fitted = None      # the part of the list that the workspace was last found to hold (step's `indices`)
         self.step_count = 0
         self.init_state()
 
@@ -166,6 +167,8 @@ class LearnedOptimizer:
             n = len(indices)
             descs = (lopt_tensor_desc * max(n, 1))(*[self._descs[i] for i in indices])
             sp = (C.c_void_p * max(n, 1))(*[self.state[i].data_ptr() for i in indices])
+            if not static:
+                self._fit_workspace(tuple(indices), n, descs)
         assert len(params) == n and len(grads) == n
         if loss is not None:
             self.set_loss(loss)
@@ -181,6 +184,20 @@ class LearnedOptimizer:
                                        C.c_void_p(self.workspace.data_ptr()), t, lr, weight_decay,
                                        self._stream()), self._ctx)
         self.step_count = t + 1
+
+    def _fit_workspace(self, key, n, descs):
+        """A part of the list may need more workspace than the whole: shorter lists are cut into lower tiles, each with
+        partial sums of its own."""
+        if key == self._fitted:
+            return
+        need = C.c_size_t()
+        _check(lib().lopt_state_bytes(self._ctx, n, descs, None, C.byref(need)), self._ctx)
+        if need.value > self.workspace.numel() * 4:
+            # earlier steps on this stream may still use the old one
+            self.workspace.record_stream(self._torch.cuda.current_stream(self.device))
+            self.workspace = self._torch.empty(need.value // 4, dtype=self._torch.float32, device=self.device)
+            self.workspace_bytes = int(need.value)
+        self._fitted = key
 
     def profile_enable(self, on: bool = True):
         _check(lib().lopt_profile_enable(self._ctx, 1 if on else 0), self._ctx)

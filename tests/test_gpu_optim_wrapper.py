@@ -100,3 +100,43 @@ def test_parameters_without_gradients_are_skipped_and_the_loss_matters_for_velo(
         assert bool((opt._engines[0].state[3] == 0).all())      # its accumulators never moved
         res[loss_value] = [p.detach().clone() for p in model.parameters()]
     assert any(not torch.equal(a, b) for a, b in zip(res[0.7], res[9.0]))   # the loss value reaches the update
+
+
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_a_step_over_a_part_of_the_list_has_the_workspace_it_needs(kind):
+    # the list without its third tensor needs 1.7 times the workspace of the whole list (tests/test_planner_cpu.py); the step
+    # is that of an optimizer made for the part, bit for bit
+    import ctypes as C
+    import torch
+    import paper_2506_10315_amd as P
+    from tests.test_planner_cpu import SUBLIST
+    cfg = Hn.make_cfg(kind) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=16)
+    w = Hn.random_weights(cfg, 9)
+    part = [0, 1, 3, 4]
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    p0 = [torch.randn(s, device="cuda:0", generator=gen) * 0.02 for s in SUBLIST]
+    g = [torch.randn(s, device="cuda:0", generator=gen) * 1e-3 for s in SUBLIST]
+    whole = P.LearnedOptimizer(cfg, w, SUBLIST)
+    alone = P.LearnedOptimizer(cfg, w, [SUBLIST[i] for i in part])
+    assert alone.workspace_bytes > whole.workspace_bytes
+    a, b = [x.clone() for x in p0], [p0[i].clone() for i in part]
+    for t in range(2):
+        whole.step([a[i] for i in part], [g[i] for i in part], lr=0.5, step=t, loss=1.0, indices=part)
+        assert whole.workspace.numel() * 4 >= alone.workspace_bytes
+        alone.step(b, [g[i] for i in part], lr=0.5, step=t, loss=1.0)
+    whole.step(a, g, lr=0.5, step=2, loss=1.0)      # and the whole list again
+    torch.cuda.synchronize()
+    for k, i in enumerate(part):
+        assert not torch.equal(a[i], p0[i])
+    whole.close()
+    whole = P.LearnedOptimizer(cfg, w, SUBLIST)
+    a = [x.clone() for x in p0]
+    for t in range(2):
+        whole.step([a[i] for i in part], [g[i] for i in part], lr=0.5, step=t, loss=1.0, indices=part)
+    torch.cuda.synchronize()
+    for k, i in enumerate(part):
+        assert torch.equal(a[i].view(torch.int32), b[k].view(torch.int32))
+        assert torch.equal(whole.state[i].view(torch.int32), alone.state[k].view(torch.int32))
+    assert torch.equal(a[2], p0[2]) and not bool(whole.state[2].any())
+    whole.close()
+    alone.close()

@@ -54,3 +54,13 @@ def test_short_lists_are_one_round_of_equal_tiles(hidden, per_cu, least, shapes)
         return
     top = max(h for h, _ in r["atile_runs"])
     assert top == min(want[0], max(m for m, _ in shapes)) and r["n_atiles"] == tiles(want[0])
+
+
+SUBLIST = [(8216, 549), (9, 1024), (2059, 48), (528, 36), (144, 8211)]   # tests/test_gpu_optim_wrapper.py steps it without the third
+
+
+def test_a_part_of_a_list_may_need_more_workspace_than_the_whole():
+    # what a caller that steps parts of a list has to provide for: the shorter list falls below the tile count from which tiles
+    # keep their full height
+    whole, part = plan(SUBLIST), plan(SUBLIST[:2] + SUBLIST[3:])
+    assert part["tensors"][0]["TR"] < whole["tensors"][0]["TR"] and part["ws_floats"] > 1.5 * whole["ws_floats"]
