@@ -7,6 +7,7 @@ import pytest
 
 import workloads as W
 from tests import harness as Hn
+from tests.test_planner_cpu import NARROW, UNALIGNED
 
 pytestmark = pytest.mark.gpu
 
@@ -100,6 +101,29 @@ def test_state_pass_field_moves_the_accumulator_update_without_changing_a_bit(ki
         opt.close()
     for x, y in zip(*outs):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind,hidden,shapes", [("small_fc_lopt", 4, NARROW), ("small_fc_lopt", 8, NARROW), ("small_fc_lopt", 16, NARROW),
+                                                ("velo", 4, UNALIGNED)])
+def test_state_pass_changes_no_bit_on_full_tiles(kind, hidden, shapes):
+    # the same for the kernel of widths up to 16 and for VeLO's unaligned rows, on lists whose tiles take several trips
+    import torch
+    import paper_2506_10315_amd as P
+    dev = "cuda:0"
+    outs = []
+    for state_pass in ("stats", "apply"):
+        cfg = Hn.make_cfg(kind, hidden=hidden, state_pass=state_pass, **({} if kind == "small_fc_lopt" else {"lstm_hidden": 32, "n_bank": 8}))
+        opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, 1), shapes, device=dev)
+        gen = torch.Generator(device=dev).manual_seed(7)
+        p = [torch.randn(s, device=dev, generator=gen) * 0.02 for s in shapes]
+        for t in range(3):
+            g = [torch.randn(s, device=dev, generator=gen) * 10.0 ** -(1 + i % 4) for i, s in enumerate(shapes)]
+            opt.step(p, g, lr=0.7, weight_decay=0.01, step=t, loss=1.5 - 0.1 * t)
+        torch.cuda.synchronize()
+        outs.append([x.clone() for x in p] + [x.clone() for x in opt.state])
+        opt.close()
+    for x, y in zip(*outs):
+        assert torch.equal(x.view(torch.int32), y.view(torch.int32))
 
 
 @pytest.mark.parametrize("groups", [2, 3, 16])

@@ -8,6 +8,7 @@ import pytest
 
 import workloads as W
 from tests import harness as Hn
+from tests.test_planner_cpu import NARROW, UNALIGNED
 
 pytestmark = pytest.mark.gpu
 
@@ -56,8 +57,8 @@ def test_unaligned_rows_at_every_sweep_boundary(kind):
 @pytest.mark.parametrize("state_pass", ["apply", "stats"])
 def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass):
     # the width-4 kernel on rows that are not 16-byte aligned: one column per lane, four rows per trip, wavefronts on 64-column
-    # segments that share out the rows of narrow tiles: one, two, three and four segments, heights around the trip of four rows
-    # times four wavefronts; beside them 16-byte aligned rows off and on the 128-byte grid
+    # segments that share out the rows of narrow tiles: one, two, three and four segments, heights around the trip of four rows and the tile
+    # (a list this short has statistics tiles of eight rows); beside them 16-byte aligned rows off and on the 128-byte grid
     cfg = Hn.make_cfg("velo", lstm_hidden=32, n_bank=8, state_pass=state_pass)
     w = Hn.random_weights(cfg, seed=22)
     shapes = [(1, 1), (2, 3), (17, 61), (15, 65), (33, 129), (64, 190), (65, 257), (130, 318), (257, 1), (4, 449), (67, 260), (66, 288)]
@@ -160,13 +161,33 @@ def test_velo_step_size_is_summed_with_few_roundings(count):
 
 @pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
 def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
-    # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of up to 128 rows x 128 columns,
-    # 64 columns a wavefront: one segment, two segments, ragged second tiles, rows off and on the 16- and 128-byte grids,
-    # heights around one row per wavefront and the tile; the accumulators written in either pass
+    # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of 128 columns, 64 columns a
+    # wavefront: one segment, two segments, ragged second tiles, rows off and on the 16- and 128-byte grids, on tiles of the
+    # least height (two rows at width 16, eight below); the accumulators written in either pass
     cfg = Hn.make_cfg("small_fc_lopt", hidden=hidden, state_pass=state_pass)
     w = Hn.random_weights(cfg, seed=30 + hidden)
     shapes = [(1, 1), (3, 15), (5, 17), (2, 63), (129, 64), (17, 65), (16, 127), (260, 128), (9, 129), (31, 193), (7, 256), (70, 300)]
     worst = Hn.run_free(Hn.Case(114, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("hidden", [4, 8, 16])
+def test_small_fc_narrow_widths_on_full_tiles(hidden):
+    # tiles of 128, 64 and 32 rows, one and two column segments, and more tiles than workgroups (tests/test_planner_cpu.py): the
+    # row prefetch, the rows that wavefronts share and the tables of a workgroup's second tile
+    cfg = Hn.make_cfg("small_fc_lopt", hidden=hidden)
+    w = Hn.random_weights(cfg, seed=60 + hidden)
+    worst = Hn.run_free(Hn.Case(118, _specs(NARROW), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_unaligned_rows_on_tiles_of_ordinary_height(kind):
+    # tiles of 64 and 320 rows whose wavefronts share one or two column segments and take several trips of four rows each, or
+    # sit on three or four segments (tests/test_planner_cpu.py); small_fc_lopt for the statistics pass, which both share
+    cfg = Hn.make_cfg(kind) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8)
+    w = Hn.random_weights(cfg, seed=64)
+    worst = Hn.run_free(Hn.Case(119, _specs(UNALIGNED), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
     assert worst["param"] <= Hn.TOL_PARAM
 
 

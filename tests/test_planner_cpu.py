@@ -64,3 +64,24 @@ def test_a_part_of_a_list_may_need_more_workspace_than_the_whole():
     # keep their full height
     whole, part = plan(SUBLIST), plan(SUBLIST[:2] + SUBLIST[3:])
     assert part["tensors"][0]["TR"] < whole["tensors"][0]["TR"] and part["ws_floats"] > 1.5 * whole["ws_floats"]
+
+
+# Lists of the GPU tests whose point is the shape of the tiles they get, and what the planner makes of them.
+NARROW = [(2100, 129), (1301, 192), (131149, 17), (700, 65), (9, 40)]
+UNALIGNED = [(70007, 5), (12005, 61), (8003, 125), (5003, 190), (2001, 449), (1003, 257), (515, 65), (70003, 3)]
+
+
+@pytest.mark.parametrize("hidden,resident", [(4, 1024), (8, 768), (16, 1024)])
+def test_the_narrow_width_list_reaches_full_tiles_and_second_tiles_of_a_workgroup(hidden, resident):
+    r = plan(NARROW, hidden=hidden)
+    # 128 rows: four and eight trips of the two and four wavefronts that share a segment at widths 4 and 8; ragged last rows
+    assert [h for h, _ in r["atile_runs"]] == [128, 52, 128, 21, 128, 64, 32, 13, 32, 28, 9]
+    assert r["n_atiles"] > 1.5 * resident
+
+
+def test_the_unaligned_list_reaches_tiles_of_ordinary_height_and_every_number_of_segments():
+    r = plan(UNALIGNED, kind="velo", lstm_hidden=32, n_bank=8)
+    assert [t["TR"] for t in r["tensors"]] == [320, 64, 64, 64, 64, 64, 64, 320]
+    # 64-column segments of a tensor's last tile; the wavefronts that share one take 4 rows each, 16 or 8 a round
+    seg = {-(-(n - 256 * ((n - 1) // 256)) // 64) for _, n in UNALIGNED}
+    assert seg == {1, 2, 3, 4} and all(m % 16 and n % 4 for m, n in UNALIGNED)
