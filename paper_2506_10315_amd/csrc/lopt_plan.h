@@ -49,10 +49,11 @@ struct Plan {
 // two launches, two waits across streams and one more drain of both kernels, about 40 us. Measured, ms a step with
 // G = 1 / 2 / 3 / 4 / 5 / 8: 20 M elements 0.370 / 0.389 / 0.410 / 0.439 / 0.458 / 0.583; 40 M 0.752 / 0.766 / 0.807 / 0.851 /
 // 0.853 / 1.020; 87 M 1.57 / 1.53 / 1.54 / 1.55 / 1.64 / 1.78; 150 M 2.78 / 2.70 / 2.70 / 2.72 / 2.73 / 2.86; 355 M 6.36 / 6.14 /
-// 6.07 / 6.02 / 6.02 / 6.08.
+// 6.07 / 6.02 / 6.02 / 6.08. With G = 4 / 6 / 8 / 16: 435 M 7.20 / 7.19 / 7.28 / -; 536 M 8.90 / 8.87 / 8.85 / -; 738 M 12.27 / 12.21 /
+// 12.20 / 12.49; 1034 M 17.29 / 17.20 / 17.18 / 17.31; 1346 M 22.32 / 22.20 / 22.13 / 22.13.
 inline int planned_groups(int override_g, uint64_t total, size_t n) {
   int G = override_g;
-  if (!G) G = total >= (1024u << 20) ? 8 : total >= (256u << 20) ? 4 : total >= (128u << 20) ? 3 : total >= (64u << 20) ? 2 : 1;
+  if (!G) G = total >= (512u << 20) ? 8 : total >= (256u << 20) ? 4 : total >= (128u << 20) ? 3 : total >= (64u << 20) ? 2 : 1;
   if ((size_t)G > n) G = (int)n;
   return G < 1 ? 1 : G;
 }

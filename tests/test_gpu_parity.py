@@ -57,8 +57,8 @@ def test_unaligned_rows_at_every_sweep_boundary(kind):
 @pytest.mark.parametrize("state_pass", ["apply", "stats"])
 def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass):
     # the width-4 kernel on rows that are not 16-byte aligned: one column per lane, four rows per trip, wavefronts on 64-column
-    # segments that share out the rows of narrow tiles: one, two, three and four segments, heights around the trip of four rows and the tile
-    # (a list this short has statistics tiles of eight rows); beside them 16-byte aligned rows off and on the 128-byte grid
+    # segments that share out the rows of narrow tiles: one, two, three and four segments, heights around the trip of four rows
+    # and the tile (eight rows on a list this short); beside them 16-byte aligned rows off and on the 128-byte grid
     cfg = Hn.make_cfg("velo", lstm_hidden=32, n_bank=8, state_pass=state_pass)
     w = Hn.random_weights(cfg, seed=22)
     shapes = [(1, 1), (2, 3), (17, 61), (15, 65), (33, 129), (64, 190), (65, 257), (130, 318), (257, 1), (4, 449), (67, 260), (66, 288)]

@@ -40,6 +40,12 @@ def test_apply_tiles_shorten_once_per_launch(hidden, groups):
     assert runs == [128, 64, 32] * groups
 
 
+@pytest.mark.parametrize("count,groups", [(1, 1), (3, 4), (7, 4), (9, 8), (20, 8)])
+def test_tensor_groups_of_long_lists(count, groups):
+    # tensors of 64 M elements, 8192 x 8192: a single one is not cut, 512 M elements and more go in eight groups
+    assert [h for h, _ in plan([(8192, 8192)] * count)["atile_runs"]] == [128, 64, 32] * min(groups, count)
+
+
 @pytest.mark.parametrize("hidden,per_cu,least", [(32, 2, 2), (16, 4, 2), (8, 3, 8), (4, 4, 8)])
 @pytest.mark.parametrize("shapes", [[(256, 256), (1, 256), (64, 256)], [(1000, 1000)], [(1700, 1400)], [(40, 30)]])
 def test_short_lists_are_one_round_of_equal_tiles(hidden, per_cu, least, shapes):
