@@ -15,9 +15,10 @@
 //   velo_lstm, velo_head : the per-tensor hypernetwork (VeLO only)
 //   apply        : rebuild features, MLP, exponentiated update (lopt_apply_mfma.hip has the
 //                  matrix-core variant for hidden width 32)
-// A tile is TR rows x 256 columns; a wavefront owns whole rows of the tile (lane l holds the
-// four consecutive columns 4l..4l+3 as one float4), so row indices are wave-uniform and the
-// column factors are loaded once per tile.
+// A tile is TR rows x 256 columns, and row indices are wave-uniform everywhere. Rows on the 16-byte grid: lane l holds the four
+// consecutive columns 4l..4l+3 as one float4 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply
+// passes of rows of a multiple of 4 KB in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
+// a wavefront stays on one segment (the row/column sums: on all four in turn).
 #include "lopt_internal.h"
 #include "lopt_device.h"
 
@@ -381,6 +382,7 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 // Rows that are not 16-byte aligned (n % 4 != 0): one column per lane, every access a coalesced dword of a 256-byte row
 // segment, kAccRows rows of loads in flight. The wavefronts of the tile sit on adjacent 64-column segments; where the tile
 // is narrower than three segments they share out its rows as well. RAW_RCP as in the aligned path below.
+// (Three segments leave the fourth wavefront without work.)
 // Kept small in registers on purpose: the kernel's register count is the larger of its two paths, and it decides how
 // many of its workgroups fit beside the apply kernel of another tensor group (the float4 path's count, with four rows
 // too). Ordinary loads: neighbouring segments share their boundary lines. 8.3 M elements of 1531 columns: 48 us with one
@@ -792,7 +794,7 @@ __global__ void __launch_bounds__(64 * kLstmWaves) k_velo_lstm(const TensorDev* 
     for (int j = 0; j < kLstmOctets; ++j) {
       if (ob + j >= o_end) break;   // wavefront-uniform
       float x[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
-      const int kh = 8 * (ob + j) + 4 * khalf - kLstmInPad;   // slots of h past H_L (the blob's padding, the cell) count as 0
+      const int kh = 8 * (ob + j) + 4 * khalf - kLstmInPad;   // slots of h past H_L (the section's padding to four) count as 0
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         x[i] = kh + i < HL ? x[i] : 0.f;
