@@ -280,13 +280,15 @@ def test_context_reused_across_different_tensor_lists_and_streams():
         assert np.array_equal(x, y)
 
 
-@pytest.mark.parametrize("kind,shapes,static", [
-    ("small_fc_lopt", [(300, 257), (64, 256), (1030,), (5,)], True),
-    ("velo", [(300, 257), (64, 256), (1030,), (5,)], True),
-    ("small_fc_lopt", [(1000, 1000)], False),
-    ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True),       # 42 M elements: the two-stream group pipeline
+@pytest.mark.parametrize("kind,shapes,static,groups", [
+    ("small_fc_lopt", [(300, 257), (64, 256), (1030,), (5,)], True, None),
+    ("velo", [(300, 257), (64, 256), (1030,), (5,)], True, None),
+    ("small_fc_lopt", [(1000, 1000)], False, None),
+    ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True, None),     # 42 M elements: one stream by default
+    ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True, 4),        # and cut into groups on two streams
+    ("small_fc_lopt", [(4096, 2560)] * 7, True, None),                     # 73 M elements: two groups by default
 ])
-def test_a_step_captured_in_a_hip_graph_replays_bit_identically(kind, shapes, static):
+def test_a_step_captured_in_a_hip_graph_replays_bit_identically(kind, shapes, static, groups):
     # After one warm-up call (tables uploaded, nothing left to allocate) a step is captured into a HIP graph: no
     # allocation, no host synchronization and no memset node inside the capture (tile counters are cleared by a kernel).
     # Replays are checked against the eager step from the same state, three times, with eager work and
@@ -294,7 +296,7 @@ def test_a_step_captured_in_a_hip_graph_replays_bit_identically(kind, shapes, st
     import torch
     import paper_2506_10315_amd as P
     dev = "cuda:0"
-    cfg = Hn.make_cfg(kind) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32)
+    cfg = Hn.make_cfg(kind, groups=groups) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32)
     w = Hn.random_weights(cfg, 2)
     specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(shapes)]
     case = Hn.Case(202, specs, "gauss_logscale")

@@ -175,7 +175,7 @@ def test_two_row_tensor_with_lane_offsets_beyond_2_to_31(capsys):
 
 
 def test_tallest_tensor_matches_its_periodic_base_pattern(capsys):
-    # 2^28 x 4: the tallest statistics tiles (64 row tiles of 4,194,304 rows), a million row blocks in the row/column
+    # 2^28 x 4: 262,144 statistics tiles of the greatest height (1024 rows), a million row blocks in the row/column
     # pass, apply tiles with one of four column strips in use
     _periodic_tensor_case("small_fc_lopt", 1 << 26, 1, _progress(capsys), "tallest")
 
@@ -252,7 +252,7 @@ def test_llama_1p3b_twenty_steps_free_running(capsys):
 
 
 def test_config2_default_launch_plan_is_bit_identical_to_one_stream_at_full_size(monkeypatch):
-    # ViT-B/16 shapes: the default plan (four tensor groups on two streams, tiles from a device counter) against every
+    # ViT-B/16 shapes: the default plan (two tensor groups on two streams, tiles from a device counter) against every
     # pass over the whole list on one stream; three steps on seeded on-device inputs; parameters and state compared
     # bit by bit on the device
     import torch
