@@ -1151,13 +1151,14 @@ __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* _
 }
 
 // theta (and alpha, if the head is not folded): scratch of n_tensors rows for the batched form, null for lists below
-// kHeadBatchMin tensors (one workgroup per tensor then does everything; cheaper in launches, dearer in weight reads).
+// kHeadBatchMin tensors (one workgroup per tensor then does everything; cheaper in launches, dearer in weight reads). The
+// form is the whole list's, also for a sub-list of it: the two round differently.
 void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* h_new, float* alpha,
                       float* theta, hipStream_t s) {
   if (L.n_tensors == 0) return;
   const int T = L.n_tensors;
   const float* hn = h_new + (size_t)L.tensor0 * A.HL;
-  const bool batched = theta && T >= kHeadBatchMin;
+  const bool batched = theta != nullptr;
   if (W.head) {
     const int ld = head_ld(A.P);
     if (batched) {

@@ -145,6 +145,29 @@ def test_group_pipeline_is_bit_identical_to_one_stream(groups, monkeypatch):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
+@pytest.mark.parametrize("n_bank", [3, 64])
+def test_tensor_groups_change_no_bit_where_the_hypernetwork_head_is_batched(n_bank):
+    # 1100 tensors take the batched head (two products with a bank of 3, one with 64), their groups of 367 would be too few
+    # for it: the choice belongs to the list, not to the group
+    import torch
+    import paper_2506_10315_amd as P
+    dev = "cuda:0"
+    shapes = [(7, 13), (33, 20)] + [(8 + i % 50,) for i in range(1098)]
+    outs = []
+    for groups in (1, 3):
+        cfg = Hn.make_cfg("velo", lstm_hidden=40, n_bank=n_bank, groups=groups)
+        opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, 3), shapes, device=dev)
+        gen = torch.Generator(device=dev).manual_seed(11)
+        p = [torch.randn(s, device=dev, generator=gen) * 0.02 for s in shapes]
+        for t in range(2):
+            g = [torch.randn(s, device=dev, generator=gen) * 1e-3 for s in shapes]
+            opt.step(p, g, lr=0.7, weight_decay=0.01, step=t, loss=1.5 - 0.1 * t)
+        torch.cuda.synchronize()
+        outs.append(torch.cat([x.reshape(-1) for x in p] + list(opt.state)).view(torch.int32).cpu())
+        opt.close()
+    assert torch.equal(*outs)
+
+
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_statistics_do_not_depend_on_the_group_a_tensor_falls_in(kind):
     # Two equal tensors, one per tensor group, with per-tile sums of g^2 (256 tiles of 8 rows) whose total depends on the order
