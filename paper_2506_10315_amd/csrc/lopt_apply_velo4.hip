@@ -193,9 +193,10 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
 // Rows that are not 16-byte aligned (n % 4 != 0). A lane owns ONE column and takes four rows of it per trip (the four
 // elements of the MFMA chains are rows instead of columns), so every access is a coalesced dword of a 256-byte row segment
 // and the column factors are one set per lane. The wavefronts of the tile sit on adjacent 64-column segments; where the
-// tile is narrower than three segments they share out its rows as well (three leave the fourth without work). The float4 form with four predicated dwords per
-// lane that this replaces touched every cache line four times: 18 tensors of 54 M elements, 2731 columns, 1.82 -> 0.52 ms.
-// Ordinary accesses, not nontemporal ones (0.83 ms): neighbouring segments share their boundary lines.
+// tile is narrower than three segments they share out its rows as well (three leave the fourth without work). The float4
+// form with four predicated dwords per lane that this replaces touched every cache line four times: 18 tensors of 54 M
+// elements, 2731 columns, 1.82 -> 0.52 ms. Ordinary accesses, not nontemporal ones (0.83 ms): neighbouring segments share
+// their boundary lines.
 template <bool RAW_RSQ, bool UPDATE_STATE>
 __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
                                                       const StepArgs& A) {

@@ -103,7 +103,7 @@ struct Launch {
   const ApplyTileDev* atiles;
   int n_atiles;
   int tensor0;   // first tensor of the sub-list this launch covers (the per-tensor kernels index from it)
-  int* apply_counter;     // tile counter of the strip-form apply kernel for this sub-list (cleared by k_finalize)
+  int* apply_counter;     // tile counter of the apply kernel for this sub-list (cleared by k_finalize)
   int resident_wgs;       // workgroups of the strip-form apply kernel that are resident at once (2 per CU)
   int beside_apply;       // this sub-list's passes run beside the apply pass of another one
 };
