@@ -1,9 +1,11 @@
 """The library's planner (csrc/lopt_plan.h) on the CPU: which tiles, blocks and workspace a tensor list gets."""
 from __future__ import annotations
 
+import atexit
 import functools
 import json
 import os
+import shutil
 import subprocess
 import tempfile
 
@@ -13,7 +15,9 @@ N_CU = 256   # compute units of an MI355X
 
 @functools.lru_cache(maxsize=None)
 def _probe():
-    out = os.path.join(tempfile.mkdtemp(prefix="lopt_planner_"), "probe")
+    where = tempfile.mkdtemp(prefix="lopt_planner_")
+    atexit.register(shutil.rmtree, where, ignore_errors=True)
+    out = os.path.join(where, "probe")
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2506_10315_amd", "csrc"),
                     os.path.join(ROOT, "tests", "planner_probe.cpp"), "-o", out], check=True, capture_output=True, text=True)
