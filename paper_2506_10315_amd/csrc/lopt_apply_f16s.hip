@@ -46,7 +46,10 @@
 //     (ReLU/split of tile A, round i+1: vector ALU only)
 //     layer-2 MFMAs, tile A, i+1   |  ReLU/split of tile B, round i+1
 //     layer-2 MFMAs, tile B, i+1   |  features of round i+2
-// and __builtin_amdgcn_sched_barrier(0) between the slices keeps the compiler from regrouping them.
+// and __builtin_amdgcn_sched_barrier(0) between the slices keeps the compiler from regrouping them. A tile of R row pairs
+// takes one step without layer 3, R - 1 full ones and layer 3 of the last pair by itself; with R rounded up to whole turns of
+// the register sets and one more full step after the last pair the pass took, us: 0.08 M elements 12.0 -> 9.2, 1 M 24.3 -> 23.0,
+// 8.3 M in rows of 1531 128 -> 122, ViT-B/16 shapes 1143 -> 1125, GPT-2-medium shapes 4690 -> 4610.
 // Workgroup = 4 wavefronts; it works through apply tiles of up to kApplyRows rows x 128 columns, one at a time.
 #include <type_traits>
 
@@ -60,7 +63,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int kStripCols = 32;
-constexpr int kRowSlack = 16;   // rows of zeros after the tile in the LDS row tables (read by the pipeline's run-out)
+constexpr int kRowSlack = 4;    // rows of zeros after the tile in the LDS row tables (the pipeline reads at most three past it)
 constexpr int kRowPre = 2;      // rows per thread whose factors are loaded ahead of the tile's set-up
 constexpr int kRowTrip = 4;     // and per trip for the rest of a tall tile
 
@@ -412,7 +415,8 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     }
   }
   // the first rounds of the streams: round k (rows r0 + 2k, +1) goes through register set k % kSets. Not earlier: with them
-  // in flight the set-up above needs more registers than leave room for a statistics workgroup on the CU (216)
+  // in flight the set-up above needs more registers than leave room for a statistics workgroup on the CU (224), and the loop
+  // comes out 3 % slower on the long lists for nothing on the short ones
   Elem es[kSets];
 #pragma unroll
   for (int s = 0; s < kSets; ++s) es[s] = fetch(r0 + 2 * s);
@@ -425,6 +429,15 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   f32x16 h2a, h2b;
   float p_e = 0.f;
   Feat f;
+  // update of rows q, q + 1 from layer 3's sums: lower lanes keep tile A (their own row), upper lanes tile B (theirs); both
+  // halves of each sum meet
+  auto store_update = [&](float da, float ma, float db, float mb, float p_old, int q) __attribute__((always_inline)) {
+    swap32x2(da, db, ma, mb);
+    const float d = (da + db) + C.b3d, mg = (ma + mb) + C.b3m;
+    const float delta = d * __expf(mg * C.exp_mult) * C.step_mult;
+    store_stream(p_old - C.lr * (delta + C.wd * p_old), (gc8)(pout + rowoff_of(q)),
+                 col_ok && q + half < r1 ? voff_pair : kNoStore);
+  };
   auto step = [&](auto do_e, Elem& e, int qe) __attribute__((always_inline)) {
     constexpr bool DO_E = decltype(do_e)::value;
     const int qn = qe + 2, qf = qe + 4;
@@ -471,12 +484,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     LOPT_SB();
     if (DO_E) {
       layer3_piece<7>(wn, h2a, h2b, da, ma, db, mb);
-      // lower lanes keep tile A (their own row), upper lanes tile B (theirs): both halves of each sum meet
-      swap32x2(da, db, ma, mb);
-      const float d = (da + db) + C.b3d, mg = (ma + mb) + C.b3m;
-      const float delta = d * __expf(mg * C.exp_mult) * C.step_mult;
-      store_stream(p_e - C.lr * (delta + C.wd * p_e), (gc8)(pout + ((size_t)qe * (size_t)n + c0)),
-                   col_ok && qe + half < r1 ? voff_pair : kNoStore);
+      store_update(da, ma, db, mb, p_e, qe);
     }
     p_e = p_n;
     LOPT_SB();
@@ -557,10 +565,30 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     feat_piece<5, RAW_RSQ>(C, es[0], rr4, t, f);
   }
   step(std::false_type{}, es[1 % kSets], r0 - 2);   // layers 1-2 of the first row pair, features of the second
-  for (int q = r0; q < r1; q += 2 * kSets) {
+  int q = r0;
+  for (; q + 2 * kSets < r1; q += 2 * kSets) {
 #pragma unroll
-    for (int s = 0; s < kSets; ++s)   // update rows q + 2s, +1 (nothing is stored past the tile); features of round +2
+    for (int s = 0; s < kSets; ++s)   // update rows q + 2s, +1; layers 1-2 of the next pair, features of the one after
       step(std::true_type{}, es[(s + 2) % kSets], q + 2 * s);
+  }
+#pragma unroll
+  for (int s = 0; s + 1 < kSets; ++s)
+    if (q + 2 < r1) {
+      step(std::true_type{}, es[(s + 2) % kSets], q);
+      q += 2;
+    }
+  // the last pair: layer 3 and the update with nothing behind them
+  {
+    float da = 0.f, ma = 0.f, db = 0.f, mb = 0.f;
+    layer3_piece<0>(L.w3[half][0], h2a, h2b, da, ma, db, mb);
+    layer3_piece<1>(L.w3[half][1], h2a, h2b, da, ma, db, mb);
+    layer3_piece<2>(L.w3[half][2], h2a, h2b, da, ma, db, mb);
+    layer3_piece<3>(L.w3[half][3], h2a, h2b, da, ma, db, mb);
+    layer3_piece<4>(L.w3[half][4], h2a, h2b, da, ma, db, mb);
+    layer3_piece<5>(L.w3[half][5], h2a, h2b, da, ma, db, mb);
+    layer3_piece<6>(L.w3[half][6], h2a, h2b, da, ma, db, mb);
+    layer3_piece<7>(L.w3[half][7], h2a, h2b, da, ma, db, mb);
+    store_update(da, ma, db, mb, p_e, q);
   }
 
   if (threadIdx.x == 0) s_tile = next_id;

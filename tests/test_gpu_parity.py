@@ -8,6 +8,7 @@ import pytest
 
 import workloads as W
 from tests import harness as Hn
+from tests.planner import plan
 from tests.test_planner_cpu import NARROW, UNALIGNED
 
 pytestmark = pytest.mark.gpu
@@ -63,6 +64,18 @@ def test_velo_one_column_per_lane_path_at_segment_and_row_boundaries(state_pass)
     w = Hn.random_weights(cfg, seed=22)
     shapes = [(1, 1), (2, 3), (17, 61), (15, 65), (33, 129), (64, 190), (65, 257), (130, 318), (257, 1), (4, 449), (67, 260), (66, 288)]
     worst = Hn.run_free(Hn.Case(113, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("state_pass", ["apply", "stats"])
+def test_strip_tiles_of_every_number_of_row_pairs(state_pass):
+    # apply tiles of 16 rows (487 of them) and last tiles of 1 to 16 rows: one to eight pairs through the pipeline, odd and even
+    # numbers of its two-pair turns, a last pair of one row
+    cfg = Hn.make_cfg("small_fc_lopt", state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=25)
+    shapes = [(16 + r, 100 + r) for r in range(16)] + [(900, 1000)]
+    assert max(h for h, _ in plan(shapes)["atile_runs"]) == 16
+    worst = Hn.run_free(Hn.Case(125, _specs(shapes), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
     assert worst["param"] <= Hn.TOL_PARAM
 
 
