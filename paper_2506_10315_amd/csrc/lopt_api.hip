@@ -79,6 +79,7 @@ struct TableStore {
   TensorDev* d_tensors = nullptr;
   TileDev* d_tiles = nullptr;
   RcItemDev* d_rcitems = nullptr;
+  TileDev* d_rctiles = nullptr;
   ApplyTileDev* d_atiles = nullptr;
   bool static_uploaded = false;    // tiles, row/column blocks and apply tiles are on the device
   bool tensors_uploaded = false;
@@ -217,10 +218,11 @@ lopt_status ensure_plan(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d) {
 // tables fit both).
 lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   Plan& pl = ctx->plan;
-  const size_t nT = pl.tensors.size(), nTi = pl.tiles.size(), nRc = pl.rcitems.size(), nAt = pl.atiles.size();
+  const size_t nT = pl.tensors.size(), nTi = pl.tiles.size(), nRc = pl.rcitems.size(), nRt = pl.rctiles.size(),
+               nAt = pl.atiles.size();
   const size_t bT = align64(nT * sizeof(TensorDev)), bTi = align64(nTi * sizeof(TileDev)),
-               bRc = align64(nRc * sizeof(RcItemDev)), bAt = align64(nAt * sizeof(ApplyTileDev));
-  const size_t need = bT + bTi + bRc + bAt;
+               bRc = align64(nRc * sizeof(RcItemDev)), bRt = align64(nRt * sizeof(TileDev)), bAt = align64(nAt * sizeof(ApplyTileDev));
+  const size_t need = bT + bTi + bRc + bRt + bAt;
   if (need == 0) return LOPT_OK;
   if (need > st.cap) {
     if (!st.growable) return fail(ctx, LOPT_ELIMIT, "device tables do not fit the fixed scratch region");
@@ -244,7 +246,8 @@ lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   st.d_tensors = (TensorDev*)dbase;
   st.d_tiles = (TileDev*)(dbase + bT);
   st.d_rcitems = (RcItemDev*)(dbase + bT + bTi);
-  st.d_atiles = (ApplyTileDev*)(dbase + bT + bTi + bRc);
+  st.d_rctiles = (TileDev*)(dbase + bT + bTi + bRc);
+  st.d_atiles = (ApplyTileDev*)(dbase + bT + bTi + bRc + bRt);
   const bool need_tensors = !st.tensors_uploaded || st.last_tensors.size() != nT ||
                             memcmp(st.last_tensors.data(), pl.tensors.data(), nT * sizeof(TensorDev)) != 0;
   const bool need_static = !st.static_uploaded;
@@ -259,8 +262,9 @@ lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   if (need_static) {
     memcpy(hbase + bT, pl.tiles.data(), nTi * sizeof(TileDev));
     memcpy(hbase + bT + bTi, pl.rcitems.data(), nRc * sizeof(RcItemDev));
-    memcpy(hbase + bT + bTi + bRc, pl.atiles.data(), nAt * sizeof(ApplyTileDev));
-    send = bT + bTi + bRc + nAt * sizeof(ApplyTileDev);
+    memcpy(hbase + bT + bTi + bRc, pl.rctiles.data(), nRt * sizeof(TileDev));
+    memcpy(hbase + bT + bTi + bRc + bRt, pl.atiles.data(), nAt * sizeof(ApplyTileDev));
+    send = bT + bTi + bRc + bRt + nAt * sizeof(ApplyTileDev);
   }
   HIP_TRY(ctx, hipMemcpyAsync(st.d_tensors, hbase, send, hipMemcpyHostToDevice, stream));
   st.last_tensors = pl.tensors;
@@ -554,7 +558,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   if (st != LOPT_OK) return st;
   const TableStore& tb = ctx->heap;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
-           (int)ctx->plan.rcitems.size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0};
+           (int)ctx->plan.rcitems.size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false};
   StepArgs A = make_args(ctx, 0, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
@@ -626,7 +630,8 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   bool strip_ok = rows_ok && mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
-           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0};
+           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0,
+           tb.d_rctiles, (int)pl.rctiles.size(), pl.short_list};
   // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
   // statistics pass only reads them: 24 + 44 instead of 40 + 28 bytes per element (configuration field state_pass).
   // The read-only statistics stream runs at 83 % of the HBM rate against 67 % for the read-write one; the strip-form
@@ -689,7 +694,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     };
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for
     auto stats_passes = [&](const Launch& S, hipStream_t s) {
-      launch_accum_stats(S, A, !state_in_apply, s);
+      launch_accum_stats(S, A, ctx->W, !state_in_apply, S.tensor0 == 0, ws + pl.oHbarPart, ws + pl.oBeff, s);
       launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
       if (velo) {
         launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, ws + pl.oHNew, s);
@@ -700,8 +705,12 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     hipStream_t aux = ctx->aux_stream;
     // the row/column pass reads only the gradients (4 of the step's 72 bytes per element): whole list, up front
     // (VeLO: the cross-tensor term rides along in these two launches, before any group rewrites its LSTM outputs)
-    launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
-    launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+    // (short lists: its second stage in the statistics launch of the first group, which the second stream waits for)
+    if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+    else {
+      launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+      launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+    }
     LAUNCH_TRY(hipEventRecord(ctx->ev_fork, stream));       // aux joins the caller's stream here ...
     LAUNCH_TRY(hipStreamWaitEvent(aux, ctx->ev_fork, 0));
     forked = true;
@@ -733,11 +742,12 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   }
 #define MARK(i) do { if (ev) LAUNCH_TRY(hipEventRecord(ev[i], stream)); } while (0)
   MARK(0);
-  launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+  if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+  else launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(1);
-  launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+  if (!pl.short_list) launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(2);
-  launch_accum_stats(L, A, !state_in_apply, stream);
+  launch_accum_stats(L, A, ctx->W, !state_in_apply, true, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(3);
   launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
   MARK(4);

@@ -108,6 +108,10 @@ __device__ __forceinline__ TileRows tile_rows(const TensorDev& T, const TileDev&
 //                (4096 columns 0.932 -> 0.887 ms, 6144 0.934 -> 0.882, 8192 0.875 -> 0.867; the first form: 0.945, 0.928, 1.10)
 // Other rows measured the same or up to 4 % slower with either, and keep the plain walk.
 struct RowWalk { int tj, base, cnt, rot, step; };
+__device__ __forceinline__ RowWalk plain_walk(const TensorDev& T, const TileDev& tile, int wave) {   // rows r0 + wave + 4 i
+  const int r0 = tile.ti * T.TR;
+  return RowWalk{tile.tj, r0 + wave, (min(T.TR, T.m - r0) - wave + 3) >> 2, 0, 4};
+}
 __device__ __forceinline__ RowWalk row_walk(const TensorDev& T, const TileDev& tile, int wave) {
   const int r0 = tile.ti * T.TR;
   const bool pitch = (T.n & 1023) == 0;

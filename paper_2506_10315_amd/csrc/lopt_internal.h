@@ -15,6 +15,7 @@ constexpr int kTileCols = 256;    // one wavefront row-segment: 64 lanes x float
 constexpr int kRowUnit = 64;      // standard tile height (taller for tall tensors, shorter for small lists)
 constexpr int kMaxRowTiles = 256; // tile height grows so that a large tensor has at most this many row tiles ...
 constexpr int kMaxTileRows = 1024; // ... up to this height (bounds the length of the per-lane fp32 partial sums)
+constexpr int kShortRows = 64;    // short lists: rows per tile of the row/column sums (16 wavefronts), rows of a statistics tile at most
 constexpr int kStatStride = 20;   // floats per tile in the per-tile statistics partials (17 used)
 constexpr int kRcStride = 12;     // floats per block in the row/column partials (9 used)
 constexpr int kNStat = 17;        // per-element statistics accumulated per tile
@@ -44,9 +45,10 @@ struct TensorDev {
   uint32_t ndim;
   int vec;                          // 0: rows are not 16-byte aligned, 1: they are (n % 4 == 0), 2: 128-byte aligned (n % 32 == 0)
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
-  int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks
+  int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks (short lists: one per statistics tile row)
+  int nrc;                          // short lists: tiles of kShortRows rows in the row/column sums
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2
-  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2
+  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [nrc][n])
   uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc)
   uint64_t oRC;                     // [3][padn]  rsqrt(c_k + eps_acc)
   uint64_t oRcPart;                 // [nrblk + ncblk][kRcStride]
@@ -54,6 +56,7 @@ struct TensorDev {
   uint64_t oStats;                  // [kStatsPerTensor] s_f
   uint64_t oScale;                  // [kStatsPerTensor] factor applied to the raw feature
   uint64_t oPrep;                   // prepared first layer: W1s[F][HP] then b1'[HP]
+  uint64_t oROld, oCOld;            // short lists: r_k [3][padm] and c_k [3][padn] as the step found them
 };
 
 struct TileDev { int tensor, ti, tj, pad; };
@@ -106,6 +109,9 @@ struct Launch {
   int* apply_counter;     // tile counter of the apply kernel for this sub-list (cleared by k_finalize)
   int resident_wgs;       // workgroups of the strip-form apply kernel that are resident at once (2 per CU)
   int beside_apply;       // this sub-list's passes run beside the apply pass of another one
+  const TileDev* rctiles; // short lists: tiles of kShortRows x kTileCols of the row/column sums
+  int n_rctiles;
+  bool short_list;        // the statistics pass finishes the row and column means itself (Plan::short_list)
 };
 
 // kernels (lopt_kernels.hip / lopt_apply_mfma.hip)
@@ -115,8 +121,12 @@ void launch_fill_zero(const Launch&, const StepArgs&, hipStream_t);
 // come before any tensor's LSTM state is rewritten
 void launch_rowcol_sums(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
 void launch_rc_update(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
-// write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s)
-void launch_accum_stats(const Launch&, const StepArgs&, bool write_state, hipStream_t);
+// short lists: the row/column sums on taller tiles, copying r_k and c_k aside
+void launch_rowcol_short(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
+// write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s). Short
+// lists: with_mix = the second stage of VeLO's cross-tensor term rides along here (there is no launch_rc_update)
+void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool write_state, bool with_mix, float* hbar_part, float* b_eff,
+                        hipStream_t);
 void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
 // lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
 void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);

@@ -19,6 +19,8 @@
 // consecutive columns 4l..4l+3 as one float4 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply
 // passes of rows of a multiple of 4 KB in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
 // a wavefront stays on one segment (the row/column sums: on all four in turn).
+#include <type_traits>
+
 #include "lopt_internal.h"
 #include "lopt_device.h"
 
@@ -103,7 +105,7 @@ __device__ __forceinline__ void mix_hbar_block(const TensorDev* __restrict__ ten
   const int j = min(chunk * kWave + lane, M.HL - 1);   // lanes past the end repeat the last unit (dropped below)
   const int t0 = slice * M.per_slice, t1 = min(t0 + M.per_slice, M.n_tensors);
   float a = 0.f;
-  for (int t = t0 + wave; t < t1; t += 16) {
+  for (int t = t0 + wave; wave < 4 && t < t1; t += 16) {   // (k_rowcol_short has sixteen wavefronts)
     float v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -114,7 +116,7 @@ __device__ __forceinline__ void mix_hbar_block(const TensorDev* __restrict__ ten
 #pragma unroll
     for (int k = 0; k < 4; ++k) a += t + 4 * k < t1 ? v[k] : 0.f;
   }
-  red[wave][lane] = a;
+  if (wave < 4) red[wave][lane] = a;
   __syncthreads();
   if (wave == 0 && chunk * kWave + lane < M.HL)
     M.part[(size_t)slice * M.HL + j] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
@@ -240,6 +242,93 @@ void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W,
   const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
   const int extra = M.n_slices * ((M.HL + kWave - 1) / kWave);
   hipLaunchKernelGGL(k_rowcol_sums, dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, L.n_tiles, M);
+}
+
+// Short lists: tiles of kShortRows rows, sixteen wavefronts with four rows in flight each, so that a column has few partial sums
+// and every workgroup of the statistics pass can add them up itself (fuse_means). r_k and c_k are copied aside for it: the
+// statistics pass writes the new ones while other workgroups still need the old.
+constexpr int kShortWaves = 16;
+
+template <bool VEC>
+__device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
+                                                  float (*colred)[kTileCols]) {
+  constexpr int R = kShortRows / kShortWaves;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = T.n, m = T.m, c0 = tile.tj * kTileCols;
+  const int r0 = tile.ti * kShortRows, r1 = min(r0 + kShortRows, m);
+  float4 v[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {   // rows past the tile: its last row, counted as 0
+    const float* __restrict__ row = T.g + (size_t)min(r0 + wave + kShortWaves * i, r1 - 1) * (unsigned)n;
+    if (VEC) v[i] = load4s<true>(row, c0 + 4 * lane, n);
+    else {
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = c0 + e * kWave + lane;
+        x[e] = row[min(c, n - 1)];
+        x[e] = c < n ? x[e] : 0.f;
+      }
+      v[i] = make_float4(x[0], x[1], x[2], x[3]);
+    }
+  }
+  const float* rst = T.st + 4 * (size_t)T.padN;   // r_k[3][padm], c_k[3][padn]
+  const int t = threadIdx.x;
+  if (tile.tj == 0 && t < 3 * kShortRows) {
+    const size_t at = (size_t)(t / kShortRows) * T.padm + r0 + t % kShortRows;
+    if (r0 + t % kShortRows < m) ws[T.oROld + at] = rst[at];
+  }
+  if (tile.ti == 0 && t >= kTileCols) {
+    const int k = t / kTileCols - 1, c = c0 + t % kTileCols;
+    if (c < n) ws[T.oCOld + (size_t)k * T.padn + c] = rst[3 * (size_t)T.padm + (size_t)k * T.padn + c];
+  }
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int r = r0 + wave + kShortWaves * i;   // wavefront-uniform
+    if (r < r1) {
+      const float ax = v[i].x * v[i].x, ay = v[i].y * v[i].y, az = v[i].z * v[i].z, aw = v[i].w * v[i].w;
+      s[0] += ax; s[1] += ay; s[2] += az; s[3] += aw;
+      const float sum = wave_sum((ax + ay) + (az + aw));
+      if (lane == 0) ws[T.oRowPart + (size_t)tile.tj * m + r] = sum;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) colred[wave][VEC ? 4 * lane + e : lane + kWave * e] = s[e];
+  __syncthreads();
+  const int c = c0 + t;
+  if (t < kTileCols && c < n) {
+    float x[kShortWaves];
+#pragma unroll
+    for (int w = 0; w < kShortWaves; ++w) x[w] = colred[w][t];
+#pragma unroll
+    for (int step = 1; step < kShortWaves; step *= 2)
+#pragma unroll
+      for (int w = 0; w < kShortWaves; w += 2 * step) x[w] += x[w + step];
+    ws[T.oColPart + (size_t)tile.ti * n + c] = x[0];
+  }
+}
+
+__global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const TensorDev* __restrict__ tensors,
+                                                                      const TileDev* __restrict__ tiles, float* __restrict__ ws,
+                                                                      int n_tiles, MixArgs M) {
+  __shared__ float colred[kShortWaves][kTileCols];
+  if ((int)blockIdx.x >= n_tiles) {
+    mix_hbar_block(tensors, M, (int)blockIdx.x - n_tiles, reinterpret_cast<float (*)[kWave]>(&colred[0][0]));
+    return;
+  }
+  const TileDev tile = tiles[blockIdx.x];
+  const TensorDev& T = tensors[tile.tensor];
+  if (T.vec) rowcol_short_tile<true>(T, tile, ws, colred);
+  else rowcol_short_tile<false>(T, tile, ws, colred);
+}
+
+void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, hipStream_t s) {
+  if (L.n_rctiles == 0) return;
+  const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
+  const int extra = M.n_slices * ((M.HL + kWave - 1) / kWave);
+  hipLaunchKernelGGL(k_rowcol_short, dim3(L.n_rctiles + extra), dim3(kWave * kShortWaves), 0, s, L.tensors, L.rctiles, L.ws,
+                     L.n_rctiles, M);
 }
 
 // ----------------------------------------------------------------------------- rc_update
@@ -373,6 +462,90 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 
 // ----------------------------------------------------------------------------- accum_stats
 
+// Short lists: the row and column means that k_rc_update finishes on others, formed by every statistics workgroup for its own
+// rows and columns (the sums in double, in index order); the workgroups of the first tile column and of the first tile row
+// also write them, with their partial sums (fuse_store).
+struct alignas(16) FuseLds {
+  float r[3][kShortRows], rr[3][kShortRows];   // r_k of the tile's rows, rsqrt(r_k + eps)
+  float c[3][kTileCols], rc[3][kTileCols];
+};
+
+__device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws, const StepArgs& A,
+                                           FuseLds& L) {
+  const int t = threadIdx.x, n = T.n, m = T.m;
+  const int c = tile.tj * kTileCols + t, r0 = tile.ti * T.TR, r = r0 + t;
+  const bool cin = c < n, rin = t < T.TR && r < m;
+  float co[3] = {0.f, 0.f, 0.f}, ro[3] = {0.f, 0.f, 0.f}, rp[4] = {0.f, 0.f, 0.f, 0.f};
+  const float* __restrict__ rowpart = ws + T.oRowPart + r;
+  if (rin) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rp[j] = rowpart[(size_t)min(j, T.nct - 1) * m];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ro[k] = ws[T.oROld + (size_t)k * T.padm + r];
+  }
+  double cs = 0.0;
+  if (cin) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) co[k] = ws[T.oCOld + (size_t)k * T.padn + c];
+    cs = strided_sum(ws + T.oColPart + c, T.nrc, (size_t)n);
+  }
+  if (rin) {
+    double rs = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rs += j < T.nct ? (double)rp[j] : 0.0;
+    if (T.nct > 4) rs += strided_sum(rowpart + 4 * (size_t)m, T.nct - 4, (size_t)m);
+    const float mean = (float)(rs / (double)n);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float b = A.fac_decay[k], v = b * ro[k] + (1.0f - b) * mean;
+      L.r[k][t] = v;
+      L.rr[k][t] = rsqrtf(v + A.eps_acc);
+    }
+  }
+  if (cin) {
+    const float mean = (float)(cs / (double)m);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float b = A.fac_decay[k], v = b * co[k] + (1.0f - b) * mean;
+      L.c[k][t] = v;
+      L.rc[k][t] = rsqrtf(v + A.eps_acc);
+    }
+  }
+  __syncthreads();
+}
+
+// Blocks of the row/column partials are the tile rows (rows) and tile columns (columns) of the tensor.
+__device__ __forceinline__ void fuse_store(const TensorDev& T, const TileDev& tile, float* __restrict__ ws, const FuseLds& L,
+                                           float (*red)[4]) {
+  float* st = T.st + 4 * (size_t)T.padN;
+  const int t = threadIdx.x;
+  auto part = [&](bool in, const float* x, const float* inv, int stride, float* acc3, float* inv3, size_t pd, int slot)
+                  __attribute__((always_inline)) {
+    float v[9];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float a = in ? x[k * stride + t] : 0.f, b = in ? inv[k * stride + t] : 0.f;
+      if (in) {
+        acc3[k * pd] = a;
+        inv3[k * pd] = b;
+      }
+      v[k] = a;
+      v[3 + k] = a * a;
+      v[6 + k] = b * b;
+    }
+    __syncthreads();   // the previous sum has been read
+    block_sum<9>(v, red, ws + T.oRcPart + (size_t)slot * kRcStride);
+  };
+  if (tile.tj == 0) {
+    const int r = tile.ti * T.TR + t;
+    part(t < T.TR && r < T.m, &L.r[0][0], &L.rr[0][0], kShortRows, st + r, ws + T.oRR + r, T.padm, tile.ti);
+  }
+  if (tile.ti == 0) {
+    const int c = tile.tj * kTileCols + t;
+    part(c < T.n, &L.c[0][0], &L.rc[0][0], kTileCols, st + 3 * (size_t)T.padm + c, ws + T.oRC + c, T.padn, T.nrblk + tile.tj);
+  }
+}
+
 // The per-element features that need a statistic of their own (the row/column-constant ones
 // follow from r_k, c_k alone). rrc[k] = rsqrt(r_k[i]+eps) * rsqrt(c_k[j]+eps); the common
 // factor sqrt(mean(r_k)+eps) of the factored features is applied per tensor in k_finalize.
@@ -389,9 +562,10 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 // row per trip and nontemporal loads, 41 us.
 constexpr int kAccRows = 4;
 
-template <bool RAW_RCP, bool WRITE>
+template <bool RAW_RCP, bool WRITE, bool FUSE>
 __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
-                                           const StepArgs& A, float (&acc)[kNStat]) {
+                                           const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
+  if (FUSE) fuse_means(T, tile, ws, A, *L);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = T.n;
   const int c0 = tile.tj * kTileCols;
@@ -407,7 +581,7 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
   const float eps = A.eps_acc;
   float rc[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) rc[k] = ws[T.oRC + (size_t)k * T.padn + c];
+  for (int k = 0; k < 3; ++k) rc[k] = FUSE ? L->rc[k][c - c0] : ws[T.oRC + (size_t)k * T.padn + c];
   for (unsigned r = r0 + kAccRows * (wave % rsplit); r < r1; r += kAccRows * rsplit) {
     float in[kAccRows][6];
 #pragma unroll
@@ -431,7 +605,7 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
       const float rs = RAW_RCP ? __builtin_amdgcn_rsqf(nv + eps) : rsqrtf(nv + eps);
       float f[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) f[k] = ws[T.oRR + (size_t)k * T.padm + r + e] * rc[k];
+      for (int k = 0; k < 3; ++k) f[k] = (FUSE ? L->rr[k][r + e - r0] : ws[T.oRR + (size_t)k * T.padm + r + e]) * rc[k];
       const float gc = fminf(fmaxf(g, -0.1f), 0.1f);
       float t;
       acc[0] += g2;
@@ -471,15 +645,16 @@ typedef float __attribute__((ext_vector_type(4))) f32x4v;
 typedef const f32x4v __attribute__((address_space(1)))* gcv4;
 typedef f32x4v __attribute__((address_space(1)))* gv4;
 
-template <bool RAW_RCP, bool WRITE>
+template <bool RAW_RCP, bool WRITE, bool FUSE>
 __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
-                                               const StepArgs& A, float (&acc)[kNStat]) {
+                                               const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
   const int lane = threadIdx.x & 63;
   const int n = T.n;
-  const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowWalk w = FUSE ? plain_walk(T, tile, wave) : row_walk(T, tile, wave);   // FUSE: the means in LDS are the tile's own
   const int col = w.tj * kTileCols + 4 * lane;
-  if (col >= n) return;
-  if (w.cnt <= 0) return;
+  const bool mine = col < n && w.cnt > 0;
+  if (!FUSE && !mine) return;
   // The first row's loads leave before the column factors are waited for: a short list's tile is one or two rows a wavefront
   // (toy list of three tensors 30.3 -> 29.6 us a step, 1000x1000 46.5 -> 45.6). The read-only form also needs 63 registers
   // this way instead of 66: eight wavefronts per SIMD (ViT-B/16 shapes beside the apply pass 1.488 -> 1.472 ms a step).
@@ -498,9 +673,17 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
     v4 = __builtin_nontemporal_load((gcv4)(T.st + 3 * pN + ro));
   };
   float4 c3[3];
+  if (FUSE) {
+    if (mine) load(0);
+    fuse_means(T, tile, ws, A, *L);
+    if (!mine) return;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) c3[k] = *reinterpret_cast<const float4*>(ws + T.oRC + (size_t)k * T.padn + col);
-  load(0);
+    for (int k = 0; k < 3; ++k) c3[k] = *reinterpret_cast<const float4*>(&L->rc[k][4 * lane]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c3[k] = *reinterpret_cast<const float4*>(ws + T.oRC + (size_t)k * T.padn + col);
+    load(0);
+  }
   float rc2[3][4];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -515,7 +698,7 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
     float rr2[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float rr = ws[T.oRR + (size_t)k * T.padm + r];
+      const float rr = FUSE ? L->rr[k][r - tile.ti * T.TR] : ws[T.oRR + (size_t)k * T.padm + r];
       rr2[k] = rr * rr;
     }
     f32x4v o1, o2, o3, ov;
@@ -556,31 +739,53 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
 // WRITE = false: the accumulators are only read (their new values are formed for the statistics and dropped); the apply
 // pass of the same step forms them again and writes them (the two default apply kernels can; a read-only stream
 // sustains a higher share of the HBM rate than a read-write one, and 16 of this pass's 40 bytes per element move there).
-template <bool RAW_RCP, bool WRITE>
+template <bool RAW_RCP, bool WRITE, bool FUSE>
 __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                        StepArgs A) {
+                                                        StepArgs A, int n_tiles, MixArgs M) {
   __shared__ float red[kNStat][4];
+  __shared__ std::conditional_t<FUSE, FuseLds, int> fuse;
+  FuseLds* L = nullptr;
+  if constexpr (FUSE) {
+    if ((int)blockIdx.x >= n_tiles) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
+      mix_bias_block(M, (int)blockIdx.x - n_tiles, &fuse.c[0][0], reinterpret_cast<float (*)[kWave]>(&fuse.r[0][0]));
+      return;
+    }
+    L = &fuse;
+  }
   const TileDev tile = tiles[blockIdx.x];
   const TensorDev& T = tensors[tile.tensor];
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  if (T.vec) accum_tile_vec<RAW_RCP, WRITE>(T, tile, ws, A, acc);
-  else accum_tile<RAW_RCP, WRITE>(T, tile, ws, A, acc);
+  if (T.vec) accum_tile_vec<RAW_RCP, WRITE, FUSE>(T, tile, ws, A, acc, L);
+  else accum_tile<RAW_RCP, WRITE, FUSE>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
+  if constexpr (FUSE) fuse_store(T, tile, ws, fuse, red);
 }
+// mix_bias_block keeps a quarter of at most 1024 units and 4 x 64 partial sums in the means' arrays
+static_assert(sizeof(FuseLds::c) + sizeof(FuseLds::rc) >= 256 * sizeof(float) && sizeof(FuseLds::r) + sizeof(FuseLds::rr) >= 4 * kWave * sizeof(float));
 
-void launch_accum_stats(const Launch& L, const StepArgs& A, bool write_state, hipStream_t s) {
+void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W, bool write_state, bool with_mix, float* hbar_part,
+                        float* b_eff, hipStream_t s) {
   if (L.n_tiles == 0) return;
   const bool raw = A.eps_acc >= 1e-30f;
-#define LOPT_LAUNCH_ACC(R, Wr) \
-  hipLaunchKernelGGL((k_accum_stats<R, Wr>), dim3(L.n_tiles), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A)
-  if (raw && write_state) LOPT_LAUNCH_ACC(true, true);
-  else if (raw) LOPT_LAUNCH_ACC(true, false);
-  else if (write_state) LOPT_LAUNCH_ACC(false, true);
-  else LOPT_LAUNCH_ACC(false, false);
+  MixArgs M{};
+  if (L.short_list && with_mix) {
+    Launch whole = L;   // the cross-tensor term is the whole list's
+    whole.n_tensors = A.n_tensors;
+    M = make_mix(whole, A, W, hbar_part, b_eff);
+  }
+  const int extra = M.n_slices ? kMixJSplit * ((4 * M.HL + kWave - 1) / kWave) : 0;
+#define LOPT_LAUNCH_ACC(R, Wr, F) \
+  hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M)
+#define LOPT_LAUNCH_ACC2(R, Wr) do { if (L.short_list) LOPT_LAUNCH_ACC(R, Wr, true); else LOPT_LAUNCH_ACC(R, Wr, false); } while (0)
+  if (raw && write_state) LOPT_LAUNCH_ACC2(true, true);
+  else if (raw) LOPT_LAUNCH_ACC2(true, false);
+  else if (write_state) LOPT_LAUNCH_ACC2(false, true);
+  else LOPT_LAUNCH_ACC2(false, false);
+#undef LOPT_LAUNCH_ACC2
 #undef LOPT_LAUNCH_ACC
 }
 

@@ -8,6 +8,7 @@
 namespace lopt {
 
 constexpr int kMaxGroups = 16;
+constexpr uint64_t kShortListFloats = 48u << 20;   // partial sums a short list's statistics pass reads, all workgroups together
 
 inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
 inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
@@ -32,6 +33,8 @@ struct Plan {
   std::vector<TensorDev> tensors;   // pointers filled per call
   std::vector<TileDev> tiles;
   std::vector<RcItemDev> rcitems;
+  std::vector<TileDev> rctiles;       // short lists: tiles of the row/column sums
+  bool short_list = false;
   std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
@@ -70,12 +73,33 @@ inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t to
   while (g <= G) bound[g++] = (int)n;
 }
 
+// Short lists: no launch of its own for the means of the rows and columns (k_rc_update: 4.5 to 6 us, a chain of load latencies).
+// Every workgroup of the statistics pass forms the ones of its own rows and columns from the partial sums, which the
+// row/column pass leaves per 64 rows for that purpose. us a step with that launch and without: 0.08 M elements (toy list) 29.6 /
+// 26.9, 1000x1000 45.7 / 43.8 (VeLO 57.7 / 55.0), 66 tensors of 2.4 M under VeLO 69.1 / 66.7, 2000x2000 107.8 / 104.4, ten layers of
+// 1024x1024 at width 16 191.8 / 188.8, nine of 2731x2731 under VeLO 896 / 882; no difference at 14 M elements (width 32), and 495.5 /
+// 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Lists in tensor
+// groups keep the launch: the statistics kernel that forms the means does not fit beside the apply kernel.
+inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink) {
+  if (total >= (64u << 20)) return false;
+  uint64_t floats = 0;
+  for (size_t i = 0; i < n; ++i) {
+    const uint64_t nrc = (uint64_t)ceil_div(d[i].rows, kShortRows), nct = (uint64_t)ceil_div(d[i].cols, kTileCols);
+    if (nrc > 96 || nct > 96) return false;
+    const uint64_t tr = kRowUnit / shrink, tiles = (uint64_t)ceil_div(d[i].rows, tr) * nct;
+    floats += tiles * (nrc * (uint64_t)(d[i].cols < kTileCols ? d[i].cols : kTileCols) + nct * tr);
+    if (floats > kShortListFloats) return false;
+  }
+  return true;
+}
+
 // Lay out tiles, row/column blocks and workspace regions for a tensor list.
 inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d, Plan* pl) {
   pl->descs.assign(d, d + n);
   pl->tensors.assign(n, TensorDev{});
   pl->tiles.clear();
   pl->rcitems.clear();
+  pl->rctiles.clear();
   pl->atiles.clear();
   pl->atile0.assign(n, 0);
   pl->total_elems = 0;
@@ -122,6 +146,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
+  pl->short_list = is_short_list(n, d, total, shrink);
   // Short lists: the smallest even apply-tile height at which every CU gets at most two tiles, if that is at most 32 rows: the
   // launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the graded heights below gave 650
   // tiles and a second, nearly empty round). The strip kernel has two workgroups per CU. The narrow one has three or four, and
@@ -165,11 +190,17 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.tile0 = (int)pl->tiles.size();
     for (int ti = 0; ti < T.nrt; ++ti)
       for (int tj = 0; tj < T.nct; ++tj) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
-    T.nrblk = ceil_div(m, kBlock);
-    T.ncblk = ceil_div(nn, kBlock);
+    T.nrblk = pl->short_list ? T.nrt : ceil_div(m, kBlock);
+    T.ncblk = ceil_div(nn, kBlock);   // = nct
     T.rc0 = (int)pl->rcitems.size();
-    for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
-    for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
+    T.nrc = ceil_div(m, kShortRows);
+    if (pl->short_list) {
+      for (int ti = 0; ti < T.nrc; ++ti)
+        for (int tj = 0; tj < T.nct; ++tj) pl->rctiles.push_back(TileDev{(int)i, ti, tj, 0});
+    } else {
+      for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
+      for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
+    }
     // apply tiles, for the kernels that read them: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
     pl->atile0[i] = (int)pl->atiles.size();
     pl->total_elems += N;
@@ -187,7 +218,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       ar0 += rows;
     }
     T.oRowPart = take((uint64_t)T.nct * m);
-    T.oColPart = take((uint64_t)T.nrt * nn);
+    T.oColPart = take((uint64_t)(pl->short_list ? T.nrc : T.nrt) * nn);
     T.oRR = take(3ull * T.padm);
     T.oRC = take(3ull * T.padn);
     T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);
@@ -195,6 +226,10 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.oStats = take(kStatsPerTensor);
     T.oScale = take(kStatsPerTensor);
     T.oPrep = take(prep_floats);
+    if (pl->short_list) {
+      T.oROld = take(3ull * T.padm);
+      T.oCOld = take(3ull * T.padn);
+    }
     pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
   }
   pl->ws_floats = off;
@@ -210,7 +245,8 @@ inline bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {
 
 inline size_t table_bytes(const Plan& pl) {
   return align64(pl.tensors.size() * sizeof(TensorDev)) + align64(pl.tiles.size() * sizeof(TileDev)) +
-         align64(pl.rcitems.size() * sizeof(RcItemDev)) + align64(pl.atiles.size() * sizeof(ApplyTileDev));
+         align64(pl.rcitems.size() * sizeof(RcItemDev)) + align64(pl.rctiles.size() * sizeof(TileDev)) +
+         align64(pl.atiles.size() * sizeof(ApplyTileDev));
 }
 
 }  // namespace lopt

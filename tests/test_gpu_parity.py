@@ -79,6 +79,20 @@ def test_strip_tiles_of_every_number_of_row_pairs(state_pass):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("rows", [6144, 6145])
+@pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("small_fc_lopt", "stats"), ("velo", "apply")])
+def test_row_and_column_means_at_the_limit_of_a_short_list(kind, state_pass, rows):
+    # up to 96 tiles of 64 rows the statistics workgroups finish the row and column means themselves; one row more and a launch of
+    # its own does. 96 column tiles; rows and columns at the edges of a tile of the sums and of the statistics
+    cfg = Hn.make_cfg(kind, state_pass=state_pass) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=33, n_bank=8,
+                                                                                             state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=26)
+    shapes = [(rows, 5), (3, 24576), (64, 256), (65, 257), (63, 255), (129, 1100), (1, 1), (1, 300)]
+    assert (plan(shapes, kind=kind)["n_rcitems"] == 0) == (rows == 6144)
+    worst = Hn.run_free(Hn.Case(126, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("velo", "apply"), ("velo", "stats")])
 def test_rows_of_a_multiple_of_4_kb(kind, state_pass):
     # widths that are a multiple of 1024 are walked by groups of four tiles (up to 3072 columns) or from a start that differs
