@@ -620,6 +620,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   float* ws = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   const bool profiling = ctx->profiling && !use_static;   // per-pass timing creates events: not on the static path
   StepArgs A = make_args(ctx, step, lr, weight_decay, (int)n);
+  float* lstm_z = pl.oLstmZ ? ws + pl.oLstmZ : nullptr;
   const bool mfma_ok = apply_mfma_available(A);
   // the strip-form kernel addresses a row pair with 32-bit byte offsets from the tile's first column: 4 (127 + cols)
   // must stay below the range of its store descriptors (2^32 - 512), which only a tensor of two or more rows and
@@ -697,7 +698,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
       launch_accum_stats(S, A, ctx->W, !state_in_apply, S.tensor0 == 0, ws + pl.oHbarPart, ws + pl.oBeff, s);
       launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
       if (velo) {
-        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, ws + pl.oHNew, s);
+        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, s);
         launch_velo_head(S, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
                          pl.head_batched ? ws + pl.oTheta : nullptr, s);
       }
@@ -706,9 +707,9 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     // the row/column pass reads only the gradients (4 of the step's 72 bytes per element): whole list, up front
     // (VeLO: the cross-tensor term rides along in these two launches, before any group rewrites its LSTM outputs)
     // (short lists: its second stage in the statistics launch of the first group, which the second stream waits for)
-    if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+    if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
     else {
-      launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+      launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
       launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
     }
     LAUNCH_TRY(hipEventRecord(ctx->ev_fork, stream));       // aux joins the caller's stream here ...
@@ -742,8 +743,8 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   }
 #define MARK(i) do { if (ev) LAUNCH_TRY(hipEventRecord(ev[i], stream)); } while (0)
   MARK(0);
-  if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
-  else launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+  if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
+  else launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
   MARK(1);
   if (!pl.short_list) launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(2);
@@ -752,7 +753,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
   MARK(4);
   if (ctx->cfg.kind == LOPT_VELO) {
-    launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, ws + pl.oHNew, stream);
+    launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, stream);
     MARK(5);
     launch_velo_head(L, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
                      pl.head_batched ? ws + pl.oTheta : nullptr, stream);

@@ -22,6 +22,11 @@ constexpr int kNStat = 17;        // per-element statistics accumulated per tile
 constexpr int kStatsPerTensor = 32;
 constexpr int kLstmInPad = 48;    // LOPT_VELO_LSTM_IN rounded up to a multiple of 4
 constexpr int kMixSlices = 64;    // at most this many slices of the tensor list in the cross-tensor mean
+// Tensor lists up to this length form the LSTM's recurrent product ahead, beside the row/column sums. us, row/column sums + LSTM,
+// in one launch / ahead: one tensor 4.4 + 9.7 / 5.4 + 4.1, 66 tensors 4.4 + 10.7 / 9.2 + 4.2, 152 tensors 58 + 14 / 66 + 5.5, 502
+// tensors 25 + 26 / 68 + 7.
+constexpr int kLstmAheadMax = 96;
+constexpr int kHeadSplitMax = 96;    // tensor lists up to this length cut the hypernetwork head's product into column blocks
 constexpr int kHeadBatchMin = 1024;  // tensor lists from this length on take the batched form of the hypernetwork head
 constexpr int kMixJSplit = 4;     // the LSTM units are cut into this many ranges when hbar Wg is formed
 #ifndef LOPT_APPLY_ROWS
@@ -119,10 +124,11 @@ void launch_fill_zero(const Launch&, const StepArgs&, hipStream_t);
 // VeLO: the two stages of the cross-tensor term (hbar = mean of the tensors' LSTM outputs of the previous step,
 // b_eff = b + hbar Wg) ride along as extra workgroups of these two launches, which always cover the WHOLE list and
 // come before any tensor's LSTM state is rewritten
-void launch_rowcol_sums(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
+// (lstm_z: room for the LSTM's recurrent product, which then rides along in the first of them; null: not formed ahead)
+void launch_rowcol_sums(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, float* lstm_z, hipStream_t);
 void launch_rc_update(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
 // short lists: the row/column sums on taller tiles, copying r_k and c_k aside
-void launch_rowcol_short(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, hipStream_t);
+void launch_rowcol_short(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, float* lstm_z, hipStream_t);
 // write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s). Short
 // lists: with_mix = the second stage of VeLO's cross-tensor term rides along here (there is no launch_rc_update)
 void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool write_state, bool with_mix, float* hbar_part, float* b_eff,
@@ -130,8 +136,9 @@ void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool 
 void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
 // lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
 void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);
+// lstm_z: the recurrent product formed ahead (null: this launch forms it)
 void launch_velo_lstm(const Launch&, const StepArgs&, const WeightsDev&, const float* lstm_u, const float* b_eff,
-                      float* h_new, hipStream_t);
+                      const float* lstm_z, float* h_new, hipStream_t);
 void launch_velo_head(const Launch&, const StepArgs&, const WeightsDev&, const float* h_new, float* alpha,
                       float* theta, hipStream_t);
 void launch_apply_small_fc(const Launch&, const StepArgs&, const WeightsDev&, hipStream_t);

@@ -93,6 +93,8 @@ struct MixArgs {
   float* part;            // [n_slices][HL] slice sums of h
   float* b_eff;           // [kMixJSplit][4 HL]: hbar Wg summed over a quarter of the units j each
   int HL, n_tensors, per_slice, n_slices;   // n_slices == 0: not VeLO, no extra workgroups
+  const float* lstm;      // WeightsDev::lstm
+  float* z;               // the LSTM's recurrent product (null: not formed ahead)
 };
 
 // Workgroup (chunk of 64 units, slice of the tensor list): lane = unit j, the four wavefronts take every fourth tensor
@@ -154,10 +156,82 @@ __device__ __forceinline__ void mix_bias_block(const MixArgs& M, int blk, float*
   }
 }
 
-static MixArgs make_mix(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff) {
+// The LSTM's recurrent product h W_h of the step before, formed here because it depends on nothing this step computes: what is
+// left behind the statistics is the product of the 48 inputs (k_velo_lstm_tail). Workgroup = 16 tensors x 8 units x 4 gates, in
+// front of the tiles of the row/column sums; its wavefronts share the octets of h slots and meet in LDS in a fixed order.
+// v_mfma_f32_16x16x4_f32 (exact products) on two column tiles; 32 tensors at a time would double the chain of a short list. As
+// extra workgroups of the statistics pass of a short list it is the longer side there (layer of 2000x2000 32 us instead of 26).
+// Out: z[tensor][unit block][gate, unit].
+constexpr int kRecurTensors = 16, kRecurOctets = 4;   // octets in flight per wavefront
+typedef float f32x16_l __attribute__((ext_vector_type(16)));
+typedef float f32x4_l __attribute__((ext_vector_type(4)));
+
+template <int WAVES>
+__device__ __forceinline__ void lstm_recur_block(const TensorDev* __restrict__ tensors, const MixArgs& M, int blk,
+                                                 float (*part)[kRecurTensors][32]) {
+  const int HL = M.HL, n_ub = (HL + 7) / 8, ub = blk % n_ub, t0 = blk / n_ub * kRecurTensors;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int quarter = lane >> 4, l16 = lane & 15;   // A: tensor l16, slot of the quad; B: column l16, slot
+  const int n_oct = lstm_k_pad(HL) / 8, first = kLstmInPad / 8;
+  const float* __restrict__ wcol = M.lstm + ((size_t)ub * (8 * n_oct) + quarter) * 32 + l16;
+  const TensorDev& T = tensors[min(t0 + l16, M.n_tensors - 1)];   // rows past the list compute on the last tensor and are dropped
+  const float* __restrict__ h = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
+  f32x4_l acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  const int per_wave = (n_oct - first + WAVES - 1) / WAVES;
+  const int o_begin = first + wave * per_wave, o_end = min(o_begin + per_wave, n_oct);
+  for (int ob = o_begin; ob < o_end; ob += kRecurOctets) {
+    float a[kRecurOctets][2], b[kRecurOctets][2][2];
+#pragma unroll
+    for (int j = 0; j < kRecurOctets; ++j) {
+      const int o = min(ob + j, o_end - 1);   // octets past the wavefront's share repeat its last one (dropped below)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        a[j][q] = h[min(8 * o + 4 * q + quarter - kLstmInPad, HL - 1)];   // slots past H_L: their weights are zero
+#pragma unroll
+        for (int c = 0; c < 2; ++c) b[j][q][c] = wcol[((size_t)o * 8 + 4 * q) * 32 + 16 * c];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kRecurOctets; ++j) {
+      if (ob + j >= o_end) break;   // wavefront-uniform
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j][q], b[j][q][c], acc[c], 0, 0, 0);
+    }
+  }
+  // accumulator register v of lane (quarter, column) is row 4 quarter + v
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave][4 * quarter + v][16 * c + l16] = acc[c][v];
+  __syncthreads();
+  for (int i = threadIdx.x; i < kRecurTensors * 32; i += 64 * WAVES) {
+    const int r = i >> 5, c = i & 31;
+    float s[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) s[w] = part[w][r][c];
+#pragma unroll
+    for (int step = 1; step < WAVES; step *= 2)
+#pragma unroll
+      for (int w = 0; w < WAVES; w += 2 * step) s[w] += s[w + step];
+    if (t0 + r < M.n_tensors) M.z[((size_t)(t0 + r) * n_ub + ub) * 32 + c] = s[0];
+  }
+}
+
+// Extra workgroups of the row/column sums (slices of the mean; the recurrent product, if it is formed ahead) and of the launch
+// that forms the gate bias.
+inline int mix_hbar_blocks(const MixArgs& M) { return M.n_slices * ((M.HL + kWave - 1) / kWave); }
+inline int mix_bias_blocks(const MixArgs& M) { return M.n_slices ? kMixJSplit * ((4 * M.HL + kWave - 1) / kWave) : 0; }
+inline int recur_blocks(const MixArgs& M) {
+  return M.n_slices && M.z ? (M.n_tensors + kRecurTensors - 1) / kRecurTensors * ((M.HL + 7) / 8) : 0;
+}
+
+static MixArgs make_mix(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z = nullptr) {
   MixArgs M{};
   if (A.kind != LOPT_VELO || L.n_tensors == 0) return M;
   M.Wg = W.Wg; M.b = W.b; M.part = hbar_part; M.b_eff = b_eff;
+  M.lstm = W.lstm; M.z = lstm_z;
   M.HL = A.HL; M.n_tensors = L.n_tensors;
   int per_slice = (L.n_tensors + kMixSlices - 1) / kMixSlices;
   if (per_slice < 16) per_slice = 16;   // four tensors in flight on each of four wavefronts
@@ -224,24 +298,31 @@ __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& t
 
 __global__ void __launch_bounds__(kBlock) k_rowcol_sums(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                        int n_tiles, MixArgs M) {
-  __shared__ float colred[4][kTileCols];
-  if ((int)blockIdx.x >= n_tiles) {   // the extra workgroups of a VeLO step: slice sums of the LSTM outputs
-    mix_hbar_block(tensors, M, (int)blockIdx.x - n_tiles, reinterpret_cast<float (*)[kWave]>(&colred[0][0]));
+                                                        int n_tiles, MixArgs M, int n_recur) {
+  __shared__ union { float col[4][kTileCols], hbar[4][kWave], z[4][kRecurTensors][32]; } red;
+  const int blk = (int)blockIdx.x - n_recur;
+  if (blk < 0) {   // the extra workgroups of a VeLO step: recurrent product, slice sums of the LSTM outputs
+    lstm_recur_block<4>(tensors, M, (int)blockIdx.x, red.z);
     return;
   }
-  const TileDev tile = tiles[blockIdx.x];
+  if (blk >= n_tiles) {
+    mix_hbar_block(tensors, M, blk - n_tiles, red.hbar);
+    return;
+  }
+  float (*colred)[kTileCols] = red.col;
+  const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
   if (T.vec) rowcol_tile<true>(T, tile, ws, colred);
   else rowcol_tile<false>(T, tile, ws, colred);
 }
 
-void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff,
+void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
                         hipStream_t s) {
   if (L.n_tiles == 0) return;
-  const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
-  const int extra = M.n_slices * ((M.HL + kWave - 1) / kWave);
-  hipLaunchKernelGGL(k_rowcol_sums, dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, L.n_tiles, M);
+  const MixArgs M = make_mix(L, A, W, hbar_part, b_eff, lstm_z);
+  const int n_recur = recur_blocks(M);
+  hipLaunchKernelGGL(k_rowcol_sums, dim3(n_recur + L.n_tiles + mix_hbar_blocks(M)), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws,
+                     L.n_tiles, M, n_recur);
 }
 
 // Short lists: tiles of kShortRows rows, sixteen wavefronts with four rows in flight each, so that a column has few partial sums
@@ -311,24 +392,31 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
 
 __global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const TensorDev* __restrict__ tensors,
                                                                       const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                                      int n_tiles, MixArgs M) {
-  __shared__ float colred[kShortWaves][kTileCols];
-  if ((int)blockIdx.x >= n_tiles) {
-    mix_hbar_block(tensors, M, (int)blockIdx.x - n_tiles, reinterpret_cast<float (*)[kWave]>(&colred[0][0]));
+                                                                      int n_tiles, MixArgs M, int n_recur) {
+  __shared__ union { float col[kShortWaves][kTileCols], hbar[4][kWave], z[kShortWaves][kRecurTensors][32]; } red;
+  const int blk = (int)blockIdx.x - n_recur;
+  if (blk < 0) {
+    lstm_recur_block<kShortWaves>(tensors, M, (int)blockIdx.x, red.z);
     return;
   }
-  const TileDev tile = tiles[blockIdx.x];
+  if (blk >= n_tiles) {
+    mix_hbar_block(tensors, M, blk - n_tiles, red.hbar);
+    return;
+  }
+  float (*colred)[kTileCols] = red.col;
+  const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
   if (T.vec) rowcol_short_tile<true>(T, tile, ws, colred);
   else rowcol_short_tile<false>(T, tile, ws, colred);
 }
 
-void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, hipStream_t s) {
+void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
+                         hipStream_t s) {
   if (L.n_rctiles == 0) return;
-  const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
-  const int extra = M.n_slices * ((M.HL + kWave - 1) / kWave);
-  hipLaunchKernelGGL(k_rowcol_short, dim3(L.n_rctiles + extra), dim3(kWave * kShortWaves), 0, s, L.tensors, L.rctiles, L.ws,
-                     L.n_rctiles, M);
+  const MixArgs M = make_mix(L, A, W, hbar_part, b_eff, lstm_z);
+  const int n_recur = recur_blocks(M);
+  hipLaunchKernelGGL(k_rowcol_short, dim3(n_recur + L.n_rctiles + mix_hbar_blocks(M)), dim3(kWave * kShortWaves), 0, s, L.tensors,
+                     L.rctiles, L.ws, L.n_rctiles, M, n_recur);
 }
 
 // ----------------------------------------------------------------------------- rc_update
@@ -452,7 +540,7 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
                       hipStream_t s) {
   if (L.n_rcitems == 0) return;
   const MixArgs M = make_mix(L, A, W, hbar_part, b_eff);
-  const int extra = M.n_slices ? kMixJSplit * ((4 * M.HL + kWave - 1) / kWave) : 0;
+  const int extra = mix_bias_blocks(M);
   // The wide form shortens the chain of loads; on longer lists its workgroups no longer all fit on the chip at once and its
   // idle wavefronts cost more than that (2219 tensors: 46 us narrow, 154 us wide).
   const int threads = L.n_rcitems + extra <= 512 ? kRcMaxThreads : kBlock;
@@ -468,6 +556,11 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 struct alignas(16) FuseLds {
   float r[3][kShortRows], rr[3][kShortRows];   // r_k of the tile's rows, rsqrt(r_k + eps)
   float c[3][kTileCols], rc[3][kTileCols];
+};
+
+union ShortLds {
+  FuseLds means;
+  struct { float hbar[1024 / kMixJSplit], red[kBlock / kWave][kWave]; } mix;   // a quarter of at most 1024 units
 };
 
 __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws, const StepArgs& A,
@@ -744,14 +837,14 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
                                                         StepArgs A, int n_tiles, MixArgs M) {
   __shared__ float red[kNStat][4];
-  __shared__ std::conditional_t<FUSE, FuseLds, int> fuse;
+  __shared__ std::conditional_t<FUSE, ShortLds, int> sh;
   FuseLds* L = nullptr;
   if constexpr (FUSE) {
     if ((int)blockIdx.x >= n_tiles) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
-      mix_bias_block(M, (int)blockIdx.x - n_tiles, &fuse.c[0][0], reinterpret_cast<float (*)[kWave]>(&fuse.r[0][0]));
+      mix_bias_block(M, (int)blockIdx.x - n_tiles, sh.mix.hbar, sh.mix.red);
       return;
     }
-    L = &fuse;
+    L = &sh.means;
   }
   const TileDev tile = tiles[blockIdx.x];
   const TensorDev& T = tensors[tile.tensor];
@@ -762,10 +855,8 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   else accum_tile<RAW_RCP, WRITE, FUSE>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
-  if constexpr (FUSE) fuse_store(T, tile, ws, fuse, red);
+  if constexpr (FUSE) fuse_store(T, tile, ws, sh.means, red);
 }
-// mix_bias_block keeps a quarter of at most 1024 units and 4 x 64 partial sums in the means' arrays
-static_assert(sizeof(FuseLds::c) + sizeof(FuseLds::rc) >= 256 * sizeof(float) && sizeof(FuseLds::r) + sizeof(FuseLds::rr) >= 4 * kWave * sizeof(float));
 
 void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W, bool write_state, bool with_mix, float* hbar_part,
                         float* b_eff, hipStream_t s) {
@@ -777,7 +868,7 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
     whole.n_tensors = A.n_tensors;
     M = make_mix(whole, A, W, hbar_part, b_eff);
   }
-  const int extra = M.n_slices ? kMixJSplit * ((4 * M.HL + kWave - 1) / kWave) : 0;
+  const int extra = mix_bias_blocks(M);
 #define LOPT_LAUNCH_ACC(R, Wr, F) \
   hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M)
 #define LOPT_LAUNCH_ACC2(R, Wr) do { if (L.short_list) LOPT_LAUNCH_ACC(R, Wr, true); else LOPT_LAUNCH_ACC(R, Wr, false); } while (0)
@@ -927,7 +1018,6 @@ void launch_finalize(const Launch& L, const StepArgs& A, const WeightsDev& W, fl
 constexpr int kLstmTensors = 32;
 constexpr int kLstmWaves = 8;
 constexpr int kLstmOctets = 9;   // octets in flight per wavefront
-typedef float f32x16_l __attribute__((ext_vector_type(16)));
 
 // Weights in the order k_velo_lstm reads them: out[ub][k][8 gate + u] for unit 8 ub + u, zero past H_L in units and slots.
 __global__ void __launch_bounds__(kBlock) k_pack_lstm(WeightsDev W, int HL, int k_pad, float* __restrict__ out) {
@@ -1030,15 +1120,86 @@ __global__ void __launch_bounds__(64 * kLstmWaves) k_velo_lstm(const TensorDev* 
   }
 }
 
+// What is left of the step where the recurrent product was formed ahead (lstm_recur_block): the 48 inputs' product, two
+// octets each by three wavefronts, and the cell equations, one thread per (tensor, unit).
+constexpr int kTailWaves = 3;
+static_assert(kLstmInPad == 16 * kTailWaves, "two octets a wavefront");
+__global__ void __launch_bounds__(kBlock) k_velo_lstm_tail(const TensorDev* __restrict__ tensors, StepArgs A, WeightsDev W,
+                                                           const float* __restrict__ lstm_u, const float* __restrict__ b_eff,
+                                                           const float* __restrict__ z, float* __restrict__ h_new) {
+  __shared__ float part[kTailWaves][32][32];   // [wavefront][tensor][column]
+  const int HL = A.HL, G = 4 * HL;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int khalf = lane >> 5, l32 = lane & 31;
+  const int t0 = blockIdx.x * kLstmTensors, u0 = blockIdx.y * 8;
+  const int tt = threadIdx.x >> 3, j = threadIdx.x & 7, unit = u0 + j;
+  const bool cell_ok = t0 + tt < A.n_tensors && unit < HL;
+  float be[4] = {0.f, 0.f, 0.f, 0.f}, zr[4] = {0.f, 0.f, 0.f, 0.f}, c_old = 0.f;
+  float* cl = nullptr;
+  if (cell_ok) {
+    const TensorDev& Tt = tensors[t0 + tt];
+    cl = Tt.st + 4 * (size_t)Tt.padN + 3 * (size_t)Tt.padm + 3 * (size_t)Tt.padn + Tt.padH;
+    c_old = cl[unit];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int gc = g * HL + unit;   // bias + cross-tensor term (its four partial sums, in order)
+      be[g] = W.b[gc] + ((b_eff[gc] + b_eff[G + gc]) + (b_eff[2 * G + gc] + b_eff[3 * G + gc]));
+      zr[g] = z[((size_t)(t0 + tt) * gridDim.y + blockIdx.y) * 32 + 8 * g + j];
+    }
+  }
+  if (wave < kTailWaves) {
+    const float* __restrict__ usrc = lstm_u + (size_t)min(t0 + l32, A.n_tensors - 1) * kLstmInPad;
+    const float* __restrict__ wcol = W.lstm + ((size_t)blockIdx.y * lstm_k_pad(HL) + 4 * khalf) * 32 + l32;
+    f32x16_l acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    float4 a[2];
+    float b[2][4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int o = 2 * wave + q;
+      a[q] = *reinterpret_cast<const float4*>(usrc + 8 * o + 4 * khalf);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[q][i] = wcol[(size_t)(8 * o + i) * 32];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float x[4] = {a[q].x, a[q].y, a[q].z, a[q].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], b[q][i], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * khalf + (v & 3)][l32] = acc[v];
+  }
+  __syncthreads();
+  if (cell_ok) {
+    float zz[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) zz[g] = be[g] + ((zr[g] + part[0][tt][8 * g + j]) + (part[1][tt][8 * g + j] + part[2][tt][8 * g + j]));
+    const float ig = 1.f / (1.f + expf(-zz[0]));
+    const float fg = 1.f / (1.f + expf(-zz[1]));
+    const float gg = tanhf(zz[2]);
+    const float og = 1.f / (1.f + expf(-zz[3]));
+    const float c = fg * c_old + ig * gg;
+    cl[unit] = c;
+    h_new[(size_t)(t0 + tt) * HL + unit] = og * tanhf(c);
+  }
+}
+
 void launch_velo_lstm(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* lstm_u, const float* b_eff,
-                      float* h_new, hipStream_t s) {
+                      const float* lstm_z, float* h_new, hipStream_t s) {
   if (L.n_tensors == 0) return;
   dim3 grid((L.n_tensors + kLstmTensors - 1) / kLstmTensors, (A.HL + 7) / 8);
   // a sub-list starts at tensor L.tensor0: the kernel indexes tensors, inputs and outputs from there
   StepArgs As = A;
   As.n_tensors = L.n_tensors;
-  hipLaunchKernelGGL(k_velo_lstm, grid, dim3(64 * kLstmWaves), 0, s, L.tensors + L.tensor0, As, W,
-                     lstm_u + (size_t)L.tensor0 * kLstmInPad, b_eff, h_new + (size_t)L.tensor0 * A.HL);
+  const TensorDev* T0 = L.tensors + L.tensor0;
+  const float* u0 = lstm_u + (size_t)L.tensor0 * kLstmInPad;
+  float* h0 = h_new + (size_t)L.tensor0 * A.HL;
+  if (lstm_z)
+    hipLaunchKernelGGL(k_velo_lstm_tail, grid, dim3(kBlock), 0, s, T0, As, W, u0, b_eff, lstm_z + (size_t)L.tensor0 * grid.y * 32, h0);
+  else
+    hipLaunchKernelGGL(k_velo_lstm, grid, dim3(64 * kLstmWaves), 0, s, T0, As, W, u0, b_eff, h0);
 }
 
 // ---- the head with its two products folded into one at lopt_create (WeightsDev::head): theta = h (W_a B) + b_a B, with the
@@ -1160,6 +1321,83 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_folded(const Tens
       const int dst = head_slot(i, H, HP, scale, s_lam, th);
       prep[dst] = th;
     }
+  }
+}
+
+// Slot i of the prepared layout is one of the zeros that pad the width H to HP.
+__device__ __forceinline__ bool head_pad(int i, int H, int HP) {
+  constexpr int F = LOPT_D_VELO;
+  int o = i;
+  if (o < (F + 1) * HP) return o % HP >= H;
+  if ((o -= (F + 1) * HP) < HP * HP) return o / HP >= H || o % HP >= H;
+  if ((o -= HP * HP) < HP) return o >= H;
+  return (o -= HP) < 2 * HP && o / 2 >= H;
+}
+
+// The same product cut into workgroups of 32 columns, so that a tensor's 309 KB of weights come in over several compute units. A
+// lane holds four columns of every 128th row, all its loads (weights and h, nothing depends on anything) leave at once; four
+// terms a lane, eight lanes by shuffles, sixteen wavefronts by a tree in LDS. ln lambda is formed by every workgroup: one term
+// a thread and trees. One tensor 6.9 -> 4.6 us, 66 tensors 7.1 -> 5.9, 152 tensors 7.6 -> 8.2 (five workgroups of 1024 threads each
+// are then more than the chip holds at once): kHeadSplitMax.
+constexpr int kSplitCols = 32, kSplitRows = 128, kSplitTrips = 1024 / kSplitRows;   // H_L <= 1024
+template <int TRIPS>
+__global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_split(const TensorDev* __restrict__ tensors,
+                                                                     float* __restrict__ ws, StepArgs A, WeightsDev W,
+                                                                     const float* __restrict__ h_new) {
+  __shared__ float part[kHeadWaves][kSplitCols], lam_part[kHeadWaves];
+  const int HL = A.HL, H = A.H, HP = A.HP, P = A.P, ld = head_ld(P);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int c0 = blockIdx.x * kSplitCols, row0 = 8 * wave + (lane >> 3);
+  const float* __restrict__ h = h_new + (size_t)blockIdx.y * HL;
+  const float4* __restrict__ m = reinterpret_cast<const float4*>(W.head + min(c0 + 4 * (lane & 7), ld - 4));
+  float4 w[TRIPS];
+  float x[TRIPS];
+#pragma unroll
+  for (int j = 0; j < TRIPS; ++j) {
+    const int k = row0 + kSplitRows * j, kc = min(k, HL - 1);
+    w[j] = m[(size_t)kc * (ld / 4)];
+    x[j] = h[kc];
+  }
+  const int kl = min(t, HL - 1);
+  const float hl = h[kl], wl = W.head[(size_t)kl * ld + P], b_lam = W.head[(size_t)HL * ld + P];
+  const int i = c0 + t;   // threads 0..31: column
+  const float bias = t < kSplitCols && i < P ? W.head[(size_t)HL * ld + i] : 0.f;
+  const TensorDev& T = tensors[blockIdx.y];
+  float* prep = ws + T.oPrep;
+  if (blockIdx.x == 0) {
+    float* hstate = T.st + 4 * (size_t)T.padN + 3 * (size_t)T.padm + 3 * (size_t)T.padn;
+    if (t < HL) hstate[t] = hl;
+    if (H != HP) {   // the padding must be zero; no workgroup writes values there
+      const int prep_n = (LOPT_D_VELO + 1) * HP + HP * HP + HP + 2 * HP + 2;
+      for (int s = t; s < prep_n; s += 64 * kHeadWaves)
+        if (head_pad(s, H, HP)) prep[s] = 0.f;
+    }
+  }
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < TRIPS; ++j) {
+    const float xv = row0 + kSplitRows * j < HL ? x[j] : 0.f;
+    a[0] += xv * w[j].x; a[1] += xv * w[j].y; a[2] += xv * w[j].z; a[3] += xv * w[j].w;
+  }
+#pragma unroll
+  for (int d = 8; d < 64; d *= 2)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], d);
+  const float lsum = wave_sum(t < HL ? hl * wl : 0.f);
+  if (lane < 8) *reinterpret_cast<float4*>(&part[wave][4 * lane]) = make_float4(a[0], a[1], a[2], a[3]);
+  if (lane == 0) lam_part[wave] = lsum;
+  __syncthreads();
+  if (t < kSplitCols && i < P) {
+    float s[kHeadWaves], l[kHeadWaves];
+#pragma unroll
+    for (int q = 0; q < kHeadWaves; ++q) { s[q] = part[q][t]; l[q] = lam_part[q]; }
+#pragma unroll
+    for (int step = 1; step < kHeadWaves; step *= 2)
+#pragma unroll
+      for (int q = 0; q < kHeadWaves; q += 2 * step) { s[q] += s[q + step]; l[q] += l[q + step]; }
+    float th = bias + s[0];
+    const int dst = head_slot(i, H, HP, ws + T.oScale, expf(b_lam + l[0]), th);
+    prep[dst] = th;
   }
 }
 
@@ -1371,6 +1609,13 @@ void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, c
       hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.head,
                          ld, A.P, W.head + (size_t)A.HL * ld, th, ld);
       hipLaunchKernelGGL(k_velo_head_scatter, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th, ld);
+    } else if (T <= kHeadSplitMax) {
+      const dim3 grid((A.P + kSplitCols - 1) / kSplitCols, T);
+#define LOPT_LAUNCH_SPLIT(N) \
+  hipLaunchKernelGGL((k_velo_head_split<N>), grid, dim3(64 * kHeadWaves), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn)
+      if (A.HL <= 4 * kSplitRows) LOPT_LAUNCH_SPLIT(4);
+      else LOPT_LAUNCH_SPLIT(kSplitTrips);
+#undef LOPT_LAUNCH_SPLIT
     } else {
       const size_t shmem = (size_t)(((A.HL + 3) & ~3) + kHeadWaves * 256) * sizeof(float);
       hipLaunchKernelGGL(k_velo_head_folded, dim3(T), dim3(64 * kHeadWaves), shmem, s, L.tensors + L.tensor0, L.ws, A, W, hn);

@@ -42,6 +42,7 @@ struct Plan {
   std::vector<size_t> state_bytes;
   uint64_t oLstmU = 0, oHNew = 0;   // VeLO scratch (floats)
   uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
+  uint64_t oLstmZ = 0;               // VeLO, lists of at most kLstmAheadMax tensors: h W_h of the step before, in tile order (0: not used)
   uint64_t oAlpha = 0, oTheta = 0;   // VeLO, long lists: bank coefficients [T][K] and per-tensor MLPs [T][P]
   bool head_batched = false;
   uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the apply kernel
@@ -81,7 +82,7 @@ inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t to
 // 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Lists in tensor
 // groups keep the launch: the statistics kernel that forms the means does not fit beside the apply kernel.
 inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink) {
-  if (total >= (64u << 20)) return false;
+  if (total >= (64u << 20) || n > 4096) return false;   // 4096: the copies of r_k and c_k are no large part of a workspace
   uint64_t floats = 0;
   for (size_t i = 0; i < n; ++i) {
     const uint64_t nrc = (uint64_t)ceil_div(d[i].rows, kShortRows), nct = (uint64_t)ceil_div(d[i].cols, kTileCols);
@@ -232,6 +233,11 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     }
     pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
   }
+  // h W_h depends on nothing this step computes. Up to kLstmAheadMax tensors it is formed beside the statistics; longer lists and
+  // workspaces that come near the fixed scratch of lopt_step_static go without the room for it
+  pl->oLstmZ = 0;
+  if (velo && n <= (size_t)kLstmAheadMax && off <= (48u << 20) / sizeof(float))
+    pl->oLstmZ = take((uint64_t)n * 32 * ceil_div(o.lstm_hidden, 8));
   pl->ws_floats = off;
 }
 

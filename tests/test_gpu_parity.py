@@ -122,6 +122,21 @@ def test_velo_folded_head_and_lstm_octets(hidden, lstm_hidden, n_bank, count):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("hidden,lstm_hidden,n_bank,count", [(4, 1024, 256, 5), (4, 520, 300, 17), (5, 130, 200, 96), (5, 130, 200, 97),
+                                                             (4, 9, 64, 16)])
+def test_velo_recurrent_product_ahead_and_head_in_column_blocks(hidden, lstm_hidden, n_bank, count):
+    # up to 96 tensors the LSTM's recurrent product is formed beside the row/column sums, in blocks of 16 tensors, and the head in
+    # blocks of 32 columns; 97 tensors take one launch for each. Widths on and off the octet, one and two batches of head rows.
+    # Two lists in one: tensor shapes below and above the limit of a short list (6145 rows), whose sums are another kernel
+    cfg = Hn.make_cfg("velo", hidden=hidden, lstm_hidden=lstm_hidden, n_bank=n_bank)
+    w = Hn.random_weights(cfg, seed=60 + lstm_hidden)
+    r = np.random.default_rng(79)
+    for first in ((7, 13), (6145, 3)):
+        shapes = [first, (33, 20)] + [(int(r.integers(8, 60)),) for _ in range(count - 2)]
+        worst = Hn.run_free(Hn.Case(127, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+        assert worst["param"] <= Hn.TOL_PARAM
+
+
 def _velo_weight_views(w, cfg):
     """The sections of a VeLO weight blob (include/lopt.h) as views of `w`."""
     HL, K, h = int(cfg.lstm_hidden), int(cfg.n_bank), int(cfg.hidden)
