@@ -106,7 +106,9 @@ __device__ __forceinline__ TileRows tile_rows(const TensorDev& T, const TileDev&
 //                (1024 columns 1.009 -> 0.907 ms, 2048 1.161 -> 0.894, 3072 0.915 -> 0.890)
 //   longer       every fourth row, as for other rows, but starting at a place that differs from tile to tile
 //                (4096 columns 0.932 -> 0.887 ms, 6144 0.934 -> 0.882, 8192 0.875 -> 0.867; the first form: 0.945, 0.928, 1.10)
-// Other rows measured the same or up to 4 % slower with either, and keep the plain walk.
+// Other rows measured the same or up to 4 % slower with either. Their wavefronts take a quarter of the tile's rows each, one after the
+// other (against every fourth row: 4352 columns 957 -> 949 us, 4128 1027 -> 997, 4100 967 -> 957, 3840 848 -> 842, ViT-B/16 shapes
+// the same, 4224 918 -> 927).
 struct RowWalk { int tj, base, cnt, rot, step; };
 __device__ __forceinline__ RowWalk plain_walk(const TensorDev& T, const TileDev& tile, int wave) {   // rows r0 + wave + 4 i
   const int r0 = tile.ti * T.TR;
@@ -119,8 +121,13 @@ __device__ __forceinline__ RowWalk row_walk(const TensorDev& T, const TileDev& t
     const int quarter = T.TR / 4, b = r0 + (tile.tj & 3) * quarter;   // TR is a multiple of 8
     return RowWalk{(tile.tj & ~3) + wave, b, min(quarter, T.m - b), 0, 1};
   }
-  const int cnt = (min(T.TR, T.m - r0) - wave + 3) >> 2;   // rows r0 + wave + 4 i
-  return RowWalk{tile.tj, r0 + wave, cnt, pitch && cnt > 0 ? tile.ti * 7 % cnt : 0, 4};
+  const int rows = min(T.TR, T.m - r0);
+  if (!pitch) {
+    const int per = (rows + 3) >> 2, b = wave * per;
+    return RowWalk{tile.tj, r0 + b, min(per, rows - b), 0, 1};
+  }
+  const int cnt = (rows - wave + 3) >> 2;   // rows r0 + wave + 4 i
+  return RowWalk{tile.tj, r0 + wave, cnt, cnt > 0 ? tile.ti * 7 % cnt : 0, 4};
 }
 __device__ __forceinline__ int walk_row(const RowWalk& w, int i) {   // 0 <= i < cnt (cnt <= 0: no rows)
   int k = i + w.rot;

@@ -189,8 +189,17 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.nrt = ceil_div(m, T.TR);
     T.nct = ceil_div(nn, kTileCols);
     T.tile0 = (int)pl->tiles.size();
-    for (int ti = 0; ti < T.nrt; ++ti)
-      for (int tj = 0; tj < T.nct; ++tj) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
+    // Table order: workgroups reach the eight dies in turn, so eight tile rows at a time, column by column, put the tiles of a row
+    // on one die, whose L2 then holds the lines that neighbours share (rows off the 128-byte grid) and writes them back whole.
+    // VeLO, us a step, before and now: four 4096 x 4100 1026 -> 976, 20 of 1000 x 1000 326 -> 317, 54 M elements of 2731 columns
+    // 871 -> 860; rows on the grid: four 4096 x 4096 877 -> 868, ViT-B/16 shapes 1164 -> 1157, Llama-1.3B shapes 17410 -> 17320, 20 of
+    // 1024 x 1024 292.3 -> 293.5. Sixteen tile rows the same, four up to 3 % slower.
+    constexpr int kDies = 8;
+    for (int t0 = 0; t0 < T.nrt; t0 += kDies) {
+      const int t1 = t0 + kDies <= T.nrt ? t0 + kDies : T.nrt;
+      for (int tj = 0; tj < T.nct; ++tj)
+        for (int ti = t0; ti < t1; ++ti) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
+    }
     T.nrblk = pl->short_list ? T.nrt : ceil_div(m, kBlock);
     T.ncblk = ceil_div(nn, kBlock);   // = nct
     T.rc0 = (int)pl->rcitems.size();
