@@ -117,6 +117,9 @@ struct Launch {
   const TileDev* rctiles; // short lists: tiles of kShortRows x kTileCols of the row/column sums
   int n_rctiles;
   bool short_list;        // the statistics pass finishes the row and column means itself (Plan::short_list)
+  int keep, keep_off;     // tiles below these numbers are read by the statistics pass with ordinary loads: rows on the 128-byte grid,
+                          // rows off the 16-byte grid (Plan::keep)
+  bool backwards;         // the statistics pass takes its tiles from the last to the first
 };
 
 // kernels (lopt_kernels.hip / lopt_apply_mfma.hip)

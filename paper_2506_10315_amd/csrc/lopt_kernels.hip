@@ -341,7 +341,7 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
 #pragma unroll
   for (int i = 0; i < R; ++i) {   // rows past the tile: its last row, counted as 0
     const float* __restrict__ row = T.g + (size_t)min(r0 + wave + kShortWaves * i, r1 - 1) * (unsigned)n;
-    if (VEC) v[i] = load4s<true>(row, c0 + 4 * lane, n);
+    if (VEC) v[i] = load4<true>(row, c0 + 4 * lane, n);
     else {
       float x[4];
 #pragma unroll
@@ -642,8 +642,9 @@ __device__ __forceinline__ void fuse_store(const TensorDev& T, const TileDev& ti
 // The per-element features that need a statistic of their own (the row/column-constant ones
 // follow from r_k, c_k alone). rrc[k] = rsqrt(r_k[i]+eps) * rsqrt(c_k[j]+eps); the common
 // factor sqrt(mean(r_k)+eps) of the factored features is applied per tensor in k_finalize.
-// Streaming accesses of this pass: nontemporal loads, ordinary stores (measured: 0.649 ms on the ViT-B/16 set
-// against 0.670 plain/plain, 0.670 plain/nontemporal, 0.680 nontemporal/nontemporal).
+// Streaming accesses of this pass on long lists: nontemporal loads, ordinary stores (measured: 0.649 ms on the ViT-B/16 set
+// against 0.670 plain/plain, 0.670 plain/nontemporal, 0.680 nontemporal/nontemporal); what is worth keeping in the cache for
+// the apply pass is read with ordinary loads (choose_loads in lopt_plan.h).
 
 // Rows that are not 16-byte aligned (n % 4 != 0): one column per lane, every access a coalesced dword of a 256-byte row
 // segment, kAccRows rows of loads in flight. The wavefronts of the tile sit on adjacent 64-column segments; where the tile
@@ -651,11 +652,14 @@ __device__ __forceinline__ void fuse_store(const TensorDev& T, const TileDev& ti
 // (Three segments leave the fourth wavefront without work.)
 // Kept small in registers on purpose: the kernel's register count is the larger of its two paths, and it decides how
 // many of its workgroups fit beside the apply kernel of another tensor group (the float4 path's count, with four rows
-// too). Ordinary loads: neighbouring segments share their boundary lines. 8.3 M elements of 1531 columns: 48 us with one
-// row per trip and nontemporal loads, 41 us.
+// too). 8.3 M elements of 1531 columns: 48 us with one row per trip and nontemporal loads, 41 us.
 constexpr int kAccRows = 4;
 
-template <bool RAW_RCP, bool WRITE, bool FUSE>
+// NT: nontemporal loads (Plan::keep).
+template <bool NT, typename P>
+__device__ __forceinline__ auto load_nt(P p) { return NT ? __builtin_nontemporal_load(p) : *p; }
+
+template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
 __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                            const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
   if (FUSE) fuse_means(T, tile, ws, A, *L);
@@ -680,10 +684,10 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
 #pragma unroll
     for (int e = 0; e < kAccRows; ++e) {   // a row past the tile reads the tile's last row and counts for nothing
       const size_t ro = (size_t)min(r + e, r1 - 1) * (unsigned)n + c;
-      in[e][0] = T.g[ro];
-      in[e][1] = T.p[ro];
+      in[e][0] = load_nt<NT>(T.g + ro);
+      in[e][1] = load_nt<NT>(T.p + ro);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) in[e][2 + k] = T.st[k * pN + ro];
+      for (int k = 0; k < 4; ++k) in[e][2 + k] = load_nt<NT>(T.st + (k * pN + ro));
     }
 #pragma unroll
     for (int e = 0; e < kAccRows; ++e) {
@@ -738,7 +742,7 @@ typedef float __attribute__((ext_vector_type(4))) f32x4v;
 typedef const f32x4v __attribute__((address_space(1)))* gcv4;
 typedef f32x4v __attribute__((address_space(1)))* gv4;
 
-template <bool RAW_RCP, bool WRITE, bool FUSE>
+template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
 __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
   const int lane = threadIdx.x & 63;
@@ -758,12 +762,12 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
   auto load = [&](int i) __attribute__((always_inline)) {
     r = walk_row(w, i);
     ro = (size_t)r * n + col;   // a multiple of 4: every section starts 16-byte aligned
-    g4 = __builtin_nontemporal_load((gcv4)(T.g + ro));
-    p4 = __builtin_nontemporal_load((gcv4)(T.p + ro));
-    m1 = __builtin_nontemporal_load((gcv4)(T.st + ro));
-    m2 = __builtin_nontemporal_load((gcv4)(T.st + pN + ro));
-    m3 = __builtin_nontemporal_load((gcv4)(T.st + 2 * pN + ro));
-    v4 = __builtin_nontemporal_load((gcv4)(T.st + 3 * pN + ro));
+    g4 = load_nt<NT>((gcv4)(T.g + ro));
+    p4 = load_nt<NT>((gcv4)(T.p + ro));
+    m1 = load_nt<NT>((gcv4)(T.st + ro));
+    m2 = load_nt<NT>((gcv4)(T.st + pN + ro));
+    m3 = load_nt<NT>((gcv4)(T.st + 2 * pN + ro));
+    v4 = load_nt<NT>((gcv4)(T.st + 3 * pN + ro));
   };
   float4 c3[3];
   if (FUSE) {
@@ -835,7 +839,8 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
 template <bool RAW_RCP, bool WRITE, bool FUSE>
 __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                        StepArgs A, int n_tiles, MixArgs M) {
+                                                        StepArgs A, int n_tiles, MixArgs M, int keep, int keep_off,
+                                                        bool backwards) {
   __shared__ float red[kNStat][4];
   __shared__ std::conditional_t<FUSE, ShortLds, int> sh;
   FuseLds* L = nullptr;
@@ -846,13 +851,16 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
     }
     L = &sh.means;
   }
-  const TileDev tile = tiles[blockIdx.x];
+  const int idx = backwards ? n_tiles - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  const TileDev tile = tiles[idx];
   const TensorDev& T = tensors[tile.tensor];
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  if (T.vec) accum_tile_vec<RAW_RCP, WRITE, FUSE>(T, tile, ws, A, acc, L);
-  else accum_tile<RAW_RCP, WRITE, FUSE>(T, tile, ws, A, acc, L);
+  if (T.vec == 2 && idx < keep) accum_tile_vec<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  else if (T.vec) accum_tile_vec<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
+  else if (idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
   if constexpr (FUSE) fuse_store(T, tile, ws, sh.means, red);
@@ -870,7 +878,8 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
   }
   const int extra = mix_bias_blocks(M);
 #define LOPT_LAUNCH_ACC(R, Wr, F) \
-  hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M)
+  hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M, \
+                     L.keep, L.keep_off, L.backwards)
 #define LOPT_LAUNCH_ACC2(R, Wr) do { if (L.short_list) LOPT_LAUNCH_ACC(R, Wr, true); else LOPT_LAUNCH_ACC(R, Wr, false); } while (0)
   if (raw && write_state) LOPT_LAUNCH_ACC2(true, true);
   else if (raw) LOPT_LAUNCH_ACC2(true, false);

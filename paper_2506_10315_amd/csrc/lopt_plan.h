@@ -35,6 +35,8 @@ struct Plan {
   std::vector<RcItemDev> rcitems;
   std::vector<TileDev> rctiles;       // short lists: tiles of the row/column sums
   bool short_list = false;
+  int keep = 0, keep_off = 0;         // see choose_loads
+  bool backwards = false;
   std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
@@ -92,6 +94,36 @@ inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, i
     if (floats > kShortListFloats) return false;
   }
   return true;
+}
+
+// How the statistics pass reads its tiles. What it reads with ordinary instead of nontemporal loads is still in the 256 MB
+// Infinity Cache when the apply pass reads it again, as far as it fits: 10 M elements of 24 bytes. us a step, two contexts in turn:
+//   short lists (on the 128-byte grid, row/column sums ordinary too): everything, also past the cache's size: VeLO 2.4 M elements
+//     62.6 -> 58.3, 4.2 M 84.6 -> 77.1, 8.4 M 132.2 -> 119.5, 21 M 293 -> 282, 31 M 427 -> 420; width 16 9.5 M 189.8 -> 186.7; width 32 12.6 M
+//     247 -> 241, 16.8 M 318.5 -> 315. From 40 M elements on from the last tile to the first, so that each pass begins where
+//     the one before it ended: 47 M 652 -> 637 (forwards 647), but 31 M 422.5 and 2.4 M 60.2
+//   rows off the 16-byte grid: ordinary (8.3 M elements width 32 209 us nontemporal 220; VeLO 8 M 143 / 161), for VeLO from 13 M on
+//     nontemporal (13.4 M 229 / 231, 16.4 M 298 / 285, 20 M 360 / 336), again but for the first 10 M
+//   long lists under VeLO: from the last tile to the first, nontemporal but for the first 10 M elements' tiles: ViT-B/16 shapes
+//     1158 -> 1150 (6.5 M 1153, 16 M 1151.5; everything 1181), Llama-1.3B shapes 17310 -> 17283
+//   long lists of small_fc_lopt: nontemporal (ViT-B/16 shapes 313 us the pass, 352 with ordinary loads).
+inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
+  constexpr uint64_t kCached = 10u << 20;
+  int cached = (int)pl->tiles.size();   // tiles of the first kCached elements
+  uint64_t seen = 0;
+  for (const TensorDev& T : pl->tensors) {
+    const uint64_t N = (uint64_t)T.m * (uint64_t)T.n;
+    if (seen + N > kCached) {
+      cached = T.tile0 + (int)((double)(kCached - seen) / (double)N * (double)((uint64_t)T.nrt * (uint64_t)T.nct));
+      break;
+    }
+    seen += N;
+  }
+  const int all = 0x7fffffff;
+  const bool velo = o.kind == LOPT_VELO;
+  pl->backwards = pl->short_list ? total >= (40u << 20) : velo;
+  pl->keep = pl->short_list ? all : velo ? cached : 0;
+  pl->keep_off = pl->short_list && velo && total >= (13u << 20) ? cached : all;
 }
 
 // Lay out tiles, row/column blocks and workspace regions for a tensor list.
@@ -248,6 +280,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   if (velo && n <= (size_t)kLstmAheadMax && off <= (48u << 20) / sizeof(float))
     pl->oLstmZ = take((uint64_t)n * 32 * ceil_div(o.lstm_hidden, 8));
   pl->ws_floats = off;
+  choose_loads(o, total, pl);
 }
 
 inline bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {
