@@ -94,6 +94,21 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned&
   lo = __builtin_bit_cast(unsigned, a);
 }
 
+// Two pairs at once, their instructions alternating: none waits for the one before it.
+__device__ __forceinline__ void split4(float a, float b, float c, float d, unsigned& hi0, unsigned& lo0, unsigned& hi1, unsigned& lo1) {
+  asm("v_cvt_pkrtz_f16_f32 %0, %2, %3\n\t"
+      "v_cvt_pkrtz_f16_f32 %1, %4, %5\n\t"
+      "v_fma_mix_f32 %2, %0, -1.0, %2 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %4, %1, -1.0, %4 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %3, %0, -1.0, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %5, %1, -1.0, %5 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_cvt_pkrtz_f16_f32 %2, %2, %3\n\t"
+      "v_cvt_pkrtz_f16_f32 %4, %4, %5"
+      : "=&v"(hi0), "=&v"(hi1), "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+  lo0 = __builtin_bit_cast(unsigned, a);
+  lo1 = __builtin_bit_cast(unsigned, c);
+}
+
 // one value -> (hi in bits 0..15, lo in bits 16..31)
 __device__ __forceinline__ unsigned split1(float a) {
   unsigned pk = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(a, 0.f));
@@ -206,16 +221,15 @@ __device__ __forceinline__ void feat_piece(const Consts& C, const Elem& e, const
     asm volatile("v_mov_b32 %0, %1" : "=v"(f.p_old) : "v"(e.p));
     split2(e.g * C.sc[0], e.p * C.sc[1], f.ph[0], f.pl[0]);
   } else if (PIECE == 1) {
-    split2(e.m1 * C.sc[2], e.m2 * C.sc[3], f.ph[1], f.pl[1]);
-    split2(e.m3 * C.sc[4], e.v * C.sc[5], f.ph[2], f.pl[2]);
+    split4(e.m1 * C.sc[2], e.m2 * C.sc[3], e.m3 * C.sc[4], e.v * C.sc[5], f.ph[1], f.pl[1], f.ph[2], f.pl[2]);
   } else if (PIECE == 2) {
     split2((e.m1 * t.rs) * C.sc[6], (e.m2 * t.rs) * C.sc[7], f.ph[3], f.pl[3]);
   } else if (PIECE == 3) {
-    split2((e.m3 * t.rs) * C.sc[8], t.rs * C.sc[9], f.ph[4], f.pl[4]);
-    split2(e.g * (rr4.x * C.fg[0]), e.g * (rr4.y * C.fg[1]), f.ph[5], f.pl[5]);
+    split4((e.m3 * t.rs) * C.sc[8], t.rs * C.sc[9], e.g * (rr4.x * C.fg[0]), e.g * (rr4.y * C.fg[1]), f.ph[4], f.pl[4], f.ph[5],
+           f.pl[5]);
   } else if (PIECE == 4) {
-    split2(e.g * (rr4.z * C.fg[2]), e.m1 * (rr4.x * C.fm[0]), f.ph[6], f.pl[6]);
-    split2(e.m2 * (rr4.y * C.fm[1]), e.m3 * (rr4.z * C.fm[2]), f.ph[7], f.pl[7]);
+    split4(e.g * (rr4.z * C.fg[2]), e.m1 * (rr4.x * C.fm[0]), e.m2 * (rr4.y * C.fm[1]), e.m3 * (rr4.z * C.fm[2]), f.ph[6], f.pl[6],
+           f.ph[7], f.pl[7]);
   } else {
     swap32x8(f.ph, f.pl);
   }
@@ -224,6 +238,10 @@ __device__ __forceinline__ void feat_piece(const Consts& C, const Elem& e, const
 // ReLU, split and pack one pair of accumulator registers of layer 1
 __device__ __forceinline__ void relu_split_pair(const f32x16& h, int idx, unsigned& hi, unsigned& lo) {
   split2(relu(h[idx]), relu(h[idx + 1]), hi, lo);
+}
+
+__device__ __forceinline__ void relu_split_pairs(const f32x16& h, int idx, unsigned (&hi)[8], unsigned (&lo)[8]) {
+  split4(relu(h[idx]), relu(h[idx + 1]), relu(h[idx + 2]), relu(h[idx + 3]), hi[idx / 2], lo[idx / 2], hi[idx / 2 + 1], lo[idx / 2 + 1]);
 }
 
 // Layer 3 for two units (accumulator registers 2*V2, 2*V2+1) of both tiles; w = d(v) m(v) d(v+1) m(v+1)
@@ -491,14 +509,13 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     // ---- phase 2: ReLU/split of tile A (vector ALU only)
     unsigned ah[8], al[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) relu_split_pair(h1a, 2 * i, ah[i], al[i]);
+    for (int i = 0; i < 8; i += 2) relu_split_pairs(h1a, 2 * i, ah, al);
     LOPT_SB();
     // ---- phase 3: layer-2 MFMAs of tile A | ReLU/split of tile B
     unsigned bh[8], bl[8];
     h2a = mfma(C.a2l[0], pk8(ah[0], ah[1], ah[2], ah[3]), C.cb2);
     LOPT_SB();
-    relu_split_pair(h1b, 0, bh[0], bl[0]);
-    relu_split_pair(h1b, 2, bh[1], bl[1]);
+    relu_split_pairs(h1b, 0, bh, bl);
     LOPT_SB();
     h2a = mfma(C.a2h[0], pk8(al[0], al[1], al[2], al[3]), h2a);
     LOPT_SB();
@@ -510,8 +527,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     LOPT_SB();
     h2a = mfma(C.a2l[1], pk8(ah[4], ah[5], ah[6], ah[7]), h2a);
     LOPT_SB();
-    relu_split_pair(h1b, 8, bh[4], bl[4]);
-    relu_split_pair(h1b, 10, bh[5], bl[5]);
+    relu_split_pairs(h1b, 8, bh, bl);
     LOPT_SB();
     h2a = mfma(C.a2h[1], pk8(al[4], al[5], al[6], al[7]), h2a);
     LOPT_SB();
