@@ -275,6 +275,13 @@ lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   return LOPT_OK;
 }
 
+TimeFeats make_time_feats(int64_t step) {
+  static const double x[LOPT_N_TIME] = {1, 3, 10, 30, 100, 300, 1000, 3000, 1e4, 3e4, 1e5};
+  TimeFeats f;
+  for (int i = 0; i < LOPT_N_TIME; ++i) f.v[i] = (float)std::tanh((double)step / x[i]);
+  return f;
+}
+
 StepArgs make_args(const lopt_ctx* ctx, int64_t step, float lr, float wd, int n_tensors) {
   StepArgs A{};
   const lopt_config& c = ctx->cfg;
@@ -641,8 +648,11 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool velo4_ok = ctx->cfg.kind == LOPT_VELO && ctx->apply_variant != LOPT_APPLY_VALU && apply_velo4_available(A);
   const bool fc4x_ok = rows_ok && ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
   const bool state_in_apply = (strip_ok || fc4x_ok || velo4_ok) && ctx->state_in_apply;
+  const bool fold = strip_ok && pl.fold_finalize;
+  TimeFeats feats{};
+  if (fold) feats = make_time_feats(step);
   auto launch_apply = [&](const Launch& La) {
-    if (strip_ok) launch_apply_f16s(La, A, ctx->W, state_in_apply, stream);
+    if (strip_ok) launch_apply_f16s(La, A, ctx->W, fold ? &feats : nullptr, state_in_apply, stream);
     else if (mfma_ok && ctx->apply_variant != LOPT_APPLY_VALU) launch_apply_mfma(La, A, ctx->W, stream);
     else if (fc4x_ok) launch_apply_fc4x(La, A, ctx->W, state_in_apply, stream);
     else if (ctx->cfg.kind == LOPT_SMALL_FC) launch_apply_small_fc(La, A, ctx->W, stream);
@@ -697,7 +707,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for
     auto stats_passes = [&](const Launch& S, hipStream_t s) {
       launch_accum_stats(S, A, ctx->W, !state_in_apply, S.tensor0 == 0, ws + pl.oHbarPart, ws + pl.oBeff, s);
-      launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
+      if (!fold) launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
       if (velo) {
         launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, s);
         launch_velo_head(S, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
@@ -751,7 +761,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   MARK(2);
   launch_accum_stats(L, A, ctx->W, !state_in_apply, true, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(3);
-  launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
+  if (!fold) launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
   MARK(4);
   if (ctx->cfg.kind == LOPT_VELO) {
     launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, stream);

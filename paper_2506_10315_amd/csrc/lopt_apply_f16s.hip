@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "lopt_apply_common.h"
+#include "lopt_finalize.h"
 
 namespace lopt {
 
@@ -256,12 +257,16 @@ __device__ __forceinline__ void layer3_piece(const float4& w, const f32x16& h2a,
 
 }  // namespace
 
-template <bool RAW_RSQ, bool UPDATE_STATE>
+// FIN: k_finalize has not run; every workgroup forms the scales of its tensor from the statistics pass's partials, and the first
+// layer from them: a launch and its chain of loads fewer (the planner's fold_finalize has the line and both sides).
+template <bool RAW_RSQ, bool UPDATE_STATE, bool FIN>
 __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __restrict__ tensors,
                                                           const ApplyTileDev* __restrict__ atiles, int n_atiles,
                                                           int* __restrict__ next_tile, float* __restrict__ ws,
-                                                          StepArgs A, const float* __restrict__ tail) {
+                                                          StepArgs A, const float* __restrict__ tail,
+                                                          const float* __restrict__ mlp, TimeFeats feats) {
   __shared__ StripLds L;
+  __shared__ std::conditional_t<FIN, FinLds, int> fin;
   __shared__ int s_tile;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
@@ -283,9 +288,19 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   for (int i = 0; i < 3; ++i) { C.bm[i] = A.mom_decay[i]; C.am[i] = 1.0f - A.mom_decay[i]; }
   C.bv = A.rms_decay; C.av = 1.0f - A.rms_decay;
   C.b3d = tail[kH * kH + kH + 2 * kH]; C.b3m = tail[kH * kH + kH + 2 * kH + 1];
+  const float* __restrict__ w1raw = tail + (kH * kH + kH + 2 * kH + 2 + 2);  // W1[28][32], not normalized
+  if (FIN && threadIdx.x >= 192 && threadIdx.x < 192 + kH) {   // the bias with the time features, the same for every tensor
+    const int u = threadIdx.x - 192;
+    float b = 0.f;
+    if (u < A.H) {
+      b = mlp[LOPT_D_SMALL_FC * A.H + u];
+#pragma unroll
+      for (int i = 0; i < LOPT_N_TIME; ++i) b += feats.v[i] * mlp[(kNF + i) * A.H + u];
+    }
+    L.b1[u] = b;
+  }
   // ---- weights of this lane, split and packed in the order the accumulator layout asks for
   {
-    const float* __restrict__ w1raw = tail + (kH * kH + kH + 2 * kH + 2 + 2);  // W1[28][32], not normalized
     unsigned ph[4], pl[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -353,10 +368,11 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   // this chain of latencies (toy list of three tensors 13.7 -> 12.1 us, 1000x1000 29.0 -> 27.1 us with the equal tiles of the planner).
   const int su = threadIdx.x & 31, srow = threadIdx.x >> 5;
   float wr = 0.f, wc = 0.f, bb = 0.f;
+  const float* __restrict__ first = FIN ? w1raw : prep;
   if (srow < 6) {
-    wr = prep[row_feat(srow) * kH + su];
-    wc = prep[col_feat(srow) * kH + su];
-  } else if (srow == 6) bb = prep[kNF * kH + su];
+    wr = first[row_feat(srow) * kH + su];
+    wc = first[col_feat(srow) * kH + su];
+  } else if (!FIN && srow == 6) bb = prep[kNF * kH + su];
   float cf[6];
   const int colx = col_ok ? col : n - 1;
 #pragma unroll
@@ -374,17 +390,27 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
       rrow[i][3 + k] = ws[T.oRR + (size_t)k * T.padm + row];
     }
   }
+  const float* scale = ws + T.oScale;
+  if constexpr (FIN) {
+    finalize_scales(T, ws, A, fin, r0 == 0 && at.c0 == 0);
+    scale = fin.scale;
+    if (srow < 6) {
+      wr *= scale[row_feat(srow)];
+      wc *= scale[col_feat(srow)];
+    }
+  }
 #pragma unroll
-  for (int i = 0; i < 10; ++i) C.sc[i] = ws[T.oScale + i];
+  for (int i = 0; i < 10; ++i)   // wave-uniform
+    C.sc[i] = FIN ? __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale[i]))) : scale[i];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    C.fg[k] = cf[3 + k] * ws[T.oScale + 10 + k];
-    C.fm[k] = cf[3 + k] * ws[T.oScale + 25 + k];
+    C.fg[k] = cf[3 + k] * scale[10 + k];
+    C.fm[k] = cf[3 + k] * scale[25 + k];
   }
   if (srow < 6) {
     L.w1row[srow][su] = wr;
     L.w1col[srow][su] = wc;
-  } else if (srow == 6) L.b1[su] = bb;
+  } else if (!FIN && srow == 6) L.b1[su] = bb;
   __syncthreads();   // w1row, w1col, b1
   // ---- column part of layer 1's C operand for this lane's column: units unit_of(v, half), v = 0..15
 #pragma unroll
@@ -617,22 +643,26 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   }   // tile loop
 }
 
-// L.apply_counter must be zero when the kernel starts (k_finalize of the same sub-list clears it).
+// L.apply_counter must be zero when the kernel starts (k_finalize of the same sub-list clears it, or k_rowcol_short).
 // update_state: the statistics pass left M_1..3 and V as they were (launch_accum_stats with write_state = false) and this
 // pass moves them.
-void launch_apply_f16s(const Launch& L, const StepArgs& A, const WeightsDev& W, bool update_state, hipStream_t s) {
+void launch_apply_f16s(const Launch& L, const StepArgs& A, const WeightsDev& W, const TimeFeats* feats, bool update_state,
+                       hipStream_t s) {
   if (L.n_atiles == 0) return;
   const int grid = L.n_atiles < L.resident_wgs ? L.n_atiles : L.resident_wgs;
   // v_rsq_f32 treats inputs below the smallest normal float as zero; with eps_acc that small the kernel
   // takes the library reciprocal square root (which rescales such inputs) instead of the bare instruction
   const bool raw = A.eps_acc >= 1e-30f;
-#define LOPT_LAUNCH_F16S(R, U)                                                                                  \
-  hipLaunchKernelGGL((k_apply_f16s<R, U>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,       \
-                     L.apply_counter, L.ws, A, W.mlp_tail)
-  if (raw && update_state) LOPT_LAUNCH_F16S(true, true);
-  else if (raw) LOPT_LAUNCH_F16S(true, false);
-  else if (update_state) LOPT_LAUNCH_F16S(false, true);
-  else LOPT_LAUNCH_F16S(false, false);
+  const TimeFeats none{};
+#define LOPT_LAUNCH_F16S(R, U, F)                                                                               \
+  hipLaunchKernelGGL((k_apply_f16s<R, U, F>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,    \
+                     L.apply_counter, L.ws, A, W.mlp_tail, W.mlp, feats ? *feats : none)
+#define LOPT_LAUNCH_F16S2(R, U) do { if (feats) LOPT_LAUNCH_F16S(R, U, true); else LOPT_LAUNCH_F16S(R, U, false); } while (0)
+  if (raw && update_state) LOPT_LAUNCH_F16S2(true, true);
+  else if (raw) LOPT_LAUNCH_F16S2(true, false);
+  else if (update_state) LOPT_LAUNCH_F16S2(false, true);
+  else LOPT_LAUNCH_F16S2(false, false);
+#undef LOPT_LAUNCH_F16S2
 #undef LOPT_LAUNCH_F16S
 }
 

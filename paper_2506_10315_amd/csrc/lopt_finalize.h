@@ -1,0 +1,112 @@
+// Second stage of the per-tensor reductions: the sums of the statistics pass's partials and what follows from them. One
+// workgroup of k_finalize per tensor, or every workgroup of the strip apply kernel for its own tensor (short lists).
+#pragma once
+
+#include "lopt_device.h"
+#include "lopt_internal.h"
+
+namespace lopt {
+
+// Adds part[0], part[stride], ... (count terms, 1..B) in double, in index order, term k to acc[k % NS]: B loads issue ahead of
+// the adds, those past the end repeat the last term and are dropped.
+template <int B, int NS>
+__device__ __forceinline__ void sum_batch(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
+  float t[B];
+#pragma unroll
+  for (int k = 0; k < B; ++k) t[k] = part[(size_t)min(k, count - 1) * stride];
+#pragma unroll
+  for (int k = 0; k < B; ++k) acc[k % NS] += k < count ? (double)t[k] : 0.0;
+}
+
+// Sums of part[0], part[stride], ... (count terms) in double, always in index order, as NS interleaved sums. Bound by load
+// latency: full batches of 32 loads, then one batch of the power of two that holds the rest.
+template <int NS>
+__device__ __forceinline__ void strided_sums(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
+  static_assert(NS == 1 || NS == 4, "every batch holds whole rounds of the NS sums");
+#pragma unroll
+  for (int k = 0; k < NS; ++k) acc[k] = 0.0;
+  for (; count > 32; count -= 32, part += 32 * stride) sum_batch<32>(part, 32, stride, acc);
+  if (count > 16) sum_batch<32>(part, count, stride, acc);
+  else if (count > 8) sum_batch<16>(part, count, stride, acc);
+  else if (count > 4) sum_batch<8>(part, count, stride, acc);
+  else if (count > 1) sum_batch<4>(part, count, stride, acc);
+  else if (count == 1) acc[0] += (double)part[0];
+}
+
+__device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
+  double acc[1];
+  strided_sums(part, count, stride, acc);
+  return acc[0];
+}
+
+// Reduces every partial of a tensor in a fixed order (double accumulation) to s_f and the per-feature scale factors. The 32 sums
+// (17 statistics over the tiles, 9 over the row blocks, 6 over the column blocks) are one column of threads each, cut into 32
+// interleaved segments: this is a chain of load latencies, and this way it is one batch of loads for up to 1024 tiles
+// (k_finalize, 1000x1000: 7.9 -> 4.8 us from eight segments and three such phases; six tensors of 0.3 M elements 5.2 -> 4.9 us).
+// A workgroup of 256 threads forms four segments per thread: the order of summation does not depend on the launch.
+constexpr int kFinSegs = 32;
+constexpr int kFinPerThread = kFinSegs / (kBlock / 32);
+static_assert(kFinPerThread == 4, "a narrow workgroup takes four segments per thread");
+struct FinLds {
+  double part[kFinSegs][32], tot[32];
+  float stats[32], scale[32];
+};
+
+// Called by all threads (1024 or 256). L.stats and L.scale are ready for all of them afterwards; store: to the workspace too.
+__device__ __forceinline__ void finalize_scales(const TensorDev& T, float* __restrict__ ws, const StepArgs& A, FinLds& L, bool store) {
+  const int q = threadIdx.x & 31, seg = threadIdx.x >> 5, n_seg = blockDim.x >> 5;
+  // tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25 sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps)
+  {
+    const float* base;
+    int count, stride;
+    if (q < kNStat) { base = ws + T.oStatPart + q; count = T.nrt * T.nct; stride = kStatStride; }
+    else if (q < 26) { base = ws + T.oRcPart + (q - kNStat); count = T.nrblk; stride = kRcStride; }
+    else { base = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3); count = T.ncblk; stride = kRcStride; }
+    // thread (seg, q): terms seg, seg + n_seg, ..., which are those of the segments seg, seg + n_seg, ... < 32 in turn
+    const int mine = seg < count ? (count - seg + n_seg - 1) / n_seg : 0;
+    base += (size_t)seg * stride;
+    if (n_seg == kFinSegs) {
+      L.part[seg][q] = strided_sum(base, mine, (size_t)kFinSegs * stride);
+    } else {
+      double a[kFinPerThread];
+      strided_sums(base, mine, (size_t)n_seg * stride, a);
+#pragma unroll
+      for (int k = 0; k < kFinPerThread; ++k) L.part[seg + n_seg * k][q] = a[k];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    double s = 0.0;
+    for (int k = 0; k < kFinSegs; ++k) s += L.part[k][q];
+    L.tot[q] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < 32) {
+    const int f = threadIdx.x;
+    const double N = (double)T.m * (double)T.n;
+    double s = 0.0;
+    double pre = 1.0;  // factor between the raw feature the kernels build and the feature itself
+    if (f < 10) s = L.tot[f] / N;
+    else if (f < 13 || (f >= 25 && f < 28)) {
+      const int k = f < 13 ? f - 10 : f - 25;
+      const double rbar = L.tot[17 + k] / (double)T.m + (double)A.eps_acc;
+      s = L.tot[f < 13 ? f : f - 12] / N * rbar;
+      pre = sqrt(rbar);
+    } else if (f < 16) s = L.tot[20 + (f - 13)] / (double)T.m;
+    else if (f < 19) s = L.tot[26 + (f - 16)] / (double)T.n;
+    else if (f < 22) s = L.tot[23 + (f - 19)] / (double)T.m;
+    else if (f < 25) s = L.tot[29 + (f - 22)] / (double)T.n;
+    else if (f == 28) s = L.tot[16] / N;
+    const float sf = (float)s;
+    const float scale = (float)(pre / sqrt((double)sf + (double)A.eps_norm));
+    L.stats[f] = sf;
+    L.scale[f] = f < A.F ? scale : 0.f;
+    if (store) {
+      ws[T.oStats + f] = f < A.F ? sf : 0.f;
+      ws[T.oScale + f] = f < A.F ? scale : 0.f;
+    }
+  }
+  __syncthreads();
+}
+
+}  // namespace lopt

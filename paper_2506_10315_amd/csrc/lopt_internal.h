@@ -21,6 +21,7 @@ constexpr int kRcStride = 12;     // floats per block in the row/column partials
 constexpr int kNStat = 17;        // per-element statistics accumulated per tile
 constexpr int kStatsPerTensor = 32;
 constexpr int kLstmInPad = 48;    // LOPT_VELO_LSTM_IN rounded up to a multiple of 4
+constexpr int kMaxGroups = 16;    // tensor groups of the two-stream pipeline, tile counters in the workspace
 constexpr int kMixSlices = 64;    // at most this many slices of the tensor list in the cross-tensor mean
 // Tensor lists up to this length form the LSTM's recurrent product ahead, beside the row/column sums. us, row/column sums + LSTM,
 // in one launch / ahead: one tensor 4.4 + 9.7 / 5.4 + 4.1, 66 tensors 4.4 + 10.7 / 9.2 + 4.2, 152 tensors 58 + 14 / 66 + 5.5, 502
@@ -82,6 +83,9 @@ struct StepArgs {
   int n_tensors;
   float loss;                 // VeLO: loss value that goes with this step's gradients
 };
+
+// Time features tanh(step / x), for the kernel that takes them from the host (k_finalize forms its own).
+struct TimeFeats { float v[LOPT_N_TIME]; };
 
 // Device weights of the optimizer, owned by the context.
 struct WeightsDev {
@@ -152,6 +156,7 @@ bool apply_fc4x_available(const StepArgs&);
 void launch_apply_fc4x(const Launch&, const StepArgs&, const WeightsDev&, bool update_state, hipStream_t);
 bool apply_velo4_available(const StepArgs&);
 void launch_apply_velo4(const Launch&, const StepArgs&, bool update_state, hipStream_t);
-void launch_apply_f16s(const Launch&, const StepArgs&, const WeightsDev&, bool update_state, hipStream_t);
+// feats not null: no k_finalize has run, every workgroup forms its tensor's scales and first layer (Plan::fold_finalize)
+void launch_apply_f16s(const Launch&, const StepArgs&, const WeightsDev&, const TimeFeats* feats, bool update_state, hipStream_t);
 
 }  // namespace lopt

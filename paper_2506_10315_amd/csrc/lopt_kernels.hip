@@ -23,6 +23,7 @@
 
 #include "lopt_internal.h"
 #include "lopt_device.h"
+#include "lopt_finalize.h"
 
 namespace lopt {
 
@@ -45,40 +46,6 @@ void launch_fill_zero(const Launch& L, const StepArgs& A, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_zero, dim3(64, nt), dim3(kBlock), 0, s, L.tensors + t0,
                        A.kind == LOPT_VELO ? 2 : 0);
   }
-}
-
-// ----------------------------------------------------------------------------- sums of partials
-
-// Adds part[0], part[stride], ... (count terms, 1..B) in double, in index order, term k to acc[k % NS]: B loads issue ahead of
-// the adds, those past the end repeat the last term and are dropped.
-template <int B, int NS>
-__device__ __forceinline__ void sum_batch(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
-  float t[B];
-#pragma unroll
-  for (int k = 0; k < B; ++k) t[k] = part[(size_t)min(k, count - 1) * stride];
-#pragma unroll
-  for (int k = 0; k < B; ++k) acc[k % NS] += k < count ? (double)t[k] : 0.0;
-}
-
-// Sums of part[0], part[stride], ... (count terms) in double, always in index order, as NS interleaved sums. Bound by load
-// latency: full batches of 32 loads, then one batch of the power of two that holds the rest.
-template <int NS>
-__device__ __forceinline__ void strided_sums(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
-  static_assert(NS == 1 || NS == 4, "every batch holds whole rounds of the NS sums");
-#pragma unroll
-  for (int k = 0; k < NS; ++k) acc[k] = 0.0;
-  for (; count > 32; count -= 32, part += 32 * stride) sum_batch<32>(part, 32, stride, acc);
-  if (count > 16) sum_batch<32>(part, count, stride, acc);
-  else if (count > 8) sum_batch<16>(part, count, stride, acc);
-  else if (count > 4) sum_batch<8>(part, count, stride, acc);
-  else if (count > 1) sum_batch<4>(part, count, stride, acc);
-  else if (count == 1) acc[0] += (double)part[0];
-}
-
-__device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
-  double acc[1];
-  strided_sums(part, count, stride, acc);
-  return acc[0];
 }
 
 // ----------------------------------------------------------------------------- VeLO cross-tensor term
@@ -392,7 +359,8 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
 
 __global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const TensorDev* __restrict__ tensors,
                                                                       const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                                      int n_tiles, MixArgs M, int n_recur) {
+                                                                      int n_tiles, MixArgs M, int n_recur, int* __restrict__ counters) {
+  if (blockIdx.x == 0 && threadIdx.x < kMaxGroups) counters[threadIdx.x] = 0;   // k_finalize does it on other lists
   __shared__ union { float col[kShortWaves][kTileCols], hbar[4][kWave], z[kShortWaves][kRecurTensors][32]; } red;
   const int blk = (int)blockIdx.x - n_recur;
   if (blk < 0) {
@@ -416,7 +384,7 @@ void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W
   const MixArgs M = make_mix(L, A, W, hbar_part, b_eff, lstm_z);
   const int n_recur = recur_blocks(M);
   hipLaunchKernelGGL(k_rowcol_short, dim3(n_recur + L.n_rctiles + mix_hbar_blocks(M)), dim3(kWave * kShortWaves), 0, s, L.tensors,
-                     L.rctiles, L.ws, L.n_rctiles, M, n_recur);
+                     L.rctiles, L.ws, L.n_rctiles, M, n_recur, L.apply_counter);
 }
 
 // ----------------------------------------------------------------------------- rc_update
@@ -891,21 +859,13 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
 
 // ----------------------------------------------------------------------------- finalize
 
-// One workgroup per tensor. Reduces every partial in a fixed order (double accumulation),
-// then writes s_f, the per-feature scale factors and the prepared first layer. The 32 sums (17 statistics over the tiles,
-// 9 over the row blocks, 6 over the column blocks) are one column of threads each, cut into 32 interleaved
-// segments: the kernel is a chain of load latencies, and this way it is one batch of loads for up to 1024 tiles
-// (1000x1000: 7.9 -> 4.8 us from eight segments and three such phases; six tensors of 0.3 M elements 5.2 -> 4.9 us).
-// A workgroup of 256 threads forms four segments per thread: the order of summation does not depend on the launch.
-constexpr int kFinSegs = 32;
-constexpr int kFinPerThread = kFinSegs / (kBlock / 32);
-static_assert(kFinPerThread == 4, "a narrow workgroup takes four segments per thread");
+// One workgroup per tensor: s_f and the per-feature scale factors (finalize_scales), then the prepared first layer or the LSTM's
+// input. (Lists whose apply launch forms the scales itself do without: Plan::fold_finalize.)
 __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                      StepArgs A, WeightsDev W, float* __restrict__ lstm_u, int tensor0,
                                                      int* __restrict__ apply_counter) {
-  __shared__ double part[kFinSegs][32];
-  __shared__ double tot[32];
-  __shared__ float s_stats[32], s_scale[32], s_tfeat[LOPT_N_TIME], s_lfeat[LOPT_N_LOSS];
+  __shared__ FinLds L;
+  __shared__ float s_tfeat[LOPT_N_TIME], s_lfeat[LOPT_N_LOSS];
   const int ti = tensor0 + (int)blockIdx.x;
   const TensorDev& T = tensors[ti];
   if (blockIdx.x == 0 && threadIdx.x == 0) *apply_counter = 0;   // the apply pass of this sub-list starts at its first tile
@@ -921,57 +881,7 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
     const double psi = copysign(log1p(fabs(l)), l);
     s_lfeat[threadIdx.x - 96] = (float)tanh(psi / xs[threadIdx.x - 96]);
   }
-  const int q = threadIdx.x & 31, seg = threadIdx.x >> 5, n_seg = blockDim.x >> 5;
-  // tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25 sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps)
-  {
-    const float* base;
-    int count, stride;
-    if (q < kNStat) { base = ws + T.oStatPart + q; count = T.nrt * T.nct; stride = kStatStride; }
-    else if (q < 26) { base = ws + T.oRcPart + (q - kNStat); count = T.nrblk; stride = kRcStride; }
-    else { base = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3); count = T.ncblk; stride = kRcStride; }
-    // thread (seg, q): terms seg, seg + n_seg, ..., which are those of the segments seg, seg + n_seg, ... < 32 in turn
-    const int mine = seg < count ? (count - seg + n_seg - 1) / n_seg : 0;
-    base += (size_t)seg * stride;
-    if (n_seg == kFinSegs) {
-      part[seg][q] = strided_sum(base, mine, (size_t)kFinSegs * stride);
-    } else {
-      double a[kFinPerThread];
-      strided_sums(base, mine, (size_t)n_seg * stride, a);
-#pragma unroll
-      for (int k = 0; k < kFinPerThread; ++k) part[seg + n_seg * k][q] = a[k];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    double s = 0.0;
-    for (int k = 0; k < kFinSegs; ++k) s += part[k][q];
-    tot[q] = s;
-  }
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    const int f = threadIdx.x;
-    const double N = (double)T.m * (double)T.n;
-    double s = 0.0;
-    double pre = 1.0;  // factor between the raw feature the kernels build and the feature itself
-    if (f < 10) s = tot[f] / N;
-    else if (f < 13 || (f >= 25 && f < 28)) {
-      const int k = f < 13 ? f - 10 : f - 25;
-      const double rbar = tot[17 + k] / (double)T.m + (double)A.eps_acc;
-      s = tot[f < 13 ? f : f - 12] / N * rbar;
-      pre = sqrt(rbar);
-    } else if (f < 16) s = tot[20 + (f - 13)] / (double)T.m;
-    else if (f < 19) s = tot[26 + (f - 16)] / (double)T.n;
-    else if (f < 22) s = tot[23 + (f - 19)] / (double)T.m;
-    else if (f < 25) s = tot[29 + (f - 22)] / (double)T.n;
-    else if (f == 28) s = tot[16] / N;
-    const float sf = (float)s;
-    const float scale = (float)(pre / sqrt((double)sf + (double)A.eps_norm));
-    s_stats[f] = sf;
-    s_scale[f] = f < A.F ? scale : 0.f;
-    ws[T.oStats + f] = f < A.F ? sf : 0.f;
-    ws[T.oScale + f] = f < A.F ? scale : 0.f;
-  }
-  __syncthreads();
+  finalize_scales(T, ws, A, L, true);
   if (A.kind == LOPT_SMALL_FC) {
     // first layer with the normalization folded in, hidden width padded with zeros to HP;
     // the un-normalized time features only shift the bias.
@@ -979,7 +889,7 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
     float* prep = ws + T.oPrep;
     for (int i = threadIdx.x; i < LOPT_N_ELEM_FEATS * HP; i += (int)blockDim.x) {
       const int f = i / HP, u = i - f * HP;
-      prep[i] = u < H ? W.mlp[f * H + u] * s_scale[f] : 0.f;
+      prep[i] = u < H ? W.mlp[f * H + u] * L.scale[f] : 0.f;
     }
     for (int u = threadIdx.x; u < HP; u += (int)blockDim.x) {
       float b = 0.f;
@@ -993,7 +903,7 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
     // LSTM input: 0.05*ln(s_f + 1e-30), time features, one-hot of min(ndim, 4), loss features
     float* u = lstm_u + (size_t)ti * kLstmInPad;
     const int t = threadIdx.x;
-    if (t < LOPT_D_VELO) u[t] = 0.05f * logf(s_stats[t] + 1e-30f);
+    if (t < LOPT_D_VELO) u[t] = 0.05f * logf(L.stats[t] + 1e-30f);
     else if (t < LOPT_D_VELO + LOPT_N_TIME) u[t] = s_tfeat[t - LOPT_D_VELO];
     else if (t < LOPT_D_VELO + LOPT_N_TIME + 5) {
       const int nd = T.ndim < 4u ? (int)T.ndim : 4;

@@ -7,7 +7,6 @@
 
 namespace lopt {
 
-constexpr int kMaxGroups = 16;
 constexpr uint64_t kShortListFloats = 48u << 20;   // partial sums a short list's statistics pass reads, all workgroups together
 
 inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
@@ -37,6 +36,7 @@ struct Plan {
   bool short_list = false;
   int keep = 0, keep_off = 0;         // see choose_loads
   bool backwards = false;
+  bool fold_finalize = false;         // strip kernel: its workgroups form their tensor's scales, k_finalize is not launched
   std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
@@ -274,6 +274,16 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     }
     pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
   }
+  // A launch fewer where every workgroup has one tile and all of them together read at most 64 MB of partials for it. us a step
+  // without and with: toy list of three tensors 26.7 / 22.9, 1000x1000 (22 MB) 42.0 / 39.8, 1200x1200 (35 MB) 50.9 / 48.3, 1400x1400 (two rounds of
+  // tiles, 70 MB) 61.1 / 60.2, seven layers of 700x700 (several rounds, 46 MB) 86.6 / 93.3, 1700x1700 87.4 / 107.5.
+  uint64_t again = 0;
+  for (size_t i = 0; i < n && pl->short_list && o.apply == ApplyTiles::Strip; ++i) {
+    const TensorDev& T = pl->tensors[i];
+    const uint64_t at = (i + 1 < n ? pl->atile0[i + 1] : pl->atiles.size()) - pl->atile0[i];
+    again += at * ((uint64_t)T.nrt * T.nct * kStatStride + (uint64_t)(T.nrblk + T.ncblk) * kRcStride);
+  }
+  pl->fold_finalize = pl->short_list && o.apply == ApplyTiles::Strip && pl->atiles.size() <= 2u * (unsigned)o.n_cu && again <= (16u << 20);
   // h W_h depends on nothing this step computes. Up to kLstmAheadMax tensors it is formed beside the statistics; longer lists and
   // workspaces that come near the fixed scratch of lopt_step_static go without the room for it
   pl->oLstmZ = 0;

@@ -79,6 +79,22 @@ def test_strip_tiles_of_every_number_of_row_pairs(state_pass):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("hidden", [32, 19])
+@pytest.mark.parametrize("shapes", [[(300, 300), (7, 130), (1, 40)], [(100, 300)] * 44])
+def test_strip_workgroups_that_form_their_tensors_scales(shapes, hidden):
+    # up to one round of 512 apply tiles the strip kernel forms the scales and the first layer from the partials itself; the second
+    # list has more and takes the launch in between. Also a width that is padded to 32; s_f as the workspace holds it is compared too.
+    # Tensors of at most 90 000 elements: in the first steps 1 / sqrt(V) of an element of small gradient is a feature of up to sqrt(N),
+    # and the fp16 pairs round its products by 2^-22 each way, 2^-21 sqrt(N) = 4.8e-4 of the rms update at a million elements (seed 27 on
+    # 1000 x 1000: 1.008e-4, the same bits whichever launch forms the scales), 1.4e-4 in the worst case here, over the bar of 1e-4
+    # only where sqrt(N) is reached and nothing else adds to the update.
+    cfg = Hn.make_cfg("small_fc_lopt", hidden=hidden)
+    w = Hn.random_weights(cfg, seed=28)
+    assert (plan(shapes)["n_atiles"] <= 512) == (len(shapes) == 3)
+    worst = Hn.run_free(Hn.Case(128, _specs(shapes), "gauss_logscale"), cfg, w, 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
 @pytest.mark.parametrize("rows", [6144, 6145])
 @pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("small_fc_lopt", "stats"), ("velo", "apply")])
 def test_row_and_column_means_at_the_limit_of_a_short_list(kind, state_pass, rows):
