@@ -275,10 +275,13 @@ lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   return LOPT_OK;
 }
 
-TimeFeats make_time_feats(int64_t step) {
-  static const double x[LOPT_N_TIME] = {1, 3, 10, 30, 100, 300, 1000, 3000, 1e4, 3e4, 1e5};
-  TimeFeats f;
-  for (int i = 0; i < LOPT_N_TIME; ++i) f.v[i] = (float)std::tanh((double)step / x[i]);
+StepFeats make_feats(int64_t step, float loss) {
+  static const double xt[LOPT_N_TIME] = {1, 3, 10, 30, 100, 300, 1000, 3000, 1e4, 3e4, 1e5};
+  static const double xl[LOPT_N_LOSS] = {1, 3, 10};
+  StepFeats f;
+  const double l = (double)loss, psi = std::copysign(std::log1p(std::fabs(l)), l);
+  for (int i = 0; i < LOPT_N_TIME; ++i) f.time[i] = (float)std::tanh((double)step / xt[i]);
+  for (int i = 0; i < LOPT_N_LOSS; ++i) f.loss[i] = (float)std::tanh(psi / xl[i]);
   return f;
 }
 
@@ -648,9 +651,9 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool velo4_ok = ctx->cfg.kind == LOPT_VELO && ctx->apply_variant != LOPT_APPLY_VALU && apply_velo4_available(A);
   const bool fc4x_ok = rows_ok && ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
   const bool state_in_apply = (strip_ok || fc4x_ok || velo4_ok) && ctx->state_in_apply;
-  const bool fold = strip_ok && pl.fold_finalize;
-  TimeFeats feats{};
-  if (fold) feats = make_time_feats(step);
+  const bool fold = (strip_ok || ctx->cfg.kind == LOPT_VELO) && pl.fold_finalize;
+  StepFeats feats{};
+  if (fold) feats = make_feats(step, ctx->loss);
   auto launch_apply = [&](const Launch& La) {
     if (strip_ok) launch_apply_f16s(La, A, ctx->W, fold ? &feats : nullptr, state_in_apply, stream);
     else if (mfma_ok && ctx->apply_variant != LOPT_APPLY_VALU) launch_apply_mfma(La, A, ctx->W, stream);
@@ -709,7 +712,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
       launch_accum_stats(S, A, ctx->W, !state_in_apply, S.tensor0 == 0, ws + pl.oHbarPart, ws + pl.oBeff, s);
       if (!fold) launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
       if (velo) {
-        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, s);
+        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, fold ? &feats : nullptr, ws + pl.oHNew, s);
         launch_velo_head(S, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
                          pl.head_batched ? ws + pl.oTheta : nullptr, s);
       }
@@ -764,7 +767,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   if (!fold) launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
   MARK(4);
   if (ctx->cfg.kind == LOPT_VELO) {
-    launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, ws + pl.oHNew, stream);
+    launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, fold ? &feats : nullptr, ws + pl.oHNew, stream);
     MARK(5);
     launch_velo_head(L, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
                      pl.head_batched ? ws + pl.oTheta : nullptr, stream);

@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
                                                           const ApplyTileDev* __restrict__ atiles, int n_atiles,
                                                           int* __restrict__ next_tile, float* __restrict__ ws,
                                                           StepArgs A, const float* __restrict__ tail,
-                                                          const float* __restrict__ mlp, TimeFeats feats) {
+                                                          const float* __restrict__ mlp, StepFeats feats) {
   __shared__ StripLds L;
   __shared__ std::conditional_t<FIN, FinLds, int> fin;
   __shared__ int s_tile;
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
     if (u < A.H) {
       b = mlp[LOPT_D_SMALL_FC * A.H + u];
 #pragma unroll
-      for (int i = 0; i < LOPT_N_TIME; ++i) b += feats.v[i] * mlp[(kNF + i) * A.H + u];
+      for (int i = 0; i < LOPT_N_TIME; ++i) b += feats.time[i] * mlp[(kNF + i) * A.H + u];
     }
     L.b1[u] = b;
   }
@@ -646,14 +646,14 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
 // L.apply_counter must be zero when the kernel starts (k_finalize of the same sub-list clears it, or k_rowcol_short).
 // update_state: the statistics pass left M_1..3 and V as they were (launch_accum_stats with write_state = false) and this
 // pass moves them.
-void launch_apply_f16s(const Launch& L, const StepArgs& A, const WeightsDev& W, const TimeFeats* feats, bool update_state,
+void launch_apply_f16s(const Launch& L, const StepArgs& A, const WeightsDev& W, const StepFeats* feats, bool update_state,
                        hipStream_t s) {
   if (L.n_atiles == 0) return;
   const int grid = L.n_atiles < L.resident_wgs ? L.n_atiles : L.resident_wgs;
   // v_rsq_f32 treats inputs below the smallest normal float as zero; with eps_acc that small the kernel
   // takes the library reciprocal square root (which rescales such inputs) instead of the bare instruction
   const bool raw = A.eps_acc >= 1e-30f;
-  const TimeFeats none{};
+  const StepFeats none{};
 #define LOPT_LAUNCH_F16S(R, U, F)                                                                               \
   hipLaunchKernelGGL((k_apply_f16s<R, U, F>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,    \
                      L.apply_counter, L.ws, A, W.mlp_tail, W.mlp, feats ? *feats : none)

@@ -22,7 +22,7 @@ __device__ __forceinline__ void sum_batch(const float* __restrict__ part, int co
 // latency: full batches of 32 loads, then one batch of the power of two that holds the rest.
 template <int NS>
 __device__ __forceinline__ void strided_sums(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
-  static_assert(NS == 1 || NS == 4, "every batch holds whole rounds of the NS sums");
+  static_assert(NS <= 32 && 32 % NS == 0, "every full batch holds whole rounds of the NS sums");
 #pragma unroll
   for (int k = 0; k < NS; ++k) acc[k] = 0.0;
   for (; count > 32; count -= 32, part += 32 * stride) sum_batch<32>(part, 32, stride, acc);
@@ -52,16 +52,41 @@ struct FinLds {
   float stats[32], scale[32];
 };
 
+// s_f and scale of feature f < 32 from the tensor's 32 sums. tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25
+// sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps).
+__device__ __forceinline__ void feature_scale(const TensorDev& T, const StepArgs& A, const double* tot, int f, float& sf, float& scale) {
+  const double N = (double)T.m * (double)T.n;
+  double s = 0.0;
+  double pre = 1.0;  // factor between the raw feature the kernels build and the feature itself
+  if (f < 10) s = tot[f] / N;
+  else if (f < 13 || (f >= 25 && f < 28)) {
+    const int k = f < 13 ? f - 10 : f - 25;
+    const double rbar = tot[17 + k] / (double)T.m + (double)A.eps_acc;
+    s = tot[f < 13 ? f : f - 12] / N * rbar;
+    pre = sqrt(rbar);
+  } else if (f < 16) s = tot[20 + (f - 13)] / (double)T.m;
+  else if (f < 19) s = tot[26 + (f - 16)] / (double)T.n;
+  else if (f < 22) s = tot[23 + (f - 19)] / (double)T.m;
+  else if (f < 25) s = tot[29 + (f - 22)] / (double)T.n;
+  else if (f == 28) s = tot[16] / N;
+  sf = (float)s;
+  scale = (float)(pre / sqrt((double)sf + (double)A.eps_norm));
+}
+
+// Where sum q of a tensor finds its terms.
+struct FinTerms { const float* base; int count, stride; };
+__device__ __forceinline__ FinTerms fin_terms(const TensorDev& T, const float* ws, int q) {
+  if (q < kNStat) return FinTerms{ws + T.oStatPart + q, T.nrt * T.nct, kStatStride};
+  if (q < 26) return FinTerms{ws + T.oRcPart + (q - kNStat), T.nrblk, kRcStride};
+  return FinTerms{ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3), T.ncblk, kRcStride};
+}
+
 // Called by all threads (1024 or 256). L.stats and L.scale are ready for all of them afterwards; store: to the workspace too.
 __device__ __forceinline__ void finalize_scales(const TensorDev& T, float* __restrict__ ws, const StepArgs& A, FinLds& L, bool store) {
   const int q = threadIdx.x & 31, seg = threadIdx.x >> 5, n_seg = blockDim.x >> 5;
-  // tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25 sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps)
   {
-    const float* base;
-    int count, stride;
-    if (q < kNStat) { base = ws + T.oStatPart + q; count = T.nrt * T.nct; stride = kStatStride; }
-    else if (q < 26) { base = ws + T.oRcPart + (q - kNStat); count = T.nrblk; stride = kRcStride; }
-    else { base = ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3); count = T.ncblk; stride = kRcStride; }
+    const auto [base0, count, stride] = fin_terms(T, ws, q);
+    const float* base = base0;
     // thread (seg, q): terms seg, seg + n_seg, ..., which are those of the segments seg, seg + n_seg, ... < 32 in turn
     const int mine = seg < count ? (count - seg + n_seg - 1) / n_seg : 0;
     base += (size_t)seg * stride;
@@ -83,22 +108,8 @@ __device__ __forceinline__ void finalize_scales(const TensorDev& T, float* __res
   __syncthreads();
   if (threadIdx.x < 32) {
     const int f = threadIdx.x;
-    const double N = (double)T.m * (double)T.n;
-    double s = 0.0;
-    double pre = 1.0;  // factor between the raw feature the kernels build and the feature itself
-    if (f < 10) s = L.tot[f] / N;
-    else if (f < 13 || (f >= 25 && f < 28)) {
-      const int k = f < 13 ? f - 10 : f - 25;
-      const double rbar = L.tot[17 + k] / (double)T.m + (double)A.eps_acc;
-      s = L.tot[f < 13 ? f : f - 12] / N * rbar;
-      pre = sqrt(rbar);
-    } else if (f < 16) s = L.tot[20 + (f - 13)] / (double)T.m;
-    else if (f < 19) s = L.tot[26 + (f - 16)] / (double)T.n;
-    else if (f < 22) s = L.tot[23 + (f - 19)] / (double)T.m;
-    else if (f < 25) s = L.tot[29 + (f - 22)] / (double)T.n;
-    else if (f == 28) s = L.tot[16] / N;
-    const float sf = (float)s;
-    const float scale = (float)(pre / sqrt((double)sf + (double)A.eps_norm));
+    float sf, scale;
+    feature_scale(T, A, L.tot, f, sf, scale);
     L.stats[f] = sf;
     L.scale[f] = f < A.F ? scale : 0.f;
     if (store) {

@@ -27,6 +27,7 @@ constexpr int kMixSlices = 64;    // at most this many slices of the tensor list
 // in one launch / ahead: one tensor 4.4 + 9.7 / 5.4 + 4.1, 66 tensors 4.4 + 10.7 / 9.2 + 4.2, 152 tensors 58 + 14 / 66 + 5.5, 502
 // tensors 25 + 26 / 68 + 7.
 constexpr int kLstmAheadMax = 96;
+constexpr int kFinTensorsMax = 8;    // tensor lists up to this length may form the LSTM's inputs in its own launch (Plan::fold_finalize)
 constexpr int kHeadSplitMax = 96;    // tensor lists up to this length cut the hypernetwork head's product into column blocks
 constexpr int kHeadBatchMin = 1024;  // tensor lists from this length on take the batched form of the hypernetwork head
 constexpr int kMixJSplit = 4;     // the LSTM units are cut into this many ranges when hbar Wg is formed
@@ -84,8 +85,8 @@ struct StepArgs {
   float loss;                 // VeLO: loss value that goes with this step's gradients
 };
 
-// Time features tanh(step / x), for the kernel that takes them from the host (k_finalize forms its own).
-struct TimeFeats { float v[LOPT_N_TIME]; };
+// Time features tanh(step / x) and VeLO's loss features, for the kernels that take them from the host (k_finalize forms its own).
+struct StepFeats { float time[LOPT_N_TIME], loss[LOPT_N_LOSS]; };
 
 // Device weights of the optimizer, owned by the context.
 struct WeightsDev {
@@ -143,9 +144,9 @@ void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool 
 void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
 // lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
 void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);
-// lstm_z: the recurrent product formed ahead (null: this launch forms it)
+// lstm_z: the recurrent product formed ahead (null: this launch forms it); feats not null: no k_finalize has run
 void launch_velo_lstm(const Launch&, const StepArgs&, const WeightsDev&, const float* lstm_u, const float* b_eff,
-                      const float* lstm_z, float* h_new, hipStream_t);
+                      const float* lstm_z, const StepFeats* feats, float* h_new, hipStream_t);
 void launch_velo_head(const Launch&, const StepArgs&, const WeightsDev&, const float* h_new, float* alpha,
                       float* theta, hipStream_t);
 void launch_apply_small_fc(const Launch&, const StepArgs&, const WeightsDev&, hipStream_t);
@@ -157,6 +158,6 @@ void launch_apply_fc4x(const Launch&, const StepArgs&, const WeightsDev&, bool u
 bool apply_velo4_available(const StepArgs&);
 void launch_apply_velo4(const Launch&, const StepArgs&, bool update_state, hipStream_t);
 // feats not null: no k_finalize has run, every workgroup forms its tensor's scales and first layer (Plan::fold_finalize)
-void launch_apply_f16s(const Launch&, const StepArgs&, const WeightsDev&, const TimeFeats* feats, bool update_state, hipStream_t);
+void launch_apply_f16s(const Launch&, const StepArgs&, const WeightsDev&, const StepFeats* feats, bool update_state, hipStream_t);
 
 }  // namespace lopt

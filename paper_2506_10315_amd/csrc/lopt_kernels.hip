@@ -1041,12 +1041,77 @@ __global__ void __launch_bounds__(64 * kLstmWaves) k_velo_lstm(const TensorDev* 
 
 // What is left of the step where the recurrent product was formed ahead (lstm_recur_block): the 48 inputs' product, two
 // octets each by three wavefronts, and the cell equations, one thread per (tensor, unit).
+// FIN: k_finalize has not run; every workgroup forms the inputs of the list's tensors (at most eight) from the partials first. Its
+// eight half wavefronts share the tensors, one, two, four or eight to a tensor; lane = sum. The segments and their order are
+// those of finalize_scales, whatever the number of tensors in the launch.
 constexpr int kTailWaves = 3;
 static_assert(kLstmInPad == 16 * kTailWaves, "two octets a wavefront");
+struct TailFin {
+  double part[4][kFinSegs][32], tot[kFinTensorsMax][32];
+  float u[kFinTensorsMax][kLstmInPad];
+};
+
+template <int NS>
+__device__ __forceinline__ void tail_sums(const FinTerms& t, int tn, int slot, TailFin& L) {
+  constexpr int HW = kFinSegs / NS;   // half wavefronts of this tensor: this one has segments slot, slot + HW, ...
+  const int q = threadIdx.x & 31;
+  double a[NS];
+  strided_sums(t.base + (size_t)slot * t.stride, slot < t.count ? (t.count - slot + HW - 1) / HW : 0, (size_t)HW * t.stride, a);
+  if (NS == kFinSegs) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) s += a[k];
+    L.tot[tn][q] = s;
+  } else {
+#pragma unroll
+    for (int k = 0; k < NS; ++k) L.part[tn][slot + HW * k][q] = a[k];
+  }
+}
+
+__device__ __forceinline__ void tail_inputs(const TensorDev* __restrict__ tensors, float* __restrict__ ws, const StepArgs& A,
+                                            const StepFeats& F, TailFin& L, bool store) {
+  const int nT = A.n_tensors, w = threadIdx.x >> 5, q = threadIdx.x & 31;
+  const int hw = nT <= 1 ? 8 : nT <= 2 ? 4 : nT <= 4 ? 2 : 1;
+  const int tn = w / hw, slot = w % hw;
+  if (tn < nT) {
+    const FinTerms t = fin_terms(tensors[tn], ws, q);
+    if (hw == 8) tail_sums<4>(t, tn, slot, L);
+    else if (hw == 4) tail_sums<8>(t, tn, slot, L);
+    else if (hw == 2) tail_sums<16>(t, tn, slot, L);
+    else tail_sums<32>(t, tn, slot, L);
+  }
+  __syncthreads();
+  if (w < nT) {
+    const TensorDev& T = tensors[w];
+    if (hw > 1) {
+      double s = 0.0;
+      for (int k = 0; k < kFinSegs; ++k) s += L.part[w][k][q];
+      L.tot[w][q] = s;
+    }
+    __builtin_amdgcn_wave_barrier();   // the tensor's 32 sums are this half wavefront's own
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    float sf, scale;
+    feature_scale(T, A, L.tot[w], q, sf, scale);
+    if (store) {
+      ws[T.oStats + q] = q < A.F ? sf : 0.f;
+      ws[T.oScale + q] = q < A.F ? scale : 0.f;
+    }
+    if (q < LOPT_D_VELO) L.u[w][q] = 0.05f * logf(sf + 1e-30f);
+    const int nd = T.ndim < 4u ? (int)T.ndim : 4;
+    if (q < LOPT_N_TIME) L.u[w][LOPT_D_VELO + q] = F.time[q];
+    if (q < 5) L.u[w][LOPT_D_VELO + LOPT_N_TIME + q] = q == nd ? 1.f : 0.f;
+    if (q < kLstmInPad - (LOPT_D_VELO + LOPT_N_TIME + 5)) L.u[w][LOPT_D_VELO + LOPT_N_TIME + 5 + q] = q < LOPT_N_LOSS ? F.loss[q] : 0.f;
+  }
+  __syncthreads();
+}
+
+template <bool FIN>
 __global__ void __launch_bounds__(kBlock) k_velo_lstm_tail(const TensorDev* __restrict__ tensors, StepArgs A, WeightsDev W,
                                                            const float* __restrict__ lstm_u, const float* __restrict__ b_eff,
-                                                           const float* __restrict__ z, float* __restrict__ h_new) {
+                                                           const float* __restrict__ z, float* __restrict__ h_new,
+                                                           float* __restrict__ ws, StepFeats F) {
   __shared__ float part[kTailWaves][32][32];   // [wavefront][tensor][column]
+  __shared__ std::conditional_t<FIN, TailFin, int> fin;
   const int HL = A.HL, G = 4 * HL;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int khalf = lane >> 5, l32 = lane & 31;
@@ -1066,8 +1131,11 @@ __global__ void __launch_bounds__(kBlock) k_velo_lstm_tail(const TensorDev* __re
       zr[g] = z[((size_t)(t0 + tt) * gridDim.y + blockIdx.y) * 32 + 8 * g + j];
     }
   }
+  if constexpr (FIN) tail_inputs(tensors, ws, A, F, fin, blockIdx.y == 0);
   if (wave < kTailWaves) {
-    const float* __restrict__ usrc = lstm_u + (size_t)min(t0 + l32, A.n_tensors - 1) * kLstmInPad;
+    const float* usrc = lstm_u;
+    if constexpr (FIN) usrc = fin.u[min(l32, A.n_tensors - 1)];
+    else usrc += (size_t)min(t0 + l32, A.n_tensors - 1) * kLstmInPad;
     const float* __restrict__ wcol = W.lstm + ((size_t)blockIdx.y * lstm_k_pad(HL) + 4 * khalf) * 32 + l32;
     f32x16_l acc;
 #pragma unroll
@@ -1106,7 +1174,7 @@ __global__ void __launch_bounds__(kBlock) k_velo_lstm_tail(const TensorDev* __re
 }
 
 void launch_velo_lstm(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* lstm_u, const float* b_eff,
-                      const float* lstm_z, float* h_new, hipStream_t s) {
+                      const float* lstm_z, const StepFeats* feats, float* h_new, hipStream_t s) {
   if (L.n_tensors == 0) return;
   dim3 grid((L.n_tensors + kLstmTensors - 1) / kLstmTensors, (A.HL + 7) / 8);
   // a sub-list starts at tensor L.tensor0: the kernel indexes tensors, inputs and outputs from there
@@ -1115,8 +1183,11 @@ void launch_velo_lstm(const Launch& L, const StepArgs& A, const WeightsDev& W, c
   const TensorDev* T0 = L.tensors + L.tensor0;
   const float* u0 = lstm_u + (size_t)L.tensor0 * kLstmInPad;
   float* h0 = h_new + (size_t)L.tensor0 * A.HL;
-  if (lstm_z)
-    hipLaunchKernelGGL(k_velo_lstm_tail, grid, dim3(kBlock), 0, s, T0, As, W, u0, b_eff, lstm_z + (size_t)L.tensor0 * grid.y * 32, h0);
+  const float* z0 = lstm_z ? lstm_z + (size_t)L.tensor0 * grid.y * 32 : nullptr;
+  if (lstm_z && feats)
+    hipLaunchKernelGGL((k_velo_lstm_tail<true>), grid, dim3(kBlock), 0, s, T0, As, W, u0, b_eff, z0, h0, L.ws, *feats);
+  else if (lstm_z)
+    hipLaunchKernelGGL((k_velo_lstm_tail<false>), grid, dim3(kBlock), 0, s, T0, As, W, u0, b_eff, z0, h0, L.ws, StepFeats{});
   else
     hipLaunchKernelGGL(k_velo_lstm, grid, dim3(64 * kLstmWaves), 0, s, T0, As, W, u0, b_eff, h0);
 }

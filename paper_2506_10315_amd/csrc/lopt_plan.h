@@ -13,6 +13,8 @@ inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
 inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }   // a up to 2^31 - 1: a + b - 1 does not fit an int
 
+constexpr uint64_t kFinBatch = 32;                // loads in flight per lane in the sums of the partials
+
 // The apply kernels that take their work from the table of apply tiles (the others walk the statistics tiles).
 enum class ApplyTiles { None, Strip, Narrow };   // k_apply_f16s; k_apply_fc4x
 
@@ -36,7 +38,8 @@ struct Plan {
   bool short_list = false;
   int keep = 0, keep_off = 0;         // see choose_loads
   bool backwards = false;
-  bool fold_finalize = false;         // strip kernel: its workgroups form their tensor's scales, k_finalize is not launched
+  bool fold_finalize = false;         // k_finalize is not launched: the strip kernel's workgroups form their tensor's scales, the
+                                      // LSTM's those of all (few) tensors
   std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
   std::vector<int> atile0;            // first apply tile of every tensor
   uint64_t total_elems = 0;
@@ -289,6 +292,14 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   pl->oLstmZ = 0;
   if (velo && n <= (size_t)kLstmAheadMax && off <= (48u << 20) / sizeof(float))
     pl->oLstmZ = take((uint64_t)n * 32 * ceil_div(o.lstm_hidden, 8));
+  // VeLO: every workgroup of the LSTM launch forms all tensors' scales and inputs, where that is at most two batches of loads for
+  // each of its eight half wavefronts, which share the tensors. us a step without and with: four tensors of 0.012 M elements (one batch)
+  // 31.2 / 29.2, 1000x1000 (two) 47.5 / 46.1, two of 900x900 (four) 50.7 / 50.7, six of 0.33 M (four) 33.7 / 34.2.
+  if (pl->oLstmZ && pl->short_list && n <= (size_t)kFinTensorsMax) {
+    const uint64_t share = n <= 1 ? 8 : n <= 2 ? 4 : n <= 4 ? 2 : 1;   // half wavefronts to a tensor
+    pl->fold_finalize = true;
+    for (const TensorDev& T : pl->tensors) pl->fold_finalize = pl->fold_finalize && (uint64_t)T.nrt * T.nct <= 2 * kFinBatch * share;
+  }
   pl->ws_floats = off;
   choose_loads(o, total, pl);
 }

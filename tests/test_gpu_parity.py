@@ -153,6 +153,19 @@ def test_velo_recurrent_product_ahead_and_head_in_column_blocks(hidden, lstm_hid
         assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("count", [1, 2, 3, 5, 8, 9])
+def test_velo_lstm_launch_that_forms_its_inputs(count):
+    # up to eight tensors share the LSTM launch's eight half wavefronts, eight, four, two or one to a tensor; nine take the launch in
+    # between. Second list: 63 and 65 statistics tiles in the largest tensor, one and two batches of a half wavefront (or, for a few
+    # tensors, one of several), and one tile more than two batches of one
+    cfg = Hn.make_cfg("velo", lstm_hidden=40, n_bank=64)
+    w = Hn.random_weights(cfg, seed=80 + count)
+    small = [(7, 13), (33, 20), (300,), (64, 256), (9, 300), (17, 17), (1, 40), (80, 3), (5, 60)]
+    for big in ((64, 256), (8 * 63, 40), (8 * 65, 40)):
+        worst = Hn.run_free(Hn.Case(129, _specs([big] + small[:count - 1]), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+        assert worst["param"] <= Hn.TOL_PARAM
+
+
 def _velo_weight_views(w, cfg):
     """The sections of a VeLO weight blob (include/lopt.h) as views of `w`."""
     HL, K, h = int(cfg.lstm_hidden), int(cfg.n_bank), int(cfg.hidden)
