@@ -53,17 +53,15 @@ struct TensorDev {
   int vec;                          // 0: rows are not 16-byte aligned, 1: they are (n % 4 == 0), 2: 128-byte aligned (n % 32 == 0)
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
   int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks (short lists: one per statistics tile row)
-  int nrc;                          // short lists: tiles of kShortRows rows in the row/column sums
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2
-  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [nrc][n])
-  uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc)
-  uint64_t oRC;                     // [3][padn]  rsqrt(c_k + eps_acc)
+  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [ceil(m / kShortRows)][n])
+  uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc); short lists: then r_k [3][padm] as the step found them
+  uint64_t oRC;                     // [3][padn]  rsqrt(c_k + eps_acc); short lists: then c_k [3][padn] as the step found them
   uint64_t oRcPart;                 // [nrblk + ncblk][kRcStride]
   uint64_t oStatPart;               // [nrt*nct][kStatStride]
   uint64_t oStats;                  // [kStatsPerTensor] s_f
   uint64_t oScale;                  // [kStatsPerTensor] factor applied to the raw feature
   uint64_t oPrep;                   // prepared first layer: W1s[F][HP] then b1'[HP]
-  uint64_t oROld, oCOld;            // short lists: r_k [3][padm] and c_k [3][padn] as the step found them
 };
 
 struct TileDev { int tensor, ti, tj, pad; };

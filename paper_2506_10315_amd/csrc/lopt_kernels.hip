@@ -15,9 +15,11 @@
 //   velo_lstm, velo_head : the per-tensor hypernetwork (VeLO only)
 //   apply        : rebuild features, MLP, exponentiated update (lopt_apply_mfma.hip has the
 //                  matrix-core variant for hidden width 32)
+// Short lists do without rc_update (k_rowcol_short leaves fewer partials, accum_stats finishes the means: fuse_means), the shortest
+// also without finalize (the apply or LSTM launch reduces its partials itself: lopt_finalize.h).
 // A tile is TR rows x 256 columns, and row indices are wave-uniform everywhere. Rows on the 16-byte grid: lane l holds the four
 // consecutive columns 4l..4l+3 as one float4 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply
-// passes of rows of a multiple of 4 KB in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
+// passes in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
 // a wavefront stays on one segment (the row/column sums: on all four in turn).
 #include <type_traits>
 
@@ -324,11 +326,11 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
   const int t = threadIdx.x;
   if (tile.tj == 0 && t < 3 * kShortRows) {
     const size_t at = (size_t)(t / kShortRows) * T.padm + r0 + t % kShortRows;
-    if (r0 + t % kShortRows < m) ws[T.oROld + at] = rst[at];
+    if (r0 + t % kShortRows < m) ws[T.oRR + 3 * (size_t)T.padm + at] = rst[at];
   }
   if (tile.ti == 0 && t >= kTileCols) {
     const int k = t / kTileCols - 1, c = c0 + t % kTileCols;
-    if (c < n) ws[T.oCOld + (size_t)k * T.padn + c] = rst[3 * (size_t)T.padm + (size_t)k * T.padn + c];
+    if (c < n) ws[T.oRC + (size_t)(3 + k) * T.padn + c] = rst[3 * (size_t)T.padm + (size_t)k * T.padn + c];
   }
   float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -542,13 +544,13 @@ __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& ti
 #pragma unroll
     for (int j = 0; j < 4; ++j) rp[j] = rowpart[(size_t)min(j, T.nct - 1) * m];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) ro[k] = ws[T.oROld + (size_t)k * T.padm + r];
+    for (int k = 0; k < 3; ++k) ro[k] = ws[T.oRR + (size_t)(3 + k) * T.padm + r];
   }
   double cs = 0.0;
   if (cin) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) co[k] = ws[T.oCOld + (size_t)k * T.padn + c];
-    cs = strided_sum(ws + T.oColPart + c, T.nrc, (size_t)n);
+    for (int k = 0; k < 3; ++k) co[k] = ws[T.oRC + (size_t)(3 + k) * T.padn + c];
+    cs = strided_sum(ws + T.oColPart + c, (m + kShortRows - 1) / kShortRows, (size_t)n);
   }
   if (rin) {
     double rs = 0.0;

@@ -130,7 +130,8 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
 }
 
 // Lay out tiles, row/column blocks and workspace regions for a tensor list.
-inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d, Plan* pl) {
+// allow_short: see the end.
+inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d, Plan* pl, bool allow_short = true) {
   pl->descs.assign(d, d + n);
   pl->tensors.assign(n, TensorDev{});
   pl->tiles.clear();
@@ -182,7 +183,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
-  pl->short_list = is_short_list(n, d, total, shrink);
+  pl->short_list = allow_short && is_short_list(n, d, total, shrink);
   // Short lists: the smallest even apply-tile height at which every CU gets at most two tiles, if that is at most 32 rows: the
   // launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the graded heights below gave 650
   // tiles and a second, nearly empty round). The strip kernel has two workgroups per CU. The narrow one has three or four, and
@@ -238,9 +239,9 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.nrblk = pl->short_list ? T.nrt : ceil_div(m, kBlock);
     T.ncblk = ceil_div(nn, kBlock);   // = nct
     T.rc0 = (int)pl->rcitems.size();
-    T.nrc = ceil_div(m, kShortRows);
+    const int nrc = ceil_div(m, kShortRows);
     if (pl->short_list) {
-      for (int ti = 0; ti < T.nrc; ++ti)
+      for (int ti = 0; ti < nrc; ++ti)
         for (int tj = 0; tj < T.nct; ++tj) pl->rctiles.push_back(TileDev{(int)i, ti, tj, 0});
     } else {
       for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
@@ -263,18 +264,14 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       ar0 += rows;
     }
     T.oRowPart = take((uint64_t)T.nct * m);
-    T.oColPart = take((uint64_t)(pl->short_list ? T.nrc : T.nrt) * nn);
-    T.oRR = take(3ull * T.padm);
-    T.oRC = take(3ull * T.padn);
+    T.oColPart = take((uint64_t)(pl->short_list ? nrc : T.nrt) * nn);
+    T.oRR = take((pl->short_list ? 6ull : 3ull) * T.padm);
+    T.oRC = take((pl->short_list ? 6ull : 3ull) * T.padn);
     T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);
     T.oStatPart = take((uint64_t)T.nrt * T.nct * kStatStride);
     T.oStats = take(kStatsPerTensor);
     T.oScale = take(kStatsPerTensor);
     T.oPrep = take(prep_floats);
-    if (pl->short_list) {
-      T.oROld = take(3ull * T.padm);
-      T.oCOld = take(3ull * T.padn);
-    }
     pl->state_bytes[i] = sizeof(float) * (4ull * T.padN + 3ull * T.padm + 3ull * T.padn + 2ull * T.padH);
   }
   // A launch fewer where every workgroup has one tile and all of them together read at most 64 MB of partials for it. us a step
@@ -302,6 +299,9 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   }
   pl->ws_floats = off;
   choose_loads(o, total, pl);
+  // A short list's copies of r_k and c_k must not take it over the fixed scratch of lopt_step_static: workspaces that come near it
+  // (vectors of millions of elements in all) keep the form without them.
+  if (pl->short_list && off > (48u << 20) / sizeof(float)) build_plan(o, n, d, pl, false);
 }
 
 inline bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {

@@ -91,3 +91,11 @@ def test_the_unaligned_list_reaches_tiles_of_ordinary_height_and_every_number_of
     # 64-column segments of a tensor's last tile; the wavefronts that share one take 4 rows each, 16 or 8 a round
     seg = {-(-(n - 256 * ((n - 1) // 256)) // 64) for _, n in UNALIGNED}
     assert seg == {1, 2, 3, 4} and all(m % 16 and n % 4 for m, n in UNALIGNED)
+
+
+def test_a_short_list_stays_within_the_fixed_scratch():
+    # vectors whose workspace (4 floats an element) fits lopt_step_static's 64 MiB: with copies of c_k (7 an element) it would not
+    vectors = [(1, 20000)] * 190
+    r = plan(vectors, hidden=4)
+    assert 48 << 20 < 4 * r["ws_floats"] < 64 << 20 and r["n_rcitems"] > 0
+    assert plan(vectors[:40], hidden=4)["n_rcitems"] == 0   # small enough for the copies
