@@ -9,6 +9,8 @@ import shutil
 import subprocess
 import tempfile
 
+from paper_2506_10315_amd.binding import flatten_shape
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 N_CU = 256   # compute units of an MI355X
 
@@ -25,13 +27,13 @@ def _probe():
 
 
 def plan(shapes, kind="small_fc_lopt", hidden=None, lstm_hidden=512, n_bank=256, groups=0):
-    """The plan of a list of (rows, cols) with the default apply kernels."""
+    """The plan of a list of shapes with the default apply kernels."""
     h = hidden if hidden is not None else 32 if kind == "small_fc_lopt" else 4
     hp = next(x for x in (4, 8, 16, 32) if h <= x)
     p = 29 * h + h + h * h + h + 2 * h + 2
     folded = n_bank >= 4 and lstm_hidden * p <= lstm_hidden * n_bank + n_bank * p
     args = [int(kind == "velo"), hp, p, lstm_hidden, n_bank, int(folded), groups, N_CU,
             0 if kind == "velo" else 1 if hp == 32 else 2]
-    r = subprocess.run([_probe(), *map(str, args)], input="\n".join(f"{m} {n}" for m, n in shapes), capture_output=True,
+    r = subprocess.run([_probe(), *map(str, args)], input="\n".join("%d %d" % flatten_shape(s)[1:] for s in shapes), capture_output=True,
                        text=True, check=True)
     return json.loads(r.stdout)

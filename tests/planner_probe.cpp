@@ -33,8 +33,10 @@ int main(int argc, char** argv) {
     if (runs.empty() || runs.back().first != t.rows) runs.push_back({t.rows, 0});
     runs.back().second++;
   }
-  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_atiles\": %zu, \"atile_runs\": [",
-         (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.atiles.size());
+  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_rctiles\": %zu, \"n_atiles\": %zu, "
+         "\"short_list\": %d, \"fold_finalize\": %d, \"lstm_ahead\": %d, \"keep\": %d, \"keep_off\": %d, \"backwards\": %d, \"atile_runs\": [",
+         (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.rctiles.size(),
+         pl.atiles.size(), pl.short_list, pl.fold_finalize, pl.oLstmZ != 0, pl.keep, pl.keep_off, pl.backwards);
   const char* sep = "";
   for (const auto& h : runs) { printf("%s[%d, %lld]", sep, h.first, h.second); sep = ", "; }
   printf("], \"tensors\": [");
