@@ -1587,7 +1587,7 @@ __global__ void __launch_bounds__(kBlock) k_velo_head_scatter(const TensorDev* _
 
 // theta (and alpha, if the head is not folded): scratch of n_tensors rows for the batched form, null for lists below
 // kHeadBatchMin tensors (one workgroup per tensor then does everything; cheaper in launches, dearer in weight reads). The
-// form is the whole list's, also for a sub-list of it: the two round differently.
+// form is the whole list's, also for a sub-list of it: the forms round differently.
 void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, const float* h_new, float* alpha,
                       float* theta, hipStream_t s) {
   if (L.n_tensors == 0) return;
@@ -1601,7 +1601,7 @@ void launch_velo_head(const Launch& L, const StepArgs& A, const WeightsDev& W, c
       hipLaunchKernelGGL(k_rows_matmul, dim3((T + 31) / 32, (A.P + 63) / 64), dim3(kBlock), 0, s, hn, A.HL, T, A.HL, W.head,
                          ld, A.P, W.head + (size_t)A.HL * ld, th, ld);
       hipLaunchKernelGGL(k_velo_head_scatter, dim3(T), dim3(kBlock), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn, th, ld);
-    } else if (T <= kHeadSplitMax) {
+    } else if (A.n_tensors <= kHeadSplitMax) {   // of the whole list, see above
       const dim3 grid((A.P + kSplitCols - 1) / kSplitCols, T);
 #define LOPT_LAUNCH_SPLIT(N) \
   hipLaunchKernelGGL((k_velo_head_split<N>), grid, dim3(64 * kHeadWaves), 0, s, L.tensors + L.tensor0, L.ws, A, W, hn)

@@ -7,6 +7,7 @@ import pytest
 
 import workloads as W
 from tests import harness as Hn
+from tests.planner import plan
 from tests.test_planner_cpu import NARROW, UNALIGNED
 
 pytestmark = pytest.mark.gpu
@@ -145,14 +146,16 @@ def test_group_pipeline_is_bit_identical_to_one_stream(groups, monkeypatch):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
-@pytest.mark.parametrize("n_bank", [3, 64])
-def test_tensor_groups_change_no_bit_where_the_hypernetwork_head_is_batched(n_bank):
+@pytest.mark.parametrize("count,n_bank", [(1100, 3), (1100, 64), (152, 3), (152, 64)])
+def test_tensor_groups_change_no_bit_in_the_hypernetwork_head(count, n_bank):
     # 1100 tensors take the batched head (two products with a bank of 3, one with 64), their groups of 367 would be too few
-    # for it: the choice belongs to the list, not to the group
+    # for it; 152 tensors take one workgroup each, their groups of about 50 would take the head in column blocks (with a bank of
+    # 64, folded): the choice belongs to the list, not to the group
     import torch
     import paper_2506_10315_amd as P
     dev = "cuda:0"
-    shapes = [(7, 13), (33, 20)] + [(8 + i % 50,) for i in range(1098)]
+    shapes = [(6145, 3), (33, 20)] + [(8 + i % 50,) for i in range(count - 2)]
+    assert plan(shapes, kind="velo", lstm_hidden=40, n_bank=n_bank)["short_list"] == 0   # short lists are another sequence
     outs = []
     for groups in (1, 3):
         cfg = Hn.make_cfg("velo", lstm_hidden=40, n_bank=n_bank, groups=groups)
