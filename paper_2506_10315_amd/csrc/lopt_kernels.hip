@@ -21,6 +21,8 @@
 // consecutive columns 4l..4l+3 as one float4 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply
 // passes in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
 // a wavefront stays on one segment (the row/column sums: on all four in turn).
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "lopt_internal.h"
@@ -1050,8 +1052,9 @@ constexpr int kTailWaves = 3;
 static_assert(kLstmInPad == 16 * kTailWaves, "two octets a wavefront");
 struct TailFin {
   double part[4][kFinSegs][32], tot[kFinTensorsMax][32];
-  float u[kFinTensorsMax][kLstmInPad];
+  alignas(16) float u[kFinTensorsMax][kLstmInPad];   // read as float4
 };
+static_assert(alignof(TailFin) == 16 && offsetof(TailFin, u) % 16 == 0 && kLstmInPad % 4 == 0, "rows of u on the 16-byte grid");
 
 template <int NS>
 __device__ __forceinline__ void tail_sums(const FinTerms& t, int tn, int slot, TailFin& L) {
@@ -1336,7 +1339,8 @@ template <int TRIPS>
 __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_split(const TensorDev* __restrict__ tensors,
                                                                      float* __restrict__ ws, StepArgs A, WeightsDev W,
                                                                      const float* __restrict__ h_new) {
-  __shared__ float part[kHeadWaves][kSplitCols], lam_part[kHeadWaves];
+  __shared__ __align__(16) float part[kHeadWaves][kSplitCols];   // written as float4
+  __shared__ float lam_part[kHeadWaves];
   const int HL = A.HL, H = A.H, HP = A.HP, P = A.P, ld = head_ld(P);
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int c0 = blockIdx.x * kSplitCols, row0 = 8 * wave + (lane >> 3);
