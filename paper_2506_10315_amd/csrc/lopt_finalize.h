@@ -9,9 +9,9 @@ namespace lopt {
 
 // Adds part[0], part[stride], ... (count terms, 1..B) in double, in index order, term k to acc[k % NS]: B loads issue ahead of
 // the adds, those past the end repeat the last term and are dropped.
-template <int B, int NS>
-__device__ __forceinline__ void sum_batch(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
-  float t[B];
+template <int B, int NS, typename P>
+__device__ __forceinline__ void sum_batch(const P* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
+  P t[B];
 #pragma unroll
   for (int k = 0; k < B; ++k) t[k] = part[(size_t)min(k, count - 1) * stride];
 #pragma unroll
@@ -19,21 +19,23 @@ __device__ __forceinline__ void sum_batch(const float* __restrict__ part, int co
 }
 
 // Sums of part[0], part[stride], ... (count terms) in double, always in index order, as NS interleaved sums. Bound by load
-// latency: full batches of 32 loads, then one batch of the power of two that holds the rest.
-template <int NS>
-__device__ __forceinline__ void strided_sums(const float* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
-  static_assert(NS <= 32 && 32 % NS == 0, "every full batch holds whole rounds of the NS sums");
+// latency: full batches of B loads (32 registers of them), then one batch of the power of two that holds the rest.
+template <int NS, typename P>
+__device__ __forceinline__ void strided_sums(const P* __restrict__ part, int count, size_t stride, double (&acc)[NS]) {
+  constexpr int B = 128 / sizeof(P);
+  static_assert(NS <= B && B % NS == 0, "every full batch holds whole rounds of the NS sums");
 #pragma unroll
   for (int k = 0; k < NS; ++k) acc[k] = 0.0;
-  for (; count > 32; count -= 32, part += 32 * stride) sum_batch<32>(part, 32, stride, acc);
-  if (count > 16) sum_batch<32>(part, count, stride, acc);
+  for (; count > B; count -= B, part += B * stride) sum_batch<B>(part, B, stride, acc);
+  if (count > 16) sum_batch<B>(part, count, stride, acc);
   else if (count > 8) sum_batch<16>(part, count, stride, acc);
   else if (count > 4) sum_batch<8>(part, count, stride, acc);
   else if (count > 1) sum_batch<4>(part, count, stride, acc);
   else if (count == 1) acc[0] += (double)part[0];
 }
 
-__device__ __forceinline__ double strided_sum(const float* __restrict__ part, int count, size_t stride) {
+template <typename P>
+__device__ __forceinline__ double strided_sum(const P* __restrict__ part, int count, size_t stride) {
   double acc[1];
   strided_sums(part, count, stride, acc);
   return acc[0];

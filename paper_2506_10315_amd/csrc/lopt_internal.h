@@ -15,7 +15,12 @@ constexpr int kTileCols = 256;    // one wavefront row-segment: 64 lanes x float
 constexpr int kRowUnit = 64;      // standard tile height (taller for tall tensors, shorter for small lists)
 constexpr int kMaxRowTiles = 256; // tile height grows so that a large tensor has at most this many row tiles ...
 constexpr int kMaxTileRows = 1024; // ... up to this height (bounds the length of the per-lane fp32 partial sums)
-constexpr int kShortRows = 64;    // short lists: rows per tile of the row/column sums (16 wavefronts), rows of a statistics tile at most
+constexpr int kShortRows = 64;    // short lists: rows of a statistics tile at most
+// Short lists: rows per tile of the row/column sums (16 wavefronts, four or eight rows each). Their column sums are doubles, of
+// which every workgroup of the statistics pass reads all for its columns: fewer and taller tiles where there would be many. us a step
+// with fp32 sums of 64 rows / doubles of 64 / doubles of 128: 2000x2000 103.2 / 106.2 / 104.3, 3000x3000 under VeLO 139.6 / 144.7 /
+// 140.2, 1000x1000 41.5 / 41.7 / 42.5, under VeLO, whose recurrent product rides along, 37.0 / 37.8 / 37.2, 512x512 there no difference.
+__host__ __device__ inline int short_rows(int m, bool velo) { return m <= (velo ? 512 : 1024) ? 64 : 128; }
 constexpr int kStatStride = 20;   // floats per tile in the per-tile statistics partials (17 used)
 constexpr int kRcStride = 12;     // floats per block in the row/column partials (9 used)
 constexpr int kNStat = 17;        // per-element statistics accumulated per tile
@@ -54,7 +59,7 @@ struct TensorDev {
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
   int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks (short lists: one per statistics tile row)
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2
-  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [ceil(m / kShortRows)][n])
+  uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [ceil(m / short_rows)][n], double)
   uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc); short lists: then r_k [3][padm] as the step found them
   uint64_t oRC;                     // [3][padn]  rsqrt(c_k + eps_acc); short lists: then c_k [3][padn] as the step found them
   uint64_t oRcPart;                 // [nrblk + ncblk][kRcStride]
@@ -117,7 +122,7 @@ struct Launch {
   int* apply_counter;     // tile counter of the apply kernel for this sub-list (cleared by k_finalize)
   int resident_wgs;       // workgroups of the strip-form apply kernel that are resident at once (2 per CU)
   int beside_apply;       // this sub-list's passes run beside the apply pass of another one
-  const TileDev* rctiles; // short lists: tiles of kShortRows x kTileCols of the row/column sums
+  const TileDev* rctiles; // short lists: tiles of short_rows x kTileCols of the row/column sums
   int n_rctiles;
   bool short_list;        // the statistics pass finishes the row and column means itself (Plan::short_list)
   int keep, keep_off;     // tiles below these numbers are read by the statistics pass with ordinary loads: rows on the 128-byte grid,

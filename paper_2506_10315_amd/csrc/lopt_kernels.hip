@@ -296,18 +296,27 @@ void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W,
                      L.n_tiles, M, n_recur);
 }
 
-// Short lists: tiles of kShortRows rows, sixteen wavefronts with four rows in flight each, so that a column has few partial sums
+// Short lists: tiles of short_rows rows, sixteen wavefronts with four or eight rows in flight each, so that a column has few partial sums
 // and every workgroup of the statistics pass can add them up itself (fuse_means). r_k and c_k are copied aside for it: the
 // statistics pass writes the new ones while other workgroups still need the old.
 constexpr int kShortWaves = 16;
 
-template <bool VEC>
+// [ceil(m / short_rows)][n] sums of g^2 over a tile's rows, added up over the wavefronts and kept in double: there are few of them, and
+// rounded to fp32 they would make the column means less exact than the sums over tiles of eight rows that lists of this length had
+// before (rms error of a mean of 128 rows 4.3e-8 with fp32 sums of 64 rows, 2.9e-8 of eight).
+template <typename F>
+__device__ __forceinline__ auto short_colpart(const TensorDev& T, F* ws) {
+  return reinterpret_cast<std::conditional_t<std::is_const_v<F>, const double, double>*>(ws + T.oColPart);
+}
+
+// R: rows per wavefront.
+template <bool VEC, int R>
 __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                   float (*colred)[kTileCols]) {
-  constexpr int R = kShortRows / kShortWaves;
+  constexpr int kRows = R * kShortWaves;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = T.n, m = T.m, c0 = tile.tj * kTileCols;
-  const int r0 = tile.ti * kShortRows, r1 = min(r0 + kShortRows, m);
+  const int r0 = tile.ti * kRows, r1 = min(r0 + kRows, m);
   float4 v[R];
 #pragma unroll
   for (int i = 0; i < R; ++i) {   // rows past the tile: its last row, counted as 0
@@ -326,9 +335,9 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
   }
   const float* rst = T.st + 4 * (size_t)T.padN;   // r_k[3][padm], c_k[3][padn]
   const int t = threadIdx.x;
-  if (tile.tj == 0 && t < 3 * kShortRows) {
-    const size_t at = (size_t)(t / kShortRows) * T.padm + r0 + t % kShortRows;
-    if (r0 + t % kShortRows < m) ws[T.oRR + 3 * (size_t)T.padm + at] = rst[at];
+  if (tile.tj == 0 && t < 3 * kRows) {
+    const size_t at = (size_t)(t / kRows) * T.padm + r0 + t % kRows;
+    if (r0 + t % kRows < m) ws[T.oRR + 3 * (size_t)T.padm + at] = rst[at];
   }
   if (tile.ti == 0 && t >= kTileCols) {
     const int k = t / kTileCols - 1, c = c0 + t % kTileCols;
@@ -350,14 +359,14 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
   __syncthreads();
   const int c = c0 + t;
   if (t < kTileCols && c < n) {
-    float x[kShortWaves];
+    double x[kShortWaves];
 #pragma unroll
-    for (int w = 0; w < kShortWaves; ++w) x[w] = colred[w][t];
+    for (int w = 0; w < kShortWaves; ++w) x[w] = (double)colred[w][t];
 #pragma unroll
     for (int step = 1; step < kShortWaves; step *= 2)
 #pragma unroll
       for (int w = 0; w < kShortWaves; w += 2 * step) x[w] += x[w + step];
-    ws[T.oColPart + (size_t)tile.ti * n + c] = x[0];
+    short_colpart(T, ws)[(size_t)tile.ti * n + c] = x[0];
   }
 }
 
@@ -378,8 +387,14 @@ __global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const Tens
   float (*colred)[kTileCols] = red.col;
   const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
-  if (T.vec) rowcol_short_tile<true>(T, tile, ws, colred);
-  else rowcol_short_tile<false>(T, tile, ws, colred);
+  constexpr int R = 64 / kShortWaves;
+  if (short_rows(T.m, M.n_slices > 0) == 64) {
+    if (T.vec) rowcol_short_tile<true, R>(T, tile, ws, colred);
+    else rowcol_short_tile<false, R>(T, tile, ws, colred);
+  } else {
+    if (T.vec) rowcol_short_tile<true, 2 * R>(T, tile, ws, colred);
+    else rowcol_short_tile<false, 2 * R>(T, tile, ws, colred);
+  }
 }
 
 void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
@@ -552,7 +567,8 @@ __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& ti
   if (cin) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) co[k] = ws[T.oRC + (size_t)(3 + k) * T.padn + c];
-    cs = strided_sum(ws + T.oColPart + c, (m + kShortRows - 1) / kShortRows, (size_t)n);
+    const int sr = short_rows(m, A.kind == LOPT_VELO);
+    cs = strided_sum(short_colpart(T, ws) + c, (m + sr - 1) / sr, (size_t)n);
   }
   if (rin) {
     double rs = 0.0;

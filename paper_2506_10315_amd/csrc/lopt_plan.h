@@ -7,7 +7,7 @@
 
 namespace lopt {
 
-constexpr uint64_t kShortListFloats = 48u << 20;   // partial sums a short list's statistics pass reads, all workgroups together
+constexpr uint64_t kShortListFloats = 48u << 20;   // what a short list's statistics pass reads of partial sums, all workgroups together
 
 inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
 inline uint64_t align64(uint64_t x) { return (x + 63) & ~(uint64_t)63; }
@@ -81,19 +81,19 @@ inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t to
 
 // Short lists: no launch of its own for the means of the rows and columns (k_rc_update: 4.5 to 6 us, a chain of load latencies).
 // Every workgroup of the statistics pass forms the ones of its own rows and columns from the partial sums, which the
-// row/column pass leaves per 64 rows for that purpose. us a step with that launch and without: 0.08 M elements (toy list) 29.6 /
+// row/column pass leaves per 64 or 128 rows for that purpose. us a step with that launch and without: 0.08 M elements (toy list) 29.6 /
 // 26.9, 1000x1000 45.7 / 43.8 (VeLO 57.7 / 55.0), 66 tensors of 2.4 M under VeLO 69.1 / 66.7, 2000x2000 107.8 / 104.4, ten layers of
 // 1024x1024 at width 16 191.8 / 188.8, nine of 2731x2731 under VeLO 896 / 882; no difference at 14 M elements (width 32), and 495.5 /
 // 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Lists in tensor
 // groups keep the launch: the statistics kernel that forms the means does not fit beside the apply kernel.
-inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink) {
+inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink, bool velo) {
   if (total >= (64u << 20) || n > 4096) return false;   // 4096: the copies of r_k and c_k are no large part of a workspace
   uint64_t floats = 0;
   for (size_t i = 0; i < n; ++i) {
-    const uint64_t nrc = (uint64_t)ceil_div(d[i].rows, kShortRows), nct = (uint64_t)ceil_div(d[i].cols, kTileCols);
-    if (nrc > 96 || nct > 96) return false;
+    if (d[i].rows > 96 * kRowUnit || d[i].cols > 96 * kTileCols) return false;
+    const uint64_t nrc = (uint64_t)ceil_div(d[i].rows, short_rows((int)d[i].rows, velo)), nct = (uint64_t)ceil_div(d[i].cols, kTileCols);
     const uint64_t tr = kRowUnit / shrink, tiles = (uint64_t)ceil_div(d[i].rows, tr) * nct;
-    floats += tiles * (nrc * (uint64_t)(d[i].cols < kTileCols ? d[i].cols : kTileCols) + nct * tr);
+    floats += tiles * (2 * nrc * (uint64_t)(d[i].cols < kTileCols ? d[i].cols : kTileCols) + nct * tr);
     if (floats > kShortListFloats) return false;
   }
   return true;
@@ -183,7 +183,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     std_tiles += (uint64_t)((d[i].rows + kRowUnit - 1) / kRowUnit) * (uint64_t)((d[i].cols + kTileCols - 1) / kTileCols);
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
-  pl->short_list = allow_short && is_short_list(n, d, total, shrink);
+  pl->short_list = allow_short && is_short_list(n, d, total, shrink, velo);
   // Short lists: the smallest even apply-tile height at which every CU gets at most two tiles, if that is at most 32 rows: the
   // launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the graded heights below gave 650
   // tiles and a second, nearly empty round). The strip kernel has two workgroups per CU. The narrow one has three or four, and
@@ -239,7 +239,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.nrblk = pl->short_list ? T.nrt : ceil_div(m, kBlock);
     T.ncblk = ceil_div(nn, kBlock);   // = nct
     T.rc0 = (int)pl->rcitems.size();
-    const int nrc = ceil_div(m, kShortRows);
+    const int nrc = ceil_div(m, short_rows(m, velo));
     if (pl->short_list) {
       for (int ti = 0; ti < nrc; ++ti)
         for (int tj = 0; tj < T.nct; ++tj) pl->rctiles.push_back(TileDev{(int)i, ti, tj, 0});
@@ -264,7 +264,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       ar0 += rows;
     }
     T.oRowPart = take((uint64_t)T.nct * m);
-    T.oColPart = take((uint64_t)(pl->short_list ? nrc : T.nrt) * nn);
+    T.oColPart = take((uint64_t)(pl->short_list ? 2 * nrc : T.nrt) * nn);   // short lists: in double
     T.oRR = take((pl->short_list ? 6ull : 3ull) * T.padm);
     T.oRC = take((pl->short_list ? 6ull : 3ull) * T.padn);
     T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);

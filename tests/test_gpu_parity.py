@@ -109,6 +109,32 @@ def test_row_and_column_means_at_the_limit_of_a_short_list(kind, state_pass, row
     assert worst["param"] <= Hn.TOL_PARAM
 
 
+@pytest.mark.parametrize("cols", [20000, 19999])
+@pytest.mark.parametrize("rows", [64, 100, 128, 256, 1025])
+def test_column_means_of_short_lists_lose_no_bits_in_their_partial_sums(rows, cols):
+    # With beta_5..7 = 0 the state's c_k are the column means themselves, rounded once to fp32. Before that only the sums of up to
+    # eight squares in a lane are formed in fp32, at least 8 ceil(rows / 64) of them of about equal size: the k-th of eight roundings,
+    # of rms 2^-24 / sqrt(3) at most, hits k / 8 of a sum, 1.79 together, and 1.2 allows for the sums' spread. fp32 sums over the
+    # lanes and fp32 partials were 3.2e-8 to 4.3e-8 off here, 2.8e-8 is what the final rounding and the lanes' sums give.
+    import torch
+    import paper_2506_10315_amd as P
+    shapes = [(rows, cols)]
+    assert plan(shapes, hidden=4)["short_list"] == 1
+    cfg = Hn.make_cfg("small_fc_lopt", hidden=4)
+    cfg.fac_decay[:] = [0.0] * 3
+    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, seed=5), shapes)
+    gen = torch.Generator(device="cuda:0").manual_seed(rows)
+    g = torch.randn(rows, cols, device="cuda:0", generator=gen) * 1e-3
+    p = torch.zeros(rows, cols, device="cuda:0")
+    opt.step([p], [g], lr=0.0)
+    exact = g.double().square().mean(0)
+    rms = lambda x: float(((x.double() - exact) / exact).square().mean().sqrt())
+    bound = (rms(exact.float()) ** 2 + (1.2 * 1.79 * 2.0 ** -24 / 3 ** 0.5) ** 2 / (8 * -(-rows // 64))) ** 0.5
+    for c in opt.state_views(0)["c"]:
+        assert rms(c.reshape(-1)) <= bound
+    opt.close()
+
+
 @pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("velo", "apply"), ("velo", "stats")])
 def test_rows_of_a_multiple_of_4_kb(kind, state_pass):
     # widths that are a multiple of 1024 are walked by groups of four tiles (up to 3072 columns) or from a start that differs

@@ -93,6 +93,16 @@ def test_the_unaligned_list_reaches_tiles_of_ordinary_height_and_every_number_of
     assert seg == {1, 2, 3, 4} and all(m % 16 and n % 4 for m, n in UNALIGNED)
 
 
+@pytest.mark.parametrize("kind,line", [("small_fc_lopt", 1024), ("velo", 512)])
+def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
+    for rows, tall in ((64, 64), (65, 64), (line, 64), (line + 1, 128), (6144, 128)):
+        r = plan([(rows, 300)], kind=kind)
+        sums = -(-rows // tall)
+        assert r["short_list"] == 1 and r["n_rctiles"] == 2 * sums
+        at = r["tensors"][0]["regions"]
+        assert at[1] % 2 == 0 and 2 * sums * 300 <= at[2] - at[1] < 2 * sums * 300 + 64
+
+
 def test_a_short_list_stays_within_the_fixed_scratch():
     # vectors whose workspace (4 floats an element) fits lopt_step_static's 64 MiB: with copies of c_k (7 an element) it would not
     vectors = [(1, 20000)] * 190
