@@ -1347,8 +1347,9 @@ __device__ __forceinline__ bool head_pad(int i, int H, int HP) {
 
 // The same product cut into workgroups of 32 columns, so that a tensor's 309 KB of weights come in over several compute units. A
 // lane holds four columns of every 128th row, all its loads (weights and h, nothing depends on anything) leave at once; four
-// terms a lane, eight lanes by shuffles, sixteen wavefronts by a tree in LDS. ln lambda is formed by every workgroup: one term
-// a thread and trees. One tensor 6.9 -> 4.6 us, 66 tensors 7.1 -> 5.9, 152 tensors 7.6 -> 8.2 (five workgroups of 1024 threads each
+// terms a lane, eight lanes by shuffles, sixteen wavefronts by a tree in LDS. ln lambda is formed by every workgroup, one term
+// a thread, in double: its absolute error is the relative error of the whole update (rms error of 512 random terms 2.5e-8; 8.3e-8 as
+// fp32 products and trees, 7.9e-8 in k_velo_head_folded). One tensor 6.9 -> 4.6 us, 66 tensors 7.1 -> 5.9, 152 tensors 7.6 -> 8.2 (five workgroups of 1024 threads each
 // are then more than the chip holds at once): kHeadSplitMax.
 constexpr int kSplitCols = 32, kSplitRows = 128, kSplitTrips = 1024 / kSplitRows;   // H_L <= 1024
 template <int TRIPS>
@@ -1356,7 +1357,7 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_split(const Tenso
                                                                      float* __restrict__ ws, StepArgs A, WeightsDev W,
                                                                      const float* __restrict__ h_new) {
   __shared__ __align__(16) float part[kHeadWaves][kSplitCols];   // written as float4
-  __shared__ float lam_part[kHeadWaves];
+  __shared__ double lam_part[kHeadWaves];
   const int HL = A.HL, H = A.H, HP = A.HP, P = A.P, ld = head_ld(P);
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int c0 = blockIdx.x * kSplitCols, row0 = 8 * wave + (lane >> 3);
@@ -1395,12 +1396,13 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_split(const Tenso
   for (int d = 8; d < 64; d *= 2)
 #pragma unroll
     for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], d);
-  const float lsum = wave_sum(t < HL ? hl * wl : 0.f);
+  const double lsum = wave_sum(t < HL ? (double)hl * (double)wl : 0.0);
   if (lane < 8) *reinterpret_cast<float4*>(&part[wave][4 * lane]) = make_float4(a[0], a[1], a[2], a[3]);
   if (lane == 0) lam_part[wave] = lsum;
   __syncthreads();
   if (t < kSplitCols && i < P) {
-    float s[kHeadWaves], l[kHeadWaves];
+    float s[kHeadWaves];
+    double l[kHeadWaves];
 #pragma unroll
     for (int q = 0; q < kHeadWaves; ++q) { s[q] = part[q][t]; l[q] = lam_part[q]; }
 #pragma unroll
@@ -1408,7 +1410,7 @@ __global__ void __launch_bounds__(64 * kHeadWaves) k_velo_head_split(const Tenso
 #pragma unroll
       for (int q = 0; q < kHeadWaves; q += 2 * step) { s[q] += s[q + step]; l[q] += l[q + step]; }
     float th = bias + s[0];
-    const int dst = head_slot(i, H, HP, ws + T.oScale, expf(b_lam + l[0]), th);
+    const int dst = head_slot(i, H, HP, ws + T.oScale, expf((float)((double)b_lam + l[0])), th);
     prep[dst] = th;
   }
 }

@@ -256,6 +256,43 @@ def test_velo_step_size_is_summed_with_few_roundings(count):
     opt.close()
 
 
+@pytest.mark.parametrize("lstm_hidden,count", [(100, 5), (512, 16), (1024, 96)])
+def test_velo_step_size_of_short_lists_loses_no_bits_in_its_sum(lstm_hidden, count):
+    # ln(lambda) = h . ws of some hundred terms of about one that cancel (ws orthogonal to every tensor's h, which does not depend on
+    # it; 4 ws, so that fp32 products and sums are 5 to 20 units of 2^-24 off). In double only its own rounding is left, far below a
+    # unit where it is near 0; 2 units for expf, 4 for the step size's way through the MLP's output layer and the update.
+    import torch
+    import paper_2506_10315_amd as P
+    cfg = Hn.make_cfg("velo", lstm_hidden=lstm_hidden)
+    w = Hn.random_weights(cfg, seed=70)
+    v = _velo_weight_views(w, cfg)
+    v["Wa"][:], v["ba"][:], v["B"][:], v["bs"][:] = 0.0, 0.0, 0.0, 0.0
+    v["Wx"][:] *= 20.0                     # outputs of every size up to one, different for every tensor
+    v["ba"][0] = 1.0
+    v["B"][0, -2] = 1.0                    # b3, direction
+    v["ws"][:] = 0.0
+    shapes = [(8 + i, 16) for i in range(count)]
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    g = [torch.randn(s, device="cuda:0", generator=gen) * 10.0 ** -(1 + i % 5) for i, s in enumerate(shapes)]
+
+    def step():
+        opt = P.LearnedOptimizer(cfg, w, shapes)
+        p = [torch.zeros(s, device="cuda:0") for s in shapes]
+        opt.step(p, g, lr=1.0, step=0, loss=1.0)
+        h = np.stack([opt.state_views(i)["h"].cpu().numpy().astype(np.float64) for i in range(count)])
+        opt.close()
+        return h, [-x.cpu().numpy().astype(np.float64) / float(np.float32(cfg.step_mult)) for x in p]
+
+    h, _ = step()
+    r = np.random.default_rng(71).uniform(-4.0, 4.0, lstm_hidden)
+    v["ws"][:] = r - h.T @ np.linalg.lstsq(h @ h.T, h @ r, rcond=None)[0]
+    h2, lam = step()
+    assert np.array_equal(h, h2)
+    ln = h @ v["ws"].astype(np.float64)
+    assert np.max(np.abs(ln)) < 1e-3 and np.max(np.abs(h * v["ws"]).sum(1)) > 0.2 * lstm_hidden
+    assert max(np.max(np.abs(x / np.exp(l) - 1.0)) for x, l in zip(lam, ln)) <= 6 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("hidden,state_pass", [(1, "apply"), (4, "stats"), (8, "apply"), (9, "stats"), (16, "apply"), (16, "stats")])
 def test_small_fc_narrow_widths_at_tile_boundaries(hidden, state_pass):
     # hidden widths up to 16 (padded to 4, 8, 16) run on fp32 matrix instructions over tiles of 128 columns, 64 columns a
