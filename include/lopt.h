@@ -120,7 +120,8 @@ typedef struct {
   uint32_t n_bank;      /* VeLO only: number K of weight-bank rows (1..1024) */
   uint32_t apply_kernel; /* lopt_apply_kernel; 0 = automatic */
   uint32_t groups;      /* tensor groups of the two-stream pipeline, 1..16 (1 = every pass over the whole list, one after
-                           the other, on the caller's stream); 0 = by list size */
+                           the other, on the caller's stream); 0 = by list size. A list has at most one group per tensor,
+                           and most lists below 64 M elements, which groups make slower, one in all. No result depends on it. */
   uint32_t state_pass;  /* lopt_state_pass; 0 = automatic */
 } lopt_config;
 

@@ -662,14 +662,10 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     else if (velo4_ok) launch_apply_velo4(La, A, state_in_apply, stream);
     else launch_apply_velo(La, A, ctx->W, stream);
   };
-  // ---- group pipeline: only where the apply pass is compute-bound (strip form), the list is large enough to
-  // pay for the extra launches, and per-pass timing is off (its events assume one pass after the other)
-  int G = 1;
+  // ---- group pipeline (Plan::groups): only where the apply pass is compute-bound (strip form; VeLO on request), the list is large
+  // enough to pay for the extra launches, and per-pass timing is off (its events assume one pass after the other)
   const bool velo = ctx->cfg.kind == LOPT_VELO;
-  if (ctx->aux_stream && !profiling) {
-    if (strip_ok) G = planned_groups(ctx->opts.groups_override, pl.total_elems, n);
-    else if (velo && ctx->opts.groups_override) G = planned_groups(ctx->opts.groups_override, pl.total_elems, n);
-  }
+  const int G = ctx->aux_stream && !profiling && (strip_ok || velo) ? pl.groups : 1;
   // From here on kernels are in flight: a HIP error leaves params and state partly updated. The context is marked
   // failed, and the second stream (if it was forked) is joined back so that the caller's stream semantics hold.
   bool forked = false;
@@ -704,15 +700,15 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
       S.tensor0 = t0; S.n_tensors = t1 - t0;
       S.apply_counter = L.apply_counter + g;
       S.beside_apply = g > 0;
-      if (!S.short_list) { S.keep = 0; S.backwards = false; }   // tile numbers of the whole list; the groups are short
+      S.keep = 0; S.backwards = false;   // tile numbers of the whole list; the groups are short
       return S;
     };
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for
     auto stats_passes = [&](const Launch& S, hipStream_t s) {
-      launch_accum_stats(S, A, ctx->W, !state_in_apply, S.tensor0 == 0, ws + pl.oHbarPart, ws + pl.oBeff, s);
-      if (!fold) launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
+      launch_accum_stats(S, A, ctx->W, !state_in_apply, ws + pl.oHbarPart, ws + pl.oBeff, s);
+      launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
       if (velo) {
-        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, fold ? &feats : nullptr, ws + pl.oHNew, s);
+        launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, nullptr, ws + pl.oHNew, s);
         launch_velo_head(S, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
                          pl.head_batched ? ws + pl.oTheta : nullptr, s);
       }
@@ -720,12 +716,8 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     hipStream_t aux = ctx->aux_stream;
     // the row/column pass reads only the gradients (4 of the step's 72 bytes per element): whole list, up front
     // (VeLO: the cross-tensor term rides along in these two launches, before any group rewrites its LSTM outputs)
-    // (short lists: its second stage in the statistics launch of the first group, which the second stream waits for)
-    if (pl.short_list) launch_rowcol_short(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
-    else {
-      launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
-      launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
-    }
+    launch_rowcol_sums(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, lstm_z, stream);
+    launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
     LAUNCH_TRY(hipEventRecord(ctx->ev_fork, stream));       // aux joins the caller's stream here ...
     LAUNCH_TRY(hipStreamWaitEvent(aux, ctx->ev_fork, 0));
     forked = true;
@@ -762,7 +754,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   MARK(1);
   if (!pl.short_list) launch_rc_update(L, A, ctx->W, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(2);
-  launch_accum_stats(L, A, ctx->W, !state_in_apply, true, ws + pl.oHbarPart, ws + pl.oBeff, stream);
+  launch_accum_stats(L, A, ctx->W, !state_in_apply, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(3);
   if (!fold) launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
   MARK(4);

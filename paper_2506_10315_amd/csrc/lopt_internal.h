@@ -141,9 +141,8 @@ void launch_rc_update(const Launch&, const StepArgs&, const WeightsDev&, float* 
 // short lists: the row/column sums on taller tiles, copying r_k and c_k aside
 void launch_rowcol_short(const Launch&, const StepArgs&, const WeightsDev&, float* hbar_part, float* b_eff, float* lstm_z, hipStream_t);
 // write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s). Short
-// lists: with_mix = the second stage of VeLO's cross-tensor term rides along here (there is no launch_rc_update)
-void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool write_state, bool with_mix, float* hbar_part, float* b_eff,
-                        hipStream_t);
+// lists: the second stage of VeLO's cross-tensor term rides along here (there is no launch_rc_update)
+void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool write_state, float* hbar_part, float* b_eff, hipStream_t);
 void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
 // lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
 void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);

@@ -854,16 +854,12 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   if constexpr (FUSE) fuse_store(T, tile, ws, sh.means, red);
 }
 
-void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W, bool write_state, bool with_mix, float* hbar_part,
-                        float* b_eff, hipStream_t s) {
+void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W, bool write_state, float* hbar_part, float* b_eff,
+                        hipStream_t s) {
   if (L.n_tiles == 0) return;
   const bool raw = A.eps_acc >= 1e-30f;
   MixArgs M{};
-  if (L.short_list && with_mix) {
-    Launch whole = L;   // the cross-tensor term is the whole list's
-    whole.n_tensors = A.n_tensors;
-    M = make_mix(whole, A, W, hbar_part, b_eff);
-  }
+  if (L.short_list) M = make_mix(L, A, W, hbar_part, b_eff);   // on other lists launch_rc_update has formed the cross-tensor term
   const int extra = mix_bias_blocks(M);
 #define LOPT_LAUNCH_ACC(R, Wr, F) \
   hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M, \

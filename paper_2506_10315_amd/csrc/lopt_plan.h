@@ -36,6 +36,7 @@ struct Plan {
   std::vector<RcItemDev> rcitems;
   std::vector<TileDev> rctiles;       // short lists: tiles of the row/column sums
   bool short_list = false;
+  int groups = 1;                     // tensor groups of the two-stream pipeline
   int keep = 0, keep_off = 0;         // see choose_loads
   bool backwards = false;
   bool fold_finalize = false;         // k_finalize is not launched: the strip kernel's workgroups form their tensor's scales, the
@@ -159,23 +160,8 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       pl->oTheta = take((uint64_t)n * (uint64_t)(o.head_folded ? head_ld(o.P) : o.P));
     }
   }
-  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off, as it is for
-  // every kernel but the strip one): the apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
-  // while the final workgroups finish (a 128-row tile is about 90 us of work, a 32-row tile a quarter of that).
   uint64_t total = 0;
   for (size_t i = 0; i < n; ++i) total += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-  const int G_plan = o.apply == ApplyTiles::Strip ? planned_groups(o.groups_override, total, n) : 1;
-  int gbound[kMaxGroups + 1];
-  group_bounds(d, n, G_plan, total, gbound);
-  std::vector<uint64_t> gtotal(G_plan, 0), gbefore(n, 0);
-  for (int g = 0; g < G_plan; ++g)
-    for (int i = gbound[g]; i < gbound[g + 1]; ++i) {
-      gbefore[i] = gtotal[g];
-      gtotal[g] += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
-    }
-  std::vector<int> group_of(n, 0);
-  for (int g = 0; g < G_plan; ++g)
-    for (int i = gbound[g]; i < gbound[g + 1]; ++i) group_of[i] = g;
   // Small parameter sets: with the standard 64-row tiles there may be fewer tiles than the chip has workgroup
   // slots (256 CUs x 2..8), so the tile height is halved until the list yields about 2048 tiles or reaches 8 rows.
   uint64_t std_tiles = 0;
@@ -184,6 +170,21 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   int shrink = 1;
   while (shrink < 8 && std_tiles * shrink < 2048) shrink *= 2;
   pl->short_list = allow_short && is_short_list(n, d, total, shrink, velo);
+  // Apply tiles get shorter towards the end of every tensor group of the pipeline (a single group if it is off, as it is for
+  // every kernel but the strip one): the apply kernel hands tiles out in table order, so the last tiles of a launch decide how long the chip idles
+  // while the final workgroups finish (a 128-row tile is about 90 us of work, a 32-row tile a quarter of that).
+  pl->groups = pl->short_list || !(o.apply == ApplyTiles::Strip || (velo && o.groups_override)) ? 1 : planned_groups(o.groups_override, total, n);
+  int gbound[kMaxGroups + 1];
+  group_bounds(d, n, pl->groups, total, gbound);
+  std::vector<uint64_t> gtotal(pl->groups, 0), gbefore(n, 0);
+  for (int g = 0; g < pl->groups; ++g)
+    for (int i = gbound[g]; i < gbound[g + 1]; ++i) {
+      gbefore[i] = gtotal[g];
+      gtotal[g] += (uint64_t)d[i].rows * (uint64_t)d[i].cols;
+    }
+  std::vector<int> group_of(n, 0);
+  for (int g = 0; g < pl->groups; ++g)
+    for (int i = gbound[g]; i < gbound[g + 1]; ++i) group_of[i] = g;
   // Short lists: the smallest even apply-tile height at which every CU gets at most two tiles, if that is at most 32 rows: the
   // launch is then one round of equal tiles (a 1000x1000 layer: 504 tiles of 16 rows, where the graded heights below gave 650
   // tiles and a second, nearly empty round). The strip kernel has two workgroups per CU. The narrow one has three or four, and

@@ -13,16 +13,24 @@ from tests.test_planner_cpu import NARROW, UNALIGNED
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(300, 257), (64, 256), (1030,), (5,), (520, 768)]
+# The same with a tensor too tall for a short list: the sequence of launches that lists of 64 M elements and more take, and the only
+# one that is cut into tensor groups.
+TALL = SHAPES + [(6145, 40)]
 
 
-def _run(kind, steps, device="cuda:0", resume_at=None, seed=0):
+def test_forms_of_the_lists():
+    for kind in ("small_fc_lopt", "velo"):
+        assert plan(SHAPES, kind=kind, groups=3)["groups"] == 1 and plan(TALL, kind=kind, groups=3)["groups"] == 3
+
+
+def _run(kind, steps, device="cuda:0", resume_at=None, seed=0, shapes=SHAPES):
     import torch
     import paper_2506_10315_amd as P
     cfg = Hn.make_cfg(kind) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32)
     w = Hn.random_weights(cfg, seed)
-    specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(SHAPES)]
+    specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(shapes)]
     case = Hn.Case(201, specs, "gauss_logscale")
-    opt = P.LearnedOptimizer(cfg, w, SHAPES, device=device)
+    opt = P.LearnedOptimizer(cfg, w, shapes, device=device)
     p = [torch.from_numpy(case.p0(i)).to(device) for i in range(len(specs))]
     for t in range(steps):
         if resume_at is not None and t == resume_at:
@@ -31,7 +39,7 @@ def _run(kind, steps, device="cuda:0", resume_at=None, seed=0):
             saved_p = [x.clone() for x in p]
             saved_s = [x.clone() for x in opt.state]
             opt.close()
-            opt = P.LearnedOptimizer(cfg, w, SHAPES, device=device)
+            opt = P.LearnedOptimizer(cfg, w, shapes, device=device)
             for dst, src in zip(opt.state, saved_s):
                 dst.copy_(src)
             p = saved_p
@@ -43,15 +51,17 @@ def _run(kind, steps, device="cuda:0", resume_at=None, seed=0):
     return out
 
 
+@pytest.mark.parametrize("shapes", [SHAPES, TALL])
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
-def test_two_runs_are_bit_identical(kind):
-    a = _run(kind, 5)
-    b = _run(kind, 5)
+def test_two_runs_are_bit_identical(kind, shapes):
+    a = _run(kind, 5, shapes=shapes)
+    b = _run(kind, 5, shapes=shapes)
     for x, y in zip(a, b):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
-def test_groups_field_of_the_configuration_selects_the_plan_per_context():
+@pytest.mark.parametrize("shapes", [SHAPES, TALL])
+def test_groups_field_of_the_configuration_selects_the_plan_per_context(shapes):
     # two contexts in one process, one with every pass over the whole list on one stream, one with three tensor groups
     # on two streams: same bits (the selection is per context, no environment involved)
     import torch
@@ -60,9 +70,9 @@ def test_groups_field_of_the_configuration_selects_the_plan_per_context():
     for groups in (1, 3):
         cfg = Hn.make_cfg("small_fc_lopt", groups=groups)
         w = Hn.random_weights(cfg, 0)
-        specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(SHAPES)]
+        specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(shapes)]
         case = Hn.Case(201, specs, "gauss_logscale")
-        opt = P.LearnedOptimizer(cfg, w, SHAPES)
+        opt = P.LearnedOptimizer(cfg, w, shapes)
         p = [torch.from_numpy(case.p0(i)).to("cuda:0") for i in range(len(specs))]
         for t in range(3):
             g = [torch.from_numpy(case.grad(i, t)).to("cuda:0") for i in range(len(specs))]
@@ -74,15 +84,16 @@ def test_groups_field_of_the_configuration_selects_the_plan_per_context():
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
+@pytest.mark.parametrize("base", [SHAPES, TALL])
 @pytest.mark.parametrize("kind,groups", [("small_fc_lopt", 1), ("small_fc_lopt", 3), ("velo", 1)])
-def test_state_pass_field_moves_the_accumulator_update_without_changing_a_bit(kind, groups):
+def test_state_pass_field_moves_the_accumulator_update_without_changing_a_bit(kind, groups, base):
     # The new M_1..3 and V are written either by the statistics pass or by the default apply kernels (split-fp16 strip
     # kernel of small_fc_lopt, width-4 kernel of VeLO), which then form them a second time with the same fp32
     # operations: parameters AND every word of the state must agree bit for bit, ragged and unaligned shapes included,
     # with and without the tensor-group pipeline.
     import torch
     import paper_2506_10315_amd as P
-    shapes = SHAPES + [(300, 257), (2, 1000), (1, 77), (129, 64)]
+    shapes = base + [(300, 257), (2, 1000), (1, 77), (129, 64)]
     outs = []
     for state_pass in ("stats", "apply"):
         if kind == "small_fc_lopt":
@@ -127,21 +138,22 @@ def test_state_pass_changes_no_bit_on_full_tiles(kind, hidden, shapes):
         assert torch.equal(x.view(torch.int32), y.view(torch.int32))
 
 
+@pytest.mark.parametrize("shapes", [SHAPES, TALL])
 @pytest.mark.parametrize("groups", [2, 3, 16])
-def test_group_pipeline_is_bit_identical_to_one_stream(groups, monkeypatch):
+def test_group_pipeline_is_bit_identical_to_one_stream(groups, shapes, monkeypatch):
     # LOPT_GROUPS (read when the context is created) cuts the list into tensor groups whose HBM-bound passes run on
     # the library's second stream beside the previous group's apply pass. The same kernels see the same tiles, so
     # the results must not change by a single bit, on the default stream and on a stream of the caller's.
     import torch
     monkeypatch.setenv("LOPT_GROUPS", "1")
-    ref = _run("small_fc_lopt", 4)
+    ref = _run("small_fc_lopt", 4, shapes=shapes)
     monkeypatch.setenv("LOPT_GROUPS", str(groups))
-    out = _run("small_fc_lopt", 4)
+    out = _run("small_fc_lopt", 4, shapes=shapes)
     for x, y in zip(ref, out):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
-        out2 = _run("small_fc_lopt", 4)
+        out2 = _run("small_fc_lopt", 4, shapes=shapes)
     for x, y in zip(ref, out2):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
@@ -173,43 +185,46 @@ def test_tensor_groups_change_no_bit_in_the_hypernetwork_head(count, n_bank):
 
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_statistics_do_not_depend_on_the_group_a_tensor_falls_in(kind):
-    # Two equal tensors, one per tensor group, with per-tile sums of g^2 (256 tiles of 8 rows) whose total depends on the order
+    # Two equal tensors, one per tensor group (a third one makes the list one that is cut), with per-tile sums of g^2 (256 tiles of 8 rows) whose total depends on the order
     # of a double summation in the last bit of the float result: 1 and 2^-24 meet a tie between two floats, 31 tiles of 2^-54
     # (every eighth) vanish one by one beside the 1 and break the tie when eight of them are added up first.
     import torch
     import paper_2506_10315_amd as P
     cfg = Hn.make_cfg(kind, groups=2) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8, groups=2)
     rows, cols = 2048, 256
-    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, 0), [(rows, cols)] * 2)
+    shapes = [(6145, 1)] + [(rows, cols)] * 2
+    assert plan(shapes, kind=kind, lstm_hidden=32, n_bank=8, groups=2)["groups"] == 2
+    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, 0), shapes)
     g = torch.zeros(rows, cols)
     g[0, 0], g[8, 0] = 1.0, 2.0 ** -12
     g[64::64, 0] = 2.0 ** -27
     gen = torch.Generator().manual_seed(1)
     p0 = torch.randn(rows, cols, generator=gen) * 0.02
-    p = [p0.to("cuda:0") for _ in range(2)]
-    opt.step(p, [g.to("cuda:0") for _ in range(2)], lr=0.7, step=0, loss=1.0)
+    p = [torch.zeros(6145, 1, device="cuda:0")] + [p0.to("cuda:0") for _ in range(2)]
+    opt.step(p, [torch.ones(6145, 1, device="cuda:0")] + [g.to("cuda:0") for _ in range(2)], lr=0.7, step=0, loss=1.0)
     torch.cuda.synchronize()
-    a, b = (x.cpu().numpy() for x in opt.stats())
+    a, b = (x.cpu().numpy() for x in opt.stats()[1:])
     assert a[0] in (np.float32(2.0 ** -19), np.nextafter(np.float32(2.0 ** -19), np.float32(1)))
     assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
-    assert torch.equal(p[0].view(torch.int32), p[1].view(torch.int32))
-    assert torch.equal(opt.state[0].view(torch.int32), opt.state[1].view(torch.int32))
+    assert torch.equal(p[1].view(torch.int32), p[2].view(torch.int32))
+    assert torch.equal(opt.state[1].view(torch.int32), opt.state[2].view(torch.int32))
     opt.close()
 
 
+@pytest.mark.parametrize("shapes", [SHAPES, TALL])
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
-def test_per_pass_timing_changes_no_result_and_names_every_pass(kind, monkeypatch):
+def test_per_pass_timing_changes_no_result_and_names_every_pass(kind, shapes, monkeypatch):
     # With lopt_profile_enable the step runs pass after pass on one stream with events in between (no tensor groups);
     # results must be bit-identical to the default launch plan, here forced to three groups.
     import torch
     import paper_2506_10315_amd as P
     monkeypatch.setenv("LOPT_GROUPS", "3")
-    ref = _run(kind, 3)
+    ref = _run(kind, 3, shapes=shapes)
     cfg = Hn.make_cfg(kind) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32)
     w = Hn.random_weights(cfg, 0)
-    specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(SHAPES)]
+    specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(shapes)]
     case = Hn.Case(201, specs, "gauss_logscale")
-    opt = P.LearnedOptimizer(cfg, w, SHAPES, device="cuda:0")
+    opt = P.LearnedOptimizer(cfg, w, shapes, device="cuda:0")
     opt.profile_enable(True)
     p = [torch.from_numpy(case.p0(i)).to("cuda:0") for i in range(len(specs))]
     for t in range(3):
@@ -311,7 +326,9 @@ def test_context_reused_across_different_tensor_lists_and_streams():
     ("velo", [(300, 257), (64, 256), (1030,), (5,)], True, None),
     ("small_fc_lopt", [(1000, 1000)], False, None),
     ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True, None),     # 42 M elements: one stream by default
-    ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True, 4),        # and cut into groups on two streams
+    ("small_fc_lopt", [(4096, 2560)] * 4 + [(2560,)] * 4, True, 4),        # also where four groups are asked for
+    ("small_fc_lopt", [(6145, 1712)] * 4 + [(2560,)] * 4, True, 4),        # taller: cut into groups on two streams
+    ("velo", [(6145, 860)] * 4 + [(2560,)] * 4, True, 3),
     ("small_fc_lopt", [(4096, 2560)] * 7, True, None),                     # 73 M elements: two groups by default
 ])
 def test_a_step_captured_in_a_hip_graph_replays_bit_identically(kind, shapes, static, groups):
@@ -322,7 +339,7 @@ def test_a_step_captured_in_a_hip_graph_replays_bit_identically(kind, shapes, st
     import torch
     import paper_2506_10315_amd as P
     dev = "cuda:0"
-    cfg = Hn.make_cfg(kind, groups=groups) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32)
+    cfg = Hn.make_cfg(kind, groups=groups) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=64, n_bank=32, groups=groups)
     w = Hn.random_weights(cfg, 2)
     specs = [W.TensorSpec(f"t{i}", s) for i, s in enumerate(shapes)]
     case = Hn.Case(202, specs, "gauss_logscale")

@@ -93,6 +93,18 @@ def test_the_unaligned_list_reaches_tiles_of_ordinary_height_and_every_number_of
     assert seg == {1, 2, 3, 4} and all(m % 16 and n % 4 for m, n in UNALIGNED)
 
 
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_short_lists_are_not_cut_into_tensor_groups(kind):
+    # the groups of a caller's own, which such lists only lose by, leave the plan of a short list as it is; a tensor of more than
+    # 6144 rows makes a list of the other form
+    for shapes, short in (([(4096, 2560)] * 4 + [(2560,)] * 4, 1), ([(6145, 1707)] * 4 + [(2560,)] * 4, 0), ([(300, 257), (5,), (64, 256)], 1)):
+        r, one = plan(shapes, kind=kind, groups=3), plan(shapes, kind=kind, groups=1)
+        assert r["short_list"] == one["short_list"] == short
+        assert (r["groups"], one["groups"]) == (1 if short else 3, 1)
+        if short:
+            assert r == one
+
+
 @pytest.mark.parametrize("kind,line", [("small_fc_lopt", 1024), ("velo", 512)])
 def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
     for rows, tall in ((64, 64), (65, 64), (line, 64), (line + 1, 128), (6144, 128)):
