@@ -85,8 +85,10 @@ inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t to
 // row/column pass leaves per 64 or 128 rows for that purpose. us a step with that launch and without: 0.08 M elements (toy list) 29.6 /
 // 26.9, 1000x1000 45.7 / 43.8 (VeLO 57.7 / 55.0), 66 tensors of 2.4 M under VeLO 69.1 / 66.7, 2000x2000 107.8 / 104.4, ten layers of
 // 1024x1024 at width 16 191.8 / 188.8, nine of 2731x2731 under VeLO 896 / 882; no difference at 14 M elements (width 32), and 495.5 /
-// 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Lists in tensor
-// groups keep the launch: the statistics kernel that forms the means does not fit beside the apply kernel.
+// 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Short lists
+// are never cut into tensor groups: the statistics kernel that forms the means does not fit beside the apply kernel, and groups
+// cost such lists more than they hide in either form (four tensors of 4096x2560 in two groups, that launch kept / without it / one
+// group: 749 / 774 / 738; under VeLO 641 / 579 / 549).
 inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink, bool velo) {
   if (total >= (64u << 20) || n > 4096) return false;   // 4096: the copies of r_k and c_k are no large part of a workspace
   uint64_t floats = 0;

@@ -185,7 +185,8 @@ def test_tensor_groups_change_no_bit_in_the_hypernetwork_head(count, n_bank):
 
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_statistics_do_not_depend_on_the_group_a_tensor_falls_in(kind):
-    # Two equal tensors, one per tensor group (a third one makes the list one that is cut), with per-tile sums of g^2 (256 tiles of 8 rows) whose total depends on the order
+    # Two equal tensors, one per tensor group (a third one makes the list one that is cut), with per-tile sums of g^2 (256 tiles
+    # of 8 rows) whose total depends on the order
     # of a double summation in the last bit of the float result: 1 and 2^-24 meet a tie between two floats, 31 tiles of 2^-54
     # (every eighth) vanish one by one beside the 1 and break the tie when eight of them are added up first.
     import torch
