@@ -103,20 +103,28 @@ inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, i
 }
 
 // How the statistics pass reads its tiles. What it reads with ordinary instead of nontemporal loads is still in the 256 MB
-// Infinity Cache when the apply pass reads it again, as far as it fits: 10 M elements of 24 bytes. us a step, two contexts in turn:
-//   short lists (on the 128-byte grid, row/column sums ordinary too): everything, also past the cache's size: VeLO 2.4 M elements
-//     62.6 -> 58.3, 4.2 M 84.6 -> 77.1, 8.4 M 132.2 -> 119.5, 21 M 293 -> 282, 31 M 427 -> 420; width 16 9.5 M 189.8 -> 186.7; width 32 12.6 M
-//     247 -> 241, 16.8 M 318.5 -> 315. From 40 M elements on from the last tile to the first, so that each pass begins where
-//     the one before it ended: 47 M 652 -> 637 (forwards 647), but 31 M 422.5 and 2.4 M 60.2
+// Infinity Cache when the apply pass reads it again, as far as it fits: 10 M elements of 24 bytes. Going from the last tile to
+// the first, it ends where the apply pass begins. us a step, two contexts in turn:
+//   short lists below 15.5 M elements: everything on the 128-byte grid ordinary (row/column sums too), forwards. VeLO 2.4 M elements
+//     62.6 -> 58.3, 4.2 M 84.6 -> 77.1, 8.4 M 132.2 -> 119.5; width 16 9.5 M 189.8 -> 186.7; width 32 12.6 M 247 -> 241
+//   short lists from there on: backwards, the first 10 M elements' tiles ordinary, for the narrow widths none, whose apply pass is
+//     longer than the cache is of use. Everything ordinary and forwards (backwards from 40 M) / this way, VeLO 17 M of 1024 columns
+//     224.7 / 219.3, 34 M 458 / 433, 34 M of 4096 448 / 428, 38 M of 2048 514 / 482; width 32 34 M 601 / 582, 42 M 737 / 721; width 16
+//     (598 nontemporal throughout) 619 / 597, 42 M of 4096 749 / 724. At 15 M VeLO 203.7 / 205.5, width 32 302 / 300, width 16 298 / 299.7, at
+//     14 M of 3072 columns VeLO 182.6 / 185.5
 //   rows off the 16-byte grid: ordinary (8.3 M elements width 32 209 us nontemporal 220; VeLO 8 M 143 / 161), for VeLO from 13 M on
-//     nontemporal (13.4 M 229 / 231, 16.4 M 298 / 285, 20 M 360 / 336), again but for the first 10 M
+//     nontemporal (13.4 M 229 / 231, 16.4 M 298 / 285, 20 M 360 / 336), again but for the first 10 M. Backwards helps here
+//     from 11 M on, which decides for lists with most of their elements off the grid. 1531 columns, forwards / backwards, 9 M VeLO 137.5 /
+//     138.3, 12 M 190 / 183, width 32 and 16 the same, 14 M VeLO 221 / 208, width 32 298 / 299.5, width 16 290 / 278, 21 M VeLO 363 / 330, width 32
+//     472 / 455, width 16 435 / 417
 //   long lists under VeLO: from the last tile to the first, nontemporal but for the first 10 M elements' tiles: ViT-B/16 shapes
 //     1158 -> 1150 (6.5 M 1153, 16 M 1151.5; everything 1181), Llama-1.3B shapes 17310 -> 17283
 //   long lists of small_fc_lopt: nontemporal (ViT-B/16 shapes 313 us the pass, 352 with ordinary loads).
 inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   constexpr uint64_t kCached = 10u << 20;
   int cached = (int)pl->tiles.size();   // tiles of the first kCached elements
-  uint64_t seen = 0;
+  uint64_t seen = 0, off_grid = 0;
+  for (const TensorDev& T : pl->tensors) off_grid += T.vec == 0 ? (uint64_t)T.m * (uint64_t)T.n : 0;
   for (const TensorDev& T : pl->tensors) {
     const uint64_t N = (uint64_t)T.m * (uint64_t)T.n;
     if (seen + N > kCached) {
@@ -127,8 +135,9 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   }
   const int all = 0x7fffffff;
   const bool velo = o.kind == LOPT_VELO;
-  pl->backwards = pl->short_list ? total >= (40u << 20) : velo;
-  pl->keep = pl->short_list ? all : velo ? cached : 0;
+  const bool small = pl->short_list && total < (2 * off_grid > total ? 11u << 20 : 31u << 19), narrow = o.apply == ApplyTiles::Narrow;
+  pl->backwards = pl->short_list ? !small : velo;
+  pl->keep = small ? all : velo || (pl->short_list && !narrow) ? cached : 0;
   pl->keep_off = pl->short_list && velo && total >= (13u << 20) ? cached : all;
 }
 

@@ -105,6 +105,22 @@ def test_short_lists_are_not_cut_into_tensor_groups(kind):
             assert r == one
 
 
+@pytest.mark.parametrize("kind,hidden", [("small_fc_lopt", 32), ("small_fc_lopt", 16), ("velo", 4)])
+def test_which_tiles_the_statistics_pass_leaves_in_the_cache(kind, hidden):
+    # up to 15.5 M elements (11 M off the 16-byte grid) all, beyond it those of the first 10 M (where the apply pass begins, so the pass goes backwards), for the
+    # narrow widths none; rows off the 16-byte grid all, under VeLO from 13 M on those of the first 10 M
+    velo, everything = kind == "velo", 2 ** 31 - 1
+    for count in (1, 8, 12, 13, 15, 16, 40, 63):
+        r = plan([(1024, 1024)] * count, kind=kind, hidden=hidden)
+        first = r["n_tiles"] * 10 // count if count > 10 else r["n_tiles"]
+        assert r["short_list"] == 1 and r["backwards"] == (count >= 16)
+        assert r["keep"] == (everything if count < 16 else first if velo or hidden == 32 else 0)
+        assert r["keep_off"] == (first if velo and count >= 13 else everything)
+    assert [plan([(1024, 1025)] * count, kind=kind, hidden=hidden)["backwards"] for count in (10, 11, 14)] == [0, 1, 1]
+    r = plan([(1024, 1024)] * 64, kind=kind, hidden=hidden)
+    assert r["short_list"] == 0 and r["backwards"] == velo and r["keep"] == (r["n_tiles"] * 10 // 64 if velo else 0)
+
+
 @pytest.mark.parametrize("kind,line", [("small_fc_lopt", 1024), ("velo", 512)])
 def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
     for rows, tall in ((64, 64), (65, 64), (line, 64), (line + 1, 128), (6144, 128)):
