@@ -7,6 +7,7 @@
 
 namespace lopt {
 
+constexpr int kThinTiles = 1024;                    // short lists: row/column tiles of fewer than sixteen rows
 constexpr uint64_t kShortListFloats = 48u << 20;   // what a short list's statistics pass reads of partial sums, all workgroups together
 
 inline uint32_t pad4(uint64_t x) { return (uint32_t)((x + 3) & ~(uint64_t)3); }
@@ -85,19 +86,25 @@ inline void group_bounds(const lopt_tensor_desc* d, size_t n, int G, uint64_t to
 // row/column pass leaves per 64 or 128 rows for that purpose. us a step with that launch and without: 0.08 M elements (toy list) 29.6 /
 // 26.9, 1000x1000 45.7 / 43.8 (VeLO 57.7 / 55.0), 66 tensors of 2.4 M under VeLO 69.1 / 66.7, 2000x2000 107.8 / 104.4, ten layers of
 // 1024x1024 at width 16 191.8 / 188.8, nine of 2731x2731 under VeLO 896 / 882; no difference at 14 M elements (width 32), and 495.5 /
-// 500 for one 5000x5000 matrix, whose tiles read 63 M partial sums again: the line lies between the last two. Short lists
+// 500 for one 5000x5000 matrix, whose tiles read 63 M words of partial sums again: the line lies between the last two. (One
+// 6000x5000, 89 M words, with that launch and without, width 16 546 / 552, VeLO 428 / 428; eight of 6000x500, 69 M, 447 / 452, 342 / 348;
+// 2x4096x4096, 34 M, 602 / 598, 427 / 431.) A tile of the row/column sums is a workgroup of sixteen wavefronts, of which most idle
+// where it has fewer than sixteen rows; the chip holds 512 of these workgroups, and from a third round on they cost more than the
+// launch: vectors of 768 elements, VeLO / width 32, 340 of them (1020 such tiles) 62.7 / 61.7 and 53.7 / 53.6, 400 of them 71.3 / 72.1
+// and 59.8 / 61.6, 600 87.9 / 91.1 and 78.6 / 83.1; but 1500 of 64x64 256 / 250. Short lists
 // are never cut into tensor groups: the statistics kernel that forms the means does not fit beside the apply kernel, and groups
 // cost such lists more than they hide in either form (four tensors of 4096x2560 in two groups, that launch kept / without it / one
 // group: 749 / 774 / 738; under VeLO 641 / 579 / 549).
 inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, int shrink, bool velo) {
   if (total >= (64u << 20) || n > 4096) return false;   // 4096: the copies of r_k and c_k are no large part of a workspace
-  uint64_t floats = 0;
+  uint64_t floats = 0, thin = 0;
   for (size_t i = 0; i < n; ++i) {
     if (d[i].rows > 96 * kRowUnit || d[i].cols > 96 * kTileCols) return false;
     const uint64_t nrc = (uint64_t)ceil_div(d[i].rows, short_rows((int)d[i].rows, velo)), nct = (uint64_t)ceil_div(d[i].cols, kTileCols);
     const uint64_t tr = kRowUnit / shrink, tiles = (uint64_t)ceil_div(d[i].rows, tr) * nct;
     floats += tiles * (2 * nrc * (uint64_t)(d[i].cols < kTileCols ? d[i].cols : kTileCols) + nct * tr);
-    if (floats > kShortListFloats) return false;
+    if (d[i].rows < 16) thin += nct;
+    if (floats > kShortListFloats || thin > kThinTiles) return false;
   }
   return true;
 }

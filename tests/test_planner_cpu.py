@@ -121,6 +121,15 @@ def test_which_tiles_the_statistics_pass_leaves_in_the_cache(kind, hidden):
     assert r["short_list"] == 0 and r["backwards"] == velo and r["keep"] == (r["n_tiles"] * 10 // 64 if velo else 0)
 
 
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_lists_of_many_tiles_of_few_rows_are_no_short_lists(kind):
+    short = lambda shapes: plan(shapes, kind=kind)["short_list"]
+    assert [short([(768,)] * n) for n in (341, 342)] == [1, 0]          # three column tiles each
+    assert [short([(15, 100)] * n) for n in (1024, 1025)] == [1, 0]
+    assert short([(16, 100)] * 1500) == 1 and short([(64, 64)] * 1500 + [(20,)] * 1024) == 1
+    assert short([(64, 64)] * 1500 + [(20,)] * 1025) == 0
+
+
 @pytest.mark.parametrize("kind,line", [("small_fc_lopt", 1024), ("velo", 512)])
 def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
     for rows, tall in ((64, 64), (65, 64), (line, 64), (line + 1, 128), (6144, 128)):
@@ -132,8 +141,10 @@ def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
 
 
 def test_a_short_list_stays_within_the_fixed_scratch():
-    # vectors whose workspace (4 floats an element) fits lopt_step_static's 64 MiB: with copies of c_k (7 an element) it would not
-    vectors = [(1, 20000)] * 190
-    r = plan(vectors, hidden=4)
-    assert 48 << 20 < 4 * r["ws_floats"] < 64 << 20 and r["n_rcitems"] > 0
-    assert plan(vectors[:40], hidden=4)["n_rcitems"] == 0   # small enough for the copies
+    # wide matrices of few rows whose workspace fits lopt_step_static's 64 MiB: with copies of c_k and column sums in double it would
+    # not (69 MiB)
+    wide = [(16, 20000)] * 110
+    r, s = plan(wide, hidden=4), plan(wide[:60], hidden=4)
+    assert r["short_list"] == 0 and r["n_rcitems"] > 0
+    assert s["short_list"] == 1 and s["n_rcitems"] == 0 and 4 * s["ws_floats"] <= 48 << 20   # small enough for the copies
+    assert 4 * s["ws_floats"] * 110 / 60 > 64 << 20 and 4 * r["ws_floats"] < 48 << 20
