@@ -32,6 +32,14 @@ constexpr int kMixSlices = 64;    // at most this many slices of the tensor list
 // in one launch / ahead: one tensor 4.4 + 9.7 / 5.4 + 4.1, 66 tensors 4.4 + 10.7 / 9.2 + 4.2, 152 tensors 58 + 14 / 66 + 5.5, 502
 // tensors 25 + 26 / 68 + 7.
 constexpr int kLstmAheadMax = 96;
+// Its workgroups, kRecurTensors tensors x 8 units each, must leave room for those of the sums: the chip holds 512 of sixteen
+// wavefronts. Tensors of 64x64, us a step in one launch / ahead, H_L 1024 32 tensors (256 workgroups) 48.2 / 42.4, 48 (384) 50.3 / 51.8, 64
+// (512) 54.2 / 56.6, 80 60.9 / 67.0, 96 61.6 / 68.7; H_L 768 64 tensors (384) 49.8 / 49.7, 80 (480) 55.0 / 52.8, 96 (576) 55.7 / 59.3; H_L 512
+// 96 tensors (384) 45.8 / 46.0.
+constexpr int kRecurTensors = 16, kRecurBlocks = 512;
+inline bool lstm_ahead(size_t n, int HL) {
+  return n <= (size_t)kLstmAheadMax && ((int)n + kRecurTensors - 1) / kRecurTensors * ((HL + 7) / 8) < kRecurBlocks;
+}
 constexpr int kFinTensorsMax = 8;    // tensor lists up to this length may form the LSTM's inputs in its own launch (Plan::fold_finalize)
 constexpr int kHeadSplitMax = 96;    // tensor lists up to this length cut the hypernetwork head's product into column blocks
 constexpr int kHeadBatchMin = 1024;  // tensor lists from this length on take the batched form of the hypernetwork head

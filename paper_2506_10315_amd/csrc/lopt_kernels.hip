@@ -133,7 +133,7 @@ __device__ __forceinline__ void mix_bias_block(const MixArgs& M, int blk, float*
 // v_mfma_f32_16x16x4_f32 (exact products) on two column tiles; 32 tensors at a time would double the chain of a short list. As
 // extra workgroups of the statistics pass of a short list it is the longer side there (layer of 2000x2000 32 us instead of 26).
 // Out: z[tensor][unit block][gate, unit].
-constexpr int kRecurTensors = 16, kRecurOctets = 4;   // octets in flight per wavefront
+constexpr int kRecurOctets = 4;   // octets in flight per wavefront
 typedef float f32x16_l __attribute__((ext_vector_type(16)));
 typedef float f32x4_l __attribute__((ext_vector_type(4)));
 

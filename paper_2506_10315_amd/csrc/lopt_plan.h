@@ -49,7 +49,7 @@ struct Plan {
   std::vector<size_t> state_bytes;
   uint64_t oLstmU = 0, oHNew = 0;   // VeLO scratch (floats)
   uint64_t oHbarPart = 0, oBeff = 0; // VeLO cross-tensor term: slice sums of h, gate bias with the term added
-  uint64_t oLstmZ = 0;               // VeLO, lists of at most kLstmAheadMax tensors: h W_h of the step before, in tile order (0: not used)
+  uint64_t oLstmZ = 0;               // VeLO, lists of few tensors (lstm_ahead): h W_h of the step before, in tile order (0: not used)
   uint64_t oAlpha = 0, oTheta = 0;   // VeLO, long lists: bank coefficients [T][K] and per-tensor MLPs [T][P]
   bool head_batched = false;
   uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the apply kernel
@@ -303,10 +303,10 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     again += at * ((uint64_t)T.nrt * T.nct * kStatStride + (uint64_t)(T.nrblk + T.ncblk) * kRcStride);
   }
   pl->fold_finalize = pl->short_list && o.apply == ApplyTiles::Strip && pl->atiles.size() <= 2u * (unsigned)o.n_cu && again <= (16u << 20);
-  // h W_h depends on nothing this step computes. Up to kLstmAheadMax tensors it is formed beside the statistics; longer lists and
+  // h W_h depends on nothing this step computes. Short lists of tensors form it beside the statistics (lstm_ahead); longer ones and
   // workspaces that come near the fixed scratch of lopt_step_static go without the room for it
   pl->oLstmZ = 0;
-  if (velo && n <= (size_t)kLstmAheadMax && off <= (48u << 20) / sizeof(float))
+  if (velo && lstm_ahead(n, o.lstm_hidden) && off <= (48u << 20) / sizeof(float))
     pl->oLstmZ = take((uint64_t)n * 32 * ceil_div(o.lstm_hidden, 8));
   // VeLO: every workgroup of the LSTM launch forms all tensors' scales and inputs, where that is at most two batches of loads for
   // each of its eight half wavefronts, which share the tensors. us a step without and with: four tensors of 0.012 M elements (one batch)

@@ -130,6 +130,13 @@ def test_lists_of_many_tiles_of_few_rows_are_no_short_lists(kind):
     assert short([(64, 64)] * 1500 + [(20,)] * 1025) == 0
 
 
+@pytest.mark.parametrize("lstm_hidden,most", [(512, 96), (680, 96), (681, 80), (768, 80), (1024, 48), (9, 96)])
+def test_the_recurrent_product_is_formed_ahead_where_it_leaves_room_for_the_sums(lstm_hidden, most):
+    # up to 96 tensors and fewer than 512 workgroups of 16 tensors x 8 units
+    ahead = lambda n: plan([(20, 20)] * n, kind="velo", lstm_hidden=lstm_hidden)["lstm_ahead"]
+    assert [ahead(n) for n in (1, most, most + 1)] == [1, 1, 0]
+
+
 @pytest.mark.parametrize("kind,line", [("small_fc_lopt", 1024), ("velo", 512)])
 def test_column_sums_of_short_lists_are_doubles_of_64_or_128_rows(kind, line):
     for rows, tall in ((64, 64), (65, 64), (line, 64), (line + 1, 128), (6144, 128)):
