@@ -847,7 +847,7 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
   if (T.vec == 2 && idx < keep) accum_tile_vec<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   else if (T.vec) accum_tile_vec<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
-  else if (idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  else if (!FUSE || idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);   // long lists: all of them
   else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
