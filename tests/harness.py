@@ -146,7 +146,7 @@ def gpu_hidden_mean(opt):
 
 
 def run_free(case: Case, cfg, weights, steps, lr_fn=lambda t: 1.0, wd=0.0, check_every=1, device="cuda:0",
-             check_stats=True, verbose=False, loss_fn=None, static=False):
+             check_stats=True, verbose=False, loss_fn=None, static=False, tol_delta=TOL_DELTA):
     """Free-running parity: GPU and oracle both start from (p0, zero state) and take `steps` steps over the whole list
     on the same gradients (and loss values); parameters, the update itself, accumulators and statistics are compared
     after every `check_every` steps."""
@@ -184,7 +184,7 @@ def run_free(case: Case, cfg, weights, steps, lr_fn=lambda t: 1.0, wd=0.0, check
                 assert e <= TOL_PARAM, f"{tag}: parameter rel err {e:.3e}"
                 e = delta_err(old_gpu[i], new_gpu, old_ora[i], p_ora[i])
                 worst["delta"] = max(worst["delta"], e)
-                assert e <= TOL_DELTA, f"{tag}: update rel err {e:.3e}"
+                assert e <= tol_delta, f"{tag}: update rel err {e:.3e}"
                 worst["acc"] = max(worst["acc"], compare_state(gpu_state_to_numpy(opt, i), st_ora[i], tag))
                 if check_stats:
                     k = ocfg.n_normalized
