@@ -238,7 +238,7 @@ lopt_status lopt_stats_offsets(const lopt_ctx* ctx, size_t n, const lopt_tensor_
                                size_t* offsets_bytes);
 
 /* Per-pass timing for benchmarks. lopt_step is a fixed sequence of LOPT_N_PASSES kernel launches
- * (a pass that a configuration does not use records zero time):
+ * (a pass that a configuration or a tensor list does without records zero time; its work is then part of the one behind it):
  *   0 rowcol_sums  1 rc_update  2 accum_stats  3 finalize  4 velo_lstm  5 velo_head  6 apply
  * With profiling enabled, lopt_step runs every pass over the whole list on the caller's stream (no
  * tensor groups, no second stream) and brackets every launch with HIP events on that stream.
