@@ -63,7 +63,7 @@ def test_two_runs_are_bit_identical(kind, shapes):
 @pytest.mark.parametrize("shapes", [SHAPES, TALL])
 def test_groups_field_of_the_configuration_selects_the_plan_per_context(shapes):
     # two contexts in one process, one with every pass over the whole list on one stream, one with three tensor groups
-    # on two streams: same bits (the selection is per context, no environment involved)
+    # on two streams (a short list stays on one): same bits (the selection is per context, no environment involved)
     import torch
     import paper_2506_10315_amd as P
     outs = []
@@ -142,7 +142,7 @@ def test_state_pass_changes_no_bit_on_full_tiles(kind, hidden, shapes):
 @pytest.mark.parametrize("groups", [2, 3, 16])
 def test_group_pipeline_is_bit_identical_to_one_stream(groups, shapes, monkeypatch):
     # LOPT_GROUPS (read when the context is created) cuts the list into tensor groups whose HBM-bound passes run on
-    # the library's second stream beside the previous group's apply pass. The same kernels see the same tiles, so
+    # the library's second stream beside the previous group's apply pass (a short list stays whole). The same kernels see the same tiles, so
     # the results must not change by a single bit, on the default stream and on a stream of the caller's.
     import torch
     monkeypatch.setenv("LOPT_GROUPS", "1")
