@@ -321,6 +321,7 @@ __global__ void __launch_bounds__(kBlock, narrow_waves_per_simd(HP)) k_apply_fc4
     if (T.vec == 2) apply_fc4x_tile<HP, true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A, tail, L);
     else apply_fc4x_tile<HP, false, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A, tail, L);
     __syncthreads();   // every wavefront is done with this tile's tables and has read s_tile
+    if (n_atiles <= (int)gridDim.x) break;   // one tile each: nobody asks (see k_apply_f16s)
     if (threadIdx.x == 0) s_tile = (int)gridDim.x + atomicAdd(next_tile, 1);
     __syncthreads();
   }
