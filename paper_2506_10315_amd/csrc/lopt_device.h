@@ -48,6 +48,31 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 typedef float f32x4n __attribute__((ext_vector_type(4)));
 
+// Four columns of a row segment of a streamed array. `seg`: the segment's first element, wave-uniform; `off`: this lane's offset in
+// BYTES. The access goes through a buffer descriptor of `bytes` bytes, what is left of the row: scalar base + 32-bit vector offset, and
+// the hardware checks every dword by itself, so that columns past the row's end read as 0 and are not written. Rows may start
+// anywhere: a four-dword access needs only the dword's alignment. Off the grid a wavefront's access touches nine 128-byte lines, on it
+// eight; one dword per lane and column touches three lines for every two.
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4v __attribute__((ext_vector_type(4)));
+
+// Bytes of a row from column c0 on, as far as a 256-column segment reaches.
+__device__ __forceinline__ unsigned segment_bytes(int n, int c0) { return 4u * (unsigned)min(n - c0, kTileCols); }
+
+template <bool NT>
+constexpr int kBufferAux = NT ? 2 : 0;   // nontemporal
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t segment_rsrc(const float* seg, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)seg, 0, (int)bytes, 0x00020000);   // raw buffer, 32-bit data
+}
+template <bool NT>
+__device__ __forceinline__ f32x4v load_quad(const float* seg, unsigned off, unsigned bytes) {
+  return __builtin_bit_cast(f32x4v, __builtin_amdgcn_raw_buffer_load_b128(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>));
+}
+template <bool NT>
+__device__ __forceinline__ void store_quad(float* seg, unsigned off, unsigned bytes, f32x4v v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4v, v), segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>);
+}
+
 // Load four consecutive floats starting at column `col` of a row of length n whose first
 // element is at `row`. VEC: the address is 16-byte aligned and n % 4 == 0.
 template <bool VEC>

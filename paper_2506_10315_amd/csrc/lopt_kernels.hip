@@ -17,10 +17,9 @@
 //                  matrix-core variant for hidden width 32)
 // Short lists do without rc_update (k_rowcol_short leaves fewer partials, accum_stats finishes the means: fuse_means), the shortest
 // also without finalize (the apply or LSTM launch reduces its partials itself: lopt_finalize.h).
-// A tile is TR rows x 256 columns, and row indices are wave-uniform everywhere. Rows on the 16-byte grid: lane l holds the four
-// consecutive columns 4l..4l+3 as one float4 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply
-// passes in the order of row_walk. Other rows: lane l holds column l of a 64-column segment and
-// a wavefront stays on one segment (the row/column sums: on all four in turn).
+// A tile is TR rows x 256 columns, and row indices are wave-uniform everywhere. Lane l holds the four consecutive columns
+// 4l..4l+3 and a wavefront takes whole rows of the tile, in the statistics and VeLO apply passes in the order of row_walk; the
+// sums and the statistics read rows off the 16-byte grid the same way (load_quad).
 #include <stddef.h>
 
 #include <type_traits>
@@ -213,31 +212,23 @@ static MixArgs make_mix(const Launch& L, const StepArgs& A, const WeightsDev& W,
 
 // ----------------------------------------------------------------------------- rowcol_sums
 
-template <bool VEC>
+// NT: nontemporal loads.
+template <bool NT>
 __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                             float (*colred)[kTileCols]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int R = VEC ? 2 : 4;   // rows in flight per wavefront
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int R = 2;   // rows in flight per wavefront
   const int n = T.n, m = T.m;
   const int c0 = tile.tj * kTileCols;
-  // g of one row: aligned rows, columns 4 lane .. 4 lane + 3 as one float4; other rows, columns lane + 64 e (coalesced dwords)
-  auto row4 = [&](unsigned r) __attribute__((always_inline)) {
-    const float* __restrict__ row = T.g + (size_t)r * (unsigned)n;
-    if (VEC) return load4s<true>(row, c0 + 4 * lane, n);
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int c = c0 + e * kWave + lane;
-      v[e] = row[min(c, n - 1)];   // columns past the end: a valid address, counted as 0
-      v[e] = c < n ? v[e] : 0.f;
-    }
-    return make_float4(v[0], v[1], v[2], v[3]);
+  const unsigned bytes = segment_bytes(n, c0);
+  auto row4 = [&](unsigned r) __attribute__((always_inline)) {   // past the last column: zeros
+    return load_quad<NT>(T.g + ((size_t)r * (unsigned)n + c0), 16u * lane, bytes);
   };
   const auto [r0, r1] = tile_rows(T, tile);
   float* __restrict__ rowpart = ws + T.oRowPart + (size_t)tile.tj * m;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   for (unsigned r = r0 + wave; r < r1; r += 4 * R) {
-    float4 v[R];
+    f32x4v v[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) v[i] = row4(min(r + 4 * i, r1 - 1));   // rows past the tile: its last row, counted as 0
     float sum[R];
@@ -254,11 +245,7 @@ __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& t
         if (r + 4 * i < r1) rowpart[r + 4 * i] = sum[i];
     }
   }
-  const int cl = VEC ? 4 * lane : lane, cs = VEC ? 1 : kWave;
-  colred[wave][cl] = s0;
-  colred[wave][cl + cs] = s1;
-  colred[wave][cl + 2 * cs] = s2;
-  colred[wave][cl + 3 * cs] = s3;
+  *reinterpret_cast<float4*>(&colred[wave][4 * lane]) = make_float4(s0, s1, s2, s3);
   __syncthreads();
   const int c = tile.tj * kTileCols + threadIdx.x;
   if (c < n) {
@@ -270,7 +257,7 @@ __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& t
 __global__ void __launch_bounds__(kBlock) k_rowcol_sums(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
                                                         int n_tiles, MixArgs M, int n_recur) {
-  __shared__ union { float col[4][kTileCols], hbar[4][kWave], z[4][kRecurTensors][32]; } red;
+  __shared__ union alignas(16) { float col[4][kTileCols], hbar[4][kWave], z[4][kRecurTensors][32]; } red;
   const int blk = (int)blockIdx.x - n_recur;
   if (blk < 0) {   // the extra workgroups of a VeLO step: recurrent product, slice sums of the LSTM outputs
     lstm_recur_block<4>(tensors, M, (int)blockIdx.x, red.z);
@@ -284,7 +271,7 @@ __global__ void __launch_bounds__(kBlock) k_rowcol_sums(const TensorDev* __restr
   const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
   if (T.vec) rowcol_tile<true>(T, tile, ws, colred);
-  else rowcol_tile<false>(T, tile, ws, colred);
+  else rowcol_tile<false>(T, tile, ws, colred);   // off the grid neighbours share lines
 }
 
 void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
@@ -310,29 +297,18 @@ __device__ __forceinline__ auto short_colpart(const TensorDev& T, F* ws) {
 }
 
 // R: rows per wavefront.
-template <bool VEC, int R>
+template <int R>
 __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                   float (*colred)[kTileCols]) {
   constexpr int kRows = R * kShortWaves;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = T.n, m = T.m, c0 = tile.tj * kTileCols;
   const int r0 = tile.ti * kRows, r1 = min(r0 + kRows, m);
-  float4 v[R];
+  f32x4v v[R];
+  const unsigned bytes = segment_bytes(n, c0);
 #pragma unroll
-  for (int i = 0; i < R; ++i) {   // rows past the tile: its last row, counted as 0
-    const float* __restrict__ row = T.g + (size_t)min(r0 + wave + kShortWaves * i, r1 - 1) * (unsigned)n;
-    if (VEC) v[i] = load4<true>(row, c0 + 4 * lane, n);
-    else {
-      float x[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int c = c0 + e * kWave + lane;
-        x[e] = row[min(c, n - 1)];
-        x[e] = c < n ? x[e] : 0.f;
-      }
-      v[i] = make_float4(x[0], x[1], x[2], x[3]);
-    }
-  }
+  for (int i = 0; i < R; ++i)   // rows past the tile: its last row, counted as 0
+    v[i] = load_quad<false>(T.g + ((size_t)min(r0 + wave + kShortWaves * i, r1 - 1) * (unsigned)n + c0), 16u * lane, bytes);
   const float* rst = T.st + 4 * (size_t)T.padN;   // r_k[3][padm], c_k[3][padn]
   const int t = threadIdx.x;
   if (tile.tj == 0 && t < 3 * kRows) {
@@ -354,8 +330,7 @@ __device__ __forceinline__ void rowcol_short_tile(const TensorDev& T, const Tile
       if (lane == 0) ws[T.oRowPart + (size_t)tile.tj * m + r] = sum;
     }
   }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) colred[wave][VEC ? 4 * lane + e : lane + kWave * e] = s[e];
+  *reinterpret_cast<float4*>(&colred[wave][4 * lane]) = make_float4(s[0], s[1], s[2], s[3]);
   __syncthreads();
   const int c = c0 + t;
   if (t < kTileCols && c < n) {
@@ -374,7 +349,7 @@ __global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const Tens
                                                                       const TileDev* __restrict__ tiles, float* __restrict__ ws,
                                                                       int n_tiles, MixArgs M, int n_recur, int* __restrict__ counters) {
   if (blockIdx.x == 0 && threadIdx.x < kMaxGroups) counters[threadIdx.x] = 0;   // k_finalize does it on other lists
-  __shared__ union { float col[kShortWaves][kTileCols], hbar[4][kWave], z[kShortWaves][kRecurTensors][32]; } red;
+  __shared__ union alignas(16) { float col[kShortWaves][kTileCols], hbar[4][kWave], z[kShortWaves][kRecurTensors][32]; } red;
   const int blk = (int)blockIdx.x - n_recur;
   if (blk < 0) {
     lstm_recur_block<kShortWaves>(tensors, M, (int)blockIdx.x, red.z);
@@ -388,13 +363,8 @@ __global__ void __launch_bounds__(kWave * kShortWaves) k_rowcol_short(const Tens
   const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
   constexpr int R = 64 / kShortWaves;
-  if (short_rows(T.m, M.n_slices > 0) == 64) {
-    if (T.vec) rowcol_short_tile<true, R>(T, tile, ws, colred);
-    else rowcol_short_tile<false, R>(T, tile, ws, colred);
-  } else {
-    if (T.vec) rowcol_short_tile<true, 2 * R>(T, tile, ws, colred);
-    else rowcol_short_tile<false, 2 * R>(T, tile, ws, colred);
-  }
+  if (short_rows(T.m, M.n_slices > 0) == 64) rowcol_short_tile<R>(T, tile, ws, colred);
+  else rowcol_short_tile<2 * R>(T, tile, ws, colred);
 }
 
 void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
@@ -591,6 +561,9 @@ __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& ti
       L.c[k][t] = v;
       L.rc[k][t] = rsqrtf(v + A.eps_acc);
     }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) L.rc[k][t] = 0.f;   // columns past the last one of a ragged row
   }
   __syncthreads();
 }
@@ -634,132 +607,45 @@ __device__ __forceinline__ void fuse_store(const TensorDev& T, const TileDev& ti
 // against 0.670 plain/plain, 0.670 plain/nontemporal, 0.680 nontemporal/nontemporal); what is worth keeping in the cache for
 // the apply pass is read with ordinary loads (choose_loads in lopt_plan.h).
 
-// Rows that are not 16-byte aligned (n % 4 != 0): one column per lane, every access a coalesced dword of a 256-byte row
-// segment, kAccRows rows of loads in flight. The wavefronts of the tile sit on adjacent 64-column segments; where the tile
-// is narrower than three segments they share out its rows as well. RAW_RCP as in the aligned path below.
-// (Three segments leave the fourth wavefront without work.)
-// Kept small in registers on purpose: the kernel's register count is the larger of its two paths, and it decides how
-// many of its workgroups fit beside the apply kernel of another tensor group (the float4 path's count, with four rows
-// too). 8.3 M elements of 1531 columns: 48 us with one row per trip and nontemporal loads, 41 us.
-constexpr int kAccRows = 4;
-
-// NT: nontemporal loads (Plan::keep).
-template <bool NT, typename P>
-__device__ __forceinline__ auto load_nt(P p) { return NT ? __builtin_nontemporal_load(p) : *p; }
-
-template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
-__device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
-                                           const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
-  if (FUSE) fuse_means(T, tile, ws, A, *L);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = T.n;
-  const int c0 = tile.tj * kTileCols;
-  const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
-  const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
-  const int seg = wave / rsplit;
-  const int c = c0 + seg * kWave + lane;
-  if (seg >= nseg || c >= n) return;
-  const auto [r0, r1] = tile_rows(T, tile);
-  const size_t pN = T.padN;
-  const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
-  const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
-  const float eps = A.eps_acc;
-  float rc[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) rc[k] = FUSE ? L->rc[k][c - c0] : ws[T.oRC + (size_t)k * T.padn + c];
-  for (unsigned r = r0 + kAccRows * (wave % rsplit); r < r1; r += kAccRows * rsplit) {
-    float in[kAccRows][6];
-#pragma unroll
-    for (int e = 0; e < kAccRows; ++e) {   // a row past the tile reads the tile's last row and counts for nothing
-      const size_t ro = (size_t)min(r + e, r1 - 1) * (unsigned)n + c;
-      in[e][0] = load_nt<NT>(T.g + ro);
-      in[e][1] = load_nt<NT>(T.p + ro);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) in[e][2 + k] = load_nt<NT>(T.st + (k * pN + ro));
-    }
-#pragma unroll
-    for (int e = 0; e < kAccRows; ++e) {
-      if (r + e >= r1) break;   // wavefront-uniform
-      const size_t ro = (size_t)(r + e) * (unsigned)n + c;
-      const float g = in[e][0], p = in[e][1], g2 = g * g;
-      // explicit fused multiply-adds: the apply pass may form the same values again (lopt_state_pass), bit for bit
-      const float nm1 = __builtin_fmaf(b1, in[e][2], a1 * g);
-      const float nm2 = __builtin_fmaf(b2, in[e][3], a2 * g);
-      const float nm3 = __builtin_fmaf(b3, in[e][4], a3 * g);
-      const float nv = __builtin_fmaf(b4, in[e][5], a4 * g2);
-      const float rs = RAW_RCP ? __builtin_amdgcn_rsqf(nv + eps) : rsqrtf(nv + eps);
-      float f[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) f[k] = (FUSE ? L->rr[k][r + e - r0] : ws[T.oRR + (size_t)k * T.padm + r + e]) * rc[k];
-      const float gc = fminf(fmaxf(g, -0.1f), 0.1f);
-      float t;
-      acc[0] += g2;
-      acc[1] += p * p;
-      acc[2] += nm1 * nm1;
-      acc[3] += nm2 * nm2;
-      acc[4] += nm3 * nm3;
-      acc[5] += nv * nv;
-      t = nm1 * rs; acc[6] += t * t;
-      t = nm2 * rs; acc[7] += t * t;
-      t = nm3 * rs; acc[8] += t * t;
-      acc[9] += rs * rs;
-      t = g * f[0]; acc[10] += t * t;
-      t = g * f[1]; acc[11] += t * t;
-      t = g * f[2]; acc[12] += t * t;
-      t = nm1 * f[0]; acc[13] += t * t;
-      t = nm2 * f[1]; acc[14] += t * t;
-      t = nm3 * f[2]; acc[15] += t * t;
-      acc[16] += gc * gc;
-      if (WRITE) {
-        T.st[ro] = nm1;
-        T.st[pN + ro] = nm2;
-        T.st[2 * pN + ro] = nm3;
-        T.st[3 * pN + ro] = nv;
-      }
-    }
-  }
-}
-
-// The same pass for tensors whose rows are 16-byte aligned (n % 4 == 0), which is nearly all of the work: a lane's
-// four columns are either all inside the tensor or all outside, so lanes past the last column sit the tile out
-// and nothing in the loop is predicated. The sums of squares are taken in the form that needs the fewest vector
+// A lane holds four consecutive columns of a row; lanes past the last column sit the tile out and nothing in the loop is
+// predicated. The sums of squares are taken in the form that needs the fewest vector
 // instructions: (M_i rsqrt(V+eps))^2 = M_i^2 / (V+eps), (g a_i b_j)^2 = g^2 a_i^2 b_j^2 (squared row and column
 // factors are formed once per row / per tile), clip(g, +-0.1)^2 = min(g^2, 0.01). RAW_RCP: the bare v_rcp_f32 (it
 // treats inputs below the smallest normal float as zero, so the launcher asks for it only when eps_acc >= 1e-30).
-typedef float __attribute__((ext_vector_type(4))) f32x4v;
-typedef const f32x4v __attribute__((address_space(1)))* gcv4;
-typedef f32x4v __attribute__((address_space(1)))* gv4;
-
+// In the last lane of a ragged row the columns past the end hold zeros, which add nothing to any sum but that of 1/(V+eps), which is set
+// to zero there. Rows off the 16-byte grid, four columns a lane against one column a lane in 64-column segments, us a step: 8.3 M
+// elements of 1531 columns 189 -> 183, width 16 143 -> 135.5, VeLO 153 -> 147.5; 54 M of 2731 columns under VeLO 838 -> 811 (with the
+// sums); 0.4 M under VeLO 37 -> 34.3. NT: nontemporal loads (Plan::keep).
 template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
-__device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
+__device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
   const int lane = threadIdx.x & 63;
   const int n = T.n;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const RowWalk w = FUSE ? plain_walk(T, tile, wave) : row_walk(T, tile, wave);   // FUSE: the means in LDS are the tile's own
-  const int col = w.tj * kTileCols + 4 * lane;
-  const bool mine = col < n && w.cnt > 0;
+  const int c0 = w.tj * kTileCols, col = c0 + 4 * lane, ncol = n - col;   // ncol: 4 or more but in a ragged row's last lane and beyond it
+  const unsigned bytes = segment_bytes(n, c0);
+  const bool mine = ncol > 0 && w.cnt > 0;
   if (!FUSE && !mine) return;
   // The first row's loads leave before the column factors are waited for: a short list's tile is one or two rows a wavefront
   // (toy list of three tensors 30.3 -> 29.6 us a step, 1000x1000 46.5 -> 45.6). The read-only form also needs 63 registers
   // this way instead of 66: eight wavefronts per SIMD (ViT-B/16 shapes beside the apply pass 1.488 -> 1.472 ms a step).
-  f32x4v g4, p4, m1, m2, m3, v4;
-  size_t ro;
-  int r;
+  struct Row { f32x4v g4, p4, m1, m2, m3, v4; size_t ro; int r; };
   const size_t pN = T.padN;
-  auto load = [&](int i) __attribute__((always_inline)) {
-    r = walk_row(w, i);
-    ro = (size_t)r * n + col;   // a multiple of 4: every section starts 16-byte aligned
-    g4 = load_nt<NT>((gcv4)(T.g + ro));
-    p4 = load_nt<NT>((gcv4)(T.p + ro));
-    m1 = load_nt<NT>((gcv4)(T.st + ro));
-    m2 = load_nt<NT>((gcv4)(T.st + pN + ro));
-    m3 = load_nt<NT>((gcv4)(T.st + 2 * pN + ro));
-    v4 = load_nt<NT>((gcv4)(T.st + 3 * pN + ro));
+  auto load = [&](int i, Row& x) __attribute__((always_inline)) {
+    x.r = walk_row(w, i);
+    const size_t ro = x.ro = (size_t)x.r * n + c0;   // rows on the grid: a multiple of 4, and every section starts 16-byte aligned
+    x.g4 = load_quad<NT>(T.g + ro, 16u * lane, bytes);
+    x.p4 = load_quad<NT>(T.p + ro, 16u * lane, bytes);
+    x.m1 = load_quad<NT>(T.st + ro, 16u * lane, bytes);
+    x.m2 = load_quad<NT>(T.st + pN + ro, 16u * lane, bytes);
+    x.m3 = load_quad<NT>(T.st + 2 * pN + ro, 16u * lane, bytes);
+    x.v4 = load_quad<NT>(T.st + 3 * pN + ro, 16u * lane, bytes);
   };
+  Row row;
   float4 c3[3];
   if (FUSE) {
-    if (mine) load(0);
+    if (mine) load(0, row);
     fuse_means(T, tile, ws, A, *L);
     if (!mine) return;
 #pragma unroll
@@ -767,19 +653,23 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
   } else {
 #pragma unroll
     for (int k = 0; k < 3; ++k) c3[k] = *reinterpret_cast<const float4*>(ws + T.oRC + (size_t)k * T.padn + col);
-    load(0);
+    load(0, row);
   }
   float rc2[3][4];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float4 c = c3[k];
     rc2[k][0] = c.x * c.x; rc2[k][1] = c.y * c.y; rc2[k][2] = c.z * c.z; rc2[k][3] = c.w * c.w;
+    if (!FUSE)   // (LDS holds zeros there)
+#pragma unroll
+      for (int e = 1; e < 4; ++e) rc2[k][e] = e < ncol ? rc2[k][e] : 0.f;
   }
   const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
   const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
   const float eps = A.eps_acc;
   const float clip2 = 0.1f * 0.1f;
-  for (int i = 0;;) {
+  auto add = [&](const Row& x) __attribute__((always_inline)) {
+    const auto& [g4, p4, m1, m2, m3, v4, ro, r] = x;
     float rr2[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -798,7 +688,8 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
       const float nv = __builtin_fmaf(b4, v4[e], a4 * g2);
       o1[e] = nm1; o2[e] = nm2; o3[e] = nm3; ov[e] = nv;
       const float s1 = nm1 * nm1, s2 = nm2 * nm2, s3 = nm3 * nm3;
-      const float rs2 = RAW_RCP ? __builtin_amdgcn_rcpf(nv + eps) : 1.0f / (nv + eps);
+      float rs2 = RAW_RCP ? __builtin_amdgcn_rcpf(nv + eps) : 1.0f / (nv + eps);
+      if (e > 0) rs2 = e < ncol ? rs2 : 0.f;
       const float f0 = rr2[0] * rc2[0][e], f1 = rr2[1] * rc2[1][e], f2 = rr2[2] * rc2[2][e];
       acc[0] += g2;
       acc[1] += p * p;
@@ -811,13 +702,23 @@ __device__ __forceinline__ void accum_tile_vec(const TensorDev& T, const TileDev
       acc[16] += fminf(g2, clip2);
     }
     if (WRITE) {
-      *(gv4)(T.st + ro) = o1;
-      *(gv4)(T.st + pN + ro) = o2;
-      *(gv4)(T.st + 2 * pN + ro) = o3;
-      *(gv4)(T.st + 3 * pN + ro) = ov;
+      store_quad<false>(T.st + ro, 16u * lane, bytes, o1);
+      store_quad<false>(T.st + pN + ro, 16u * lane, bytes, o2);
+      store_quad<false>(T.st + 2 * pN + ro, 16u * lane, bytes, o3);
+      store_quad<false>(T.st + 3 * pN + ro, 16u * lane, bytes, ov);
     }
+  };
+  for (int i = 0;;) {
+    add(row);
+    // Beside the apply pass of another tensor group there is room for 64 registers: the sums are pinned here, or the compiler
+    // moves the next row's loads in front of them (95 registers, ViT-B/16 shapes 1.472 -> 1.547 ms a step). Without such a
+    // neighbour that order is as good or 1 % better.
+    if (!FUSE)
+      asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
+                   "+v"(acc[7]), "+v"(acc[8]), "+v"(acc[9]), "+v"(acc[10]), "+v"(acc[11]), "+v"(acc[12]), "+v"(acc[13]),
+                   "+v"(acc[14]), "+v"(acc[15]), "+v"(acc[16]) :: "memory");
     if (++i >= w.cnt) break;
-    load(i);
+    load(i, row);
   }
 }
 
@@ -845,9 +746,8 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  if (T.vec == 2 && idx < keep) accum_tile_vec<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
-  else if (T.vec) accum_tile_vec<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
-  else if (!FUSE || idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);   // long lists: all of them
+  // rows off the 16-byte grid of long lists: ordinary loads for all tiles
+  if (T.vec == 2 ? idx < keep : T.vec == 0 && (!FUSE || idx < keep_off)) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);

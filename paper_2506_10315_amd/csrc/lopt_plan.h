@@ -238,7 +238,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     const int min_tr = (ceil_div(m, max_rt) + 7) & ~7;
     if (T.TR < min_tr) T.TR = min_tr;
     // ... unless that makes a tile taller than kMaxTileRows: a lane sums up to kMaxTileRows values in fp32 (a quarter of the
-    // tile's rows at four values each, or on rows off the 16-byte grid every row of a segment at one), and such a partial
+    // tile's rows at four values each), and such a partial
     // sum must stay at about a thousand terms. Tensors of more than kMaxRowTiles * kMaxTileRows rows get more row tiles instead.
     if (T.TR > kMaxTileRows) T.TR = kMaxTileRows;
     T.nrt = ceil_div(m, T.TR);
