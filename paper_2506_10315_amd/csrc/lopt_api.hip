@@ -218,7 +218,7 @@ lopt_status ensure_plan(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* d) {
 // tables fit both).
 lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   Plan& pl = ctx->plan;
-  const size_t nT = pl.tensors.size(), nTi = pl.tiles.size(), nRc = pl.rcitems.size(), nRt = pl.rctiles.size(),
+  const size_t nT = pl.tensors.size(), nTi = pl.tiles.size(), nRc = pl.rc_blocks().size(), nRt = pl.rctiles.size(),
                nAt = pl.atiles.size();
   const size_t bT = align64(nT * sizeof(TensorDev)), bTi = align64(nTi * sizeof(TileDev)),
                bRc = align64(nRc * sizeof(RcItemDev)), bRt = align64(nRt * sizeof(TileDev)), bAt = align64(nAt * sizeof(ApplyTileDev));
@@ -261,7 +261,7 @@ lopt_status upload_tables(lopt_ctx* ctx, TableStore& st, hipStream_t stream) {
   size_t send = nT * sizeof(TensorDev);
   if (need_static) {
     memcpy(hbase + bT, pl.tiles.data(), nTi * sizeof(TileDev));
-    memcpy(hbase + bT + bTi, pl.rcitems.data(), nRc * sizeof(RcItemDev));
+    memcpy(hbase + bT + bTi, pl.rc_blocks().data(), nRc * sizeof(RcItemDev));
     memcpy(hbase + bT + bTi + bRc, pl.rctiles.data(), nRt * sizeof(TileDev));
     memcpy(hbase + bT + bTi + bRc + bRt, pl.atiles.data(), nAt * sizeof(ApplyTileDev));
     send = bT + bTi + bRc + bRt + nAt * sizeof(ApplyTileDev);
@@ -568,7 +568,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   if (st != LOPT_OK) return st;
   const TableStore& tb = ctx->heap;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
-           (int)ctx->plan.rcitems.size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false};
+           (int)ctx->plan.rc_blocks().size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false};
   StepArgs A = make_args(ctx, 0, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
@@ -640,7 +640,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool rows_ok = pl.max_rows <= 0x7fffffff - 63;
   bool strip_ok = rows_ok && mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
-  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rcitems.size(),
+  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rc_blocks().size(),
            tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0,
            tb.d_rctiles, (int)pl.rctiles.size(), pl.short_list, pl.keep, pl.keep_off, pl.backwards};
   // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the

@@ -65,7 +65,7 @@ struct TensorDev {
   uint32_t ndim;
   int vec;                          // 0: rows are not 16-byte aligned, 1: they are (n % 4 == 0), 2: 128-byte aligned (n % 32 == 0)
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
-  int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks (short lists: one per statistics tile row)
+  int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2
   uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [ceil(m / short_rows)][n], double)
   uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc); short lists: then r_k [3][padm] as the step found them
@@ -121,7 +121,7 @@ inline bool head_folds(int HL, int K, int P) { return K >= 4 && (size_t)HL * P <
 struct Launch {
   const TensorDev* tensors;
   const TileDev* tiles;
-  const RcItemDev* rcitems;
+  const RcItemDev* rcitems;   // row and column blocks: workgroups of k_rc_update, on short lists of the statistics pass
   float* ws;
   int n_tensors, n_tiles, n_rcitems;
   const ApplyTileDev* atiles;

@@ -378,21 +378,48 @@ void launch_rowcol_short(const Launch& L, const StepArgs& A, const WeightsDev& W
 
 // ----------------------------------------------------------------------------- rc_update
 
-// Sums over the workgroup's first four wavefronts (256 threads) of NV values per thread, to out[0..NV).
+// Sums over the workgroup's first four wavefronts (256 threads) of NV values per thread, to out[0..NV). A tree throughout: four values
+// are folded into one register while the four lanes of a quad are added up (lane l ends with value l & 3), the quads of a row
+// of 16 lanes by rotations, the sixteen rows in LDS. A tree per value over the whole wavefront takes three times the instructions, and
+// on a short list they are a fifth of the statistics pass (toy list of three tensors: 1.1 of 6.8 us, now 0.5).
+constexpr int kRedStride = 20;   // floats: sixteen rows, and two lanes at most on a bank
 template <int NV>
-__device__ __forceinline__ void block_sum(float (&v)[NV], float (*red)[4], float* out) {
+__device__ __forceinline__ void block_sum(const float (&v)[NV], float (*red)[kRedStride], float* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int N16 = NV < 16 ? NV : 16, Q = (N16 + 3) / 4;
   if (wave < 4) {
+    const int row = 4 * wave + (lane >> 4), q = lane & 15;
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float s[4];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      float s = wave_sum(v[q]);
-      if (lane == 0) red[q][wave] = s;
+    for (int i = 0; i < 4; ++i) {
+      if (i >= Q) { s[i] = 0.f; continue; }
+      const float x0 = v[4 * i], x1 = 4 * i + 1 < N16 ? v[4 * i + 1] : 0.f;
+      const float x2 = 4 * i + 2 < N16 ? v[4 * i + 2] : 0.f, x3 = 4 * i + 3 < N16 ? v[4 * i + 3] : 0.f;
+      const float y0 = (b0 ? x1 : x0) + dpp_f<0xB1>(b0 ? x0 : x1);   // lane ^ 1
+      const float y1 = (b0 ? x3 : x2) + dpp_f<0xB1>(b0 ? x2 : x3);
+      float t = (b1 ? y1 : y0) + dpp_f<0x4E>(b1 ? y0 : y1);          // lane ^ 2
+      t += dpp_f<0x124>(t);                                          // rotations by 4 and 8 within the row
+      s[i] = t + dpp_f<0x128>(t);
+    }
+    const float lo = lane & 4 ? s[1] : s[0], hi = lane & 4 ? s[3] : s[2];
+    if (q < N16) red[q][row] = lane & 8 ? hi : lo;
+#pragma unroll
+    for (int j = 16; j < NV; ++j) {
+      float t = v[j];
+      t += dpp_f<0xB1>(t);
+      t += dpp_f<0x4E>(t);
+      t += dpp_f<0x124>(t);
+      t += dpp_f<0x128>(t);
+      if (q == 0) red[j][row] = t;
     }
   }
   __syncthreads();
   if (threadIdx.x < NV) {
-    const int q = threadIdx.x;
-    out[q] = (red[q][0] + red[q][1]) + (red[q][2] + red[q][3]);
+    const float4* r = reinterpret_cast<const float4*>(red[threadIdx.x]);
+    float4 a = r[0], b = r[1], c = r[2], d = r[3];
+    out[threadIdx.x] = (((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w))) +
+                       (((c.x + c.y) + (c.z + c.w)) + ((d.x + d.y) + (d.z + d.w)));
   }
 }
 
@@ -432,7 +459,7 @@ constexpr int kRcMaxThreads = 4 * kBlock;
 __global__ void __launch_bounds__(kRcMaxThreads) k_rc_update(const TensorDev* __restrict__ tensors,
                                                       const RcItemDev* __restrict__ items, float* __restrict__ ws,
                                                       StepArgs A, int n_items, MixArgs M) {
-  __shared__ float red[9][4];
+  __shared__ __align__(16) float red[9][kRedStride];
   __shared__ double tree[kRcMaxThreads];
   if ((int)blockIdx.x >= n_items) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
     __shared__ float hbar[1024];
@@ -508,12 +535,27 @@ void launch_rc_update(const Launch& L, const StepArgs& A, const WeightsDev& W, f
 // ----------------------------------------------------------------------------- accum_stats
 
 // Short lists: the row and column means that k_rc_update finishes on others, formed by every statistics workgroup for its own
-// rows and columns (the sums in double, in index order); the workgroups of the first tile column and of the first tile row
-// also write them, with their partial sums (fuse_store).
+// rows and columns (the sums in double, in index order). The new r_k and c_k and their partial sums are written by workgroups of
+// their own (short_rc_block): at the end of the tiles of the first row and column they made the launch 1.1 to 2.2 us longer. They
+// come behind the tiles where the chip holds those at once, and in front where it does not and they would be its last round (us a
+// step under VeLO, in front / behind, 6 tensors of 0.33 M elements 33.8 / 33.2, 66 of 2.4 M, 1180 tiles, 59.0 / 55.8, 4 M, 2000 tiles,
+// 75.1 / 75.1; 17 M, 4200 tiles, 191 / 196).
 struct alignas(16) FuseLds {
-  float r[3][kShortRows], rr[3][kShortRows];   // r_k of the tile's rows, rsqrt(r_k + eps)
-  float c[3][kTileCols], rc[3][kTileCols];
+  float rr[3][kShortRows];   // rsqrt(r_k + eps) of the tile's rows
+  float rc[3][kTileCols];
 };
+
+// Sums of the partials of a row and of a column.
+__device__ __forceinline__ double short_row_sum(const TensorDev& T, const float* __restrict__ ws, int r) {
+  return strided_sum(ws + T.oRowPart + r, T.nct, (size_t)T.m);
+}
+__device__ __forceinline__ double short_col_sum(const TensorDev& T, const float* __restrict__ ws, const StepArgs& A, int c) {
+  const int sr = short_rows(T.m, A.kind == LOPT_VELO);
+  return strided_sum(short_colpart(T, ws) + c, (T.m + sr - 1) / sr, (size_t)T.n);
+}
+__device__ __forceinline__ float new_factor(const StepArgs& A, int k, float old, float mean) {
+  return A.fac_decay[k] * old + (1.0f - A.fac_decay[k]) * mean;
+}
 
 union ShortLds {
   FuseLds means;
@@ -523,81 +565,61 @@ union ShortLds {
 __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws, const StepArgs& A,
                                            FuseLds& L) {
   const int t = threadIdx.x, n = T.n, m = T.m;
-  const int c = tile.tj * kTileCols + t, r0 = tile.ti * T.TR, r = r0 + t;
+  const int c = tile.tj * kTileCols + t, r = tile.ti * T.TR + t;
   const bool cin = c < n, rin = t < T.TR && r < m;
-  float co[3] = {0.f, 0.f, 0.f}, ro[3] = {0.f, 0.f, 0.f}, rp[4] = {0.f, 0.f, 0.f, 0.f};
-  const float* __restrict__ rowpart = ws + T.oRowPart + r;
-  if (rin) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) rp[j] = rowpart[(size_t)min(j, T.nct - 1) * m];
+  float co[3] = {0.f, 0.f, 0.f}, ro[3] = {0.f, 0.f, 0.f};
+  if (rin)
 #pragma unroll
     for (int k = 0; k < 3; ++k) ro[k] = ws[T.oRR + (size_t)(3 + k) * T.padm + r];
-  }
-  double cs = 0.0;
-  if (cin) {
+  if (cin)
 #pragma unroll
     for (int k = 0; k < 3; ++k) co[k] = ws[T.oRC + (size_t)(3 + k) * T.padn + c];
-    const int sr = short_rows(m, A.kind == LOPT_VELO);
-    cs = strided_sum(short_colpart(T, ws) + c, (m + sr - 1) / sr, (size_t)n);
-  }
-  if (rin) {
-    double rs = 0.0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) rs += j < T.nct ? (double)rp[j] : 0.0;
-    if (T.nct > 4) rs += strided_sum(rowpart + 4 * (size_t)m, T.nct - 4, (size_t)m);
-    const float mean = (float)(rs / (double)n);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float b = A.fac_decay[k], v = b * ro[k] + (1.0f - b) * mean;
-      L.r[k][t] = v;
-      L.rr[k][t] = rsqrtf(v + A.eps_acc);
-    }
-  }
+  double rs = 0.0, cs = 0.0;
+  if (rin) rs = short_row_sum(T, ws, r);
   if (cin) {
+    cs = short_col_sum(T, ws, A, c);
     const float mean = (float)(cs / (double)m);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float b = A.fac_decay[k], v = b * co[k] + (1.0f - b) * mean;
-      L.c[k][t] = v;
-      L.rc[k][t] = rsqrtf(v + A.eps_acc);
-    }
+    for (int k = 0; k < 3; ++k) L.rc[k][t] = rsqrtf(new_factor(A, k, co[k], mean) + A.eps_acc);
   } else {
 #pragma unroll
     for (int k = 0; k < 3; ++k) L.rc[k][t] = 0.f;   // columns past the last one of a ragged row
   }
+  if (rin) {
+    const float mean = (float)(rs / (double)n);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) L.rr[k][t] = rsqrtf(new_factor(A, k, ro[k], mean) + A.eps_acc);
+  }
   __syncthreads();
 }
 
-// Blocks of the row/column partials are the tile rows (rows) and tile columns (columns) of the tensor.
-__device__ __forceinline__ void fuse_store(const TensorDev& T, const TileDev& tile, float* __restrict__ ws, const FuseLds& L,
-                                           float (*red)[4]) {
-  float* st = T.st + 4 * (size_t)T.padN;
-  const int t = threadIdx.x;
-  auto part = [&](bool in, const float* x, const float* inv, int stride, float* acc3, float* inv3, size_t pd, int slot)
-                  __attribute__((always_inline)) {
-    float v[9];
+// 256 rows or columns of a tensor: what k_rc_update does on longer lists, from the partial sums of short ones.
+__device__ __forceinline__ void short_rc_block(const TensorDev& T, const RcItemDev& it, float* __restrict__ ws, const StepArgs& A,
+                                               float (*red)[kRedStride]) {
+  const int idx = it.blk * kBlock + (int)threadIdx.x, dim = it.is_col ? T.n : T.m;
+  const size_t pd = it.is_col ? T.padn : T.padm;
+  float* acc3 = T.st + 4 * (size_t)T.padN + (it.is_col ? 3 * (size_t)T.padm : 0) + idx;
+  float* inv3 = ws + (it.is_col ? T.oRC : T.oRR) + idx;
+  float v[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) v[q] = 0.f;
+  if (idx < dim) {
+    float old[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) old[k] = acc3[(size_t)k * pd];
+    const double sum = it.is_col ? short_col_sum(T, ws, A, idx) : short_row_sum(T, ws, idx);
+    const float mean = (float)(sum / (double)(it.is_col ? T.m : T.n));
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float a = in ? x[k * stride + t] : 0.f, b = in ? inv[k * stride + t] : 0.f;
-      if (in) {
-        acc3[k * pd] = a;
-        inv3[k * pd] = b;
-      }
-      v[k] = a;
-      v[3 + k] = a * a;
-      v[6 + k] = b * b;
+      const float r = new_factor(A, k, old[k], mean), rr = rsqrtf(r + A.eps_acc);
+      acc3[(size_t)k * pd] = r;
+      inv3[(size_t)k * pd] = rr;
+      v[k] = r;   // (the columns' plain sum is not used)
+      v[3 + k] = r * r;
+      v[6 + k] = rr * rr;
     }
-    __syncthreads();   // the previous sum has been read
-    block_sum<9>(v, red, ws + T.oRcPart + (size_t)slot * kRcStride);
-  };
-  if (tile.tj == 0) {
-    const int r = tile.ti * T.TR + t;
-    part(t < T.TR && r < T.m, &L.r[0][0], &L.rr[0][0], kShortRows, st + r, ws + T.oRR + r, T.padm, tile.ti);
   }
-  if (tile.ti == 0) {
-    const int c = tile.tj * kTileCols + t;
-    part(c < T.n, &L.c[0][0], &L.rc[0][0], kTileCols, st + 3 * (size_t)T.padm + c, ws + T.oRC + c, T.padn, T.nrblk + tile.tj);
-  }
+  block_sum<9>(v, red, ws + T.oRcPart + (size_t)((it.is_col ? T.nrblk : 0) + it.blk) * kRcStride);
 }
 
 // The per-element features that need a statistic of their own (the row/column-constant ones
@@ -729,18 +751,29 @@ template <bool RAW_RCP, bool WRITE, bool FUSE>
 __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
                                                         StepArgs A, int n_tiles, MixArgs M, int keep, int keep_off,
-                                                        bool backwards) {
-  __shared__ float red[kNStat][4];
+                                                        bool backwards, const RcItemDev* __restrict__ rcitems, int n_rcitems,
+                                                        bool rc_first) {
+  __shared__ __align__(16) float red[kNStat][kRedStride];
   __shared__ std::conditional_t<FUSE, ShortLds, int> sh;
   FuseLds* L = nullptr;
+  int idx = (int)blockIdx.x;
   if constexpr (FUSE) {
-    if ((int)blockIdx.x >= n_tiles) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
-      mix_bias_block(M, (int)blockIdx.x - n_tiles, sh.mix.hbar, sh.mix.red);
+    const int n_mix = (int)gridDim.x - n_tiles - n_rcitems;
+    if (idx < n_mix) {   // the extra workgroups of a VeLO step: mean of the LSTM outputs, gate bias
+      mix_bias_block(M, idx, sh.mix.hbar, sh.mix.red);
       return;
     }
+    idx -= n_mix;
+    const int rc = rc_first ? idx : idx - n_tiles;
+    if (rc >= 0 && rc < n_rcitems) {
+      const RcItemDev it = rcitems[rc];
+      short_rc_block(tensors[it.tensor], it, ws, A, red);
+      return;
+    }
+    if (rc_first) idx -= n_rcitems;
     L = &sh.means;
   }
-  const int idx = backwards ? n_tiles - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  if (backwards) idx = n_tiles - 1 - idx;
   const TileDev tile = tiles[idx];
   const TensorDev& T = tensors[tile.tensor];
   float acc[kNStat];
@@ -751,7 +784,6 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
-  if constexpr (FUSE) fuse_store(T, tile, ws, sh.means, red);
 }
 
 void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W, bool write_state, float* hbar_part, float* b_eff,
@@ -760,10 +792,11 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
   const bool raw = A.eps_acc >= 1e-30f;
   MixArgs M{};
   if (L.short_list) M = make_mix(L, A, W, hbar_part, b_eff);   // on other lists launch_rc_update has formed the cross-tensor term
-  const int extra = mix_bias_blocks(M);
+  const int n_rc = L.short_list ? L.n_rcitems : 0, extra = n_rc + mix_bias_blocks(M);
+  const bool rc_first = L.n_tiles > 4 * L.resident_wgs;   // eight workgroups a CU
 #define LOPT_LAUNCH_ACC(R, Wr, F) \
   hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M, \
-                     L.keep, L.keep_off, L.backwards)
+                     L.keep, L.keep_off, L.backwards, L.rcitems, n_rc, rc_first)
 #define LOPT_LAUNCH_ACC2(R, Wr) do { if (L.short_list) LOPT_LAUNCH_ACC(R, Wr, true); else LOPT_LAUNCH_ACC(R, Wr, false); } while (0)
   if (raw && write_state) LOPT_LAUNCH_ACC2(true, true);
   else if (raw) LOPT_LAUNCH_ACC2(true, false);

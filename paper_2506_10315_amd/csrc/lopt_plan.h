@@ -34,7 +34,8 @@ struct Plan {
   std::vector<lopt_tensor_desc> descs;
   std::vector<TensorDev> tensors;   // pointers filled per call
   std::vector<TileDev> tiles;
-  std::vector<RcItemDev> rcitems;
+  std::vector<RcItemDev> rcitems;     // blocks of k_rc_update (none on short lists)
+  std::vector<RcItemDev> rcshort;     // short lists: the same blocks, workgroups of the statistics pass (short_rc_block)
   std::vector<TileDev> rctiles;       // short lists: tiles of the row/column sums
   bool short_list = false;
   int groups = 1;                     // tensor groups of the two-stream pipeline
@@ -54,6 +55,7 @@ struct Plan {
   bool head_batched = false;
   uint64_t oCounters = 0;           // kMaxGroups ints: tile counters of the apply kernel
   uint64_t ws_floats = 0;
+  const std::vector<RcItemDev>& rc_blocks() const { return short_list ? rcshort : rcitems; }
 };
 
 // Number of tensor groups of the two-stream pipeline for a list of `total` elements (0 override = by size). A group more costs
@@ -155,6 +157,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   pl->tensors.assign(n, TensorDev{});
   pl->tiles.clear();
   pl->rcitems.clear();
+  pl->rcshort.clear();
   pl->rctiles.clear();
   pl->atiles.clear();
   pl->atile0.assign(n, 0);
@@ -255,17 +258,17 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       for (int tj = 0; tj < T.nct; ++tj)
         for (int ti = t0; ti < t1; ++ti) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
     }
-    T.nrblk = pl->short_list ? T.nrt : ceil_div(m, kBlock);
-    T.ncblk = ceil_div(nn, kBlock);   // = nct
+    T.nrblk = ceil_div(m, kBlock);
+    T.ncblk = ceil_div(nn, kBlock);
     T.rc0 = (int)pl->rcitems.size();
     const int nrc = ceil_div(m, short_rows(m, velo));
     if (pl->short_list) {
       for (int ti = 0; ti < nrc; ++ti)
         for (int tj = 0; tj < T.nct; ++tj) pl->rctiles.push_back(TileDev{(int)i, ti, tj, 0});
-    } else {
-      for (int b = 0; b < T.nrblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 0, b, 0});
-      for (int b = 0; b < T.ncblk; ++b) pl->rcitems.push_back(RcItemDev{(int)i, 1, b, 0});
     }
+    std::vector<RcItemDev>& rc = pl->short_list ? pl->rcshort : pl->rcitems;
+    for (int b = 0; b < T.nrblk; ++b) rc.push_back(RcItemDev{(int)i, 0, b, 0});
+    for (int b = 0; b < T.ncblk; ++b) rc.push_back(RcItemDev{(int)i, 1, b, 0});
     // apply tiles, for the kernels that read them: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
     pl->atile0[i] = (int)pl->atiles.size();
     pl->total_elems += N;
@@ -333,7 +336,7 @@ inline bool same_descs(const Plan& pl, size_t n, const lopt_tensor_desc* d) {
 
 inline size_t table_bytes(const Plan& pl) {
   return align64(pl.tensors.size() * sizeof(TensorDev)) + align64(pl.tiles.size() * sizeof(TileDev)) +
-         align64(pl.rcitems.size() * sizeof(RcItemDev)) + align64(pl.rctiles.size() * sizeof(TileDev)) +
+         align64(pl.rc_blocks().size() * sizeof(RcItemDev)) + align64(pl.rctiles.size() * sizeof(TileDev)) +
          align64(pl.atiles.size() * sizeof(ApplyTileDev));
 }
 
