@@ -69,9 +69,44 @@ __device__ __forceinline__ f32x4v load_quad(const float* seg, unsigned off, unsi
   return __builtin_bit_cast(f32x4v, __builtin_amdgcn_raw_buffer_load_b128(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>));
 }
 template <bool NT>
+__device__ __forceinline__ float load_one(const float* seg, unsigned off, unsigned bytes) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>));
+}
+template <bool NT>
+__device__ __forceinline__ void store_one(float* seg, unsigned off, unsigned bytes, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>);
+}
+template <bool NT>
 __device__ __forceinline__ void store_quad(float* seg, unsigned off, unsigned bytes, f32x4v v) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4v, v), segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>);
 }
+
+// Narrow tensors, up to kNarrowCols columns: with four columns a lane most lanes of a row access would idle. A lane owns ONE column of a
+// 64-column segment, and where several rows fit into the 64 lanes the wavefront takes that many at a time: consecutive rows of a tensor are
+// consecutive in memory, so the access is one contiguous run of dwords. The wavefronts of the tile share out its rows (two segments:
+// two wavefronts each). us a step with four columns and one row an access / this way: 4.2 M elements in 9, 3, 33 and 65 columns, width 32 858 / 588, VeLO
+// 911 / 134; in 8, 4, 32 and 64 columns 907 / 579 and 990 / 115; twenty of 6000x27 under VeLO 181 / 78; twelve of 4000x101 102 / 88, of 4000x127 120 /
+// 109, of 4000x128 109.7 / 106. From 129 columns on a lane in two works with four columns: 4000x133, four columns / one (64-column
+// segments) 126 / 131, 4000x161 138 / 143.
+constexpr int kNarrowCols = 128;
+struct NarrowWalk {
+  int col;             // this lane's column (col_ok: it is one)
+  bool col_ok;
+  int rows, sub;       // rows of one access, this lane's among them
+  unsigned off;        // offset of the lane's element from the first row's first, in bytes
+  int first, step;     // the wavefront's first row, from the tile's first, and the distance to its next for `per_trip` accesses a trip
+  __device__ __forceinline__ NarrowWalk(int n, int per_trip) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int two = n > kWave ? 1 : 0, seg = two ? wave >> 1 : 0, share = two ? wave & 1 : wave;
+    rows = n > kWave ? 1 : kWave / n;
+    sub = n > kWave ? 0 : lane / n;
+    col = seg * kWave + lane - sub * n;
+    col_ok = sub < rows && col < n;
+    off = 4u * (unsigned)(sub * n + col);
+    first = share * per_trip * rows;
+    step = (two ? 2 : 4) * per_trip * rows;
+  }
+};
 
 // Load four consecutive floats starting at column `col` of a row of length n whose first
 // element is at `row`. VEC: the address is 16-byte aligned and n % 4 == 0.

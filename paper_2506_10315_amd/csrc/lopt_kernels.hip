@@ -212,12 +212,11 @@ static MixArgs make_mix(const Launch& L, const StepArgs& A, const WeightsDev& W,
 
 // ----------------------------------------------------------------------------- rowcol_sums
 
-// NT: nontemporal loads.
-template <bool NT>
+// NT: nontemporal loads. R: rows in flight per wavefront.
+template <bool NT, int R>
 __device__ __forceinline__ void rowcol_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                             float (*colred)[kTileCols]) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  constexpr int R = 2;   // rows in flight per wavefront
   const int n = T.n, m = T.m;
   const int c0 = tile.tj * kTileCols;
   const unsigned bytes = segment_bytes(n, c0);
@@ -270,8 +269,9 @@ __global__ void __launch_bounds__(kBlock) k_rowcol_sums(const TensorDev* __restr
   float (*colred)[kTileCols] = red.col;
   const TileDev tile = tiles[blk];
   const TensorDev& T = tensors[tile.tensor];
-  if (T.vec) rowcol_tile<true>(T, tile, ws, colred);
-  else rowcol_tile<false>(T, tile, ws, colred);   // off the grid neighbours share lines
+  if (T.n <= kNarrowCols) rowcol_tile<false, 8>(T, tile, ws, colred);
+  else if (T.vec) rowcol_tile<true, 2>(T, tile, ws, colred);
+  else rowcol_tile<false, 2>(T, tile, ws, colred);   // off the grid neighbours share lines
 }
 
 void launch_rowcol_sums(const Launch& L, const StepArgs& A, const WeightsDev& W, float* hbar_part, float* b_eff, float* lstm_z,
@@ -744,6 +744,72 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
   }
 }
 
+// Narrow tensors: one column a lane (NarrowWalk), the same sums. A row past the tile adds nothing: its values read as 0.
+constexpr int kNarrowTrip = 2;   // accesses in flight
+template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
+__device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& tile, float* __restrict__ ws, const StepArgs& A,
+                                             float (&acc)[kNStat], FuseLds* L) {
+  if (FUSE) fuse_means(T, tile, ws, A, *L);
+  const int n = T.n;
+  const NarrowWalk w(n, kNarrowTrip);
+  if (!w.col_ok) return;
+  const auto [r0, r1] = tile_rows(T, tile);
+  const size_t pN = T.padN;
+  const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
+  const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
+  const float eps = A.eps_acc, clip2 = 0.1f * 0.1f;
+  float rc2[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float rc = FUSE ? L->rc[k][w.col] : ws[T.oRC + (size_t)k * T.padn + w.col];
+    rc2[k] = rc * rc;
+  }
+  for (unsigned r = r0 + w.first; r < r1; r += w.step) {
+    float in[kNarrowTrip][6], rr[kNarrowTrip][3];
+    const size_t ro = (size_t)r * (unsigned)n;
+    const unsigned bytes = 4u * (unsigned)n * min(r1 - r, (unsigned)(kNarrowTrip * w.rows));   // of the rows this trip takes
+#pragma unroll
+    for (int e = 0; e < kNarrowTrip; ++e) {
+      const unsigned off = w.off + 4u * (unsigned)(e * w.rows * n);
+      in[e][0] = load_one<NT>(T.g + ro, off, bytes);
+      in[e][1] = load_one<NT>(T.p + ro, off, bytes);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) in[e][2 + k] = load_one<NT>(T.st + k * pN + ro, off, bytes);
+      const unsigned row = min(r + e * w.rows + w.sub, r1 - 1);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) rr[e][k] = FUSE ? L->rr[k][row - r0] : ws[T.oRR + (size_t)k * T.padm + row];
+    }
+#pragma unroll
+    for (int e = 0; e < kNarrowTrip; ++e) {
+      const float g = in[e][0], p = in[e][1], g2 = g * g;
+      const float nm1 = __builtin_fmaf(b1, in[e][2], a1 * g);
+      const float nm2 = __builtin_fmaf(b2, in[e][3], a2 * g);
+      const float nm3 = __builtin_fmaf(b3, in[e][4], a3 * g);
+      const float nv = __builtin_fmaf(b4, in[e][5], a4 * g2);
+      const float s1 = nm1 * nm1, s2 = nm2 * nm2, s3 = nm3 * nm3;
+      float rs2 = RAW_RCP ? __builtin_amdgcn_rcpf(nv + eps) : 1.0f / (nv + eps);
+      rs2 = r + e * w.rows + w.sub < r1 ? rs2 : 0.f;
+      const float f0 = rr[e][0] * rr[e][0] * rc2[0], f1 = rr[e][1] * rr[e][1] * rc2[1], f2 = rr[e][2] * rr[e][2] * rc2[2];
+      acc[0] += g2;
+      acc[1] += p * p;
+      acc[2] += s1; acc[3] += s2; acc[4] += s3;
+      acc[5] += nv * nv;
+      acc[6] += s1 * rs2; acc[7] += s2 * rs2; acc[8] += s3 * rs2;
+      acc[9] += rs2;
+      acc[10] += g2 * f0; acc[11] += g2 * f1; acc[12] += g2 * f2;
+      acc[13] += s1 * f0; acc[14] += s2 * f1; acc[15] += s3 * f2;
+      acc[16] += fminf(g2, clip2);
+      if (WRITE) {
+        const unsigned off = w.off + 4u * (unsigned)(e * w.rows * n);
+        store_one<false>(T.st + ro, off, bytes, nm1);
+        store_one<false>(T.st + pN + ro, off, bytes, nm2);
+        store_one<false>(T.st + 2 * pN + ro, off, bytes, nm3);
+        store_one<false>(T.st + 3 * pN + ro, off, bytes, nv);
+      }
+    }
+  }
+}
+
 // WRITE = false: the accumulators are only read (their new values are formed for the statistics and dropped); the apply
 // pass of the same step forms them again and writes them (the two default apply kernels can; a read-only stream
 // sustains a higher share of the HBM rate than a read-write one, and 16 of this pass's 40 bytes per element move there).
@@ -780,7 +846,8 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
   // rows off the 16-byte grid of long lists: ordinary loads for all tiles
-  if (T.vec == 2 ? idx < keep : T.vec == 0 && (!FUSE || idx < keep_off)) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  if (T.n <= kNarrowCols) accum_narrow<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  else if (T.vec == 2 ? idx < keep : T.vec == 0 && (!FUSE || idx < keep_off)) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);

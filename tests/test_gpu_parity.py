@@ -505,3 +505,36 @@ def test_tiny_eps_acc_takes_the_library_reciprocal_roots(kind):
         worst = Hn.run_free(Hn.Case(108, _specs([(130, 260), (64, 256), (300,), (70, 36)]), "gauss_logscale"), cfg, w, 3,
                             lr_fn=lambda t: 0.9, wd=0.01)
         assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("tall", [[], [(6145, 2)]])
+@pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("small_fc_lopt", "stats"), ("velo", "apply"), ("velo", "stats")])
+def test_narrow_rows_several_to_an_access(kind, state_pass, tall):
+    # tensors of up to 128 columns: one column a lane, 64 / n rows to an access, one or two 64-column segments whose rows the wavefronts
+    # share; row counts around the rows of an access and of a trip, on and off the 16-byte grid, short lists and (with a tensor of
+    # more rows than those may have) the ordinary form. 129 to 131 columns beside them: a second tile of one to three columns.
+    cfg = Hn.make_cfg(kind, state_pass=state_pass) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8, state_pass=state_pass)
+    w = Hn.random_weights(cfg, seed=33)
+    shapes = [(63, 1), (64, 1), (65, 1), (129, 1), (31, 2), (21, 3), (43, 3), (16, 4), (8, 8), (7, 9), (29, 9), (3, 21), (2, 32), (9, 32), (5, 33),
+              (64, 33), (1, 63), (17, 64), (65, 64), (6, 65), (31, 100), (9, 127), (70, 128), (3, 129), (33, 130), (8, 131), (1, 7), (1, 128)] + tall
+    assert plan(shapes, kind=kind, lstm_hidden=32, n_bank=8)["short_list"] == (not tall)
+    worst = Hn.run_free(Hn.Case(133, _specs(shapes), "gauss_logscale"), cfg, w, 3, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("cols", [1, 9, 63, 65, 127, 129, 255, 257, 258, 259, 515])
+def test_velo_rows_off_the_grid_write_nothing_beside_the_tensor(cols):
+    # parameters and gradients between guard values: the last access of a row ends with the row, that of a tensor with the tensor
+    import torch
+    import paper_2506_10315_amd as P
+    rows, cfg = 13, Hn.make_cfg("velo", lstm_hidden=32, n_bank=8)
+    n = rows * cols
+    gen = torch.Generator(device="cuda:0").manual_seed(cols)
+    flat = torch.randn(n + 128, device="cuda:0", generator=gen) * 0.02
+    grad = torch.randn(n, device="cuda:0", generator=gen) * 1e-3
+    before = flat.clone()
+    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, seed=34), [(rows, cols)])
+    opt.step([flat[64:64 + n].view(rows, cols)], [grad.view(rows, cols)], lr=1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(flat[:64], before[:64]) and torch.equal(flat[64 + n:], before[64 + n:])
+    assert float((flat[64:64 + n] != before[64:64 + n]).float().mean()) > 0.9
