@@ -16,6 +16,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kVF = LOPT_D_VELO;  // 29
 constexpr int kVH = 4;
+constexpr unsigned kNoColumn = 0xFFFFF000u;   // byte offset beyond every descriptor: reads as 0, is not written
 constexpr int kVE = 17;           // features that vary per element: 0..12, 25..27, 28
 
 __device__ __forceinline__ constexpr int velo_elem_feat(int i) { return i < 13 ? i : 12 + i; }   // 0..12, 25..28
@@ -33,20 +34,16 @@ __device__ __forceinline__ float relu1(float x) {
 // share their first and last line with the neighbouring tiles, which nontemporal accesses fetch and write twice: there
 // ordinary ones are faster (18 matrices of 2732 columns: 0.587 -> 0.496 ms; on the grid, ViT-B/16 shapes, they cost the
 // next step's statistics pass more than this pass gains).
-template <bool NT>
-__device__ __forceinline__ float4 load4x(const float* __restrict__ row, int col, int n) {
-  return NT ? load4s<true>(row, col, n) : load4<true>(row, col, n);
-}
-template <bool NT>
-__device__ __forceinline__ void store4x(float* __restrict__ row, int col, int n, float4 v) {
-  if (NT) store4s<true>(row, col, n, v);
-  else store4<true>(row, col, n, v);
-}
-
-template <bool NT, bool RAW_RSQ, bool UPDATE_STATE>
-__device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
+// MASK: lanes past the last column take no part in the accesses, instead of leaving it to the range check. Rows on the 16-byte but off the
+// 128-byte grid are faster with it (two of 4096x4100 508 -> 500 us a step, twelve of 4000x132 127 -> 122), rows off the 16-byte grid without
+// (16001x9001 2139 -> 2085, 54 M elements of 2731 columns 782 -> 777; 4000x191 the other way, 132 / 134), rows on the 128-byte grid are
+// the same either way to 0.3 %.
+// Rows off the 16-byte grid, four columns a lane against one column a lane: 54 M of 2731 columns 808 -> 777 us a step, 16001x9001 2137 ->
+// 2085, 8.2 M of 2731 columns 144 -> 138, five layers of 777 61 -> 57.
+template <bool NT, bool MASK, bool RAW_RSQ, bool UPDATE_STATE>
+__device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const RowWalk& w, const float* __restrict__ ws,
                                                  const StepArgs& A) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int i4 = lane & 3;
   // prepared per-tensor MLP: W1s[29][4] (normalization folded in) b1[4] W2[4][4] b2[4] W3[4][2] b3[2]
   const float* __restrict__ prep = ws + T.oPrep;
@@ -66,8 +63,9 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
   const f32x4 c3 = {B3[0], B3[1], 0.f, 0.f};
 
   const int n = T.n;
-  const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(wave));
-  const int col = w.tj * kTileCols + 4 * lane;
+  // columns past the row's end (load_quad) and rows' pad columns of r_k and c_k: computed on, never stored
+  const int c0 = w.tj * kTileCols, col = c0 + 4 * lane;
+  const unsigned off = 16u * lane, bytes = segment_bytes(n, c0);
   float4 rc[3];
   f32x4 colv[4];   // per column of this lane: sum over the 6 column-constant features, for the 4 hidden units
   {
@@ -103,13 +101,16 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
 
   for (int i = 0; i < w.cnt; ++i) {
     const int r = walk_row(w, i);
-    const size_t ro = (size_t)r * n;
-    const float4 g4 = load4x<NT>(T.g + ro, col, n);
-    const float4 p4 = load4x<NT>(T.p + ro, col, n);
-    const float4 m1 = load4x<NT>(M1 + ro, col, n);
-    const float4 m2 = load4x<NT>(M2 + ro, col, n);
-    const float4 m3 = load4x<NT>(M3 + ro, col, n);
-    const float4 v4 = load4x<NT>(Vp + ro, col, n);
+    const size_t ro = (size_t)r * n + c0;
+    f32x4v g4 = {0.f, 0.f, 0.f, 0.f}, p4 = g4, m1 = g4, m2 = g4, m3 = g4, v4 = g4;
+    if (!MASK || col < n) {
+      g4 = load_quad<NT>(T.g + ro, off, bytes);
+      p4 = load_quad<NT>(T.p + ro, off, bytes);
+      m1 = load_quad<NT>(M1 + ro, off, bytes);
+      m2 = load_quad<NT>(M2 + ro, off, bytes);
+      m3 = load_quad<NT>(M3 + ro, off, bytes);
+      v4 = load_quad<NT>(Vp + ro, off, bytes);
+    }
     float rr[3], rv[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -130,11 +131,11 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
     }
     float x[4][kVE];
     f32x4 h[4];
-    float n1[4], n2[4], n3[4], nv[4];
+    f32x4v n1, n2, n3, nv;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float g = get(g4, e);
-      float q1 = get(m1, e), q2 = get(m2, e), q3 = get(m3, e), v = get(v4, e);
+      const float g = g4[e];
+      float q1 = m1[e], q2 = m2[e], q3 = m3[e], v = v4[e];
       if (UPDATE_STATE) {
         q1 = __builtin_fmaf(bm1, q1, am1 * g);
         q2 = __builtin_fmaf(bm2, q2, am2 * g);
@@ -144,18 +145,18 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
       }
       const float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(v + eps) : rsqrtf(v + eps);
       const float f0 = rr[0] * get(rc[0], e), f1 = rr[1] * get(rc[1], e), f2 = rr[2] * get(rc[2], e);
-      x[e][0] = g; x[e][1] = get(p4, e); x[e][2] = q1; x[e][3] = q2; x[e][4] = q3; x[e][5] = v;
+      x[e][0] = g; x[e][1] = p4[e]; x[e][2] = q1; x[e][3] = q2; x[e][4] = q3; x[e][5] = v;
       x[e][6] = q1 * rs; x[e][7] = q2 * rs; x[e][8] = q3 * rs; x[e][9] = rs;
       x[e][10] = g * f0; x[e][11] = g * f1; x[e][12] = g * f2;
       x[e][13] = q1 * f0; x[e][14] = q2 * f1; x[e][15] = q3 * f2;
       x[e][16] = fminf(fmaxf(g, -0.1f), 0.1f);
       h[e] = rowv + colv[e];
     }
-    if (UPDATE_STATE) {   // stored while the values are live as features anyway
-      store4x<NT>(M1 + ro, col, n, make_float4(n1[0], n1[1], n1[2], n1[3]));
-      store4x<NT>(M2 + ro, col, n, make_float4(n2[0], n2[1], n2[2], n2[3]));
-      store4x<NT>(M3 + ro, col, n, make_float4(n3[0], n3[1], n3[2], n3[3]));
-      store4x<NT>(Vp + ro, col, n, make_float4(nv[0], nv[1], nv[2], nv[3]));
+    if (UPDATE_STATE && (!MASK || col < n)) {   // stored while the values are live as features anyway
+      store_quad<NT>(M1 + ro, off, bytes, n1);
+      store_quad<NT>(M2 + ro, off, bytes, n2);
+      store_quad<NT>(M3 + ro, off, bytes, n3);
+      store_quad<NT>(Vp + ro, off, bytes, nv);
     }
     // layer 1: the four elements of the lane are four independent accumulation chains
 #pragma unroll
@@ -179,38 +180,27 @@ __device__ __forceinline__ void apply_velo4_tile(const TensorDev& T, const TileD
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(a3[k], relu1(h2[e][k]), o[e], 0, 0, 0);
     }
-    float pn[4];
+    f32x4v pn;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float delta = o[e][0] * __expf(o[e][1] * A.exp_mult) * A.step_mult;
-      const float p = get(p4, e);
+      const float p = p4[e];
       pn[e] = p - lr * (delta + wd * p);
     }
-    store4x<NT>(T.p + ro, col, n, make_float4(pn[0], pn[1], pn[2], pn[3]));
+    if (!MASK || col < n) store_quad<NT>(T.p + ro, off, bytes, pn);
   }
 }
 
-// Rows that are not 16-byte aligned (n % 4 != 0). A lane owns ONE column and takes four rows of it per trip (the four
-// elements of the MFMA chains are rows instead of columns), so every access is a coalesced dword of a 256-byte row segment
-// and the column factors are one set per lane. The wavefronts of the tile sit on adjacent 64-column segments; where the
-// tile is narrower than three segments they share out its rows as well (three leave the fourth without work). The float4
-// form with four predicated dwords per lane that this replaces touched every cache line four times: 18 tensors of 54 M
-// elements, 2731 columns, 1.82 -> 0.52 ms. Ordinary accesses, not nontemporal ones (0.83 ms): neighbouring segments share
-// their boundary lines.
+// Narrow tensors: one column a lane (NarrowWalk), four accesses per trip (the four elements of the MFMA chains are rows instead of
+// columns). Ordinary accesses: neighbouring wavefronts share their boundary lines.
 template <bool RAW_RSQ, bool UPDATE_STATE>
-__device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
+__device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const TileDev& tile, const float* __restrict__ ws,
                                                       const StepArgs& A) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i4 = lane & 3;
+  const int i4 = threadIdx.x & 3;
   const int n = T.n;
-  const int c0 = tile.tj * kTileCols;
-  const int nseg = (min(n - c0, kTileCols) + kWave - 1) / kWave;
-  const int rsplit = nseg == 1 ? 4 : nseg == 2 ? 2 : 1;   // wavefronts that share a segment's rows
-  const int seg = wave / rsplit;
-  if (seg >= nseg) return;
-  const int col = c0 + seg * kWave + lane;
-  const bool col_ok = col < n;
-  const unsigned cc = (unsigned)(col_ok ? col : n - 1);   // lanes past the end compute on the last column and store nothing
+  const NarrowWalk w(n, 4);
+  const unsigned cc = (unsigned)min(w.col, n - 1);   // lanes without a column compute on the last one and store nothing
+  const unsigned lane_off = w.col_ok ? w.off : kNoColumn;
   const float* __restrict__ prep = ws + T.oPrep;
   const float* __restrict__ W2 = prep + (kVF + 1) * kVH;
   const float* __restrict__ B2 = W2 + kVH * kVH;
@@ -253,29 +243,31 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
   const float bm1 = A.mom_decay[0], bm2 = A.mom_decay[1], bm3 = A.mom_decay[2], bv = A.rms_decay;
   const float am1 = 1.0f - bm1, am2 = 1.0f - bm2, am3 = 1.0f - bm3, av = 1.0f - bv;
   const auto [r0, r1] = tile_rows(T, tile);
-  for (unsigned r = r0 + 4 * (wave % rsplit); r < r1; r += 4 * rsplit) {
+  for (unsigned r = r0 + w.first; r < r1; r += w.step) {
+    const size_t ro = (size_t)r * (unsigned)n;
+    const unsigned bytes = 4u * (unsigned)n * min(r1 - r, (unsigned)(4 * w.rows));   // of the rows this trip takes: others read as 0
     float e_in[4][6];
+    unsigned off[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {   // rows past the tile read its last row and store nothing
-      const size_t ro = (size_t)min(r + e, r1 - 1) * (unsigned)n;
-      e_in[e][0] = T.g[ro + cc];
-      e_in[e][1] = T.p[ro + cc];
+    for (int e = 0; e < 4; ++e) {
+      off[e] = w.col_ok ? lane_off + 4u * (unsigned)(e * w.rows * n) : kNoColumn;
+      e_in[e][0] = load_one<false>(T.g + ro, off[e], bytes);
+      e_in[e][1] = load_one<false>(T.p + ro, off[e], bytes);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) e_in[e][2 + k] = T.st[k * pN + ro + cc];
+      for (int k = 0; k < 4; ++k) e_in[e][2 + k] = load_one<false>(T.st + k * pN + ro, off[e], bytes);
     }
     float x[4][kVE];
     f32x4 h[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const unsigned row = min(r + e, r1 - 1);
-      const size_t ro = (size_t)row * (unsigned)n;
+      const unsigned row = min(r + e * w.rows + w.sub, r1 - 1);
       float rr[3], rv[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         rr[k] = ws[T.oRR + (size_t)k * T.padm + row];
         rv[k] = rst[(size_t)k * T.padm + row];
       }
-      f32x4 rowv;   // bias + row-constant features (wave-uniform)
+      f32x4 rowv;   // bias + row-constant features of this lane's row
 #pragma unroll
       for (int u = 0; u < kVH; ++u) {
         float a = prep[kVF * kVH + u];
@@ -293,12 +285,10 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
         q2 = __builtin_fmaf(bm2, q2, am2 * g);
         q3 = __builtin_fmaf(bm3, q3, am3 * g);
         v = __builtin_fmaf(bv, v, av * (g * g));
-        if (r + e < r1 && col_ok) {
-          T.st[ro + cc] = q1;
-          T.st[pN + ro + cc] = q2;
-          T.st[2 * pN + ro + cc] = q3;
-          T.st[3 * pN + ro + cc] = v;
-        }
+        store_one<false>(T.st + ro, off[e], bytes, q1);
+        store_one<false>(T.st + pN + ro, off[e], bytes, q2);
+        store_one<false>(T.st + 2 * pN + ro, off[e], bytes, q3);
+        store_one<false>(T.st + 3 * pN + ro, off[e], bytes, v);
       }
       const float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(v + eps) : rsqrtf(v + eps);
       const float f0 = rr[0] * rc[0], f1 = rr[1] * rc[1], f2 = rr[2] * rc[2];
@@ -334,7 +324,7 @@ __device__ __forceinline__ void apply_velo4_tile_cols(const TensorDev& T, const 
     for (int e = 0; e < 4; ++e) {
       const float delta = o[e][0] * __expf(o[e][1] * A.exp_mult) * A.step_mult;
       const float p = e_in[e][1];
-      if (r + e < r1 && col_ok) T.p[(size_t)(r + e) * (unsigned)n + cc] = p - lr * (delta + wd * p);
+      store_one<false>(T.p + ro, off[e], bytes, p - lr * (delta + wd * p));
     }
   }
 }
@@ -345,9 +335,13 @@ __global__ void __launch_bounds__(kBlock, 4) k_apply_velo4(const TensorDev* __re
                                                         StepArgs A) {
   const TileDev tile = tiles[blockIdx.x];
   const TensorDev& T = tensors[tile.tensor];
-  if (T.vec == 2) apply_velo4_tile<true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
-  else if (T.vec) apply_velo4_tile<false, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
-  else apply_velo4_tile_cols<RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
+  if (T.n <= kNarrowCols) apply_velo4_narrow<RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
+  else {
+    const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (T.vec == 2) apply_velo4_tile<true, false, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
+    else if (T.vec) apply_velo4_tile<false, true, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
+    else apply_velo4_tile<false, false, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
+  }
 }
 
 bool apply_velo4_available(const StepArgs& A) { return A.kind == LOPT_VELO && A.H == kVH && A.HP == kVH; }
