@@ -652,8 +652,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool fc4x_ok = rows_ok && ctx->apply_variant != LOPT_APPLY_VALU && apply_fc4x_available(A);   // small_fc_lopt, width up to 16
   const bool state_in_apply = (strip_ok || fc4x_ok || velo4_ok) && ctx->state_in_apply;
   const bool fold = (strip_ok || ctx->cfg.kind == LOPT_VELO) && pl.fold_finalize;
-  StepFeats feats{};
-  if (fold) feats = make_feats(step, ctx->loss);
+  const StepFeats feats = make_feats(step, ctx->loss);
   auto launch_apply = [&](const Launch& La) {
     if (strip_ok) launch_apply_f16s(La, A, ctx->W, fold ? &feats : nullptr, state_in_apply, stream);
     else if (mfma_ok && ctx->apply_variant != LOPT_APPLY_VALU) launch_apply_mfma(La, A, ctx->W, stream);
@@ -706,7 +705,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for
     auto stats_passes = [&](const Launch& S, hipStream_t s) {
       launch_accum_stats(S, A, ctx->W, !state_in_apply, ws + pl.oHbarPart, ws + pl.oBeff, s);
-      launch_finalize(S, A, ctx->W, ws + pl.oLstmU, s);
+      launch_finalize(S, A, ctx->W, feats, ws + pl.oLstmU, s);
       if (velo) {
         launch_velo_lstm(S, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, nullptr, ws + pl.oHNew, s);
         launch_velo_head(S, A, ctx->W, ws + pl.oHNew, pl.head_batched ? ws + pl.oAlpha : nullptr,
@@ -756,7 +755,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   MARK(2);
   launch_accum_stats(L, A, ctx->W, !state_in_apply, ws + pl.oHbarPart, ws + pl.oBeff, stream);
   MARK(3);
-  if (!fold) launch_finalize(L, A, ctx->W, ws + pl.oLstmU, stream);
+  if (!fold) launch_finalize(L, A, ctx->W, feats, ws + pl.oLstmU, stream);
   MARK(4);
   if (ctx->cfg.kind == LOPT_VELO) {
     launch_velo_lstm(L, A, ctx->W, ws + pl.oLstmU, ws + pl.oBeff, lstm_z, fold ? &feats : nullptr, ws + pl.oHNew, stream);

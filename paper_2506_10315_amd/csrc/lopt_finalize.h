@@ -55,22 +55,19 @@ struct FinLds {
 };
 
 // s_f and scale of feature f < 32 from the tensor's 32 sums. tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25
-// sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps).
+// sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps). One division for all features: a branch per kind of feature, each with a division
+// in double of its own, was a third of the kernel's time on a short list.
 __device__ __forceinline__ void feature_scale(const TensorDev& T, const StepArgs& A, const double* tot, int f, float& sf, float& scale) {
-  const double N = (double)T.m * (double)T.n;
-  double s = 0.0;
-  double pre = 1.0;  // factor between the raw feature the kernels build and the feature itself
-  if (f < 10) s = tot[f] / N;
-  else if (f < 13 || (f >= 25 && f < 28)) {
-    const int k = f < 13 ? f - 10 : f - 25;
-    const double rbar = tot[17 + k] / (double)T.m + (double)A.eps_acc;
-    s = tot[f < 13 ? f : f - 12] / N * rbar;
-    pre = sqrt(rbar);
-  } else if (f < 16) s = tot[20 + (f - 13)] / (double)T.m;
-  else if (f < 19) s = tot[26 + (f - 16)] / (double)T.n;
-  else if (f < 22) s = tot[23 + (f - 19)] / (double)T.m;
-  else if (f < 25) s = tot[29 + (f - 22)] / (double)T.n;
-  else if (f == 28) s = tot[16] / N;
+  const double m = (double)T.m, n = (double)T.n;
+  const bool fac = (f >= 10 && f < 13) || (f >= 25 && f < 28), clip = f == 28;
+  const int k = fac ? (f < 13 ? f - 10 : f - 25) : 0;
+  const int q = f < 13 ? f : f < 16 ? 20 + (f - 13) : f < 19 ? 26 + (f - 16) : f < 22 ? 23 + (f - 19) : f < 25 ? 29 + (f - 22) : clip ? 16 : f < 28 ? f - 12 : 0;
+  const bool row = (f >= 13 && f < 16) || (f >= 19 && f < 22), col = (f >= 16 && f < 19) || (f >= 22 && f < 25);
+  const double rbar = tot[17 + k] / m + (double)A.eps_acc;
+  double s = tot[q] / (row ? m : col ? n : m * n);
+  s = fac ? s * rbar : s;
+  s = f < 29 ? s : 0.0;
+  const double pre = fac ? sqrt(rbar) : 1.0;  // factor between the raw feature the kernels build and the feature itself
   sf = (float)s;
   scale = (float)(pre / sqrt((double)sf + (double)A.eps_norm));
 }
@@ -81,6 +78,14 @@ __device__ __forceinline__ FinTerms fin_terms(const TensorDev& T, const float* w
   if (q < kNStat) return FinTerms{ws + T.oStatPart + q, T.nrt * T.nct, kStatStride};
   if (q < 26) return FinTerms{ws + T.oRcPart + (q - kNStat), T.nrblk, kRcStride};
   return FinTerms{ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3), T.ncblk, kRcStride};
+}
+
+// Sum of the 32 segments of one sum, in a fixed order: part[0], part[32], ...
+__device__ __forceinline__ double segment_sum(const double* part) {
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < kFinSegs; ++k) s[k % 4] += part[32 * k];
+  return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // Called by all threads (1024 or 256). L.stats and L.scale are ready for all of them afterwards; store: to the workspace too.
@@ -102,11 +107,7 @@ __device__ __forceinline__ void finalize_scales(const TensorDev& T, float* __res
     }
   }
   __syncthreads();
-  if (threadIdx.x < 32) {
-    double s = 0.0;
-    for (int k = 0; k < kFinSegs; ++k) s += L.part[k][q];
-    L.tot[q] = s;
-  }
+  if (threadIdx.x < 32) L.tot[q] = segment_sum(&L.part[0][q]);
   __syncthreads();
   if (threadIdx.x < 32) {
     const int f = threadIdx.x;

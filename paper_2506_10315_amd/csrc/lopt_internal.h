@@ -96,7 +96,8 @@ struct StepArgs {
   float loss;                 // VeLO: loss value that goes with this step's gradients
 };
 
-// Time features tanh(step / x) and VeLO's loss features, for the kernels that take them from the host (k_finalize forms its own).
+// Time features tanh(step / x) and VeLO's loss features tanh(psi / x), psi = sign(loss) ln(1 + |loss|), formed in double by the host: on the
+// device fourteen tanh in double held up the sums of k_finalize (0.3 to 0.5 us of it).
 struct StepFeats { float time[LOPT_N_TIME], loss[LOPT_N_LOSS]; };
 
 // Device weights of the optimizer, owned by the context.
@@ -151,7 +152,7 @@ void launch_rowcol_short(const Launch&, const StepArgs&, const WeightsDev&, floa
 // write_state = false: M_1..3 and V stay as they are (the strip-form apply pass updates them, see launch_apply_f16s). Short
 // lists: the second stage of VeLO's cross-tensor term rides along here (there is no launch_rc_update)
 void launch_accum_stats(const Launch&, const StepArgs&, const WeightsDev&, bool write_state, float* hbar_part, float* b_eff, hipStream_t);
-void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, float* lstm_u, hipStream_t);
+void launch_finalize(const Launch&, const StepArgs&, const WeightsDev&, const StepFeats&, float* lstm_u, hipStream_t);
 // lopt_create: fills WeightsDev::lstm and, if `head` is not null, WeightsDev::head
 void launch_velo_pack(const WeightsDev&, int HL, int K, int P, float* lstm, float* head, hipStream_t);
 // lstm_z: the recurrent product formed ahead (null: this launch forms it); feats not null: no k_finalize has run

@@ -879,24 +879,11 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
 // input. (Lists whose apply launch forms the scales itself do without: Plan::fold_finalize.)
 __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __restrict__ tensors, float* __restrict__ ws,
                                                      StepArgs A, WeightsDev W, float* __restrict__ lstm_u, int tensor0,
-                                                     int* __restrict__ apply_counter) {
+                                                     int* __restrict__ apply_counter, StepFeats F) {
   __shared__ FinLds L;
-  __shared__ float s_tfeat[LOPT_N_TIME], s_lfeat[LOPT_N_LOSS];
   const int ti = tensor0 + (int)blockIdx.x;
   const TensorDev& T = tensors[ti];
   if (blockIdx.x == 0 && threadIdx.x == 0) *apply_counter = 0;   // the apply pass of this sub-list starts at its first tile
-  if (threadIdx.x >= 64 && threadIdx.x < 64 + LOPT_N_TIME) {
-    // time features tanh(t/x) (feature table of small_fc_lopt, row "Time Features")
-    const double xs[LOPT_N_TIME] = {1, 3, 10, 30, 100, 300, 1000, 3000, 1e4, 3e4, 1e5};
-    s_tfeat[threadIdx.x - 64] = (float)tanh((double)A.step / xs[threadIdx.x - 64]);
-  }
-  if (threadIdx.x >= 96 && threadIdx.x < 96 + LOPT_N_LOSS) {
-    // loss features tanh(psi / x), psi = sign(loss) ln(1 + |loss|) (the loss value VeLO's step is given)
-    const double xs[LOPT_N_LOSS] = {1, 3, 10};
-    const double l = (double)A.loss;
-    const double psi = copysign(log1p(fabs(l)), l);
-    s_lfeat[threadIdx.x - 96] = (float)tanh(psi / xs[threadIdx.x - 96]);
-  }
   finalize_scales(T, ws, A, L, true);
   if (A.kind == LOPT_SMALL_FC) {
     // first layer with the normalization folded in, hidden width padded with zeros to HP;
@@ -911,7 +898,7 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
       float b = 0.f;
       if (u < H) {
         b = W.mlp[LOPT_D_SMALL_FC * H + u];
-        for (int i = 0; i < LOPT_N_TIME; ++i) b += s_tfeat[i] * W.mlp[(LOPT_N_ELEM_FEATS + i) * H + u];
+        for (int i = 0; i < LOPT_N_TIME; ++i) b += F.time[i] * W.mlp[(LOPT_N_ELEM_FEATS + i) * H + u];
       }
       prep[LOPT_N_ELEM_FEATS * HP + u] = b;
     }
@@ -920,22 +907,22 @@ __global__ void __launch_bounds__(32 * kFinSegs) k_finalize(const TensorDev* __r
     float* u = lstm_u + (size_t)ti * kLstmInPad;
     const int t = threadIdx.x;
     if (t < LOPT_D_VELO) u[t] = 0.05f * logf(L.stats[t] + 1e-30f);
-    else if (t < LOPT_D_VELO + LOPT_N_TIME) u[t] = s_tfeat[t - LOPT_D_VELO];
+    else if (t < LOPT_D_VELO + LOPT_N_TIME) u[t] = F.time[t - LOPT_D_VELO];
     else if (t < LOPT_D_VELO + LOPT_N_TIME + 5) {
       const int nd = T.ndim < 4u ? (int)T.ndim : 4;
       u[t] = (t - (LOPT_D_VELO + LOPT_N_TIME)) == nd ? 1.f : 0.f;
-    } else if (t < LOPT_VELO_LSTM_IN) u[t] = s_lfeat[t - (LOPT_D_VELO + LOPT_N_TIME + 5)];
+    } else if (t < LOPT_VELO_LSTM_IN) u[t] = F.loss[t - (LOPT_D_VELO + LOPT_N_TIME + 5)];
     else if (t < kLstmInPad) u[t] = 0.f;
   }
 }
 
-void launch_finalize(const Launch& L, const StepArgs& A, const WeightsDev& W, float* lstm_u, hipStream_t s) {
+void launch_finalize(const Launch& L, const StepArgs& A, const WeightsDev& W, const StepFeats& F, float* lstm_u, hipStream_t s) {
   if (L.n_tensors == 0) return;
   // long lists have more workgroups than the chip holds at once: there small ones win; beside the apply pass of another
   // tensor group only small ones find room (eight groups of 388 tensors: 18 us a launch, 53 us with 1024 threads)
   const int threads = L.n_tensors <= 512 && !L.beside_apply ? 32 * kFinSegs : kBlock;
   hipLaunchKernelGGL(k_finalize, dim3(L.n_tensors), dim3(threads), 0, s, L.tensors, L.ws, A, W, lstm_u, L.tensor0,
-                     L.apply_counter);
+                     L.apply_counter, F);
 }
 
 // ----------------------------------------------------------------------------- VeLO hypernetwork
@@ -1075,10 +1062,10 @@ __device__ __forceinline__ void tail_sums(const FinTerms& t, int tn, int slot, T
   double a[NS];
   strided_sums(t.base + (size_t)slot * t.stride, slot < t.count ? (t.count - slot + HW - 1) / HW : 0, (size_t)HW * t.stride, a);
   if (NS == kFinSegs) {
-    double s = 0.0;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};   // as segment_sum
 #pragma unroll
-    for (int k = 0; k < NS; ++k) s += a[k];
-    L.tot[tn][q] = s;
+    for (int k = 0; k < NS; ++k) s[k % 4] += a[k];
+    L.tot[tn][q] = (s[0] + s[1]) + (s[2] + s[3]);
   } else {
 #pragma unroll
     for (int k = 0; k < NS; ++k) L.part[tn][slot + HW * k][q] = a[k];
@@ -1100,11 +1087,7 @@ __device__ __forceinline__ void tail_inputs(const TensorDev* __restrict__ tensor
   __syncthreads();
   if (w < nT) {
     const TensorDev& T = tensors[w];
-    if (hw > 1) {
-      double s = 0.0;
-      for (int k = 0; k < kFinSegs; ++k) s += L.part[w][k][q];
-      L.tot[w][q] = s;
-    }
+    if (hw > 1) L.tot[w][q] = segment_sum(&L.part[w][0][q]);
     __builtin_amdgcn_wave_barrier();   // the tensor's 32 sums are this half wavefront's own
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     float sf, scale;
