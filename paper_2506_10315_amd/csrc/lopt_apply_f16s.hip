@@ -142,17 +142,20 @@ typedef const char __attribute__((address_space(1)))* gcc8;
 
 // One dword per array at (wave-uniform row offset in elements) + (lane offset in BYTES, 32 bits): written so
 // that the address is scalar base + zero-extended 32-bit vector offset, the form a global load takes directly.
+template <bool NT>
 __device__ __forceinline__ float ld_stream(gcf32 base, size_t rowoff, unsigned voff_bytes) {
-  return __builtin_nontemporal_load((gcf32)((gcc8)(base + rowoff) + voff_bytes));
+  const gcf32 at = (gcf32)((gcc8)(base + rowoff) + voff_bytes);
+  return NT ? __builtin_nontemporal_load(at) : *at;
 }
+template <bool NT>
 __device__ __forceinline__ Elem load_elem(const Streams& S, size_t rowoff, unsigned voff_bytes) {
   Elem e;
-  e.g = ld_stream(S.g, rowoff, voff_bytes);
-  e.p = ld_stream(S.p, rowoff, voff_bytes);
-  e.m1 = ld_stream(S.m1, rowoff, voff_bytes);
-  e.m2 = ld_stream(S.m2, rowoff, voff_bytes);
-  e.m3 = ld_stream(S.m3, rowoff, voff_bytes);
-  e.v = ld_stream(S.v, rowoff, voff_bytes);
+  e.g = ld_stream<NT>(S.g, rowoff, voff_bytes);
+  e.p = ld_stream<NT>(S.p, rowoff, voff_bytes);
+  e.m1 = ld_stream<NT>(S.m1, rowoff, voff_bytes);
+  e.m2 = ld_stream<NT>(S.m2, rowoff, voff_bytes);
+  e.m3 = ld_stream<NT>(S.m3, rowoff, voff_bytes);
+  e.v = ld_stream<NT>(S.v, rowoff, voff_bytes);
   return e;
 }
 
@@ -259,7 +262,8 @@ __device__ __forceinline__ void layer3_piece(const float4& w, const f32x16& h2a,
 
 // FIN: k_finalize has not run; every workgroup forms the scales of its tensor from the statistics pass's partials, and the first
 // layer from them: a launch and its chain of loads fewer (the planner's fold_finalize has the line and both sides).
-template <bool RAW_RSQ, bool UPDATE_STATE, bool FIN>
+// NT: nontemporal loads (Launch::strip_ordinary).
+template <bool RAW_RSQ, bool UPDATE_STATE, bool FIN, bool NT>
 __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __restrict__ tensors,
                                                           const ApplyTileDev* __restrict__ atiles, int n_atiles,
                                                           int* __restrict__ next_tile, float* __restrict__ ws,
@@ -364,7 +368,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __res
   auto fetch = [&](int q) __attribute__((always_inline)) {
     const bool in_tile = q < r1;
     const int qc = in_tile ? q : r1 - 1;
-    return load_elem(S, (size_t)qc * (size_t)n + c0, in_tile && qc + 1 < m ? voff_pair : colc_);
+    return load_elem<NT>(S, (size_t)qc * (size_t)n + c0, in_tile && qc + 1 < m ? voff_pair : colc_);
   };
 
   // ---- the loads of the set-up leave before the first wait for one: the prepared first layer, the scales, this lane's
@@ -658,10 +662,15 @@ void launch_apply_f16s(const Launch& L, const StepArgs& A, const WeightsDev& W, 
   // takes the library reciprocal square root (which rescales such inputs) instead of the bare instruction
   const bool raw = A.eps_acc >= 1e-30f;
   const StepFeats none{};
-#define LOPT_LAUNCH_F16S(R, U, F)                                                                               \
-  hipLaunchKernelGGL((k_apply_f16s<R, U, F>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,    \
+#define LOPT_LAUNCH_F16S(R, U, F, NT)                                                                           \
+  hipLaunchKernelGGL((k_apply_f16s<R, U, F, NT>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,    \
                      L.apply_counter, L.ws, A, W.mlp_tail, W.mlp, feats ? *feats : none)
-#define LOPT_LAUNCH_F16S2(R, U) do { if (feats) LOPT_LAUNCH_F16S(R, U, true); else LOPT_LAUNCH_F16S(R, U, false); } while (0)
+#define LOPT_LAUNCH_F16S2(R, U)                                   \
+  do {                                                            \
+    if (feats) LOPT_LAUNCH_F16S(R, U, true, true);                \
+    else if (L.strip_ordinary) LOPT_LAUNCH_F16S(R, U, false, false); \
+    else LOPT_LAUNCH_F16S(R, U, false, true);                     \
+  } while (0)
   if (raw && update_state) LOPT_LAUNCH_F16S2(true, true);
   else if (raw) LOPT_LAUNCH_F16S2(true, false);
   else if (update_state) LOPT_LAUNCH_F16S2(false, true);

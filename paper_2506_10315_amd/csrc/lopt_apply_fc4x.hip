@@ -311,14 +311,14 @@ template <int HP, bool RAW_RSQ, bool UPDATE_STATE>
 __global__ void __launch_bounds__(kBlock, narrow_waves_per_simd(HP)) k_apply_fc4x(const TensorDev* __restrict__ tensors,
                                                                                const ApplyTileDev* __restrict__ atiles, int n_atiles,
                                                                                int* __restrict__ next_tile, float* __restrict__ ws,
-                                                                               StepArgs A, const float* __restrict__ tail) {
+                                                                               StepArgs A, const float* __restrict__ tail, bool off_grid_nt) {
   __shared__ Fc4Lds<HP> L;
   __shared__ int s_tile;
   for (int tile_id = blockIdx.x; tile_id < n_atiles; tile_id = s_tile) {   // workgroup-uniform
     const ApplyTileDev tile = atiles[tile_id];
     const TensorDev& T = tensors[tile.tensor];
-    // nontemporal accesses where no line is shared between wavefronts (rows on the 128-byte grid)
-    if (T.vec == 2) apply_fc4x_tile<HP, true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A, tail, L);
+    // nontemporal accesses where no line is shared between wavefronts (rows on the 128-byte grid), and by choose_loads
+    if (T.vec == 2 || (T.vec == 0 && off_grid_nt)) apply_fc4x_tile<HP, true, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A, tail, L);
     else apply_fc4x_tile<HP, false, RAW_RSQ, UPDATE_STATE>(T, tile, ws, A, tail, L);
     __syncthreads();   // every wavefront is done with this tile's tables and has read s_tile
     if (n_atiles <= (int)gridDim.x) break;   // one tile each: nobody asks (see k_apply_f16s)
@@ -338,7 +338,7 @@ void launch_apply_fc4x(const Launch& L, const StepArgs& A, const WeightsDev& W, 
   const int grid = L.n_atiles < resident ? L.n_atiles : resident;
 #define LOPT_LAUNCH_FC4X(HP, R, U)                                                                                    \
   hipLaunchKernelGGL((k_apply_fc4x<HP, R, U>), dim3(grid), dim3(kBlock), 0, s, L.tensors, L.atiles, L.n_atiles,       \
-                     L.apply_counter, L.ws, A, W.mlp_tail)
+                     L.apply_counter, L.ws, A, W.mlp_tail, L.off_grid_nt)
 #define LOPT_LAUNCH_FC4X_W(HP)                          \
   do {                                                  \
     if (raw && update_state) LOPT_LAUNCH_FC4X(HP, true, true);  \

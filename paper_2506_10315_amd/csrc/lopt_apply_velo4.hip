@@ -332,13 +332,13 @@ __device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const Til
 template <bool RAW_RSQ, bool UPDATE_STATE>
 __global__ void __launch_bounds__(kBlock, 4) k_apply_velo4(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                        StepArgs A) {
+                                                        StepArgs A, bool off_grid_nt) {
   const TileDev tile = tiles[blockIdx.x];
   const TensorDev& T = tensors[tile.tensor];
   if (T.n <= kNarrowCols) apply_velo4_narrow<RAW_RSQ, UPDATE_STATE>(T, tile, ws, A);
   else {
     const RowWalk w = row_walk(T, tile, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-    if (T.vec == 2) apply_velo4_tile<true, false, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
+    if (T.vec == 2 || (T.vec == 0 && off_grid_nt)) apply_velo4_tile<true, false, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
     else if (T.vec) apply_velo4_tile<false, true, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
     else apply_velo4_tile<false, false, RAW_RSQ, UPDATE_STATE>(T, w, ws, A);
   }
@@ -352,7 +352,7 @@ void launch_apply_velo4(const Launch& L, const StepArgs& A, bool update_state, h
   // library reciprocal square root (which rescales such inputs) instead of the bare instruction
   const bool raw = A.eps_acc >= 1e-30f;
 #define LOPT_LAUNCH_V4(R, U) \
-  hipLaunchKernelGGL((k_apply_velo4<R, U>), dim3(L.n_tiles), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A)
+  hipLaunchKernelGGL((k_apply_velo4<R, U>), dim3(L.n_tiles), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.off_grid_nt)
   if (raw && update_state) LOPT_LAUNCH_V4(true, true);
   else if (raw) LOPT_LAUNCH_V4(true, false);
   else if (update_state) LOPT_LAUNCH_V4(false, true);

@@ -137,6 +137,8 @@ struct Launch {
   int keep, keep_off;     // tiles below these numbers are read by the statistics pass with ordinary loads: rows on the 128-byte grid,
                           // rows off the 16-byte grid (Plan::keep)
   bool backwards;         // the statistics pass takes its tiles from the last to the first
+  bool strip_ordinary;    // the strip kernel reads with ordinary loads, the narrow and the VeLO kernel access rows off the 16-byte
+  bool off_grid_nt;       // grid nontemporally (Plan)
 };
 
 // kernels (lopt_kernels.hip / lopt_apply_mfma.hip)

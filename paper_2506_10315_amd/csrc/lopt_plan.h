@@ -41,6 +41,7 @@ struct Plan {
   int groups = 1;                     // tensor groups of the two-stream pipeline
   int keep = 0, keep_off = 0;         // see choose_loads
   bool backwards = false;
+  bool strip_ordinary = false, off_grid_nt = false;   // see choose_loads
   bool fold_finalize = false;         // k_finalize is not launched: the strip kernel's workgroups form their tensor's scales, the
                                       // LSTM's those of all (few) tensors
   std::vector<ApplyTileDev> atiles;   // apply tiles (none for ApplyTiles::None)
@@ -132,8 +133,11 @@ inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, i
 inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   constexpr uint64_t kCached = 10u << 20;
   int cached = (int)pl->tiles.size();   // tiles of the first kCached elements
-  uint64_t seen = 0, off_grid = 0;
-  for (const TensorDev& T : pl->tensors) off_grid += T.vec == 0 ? (uint64_t)T.m * (uint64_t)T.n : 0;
+  uint64_t seen = 0, off_grid = 0, off_line = 0;
+  for (const TensorDev& T : pl->tensors) {
+    off_grid += T.vec == 0 ? (uint64_t)T.m * (uint64_t)T.n : 0;
+    off_line += T.vec != 2 ? (uint64_t)T.m * (uint64_t)T.n : 0;
+  }
   for (const TensorDev& T : pl->tensors) {
     const uint64_t N = (uint64_t)T.m * (uint64_t)T.n;
     if (seen + N > kCached) {
@@ -148,6 +152,16 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   pl->backwards = pl->short_list ? !small : velo;
   pl->keep = small ? all : velo || (pl->short_list && !narrow) ? cached : 0;
   pl->keep_off = pl->short_list && velo && total >= (13u << 20) ? cached : all;
+  // The apply pass. Width 32 reads 128 bytes of a row at a time; off the 128-byte grid these share their lines with the neighbours, which
+  // nontemporal loads fetch again. us a step, nontemporal / ordinary: 3.2 M elements of 901 columns 92 / 87, 6 M of 1225 144 / 141, 8.2 M of
+  // 1531 179.4 / 181.6, 9 M of 1501 191 / 191, 12 M of 1733 253 / 252, 20 M of 2237 409 / 402, 24 M of 2451 499 / 486, 44 M of 3301 1004 / 823, 108 M of 6001 2554 / 1989; 4 M of 1000 103 / 99.5, 17 M of 2052 371 / 344, 128 M of 8004 2842 / 2270. On the
+  // grid it is the cache that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 / 322,
+  // ViT-B/16 shapes 1464 / 1482.
+  pl->strip_ordinary = 2 * off_line > total ? total < (7u << 20) || total >= (13u << 20) : total < (11u << 19);
+  // VeLO and the narrow widths: rows off the 16-byte grid, ordinary / nontemporal, VeLO 4.8 M elements of 1101 columns 81.5 / 87, 6 M of 1225 101 / 100, 9 M
+  // 148.5 / 138, 12 M 189 / 174, 16 M 252 / 238, 20 M 303 / 296, 24 M 357 / 360, 54 M 779 / 821; width 16 4 M 91 / 100, 6 M 136 / 144, 7.3 M 164.5 / 164, 9 M 195 / 192, 16 M 333 /
+  // 321, 20 M 396 / 403. (Rows on the 16-byte but off the 128-byte grid: VeLO 9 M 150.6 / 150.3, 17 M 269 / 285.)
+  pl->off_grid_nt = total >= (velo ? 6u : 7u) << 20 && total < (velo ? 21u : 18u) << 20;
 }
 
 // Lay out tiles, row/column blocks and workspace regions for a tensor list.

@@ -538,3 +538,13 @@ def test_velo_rows_off_the_grid_write_nothing_beside_the_tensor(cols):
     torch.cuda.synchronize()
     assert torch.equal(flat[:64], before[:64]) and torch.equal(flat[64 + n:], before[64 + n:])
     assert float((flat[64:64 + n] != before[64:64 + n]).float().mean()) > 0.9
+
+
+@pytest.mark.parametrize("kind,hidden", [("velo", 4), ("small_fc_lopt", 16), ("small_fc_lopt", 32)])
+def test_rows_off_the_grid_with_either_kind_of_access_in_the_apply_pass(kind, hidden):
+    # lists long enough for the apply pass to access rows off the 16-byte grid nontemporally (VeLO and width 16 from 6 and 7 M elements
+    # on, width 32 from 7 to 13 M); shorter ones, with ordinary accesses, are everywhere above
+    cfg = Hn.make_cfg(kind, hidden=hidden) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8)
+    shapes = [(2700, 2731), (65, 258), (7,)]
+    worst = Hn.run_free(Hn.Case(135, _specs(shapes), "gauss_logscale"), cfg, Hn.random_weights(cfg, seed=35), 1, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
