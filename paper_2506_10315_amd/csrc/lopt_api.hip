@@ -568,7 +568,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   if (st != LOPT_OK) return st;
   const TableStore& tb = ctx->heap;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
-           (int)ctx->plan.rc_blocks().size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false, false, false};
+           (int)ctx->plan.rc_blocks().size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false, false, false, false};
   StepArgs A = make_args(ctx, 0, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
@@ -642,7 +642,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rc_blocks().size(),
            tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0,
-           tb.d_rctiles, (int)pl.rctiles.size(), pl.short_list, pl.keep, pl.keep_off, pl.backwards, pl.strip_ordinary, pl.off_grid_nt};
+           tb.d_rctiles, (int)pl.rctiles.size(), pl.short_list, pl.keep, pl.keep_off, pl.keep_line, pl.backwards, pl.strip_ordinary, pl.off_grid_nt};
   // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
   // statistics pass only reads them: 24 + 44 instead of 40 + 28 bytes per element (configuration field state_pass).
   // The read-only statistics stream runs at 83 % of the HBM rate against 67 % for the read-write one; the strip-form
@@ -700,6 +700,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
       S.apply_counter = L.apply_counter + g;
       S.beside_apply = g > 0;
       S.keep = 0; S.backwards = false;   // tile numbers of the whole list; the groups are short
+      if (velo) S.keep_off = 0;
       return S;
     };
     // accumulator update + statistics + per-tensor finalize of one group: what its apply pass waits for

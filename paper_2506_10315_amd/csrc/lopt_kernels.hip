@@ -816,7 +816,7 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
 template <bool RAW_RCP, bool WRITE, bool FUSE>
 __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
-                                                        StepArgs A, int n_tiles, MixArgs M, int keep, int keep_off,
+                                                        StepArgs A, int n_tiles, MixArgs M, int keep, bool keep_line, int keep_off,
                                                         bool backwards, const RcItemDev* __restrict__ rcitems, int n_rcitems,
                                                         bool rc_first) {
   __shared__ __align__(16) float red[kNStat][kRedStride];
@@ -845,9 +845,9 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  // rows off the 16-byte grid of long lists: ordinary loads for all tiles
   if (T.n <= kNarrowCols) accum_narrow<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
-  else if (T.vec == 2 ? idx < keep : T.vec == 0 && (!FUSE || idx < keep_off)) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  // (written so that it costs no register: one more and the pass no longer fits beside the apply kernel)
+  else if (T.vec == 2 ? idx < keep : (T.vec == 0 || (FUSE && keep_line)) && idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
@@ -863,7 +863,7 @@ void launch_accum_stats(const Launch& L, const StepArgs& A, const WeightsDev& W,
   const bool rc_first = L.n_tiles > 4 * L.resident_wgs;   // eight workgroups a CU
 #define LOPT_LAUNCH_ACC(R, Wr, F) \
   hipLaunchKernelGGL((k_accum_stats<R, Wr, F>), dim3(L.n_tiles + extra), dim3(kBlock), 0, s, L.tensors, L.tiles, L.ws, A, L.n_tiles, M, \
-                     L.keep, L.keep_off, L.backwards, L.rcitems, n_rc, rc_first)
+                     L.keep, L.keep_line, L.keep_off, L.backwards, L.rcitems, n_rc, rc_first)
 #define LOPT_LAUNCH_ACC2(R, Wr) do { if (L.short_list) LOPT_LAUNCH_ACC(R, Wr, true); else LOPT_LAUNCH_ACC(R, Wr, false); } while (0)
   if (raw && write_state) LOPT_LAUNCH_ACC2(true, true);
   else if (raw) LOPT_LAUNCH_ACC2(true, false);
