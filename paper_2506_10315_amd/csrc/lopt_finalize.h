@@ -61,7 +61,8 @@ __device__ __forceinline__ void feature_scale(const TensorDev& T, const StepArgs
   const double m = (double)T.m, n = (double)T.n;
   const bool fac = (f >= 10 && f < 13) || (f >= 25 && f < 28), clip = f == 28;
   const int k = fac ? (f < 13 ? f - 10 : f - 25) : 0;
-  const int q = f < 13 ? f : f < 16 ? 20 + (f - 13) : f < 19 ? 26 + (f - 16) : f < 22 ? 23 + (f - 19) : f < 25 ? 29 + (f - 22) : clip ? 16 : f < 28 ? f - 12 : 0;
+  const int q = f < 13 ? f : f < 16 ? 20 + (f - 13) : f < 19 ? 26 + (f - 16) : f < 22 ? 23 + (f - 19) : f < 25 ? 29 + (f - 22)
+              : f < 28 ? f - 12 : clip ? 16 : 0;
   const bool row = (f >= 13 && f < 16) || (f >= 19 && f < 22), col = (f >= 16 && f < 19) || (f >= 22 && f < 25);
   const double rbar = tot[17 + k] / m + (double)A.eps_acc;
   double s = tot[q] / (row ? m : col ? n : m * n);

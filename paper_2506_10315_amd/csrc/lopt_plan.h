@@ -129,11 +129,12 @@ inline bool is_short_list(size_t n, const lopt_tensor_desc* d, uint64_t total, i
 //     138.3, 12 M 190 / 183, width 32 and 16 the same, 14 M VeLO 221 / 208, width 32 298 / 299.5, width 16 290 / 278, 21 M VeLO 363 / 330, width 32
 //     472 / 455, width 16 435 / 417
 //   rows on the 16-byte but off the 128-byte grid: in short lists as rows off the 16-byte grid, for the other widths between 1.5 M and 13 M
-//     elements. Nontemporal / so, VeLO 1 M elements of 1000 columns 38.5 / 35.3, 4 M of 1000 75.3 / 69.5, 9 M of 1500 150.8 / 147.8, 17 M of 2052
-//     270 / 268, 32 M of 2828 500 / 491; width 32 1.1 M of 516 41.2 / 42.6, 1.4 M of 600 43 / 43, 2.2 M of 740 69.8 / 66.5, 4 M 100.4 / 96.6, 9 M 194 / 188.5, 17 M
-//     351 / 357, 32 M 637 / 645; width 16 1.4 M 49.1 / 47.8, 4 M 92.6 / 90.1. Long lists: one 8004x8004 932 / 951 and 1195 / 1219
-//   rows off the 16-byte grid of long lists, ordinary / nontemporal: VeLO 72 M of 6001 columns 1042 / 1006, 84 M of 4099 1197 / 1166; width 32 1375 / 1404,
-//     1611 / 1652
+//     elements. Nontemporal / so, VeLO 1 M elements of 1000 columns 38.5 / 35.3, 4 M of 1000 75.3 / 69.5, 9 M of 1500 150.8 / 147.8, 17 M of
+//     2052 270 / 268, 32 M of 2828 500 / 491; width 32 1.1 M of 516 41.2 / 42.6, 1.4 M of 600 43 / 43, 2.2 M of 740 69.8 / 66.5, 4 M 100.4 /
+//     96.6, 9 M 194 / 188.5, 17 M 351 / 357, 32 M 637 / 645; width 16 1.4 M 49.1 / 47.8, 4 M 92.6 / 90.1. Long lists: one 8004x8004 932 / 951
+//     and 1195 / 1219
+//   rows off the 16-byte grid of long lists, ordinary / nontemporal: VeLO 72 M of 6001 columns 1042 / 1006, 84 M of 4099 1197 / 1166; width
+//     32 1375 / 1404, 1611 / 1652
 //   long lists under VeLO: from the last tile to the first, nontemporal but for the first 10 M elements' tiles: ViT-B/16 shapes
 //     1158 -> 1150 (6.5 M 1153, 16 M 1151.5; everything 1181), Llama-1.3B shapes 17310 -> 17283
 //   long lists of small_fc_lopt: nontemporal (ViT-B/16 shapes 313 us the pass, 352 with ordinary loads).
@@ -162,13 +163,15 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   pl->keep_off = velo && (!pl->short_list || total >= (13u << 20)) ? cached : all;
   // The apply pass. Width 32 reads 128 bytes of a row at a time; off the 128-byte grid these share their lines with the neighbours, which
   // nontemporal loads fetch again. us a step, nontemporal / ordinary: 3.2 M elements of 901 columns 92 / 87, 6 M of 1225 144 / 141, 8.2 M of
-  // 1531 179.4 / 181.6, 9 M of 1501 191 / 191, 12 M of 1733 253 / 252, 20 M of 2237 409 / 402, 24 M of 2451 499 / 486, 44 M of 3301 1004 / 823, 108 M of 6001 2554 / 1989; 4 M of 1000 103 / 99.5, 17 M of 2052 371 / 344, 128 M of 8004 2842 / 2270. On the
-  // grid it is the cache that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 / 322,
-  // ViT-B/16 shapes 1464 / 1482.
+  // 1531 179.4 / 181.6, 9 M of 1501 191 / 191, 12 M of 1733 253 / 252, 20 M of 2237 409 / 402, 24 M of 2451 499 / 486, 44 M of 3301 1004 /
+  // 823, 108 M of 6001 2554 / 1989; 4 M of 1000 103 / 99.5, 17 M of 2052 371 / 344, 128 M of 8004 2842 / 2270. On the grid it is the cache
+  // that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 /
+  // 322, ViT-B/16 shapes 1464 / 1482.
   pl->strip_ordinary = 2 * off_line > total ? total < (7u << 20) || total >= (13u << 20) : total < (11u << 19);
-  // VeLO and the narrow widths: rows off the 16-byte grid, ordinary / nontemporal, VeLO 4.8 M elements of 1101 columns 81.5 / 87, 6 M of 1225 101 / 100, 9 M
-  // 148.5 / 138, 12 M 189 / 174, 16 M 252 / 238, 20 M 303 / 296, 24 M 357 / 360, 54 M 779 / 821; width 16 4 M 91 / 100, 6 M 136 / 144, 7.3 M 164.5 / 164, 9 M 195 / 192, 16 M 333 /
-  // 321, 20 M 396 / 403. (Rows on the 16-byte but off the 128-byte grid: VeLO 9 M 150.6 / 150.3, 17 M 269 / 285.)
+  // VeLO and the narrow widths: rows off the 16-byte grid, ordinary / nontemporal, VeLO 4.8 M elements of 1101 columns 81.5 / 87, 6 M of 1225
+  // 101 / 100, 9 M 148.5 / 138, 12 M 189 / 174, 16 M 252 / 238, 20 M 303 / 296, 24 M 357 / 360, 54 M 779 / 821; width 16 4 M 91 / 100, 6 M
+  // 136 / 144, 7.3 M 164.5 / 164, 9 M 195 / 192, 16 M 333 / 321, 20 M 396 / 403. (Rows on the 16-byte but off the 128-byte grid: VeLO 9 M
+  // 150.6 / 150.3, 17 M 269 / 285.)
   pl->off_grid_nt = total >= (velo ? 6u : 7u) << 20 && total < (velo ? 21u : 18u) << 20;
 }
 
