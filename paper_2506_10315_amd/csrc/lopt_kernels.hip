@@ -629,16 +629,38 @@ __device__ __forceinline__ void short_rc_block(const TensorDev& T, const RcItemD
 // against 0.670 plain/plain, 0.670 plain/nontemporal, 0.680 nontemporal/nontemporal); what is worth keeping in the cache for
 // the apply pass is read with ordinary loads (choose_loads in lopt_plan.h).
 
+// What one element adds to the sums. Every feature is formed before it is squared: the squares of its factors leave the fp32
+// range long before the feature does ((g a_i b_j)^2 taken as g^2 (a_i^2 b_j^2) and M_i^2 / (V+eps): 0.3 % off for gradients of 1e-19, wrong
+// altogether below 1e-21 and above 1e11, NaN for a gradient of zeros where eps_acc is below 5e-20). Products of squares save nine of some
+// fifty vector instructions an element, but these streams wait for memory. us a step, squares / this way: 1000x1000 35.3 / 34.5,
+// 8.2 M elements of 1531 columns 180 / 179, 54 M of 2731 under VeLO 779 / 778, ViT-B/16 shapes under VeLO 1130 / 1130; beside the apply pass
+// of another tensor group, which wants the vector units too, ViT-B/16 shapes 1480 / 1483.5, 355 M elements 5865 / 5881.
+__device__ __forceinline__ void add_squares(float (&acc)[kNStat], float g, float g2, float p, const float (&m)[3], float v, float rs,
+                                            const float (&f)[3]) {
+  const float clip2 = 0.1f * 0.1f;   // clip(g, +-0.1)^2 = min(g^2, 0.01)
+  acc[0] += g2;
+  acc[1] += p * p;
+  acc[5] += v * v;
+  acc[9] += rs * rs;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float mn = m[k] * rs, gf = g * f[k], mf = m[k] * f[k];
+    acc[2 + k] += m[k] * m[k];
+    acc[6 + k] += mn * mn;
+    acc[10 + k] += gf * gf;
+    acc[13 + k] += mf * mf;
+  }
+  acc[16] += fminf(g2, clip2);
+}
+
 // A lane holds four consecutive columns of a row; lanes past the last column sit the tile out and nothing in the loop is
-// predicated. The sums of squares are taken in the form that needs the fewest vector
-// instructions: (M_i rsqrt(V+eps))^2 = M_i^2 / (V+eps), (g a_i b_j)^2 = g^2 a_i^2 b_j^2 (squared row and column
-// factors are formed once per row / per tile), clip(g, +-0.1)^2 = min(g^2, 0.01). RAW_RCP: the bare v_rcp_f32 (it
-// treats inputs below the smallest normal float as zero, so the launcher asks for it only when eps_acc >= 1e-30).
+// predicated. RAW_RSQ: the bare v_rsq_f32 (it treats inputs below the smallest normal float as zero, so the launcher asks for it
+// only when eps_acc >= 1e-30).
 // In the last lane of a ragged row the columns past the end hold zeros, which add nothing to any sum but that of 1/(V+eps), which is set
 // to zero there. Rows off the 16-byte grid, four columns a lane against one column a lane in 64-column segments, us a step: 8.3 M
 // elements of 1531 columns 189 -> 183, width 16 143 -> 135.5, VeLO 153 -> 147.5; 54 M of 2731 columns under VeLO 838 -> 811 (with the
 // sums); 0.4 M under VeLO 37 -> 34.3. NT: nontemporal loads (Plan::keep).
-template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
+template <bool RAW_RSQ, bool WRITE, bool FUSE, bool NT>
 __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& tile, float* __restrict__ ws,
                                                const StepArgs& A, float (&acc)[kNStat], FuseLds* L) {
   const int lane = threadIdx.x & 63;
@@ -677,27 +699,23 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
     for (int k = 0; k < 3; ++k) c3[k] = *reinterpret_cast<const float4*>(ws + T.oRC + (size_t)k * T.padn + col);
     load(0, row);
   }
-  float rc2[3][4];
+  float rc[3][4];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float4 c = c3[k];
-    rc2[k][0] = c.x * c.x; rc2[k][1] = c.y * c.y; rc2[k][2] = c.z * c.z; rc2[k][3] = c.w * c.w;
+    rc[k][0] = c.x; rc[k][1] = c.y; rc[k][2] = c.z; rc[k][3] = c.w;
     if (!FUSE)   // (LDS holds zeros there)
 #pragma unroll
-      for (int e = 1; e < 4; ++e) rc2[k][e] = e < ncol ? rc2[k][e] : 0.f;
+      for (int e = 1; e < 4; ++e) rc[k][e] = e < ncol ? rc[k][e] : 0.f;
   }
   const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
   const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
   const float eps = A.eps_acc;
-  const float clip2 = 0.1f * 0.1f;
   auto add = [&](const Row& x) __attribute__((always_inline)) {
     const auto& [g4, p4, m1, m2, m3, v4, ro, r] = x;
-    float rr2[3];
+    float rr[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float rr = FUSE ? L->rr[k][r - tile.ti * T.TR] : ws[T.oRR + (size_t)k * T.padm + r];
-      rr2[k] = rr * rr;
-    }
+    for (int k = 0; k < 3; ++k) rr[k] = FUSE ? L->rr[k][r - tile.ti * T.TR] : ws[T.oRR + (size_t)k * T.padm + r];
     f32x4v o1, o2, o3, ov;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -709,19 +727,9 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
       const float nm3 = __builtin_fmaf(b3, m3[e], a3 * g);
       const float nv = __builtin_fmaf(b4, v4[e], a4 * g2);
       o1[e] = nm1; o2[e] = nm2; o3[e] = nm3; ov[e] = nv;
-      const float s1 = nm1 * nm1, s2 = nm2 * nm2, s3 = nm3 * nm3;
-      float rs2 = RAW_RCP ? __builtin_amdgcn_rcpf(nv + eps) : 1.0f / (nv + eps);
-      if (e > 0) rs2 = e < ncol ? rs2 : 0.f;
-      const float f0 = rr2[0] * rc2[0][e], f1 = rr2[1] * rc2[1][e], f2 = rr2[2] * rc2[2][e];
-      acc[0] += g2;
-      acc[1] += p * p;
-      acc[2] += s1; acc[3] += s2; acc[4] += s3;
-      acc[5] += nv * nv;
-      acc[6] += s1 * rs2; acc[7] += s2 * rs2; acc[8] += s3 * rs2;
-      acc[9] += rs2;
-      acc[10] += g2 * f0; acc[11] += g2 * f1; acc[12] += g2 * f2;
-      acc[13] += s1 * f0; acc[14] += s2 * f1; acc[15] += s3 * f2;
-      acc[16] += fminf(g2, clip2);
+      float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(nv + eps) : rsqrtf(nv + eps);
+      if (e > 0) rs = e < ncol ? rs : 0.f;
+      add_squares(acc, g, g2, p, {nm1, nm2, nm3}, nv, rs, {rr[0] * rc[0][e], rr[1] * rc[1][e], rr[2] * rc[2][e]});
     }
     if (WRITE) {
       store_quad<false>(T.st + ro, 16u * lane, bytes, o1);
@@ -746,7 +754,7 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
 
 // Narrow tensors: one column a lane (NarrowWalk), the same sums. A row past the tile adds nothing: its values read as 0.
 constexpr int kNarrowTrip = 2;   // accesses in flight
-template <bool RAW_RCP, bool WRITE, bool FUSE, bool NT>
+template <bool RAW_RSQ, bool WRITE, bool FUSE, bool NT>
 __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& tile, float* __restrict__ ws, const StepArgs& A,
                                              float (&acc)[kNStat], FuseLds* L) {
   if (FUSE) fuse_means(T, tile, ws, A, *L);
@@ -757,13 +765,10 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
   const size_t pN = T.padN;
   const float b1 = A.mom_decay[0], b2 = A.mom_decay[1], b3 = A.mom_decay[2], b4 = A.rms_decay;
   const float a1 = 1.0f - b1, a2 = 1.0f - b2, a3 = 1.0f - b3, a4 = 1.0f - b4;
-  const float eps = A.eps_acc, clip2 = 0.1f * 0.1f;
-  float rc2[3];
+  const float eps = A.eps_acc;
+  float rc[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const float rc = FUSE ? L->rc[k][w.col] : ws[T.oRC + (size_t)k * T.padn + w.col];
-    rc2[k] = rc * rc;
-  }
+  for (int k = 0; k < 3; ++k) rc[k] = FUSE ? L->rc[k][w.col] : ws[T.oRC + (size_t)k * T.padn + w.col];
   for (unsigned r = r0 + w.first; r < r1; r += w.step) {
     float in[kNarrowTrip][6], rr[kNarrowTrip][3];
     const size_t ro = (size_t)r * (unsigned)n;
@@ -786,19 +791,9 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
       const float nm2 = __builtin_fmaf(b2, in[e][3], a2 * g);
       const float nm3 = __builtin_fmaf(b3, in[e][4], a3 * g);
       const float nv = __builtin_fmaf(b4, in[e][5], a4 * g2);
-      const float s1 = nm1 * nm1, s2 = nm2 * nm2, s3 = nm3 * nm3;
-      float rs2 = RAW_RCP ? __builtin_amdgcn_rcpf(nv + eps) : 1.0f / (nv + eps);
-      rs2 = r + e * w.rows + w.sub < r1 ? rs2 : 0.f;
-      const float f0 = rr[e][0] * rr[e][0] * rc2[0], f1 = rr[e][1] * rr[e][1] * rc2[1], f2 = rr[e][2] * rr[e][2] * rc2[2];
-      acc[0] += g2;
-      acc[1] += p * p;
-      acc[2] += s1; acc[3] += s2; acc[4] += s3;
-      acc[5] += nv * nv;
-      acc[6] += s1 * rs2; acc[7] += s2 * rs2; acc[8] += s3 * rs2;
-      acc[9] += rs2;
-      acc[10] += g2 * f0; acc[11] += g2 * f1; acc[12] += g2 * f2;
-      acc[13] += s1 * f0; acc[14] += s2 * f1; acc[15] += s3 * f2;
-      acc[16] += fminf(g2, clip2);
+      float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(nv + eps) : rsqrtf(nv + eps);
+      rs = r + e * w.rows + w.sub < r1 ? rs : 0.f;
+      add_squares(acc, g, g2, p, {nm1, nm2, nm3}, nv, rs, {rr[e][0] * rc[0], rr[e][1] * rc[1], rr[e][2] * rc[2]});
       if (WRITE) {
         const unsigned off = w.off + 4u * (unsigned)(e * w.rows * n);
         store_one<false>(T.st + ro, off, bytes, nm1);
@@ -813,8 +808,10 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
 // WRITE = false: the accumulators are only read (their new values are formed for the statistics and dropped); the apply
 // pass of the same step forms them again and writes them (the two default apply kernels can; a read-only stream
 // sustains a higher share of the HBM rate than a read-write one, and 16 of this pass's 40 bytes per element move there).
-template <bool RAW_RCP, bool WRITE, bool FUSE>
-__global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restrict__ tensors,
+// Registers: where nothing is fused in, 64 are asked for (eight wavefronts a SIMD), with the stores 72. With 65 the reading form
+// no longer fits beside the apply kernel of another tensor group (ViT-B/16 shapes 1510 -> 1567 us a step, 355 M elements 5939 -> 6278).
+template <bool RAW_RSQ, bool WRITE, bool FUSE>
+__global__ void __launch_bounds__(kBlock, FUSE ? 1 : WRITE ? 7 : 8) k_accum_stats(const TensorDev* __restrict__ tensors,
                                                         const TileDev* __restrict__ tiles, float* __restrict__ ws,
                                                         StepArgs A, int n_tiles, MixArgs M, int keep, bool keep_line, int keep_off,
                                                         bool backwards, const RcItemDev* __restrict__ rcitems, int n_rcitems,
@@ -845,10 +842,10 @@ __global__ void __launch_bounds__(kBlock) k_accum_stats(const TensorDev* __restr
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  if (T.n <= kNarrowCols) accum_narrow<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  if (T.n <= kNarrowCols) accum_narrow<RAW_RSQ, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   // (written so that it costs no register: one more and the pass no longer fits beside the apply kernel)
-  else if (T.vec == 2 ? idx < keep : (T.vec == 0 || (FUSE && keep_line)) && idx < keep_off) accum_tile<RAW_RCP, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
-  else accum_tile<RAW_RCP, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
+  else if (T.vec == 2 ? idx < keep : (T.vec == 0 || (FUSE && keep_line)) && idx < keep_off) accum_tile<RAW_RSQ, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  else accum_tile<RAW_RSQ, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
   const int lt = tile.ti * T.nct + tile.tj;
   block_sum<kNStat>(acc, red, ws + T.oStatPart + (size_t)lt * kStatStride);
 }

@@ -548,3 +548,56 @@ def test_rows_off_the_grid_with_either_kind_of_access_in_the_apply_pass(kind, hi
     shapes = [(2700, 2731), (65, 258), (7,)]
     worst = Hn.run_free(Hn.Case(135, _specs(shapes), "gauss_logscale"), cfg, Hn.random_weights(cfg, seed=35), 1, lr_fn=lambda t: 0.5, wd=0.01)
     assert worst["param"] <= Hn.TOL_PARAM
+
+
+RANGE_SHAPES = [(33, 131), (20, 259), (31, 100), (40, 7), (64, 256), (40, 132), (1, 1031)]   # off the 16-byte grid, narrow, on it, a vector
+
+
+@pytest.mark.parametrize("tall", [[], [(6145, 2)]])
+@pytest.mark.parametrize("kind,state_pass", [("small_fc_lopt", "apply"), ("small_fc_lopt", "stats"), ("velo", "apply")])
+@pytest.mark.parametrize("scale", [2.5e-23, 1e-21, 1e-19, 1e9, 1e12])
+def test_statistics_of_gradients_whose_squares_leave_the_fp32_range(scale, kind, state_pass, tall):
+    # g sqrt(mean r / (r c)) is a number of ordinary size for gradients of any scale; g^2 is not. Each statistic that fp32 holds has to be
+    # right, in short lists and (with a tensor of more rows than those may have) the ordinary form. Steps from zero state: M_1 = 0.1 g.
+    # The first column and row are 100 times smaller than the rest.
+    import torch
+    import paper_2506_10315_amd as P
+    from oracle import lopt_oracle as O
+    lstm = {} if kind == "small_fc_lopt" else dict(lstm_hidden=32, n_bank=8)
+    cfg = Hn.make_cfg(kind, state_pass=state_pass, **lstm)
+    shapes = RANGE_SHAPES + tall
+    assert plan(shapes, kind=kind, **lstm)["short_list"] == (not tall)
+    ocfg, rng = Hn.oracle_config_from(cfg), np.random.default_rng(41)
+    ps = [rng.standard_normal(s).astype(np.float32) * np.float32(0.02) for s in shapes]
+    gs = [(rng.standard_normal(s) * scale).astype(np.float32) for s in shapes]
+    for g in gs:
+        g[0] *= np.float32(0.01) if g.shape[0] > 1 else np.float32(1)
+        g[:, 0] *= np.float32(0.01)
+    opt = P.LearnedOptimizer(cfg, Hn.random_weights(cfg, seed=36), shapes)
+    opt.step([torch.from_numpy(p).cuda() for p in ps], [torch.from_numpy(g).cuda() for g in gs], lr=1.0, loss=1.0)
+    torch.cuda.synchronize()
+    for i, got in enumerate(opt.stats()):
+        st = O.init_state(*shapes[i], ocfg)
+        O.update_accumulators(st, gs[i], ocfg)
+        want = O.tensor_statistics(ps[i], gs[i], st, ocfg, 0)[:ocfg.n_normalized]
+        rel = np.abs(got.cpu().numpy().astype(np.float64) - want) / (want + ocfg.eps_norm)
+        # a sum of squares beyond fp32, or of values whose squares (those of r, c and V: fourth powers of g) are, is not held at all
+        held = want * np.prod(shapes[i]) < 1e38
+        assert held[6:13].all() and held[22:25].all()
+        assert rel[held].max() <= Hn.TOL_STATS, (shapes[i], int(np.argmax(np.where(held, rel, 0.0))), rel[held].max())
+
+
+@pytest.mark.parametrize("tall", [[], [(6145, 2)]])
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+@pytest.mark.parametrize("eps", [1e-24, 1e-32])
+def test_zero_gradients_with_a_small_eps_acc(eps, kind, tall):
+    # a layer that gets no gradient: 1/(r+eps) and 1/(c+eps) are in the fp32 range, their product is not
+    class Zeros(Hn.Case):
+        def grad(self, i, step):
+            return super().grad(i, step) * np.float32(0 if i % 2 == 0 else 1e-12)
+
+    cfg = Hn.make_cfg(kind, **({} if kind == "small_fc_lopt" else dict(lstm_hidden=32, n_bank=8)))
+    cfg.eps_acc = eps
+    shapes = [s for s in RANGE_SHAPES for _ in range(2)] + tall
+    worst = Hn.run_free(Zeros(136, _specs(shapes)), cfg, Hn.random_weights(cfg, seed=37), 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
