@@ -77,8 +77,8 @@ __device__ __forceinline__ void feature_scale(const TensorDev& T, const StepArgs
 struct FinTerms { const float* base; int count, stride; };
 __device__ __forceinline__ FinTerms fin_terms(const TensorDev& T, const float* ws, int q) {
   if (q < kNStat) return FinTerms{ws + T.oStatPart + q, T.nrt * T.nct, kStatStride};
-  if (q < 26) return FinTerms{ws + T.oRcPart + (q - kNStat), T.nrblk, kRcStride};
-  return FinTerms{ws + T.oRcPart + (size_t)T.nrblk * kRcStride + (q - 26 + 3), T.ncblk, kRcStride};
+  if (q < 26) return FinTerms{ws + T.oRcPart + (q - kNStat), T.nrpart, kRcStride};
+  return FinTerms{ws + T.oRcPart + (size_t)T.nrpart * kRcStride + (q - 26 + 3), T.ncpart, kRcStride};
 }
 
 // Sum of the 32 segments of one sum, in a fixed order: part[0], part[32], ...

@@ -22,7 +22,7 @@ constexpr int kShortRows = 64;    // short lists: rows of a statistics tile at m
 // 140.2, 1000x1000 41.5 / 41.7 / 42.5, under VeLO, whose recurrent product rides along, 37.0 / 37.8 / 37.2, 512x512 there no difference.
 __host__ __device__ inline int short_rows(int m, bool velo) { return m <= (velo ? 512 : 1024) ? 64 : 128; }
 constexpr int kStatStride = 20;   // floats per tile in the per-tile statistics partials (17 used)
-constexpr int kRcStride = 12;     // floats per block in the row/column partials (9 used)
+constexpr int kRcStride = 12;     // floats per entry of the row/column partials (9 used)
 constexpr int kNStat = 17;        // per-element statistics accumulated per tile
 constexpr int kStatsPerTensor = 32;
 constexpr int kLstmInPad = 48;    // LOPT_VELO_LSTM_IN rounded up to a multiple of 4
@@ -65,12 +65,12 @@ struct TensorDev {
   uint32_t ndim;
   int vec;                          // 0: rows are not 16-byte aligned, 1: they are (n % 4 == 0), 2: 128-byte aligned (n % 32 == 0)
   int TR, nrt, nct, tile0;          // tile height, tile grid, first global tile id
-  int rc0, nrblk, ncblk;            // first row/col block id, number of row and column blocks
+  int rc0, nrpart, ncpart;          // first row/col block id, number of row and column partials: one a block, short lists two
   uint64_t oRowPart;                // [nct][m]   sum over the tile's columns of g^2
   uint64_t oColPart;                // [nrt][n]   sum over the tile's rows of g^2 (short lists: [ceil(m / short_rows)][n], double)
   uint64_t oRR;                     // [3][padm]  rsqrt(r_k + eps_acc); short lists: then r_k [3][padm] as the step found them
   uint64_t oRC;                     // [3][padn]  rsqrt(c_k + eps_acc); short lists: then c_k [3][padn] as the step found them
-  uint64_t oRcPart;                 // [nrblk + ncblk][kRcStride]
+  uint64_t oRcPart;                 // [nrpart + ncpart][kRcStride]
   uint64_t oStatPart;               // [nrt*nct][kStatStride]
   uint64_t oStats;                  // [kStatsPerTensor] s_f
   uint64_t oScale;                  // [kStatsPerTensor] factor applied to the raw feature

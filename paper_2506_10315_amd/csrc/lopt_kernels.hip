@@ -516,7 +516,7 @@ __global__ void __launch_bounds__(kRcMaxThreads) k_rc_update(const TensorDev* __
       v[6 + k] = rr * rr;
     }
   }
-  const int slot = it.is_col ? T.nrblk + it.blk : it.blk;
+  const int slot = it.is_col ? T.nrpart + it.blk : it.blk;
   block_sum<9>(v, red, ws + T.oRcPart + (size_t)slot * kRcStride);
 }
 
@@ -559,6 +559,7 @@ __device__ __forceinline__ float new_factor(const StepArgs& A, int k, float old,
 
 union ShortLds {
   FuseLds means;
+  double rc[9][kBlock / kWave];
   struct { float hbar[1024 / kMixJSplit], red[kBlock / kWave][kWave]; } mix;   // a quarter of at most 1024 units
 };
 
@@ -593,16 +594,18 @@ __device__ __forceinline__ void fuse_means(const TensorDev& T, const TileDev& ti
   __syncthreads();
 }
 
-// 256 rows or columns of a tensor: what k_rc_update does on longer lists, from the partial sums of short ones.
+// 256 rows or columns of a tensor: what k_rc_update does on longer lists, from the partial sums of short ones. Their nine sums are
+// doubles, handed on as two floats: few blocks make up a tensor here, so that the rounding of each would be as large as that of the
+// statistic (256 rows in fp32 4.6e-8, 1000 rows 2.4e-8; partials of 8 rows each, which these blocks replace, 3.6e-9).
 __device__ __forceinline__ void short_rc_block(const TensorDev& T, const RcItemDev& it, float* __restrict__ ws, const StepArgs& A,
-                                               float (*red)[kRedStride]) {
+                                               double (*red)[kBlock / kWave]) {
   const int idx = it.blk * kBlock + (int)threadIdx.x, dim = it.is_col ? T.n : T.m;
   const size_t pd = it.is_col ? T.padn : T.padm;
   float* acc3 = T.st + 4 * (size_t)T.padN + (it.is_col ? 3 * (size_t)T.padm : 0) + idx;
   float* inv3 = ws + (it.is_col ? T.oRC : T.oRR) + idx;
-  float v[9];
+  double v[9];
 #pragma unroll
-  for (int q = 0; q < 9; ++q) v[q] = 0.f;
+  for (int q = 0; q < 9; ++q) v[q] = 0.0;
   if (idx < dim) {
     float old[3];
 #pragma unroll
@@ -615,11 +618,24 @@ __device__ __forceinline__ void short_rc_block(const TensorDev& T, const RcItemD
       acc3[(size_t)k * pd] = r;
       inv3[(size_t)k * pd] = rr;
       v[k] = r;   // (the columns' plain sum is not used)
-      v[3 + k] = r * r;
-      v[6 + k] = rr * rr;
+      v[3 + k] = (double)r * r;
+      v[6 + k] = (double)rr * rr;
     }
   }
-  block_sum<9>(v, red, ws + T.oRcPart + (size_t)((it.is_col ? T.nrblk : 0) + it.blk) * kRcStride);
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const double s = wave_sum(v[q]);
+    if (t % kWave == 0) red[q][t / kWave] = s;
+  }
+  __syncthreads();
+  if (t < 9) {
+    const double s = (red[t][0] + red[t][1]) + (red[t][2] + red[t][3]);
+    const float hi = (float)s, lo = isinf(hi) ? 0.f : (float)(s - (double)hi);   // beyond fp32 the sum is infinite, as on longer lists
+    float* part = ws + T.oRcPart + (size_t)((it.is_col ? T.nrpart : 0) + 2 * it.blk) * kRcStride + t;
+    part[0] = hi;
+    part[kRcStride] = lo;
+  }
 }
 
 // The per-element features that need a statistic of their own (the row/column-constant ones
@@ -830,7 +846,7 @@ __global__ void __launch_bounds__(kBlock, FUSE ? 1 : WRITE ? 7 : 8) k_accum_stat
     const int rc = rc_first ? idx : idx - n_tiles;
     if (rc >= 0 && rc < n_rcitems) {
       const RcItemDev it = rcitems[rc];
-      short_rc_block(tensors[it.tensor], it, ws, A, red);
+      short_rc_block(tensors[it.tensor], it, ws, A, sh.rc);
       return;
     }
     if (rc_first) idx -= n_rcitems;

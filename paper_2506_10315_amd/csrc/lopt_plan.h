@@ -283,8 +283,9 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
       for (int tj = 0; tj < T.nct; ++tj)
         for (int ti = t0; ti < t1; ++ti) pl->tiles.push_back(TileDev{(int)i, ti, tj, 0});
     }
-    T.nrblk = ceil_div(m, kBlock);
-    T.ncblk = ceil_div(nn, kBlock);
+    const int nrblk = ceil_div(m, kBlock), ncblk = ceil_div(nn, kBlock);
+    T.nrpart = pl->short_list ? 2 * nrblk : nrblk;   // short lists: two floats make a double (short_rc_block)
+    T.ncpart = pl->short_list ? 2 * ncblk : ncblk;
     T.rc0 = (int)pl->rcitems.size();
     const int nrc = ceil_div(m, short_rows(m, velo));
     if (pl->short_list) {
@@ -292,8 +293,8 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
         for (int tj = 0; tj < T.nct; ++tj) pl->rctiles.push_back(TileDev{(int)i, ti, tj, 0});
     }
     std::vector<RcItemDev>& rc = pl->short_list ? pl->rcshort : pl->rcitems;
-    for (int b = 0; b < T.nrblk; ++b) rc.push_back(RcItemDev{(int)i, 0, b, 0});
-    for (int b = 0; b < T.ncblk; ++b) rc.push_back(RcItemDev{(int)i, 1, b, 0});
+    for (int b = 0; b < nrblk; ++b) rc.push_back(RcItemDev{(int)i, 0, b, 0});
+    for (int b = 0; b < ncblk; ++b) rc.push_back(RcItemDev{(int)i, 1, b, 0});
     // apply tiles, for the kernels that read them: up to kApplyRows x kApplyCols, shorter for small lists like the statistics tiles
     pl->atile0[i] = (int)pl->atiles.size();
     pl->total_elems += N;
@@ -314,7 +315,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
     T.oColPart = take((uint64_t)(pl->short_list ? 2 * nrc : T.nrt) * nn);   // short lists: in double
     T.oRR = take((pl->short_list ? 6ull : 3ull) * T.padm);
     T.oRC = take((pl->short_list ? 6ull : 3ull) * T.padn);
-    T.oRcPart = take((uint64_t)(T.nrblk + T.ncblk) * kRcStride);
+    T.oRcPart = take((uint64_t)(T.nrpart + T.ncpart) * kRcStride);
     T.oStatPart = take((uint64_t)T.nrt * T.nct * kStatStride);
     T.oStats = take(kStatsPerTensor);
     T.oScale = take(kStatsPerTensor);
@@ -328,7 +329,7 @@ inline void build_plan(const PlanOptions& o, size_t n, const lopt_tensor_desc* d
   for (size_t i = 0; i < n && pl->short_list && o.apply == ApplyTiles::Strip; ++i) {
     const TensorDev& T = pl->tensors[i];
     const uint64_t at = (i + 1 < n ? pl->atile0[i + 1] : pl->atiles.size()) - pl->atile0[i];
-    again += at * ((uint64_t)T.nrt * T.nct * kStatStride + (uint64_t)(T.nrblk + T.ncblk) * kRcStride);
+    again += at * ((uint64_t)T.nrt * T.nct * kStatStride + (uint64_t)(T.nrpart + T.ncpart) * kRcStride);
   }
   pl->fold_finalize = pl->short_list && o.apply == ApplyTiles::Strip && pl->atiles.size() <= 2u * (unsigned)o.n_cu && again <= (16u << 20);
   // h W_h depends on nothing this step computes. Short lists of tensors form it beside the statistics (lstm_ahead); longer ones and

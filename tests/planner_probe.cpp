@@ -43,7 +43,7 @@ int main(int argc, char** argv) {
   for (size_t i = 0; i < d.size(); ++i) {
     const lopt::TensorDev& T = pl.tensors[i];
     printf("%s{\"TR\": %d, \"nrt\": %d, \"nct\": %d, \"nrblk\": %d, \"ncblk\": %d, \"state_bytes\": %zu, "
-           "\"regions\": [%llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu]}", i ? ", " : "", T.TR, T.nrt, T.nct, T.nrblk, T.ncblk,
+           "\"regions\": [%llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu, %llu]}", i ? ", " : "", T.TR, T.nrt, T.nct, T.nrpart, T.ncpart,
            pl.state_bytes[i], (unsigned long long)T.oRowPart, (unsigned long long)T.oColPart, (unsigned long long)T.oRR,
            (unsigned long long)T.oRC, (unsigned long long)T.oRcPart, (unsigned long long)T.oStatPart, (unsigned long long)T.oStats,
            (unsigned long long)T.oScale, (unsigned long long)T.oPrep);
