@@ -262,7 +262,7 @@ __device__ __forceinline__ void layer3_piece(const float4& w, const f32x16& h2a,
 
 // FIN: k_finalize has not run; every workgroup forms the scales of its tensor from the statistics pass's partials, and the first
 // layer from them: a launch and its chain of loads fewer (the planner's fold_finalize has the line and both sides).
-// NT: nontemporal loads (Launch::strip_ordinary).
+// NT: nontemporal loads (Launch::strip_ordinary; lists that fold the finalize always).
 template <bool RAW_RSQ, bool UPDATE_STATE, bool FIN, bool NT>
 __global__ void __launch_bounds__(kBlock, 2) k_apply_f16s(const TensorDev* __restrict__ tensors,
                                                           const ApplyTileDev* __restrict__ atiles, int n_atiles,

@@ -167,7 +167,10 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   // 823, 108 M of 6001 2554 / 1989; 4 M of 1000 103 / 99.5, 17 M of 2052 371 / 344, 128 M of 8004 2842 / 2270. On the grid it is the cache
   // that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 /
   // 322, ViT-B/16 shapes 1464 / 1482.
-  pl->strip_ordinary = 2 * off_line > total ? total < (7u << 20) || total >= (13u << 20) : total < (11u << 19);
+  // Lists that fold the finalize read nontemporally, the shorter of them either way to 5 %: 0.08 M elements in three tensors 17.0 / 16.6,
+  // two of 300x300 19.3 / 19.9, 512x512 20.3 / 21.3, 777x1200 32.9 / 34.6, 901x901 33.6 / 34.0, 1000x1000 34.6 / 35.6, 1100x1024 40.1 / 38.4,
+  // 1200x1200 43.6 / 44.6.
+  pl->strip_ordinary = !pl->fold_finalize && (2 * off_line > total ? total < (7u << 20) || total >= (13u << 20) : total < (11u << 19));
   // VeLO and the narrow widths: rows off the 16-byte grid, ordinary / nontemporal, VeLO 4.8 M elements of 1101 columns 81.5 / 87, 6 M of 1225
   // 101 / 100, 9 M 148.5 / 138, 12 M 189 / 174, 16 M 252 / 238, 20 M 303 / 296, 24 M 357 / 360, 54 M 779 / 821; width 16 4 M 91 / 100, 6 M
   // 136 / 144, 7.3 M 164.5 / 164, 9 M 195 / 192, 16 M 333 / 321, 20 M 396 / 403. (Rows on the 16-byte but off the 128-byte grid: VeLO 9 M

@@ -33,10 +33,12 @@ int main(int argc, char** argv) {
     if (runs.empty() || runs.back().first != t.rows) runs.push_back({t.rows, 0});
     runs.back().second++;
   }
-  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_rctiles\": %zu, \"n_atiles\": %zu, "
-         "\"short_list\": %d, \"groups\": %d, \"fold_finalize\": %d, \"lstm_ahead\": %d, \"keep\": %d, \"keep_off\": %d, \"backwards\": %d, \"atile_runs\": [",
-         (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.rctiles.size(),
-         pl.atiles.size(), pl.short_list, pl.groups, pl.fold_finalize, pl.oLstmZ != 0, pl.keep, pl.keep_off, pl.backwards);
+  printf("{\"ws_floats\": %llu, \"table_bytes\": %zu, \"n_tiles\": %zu, \"n_rcitems\": %zu, \"n_rcshort\": %zu, \"n_rctiles\": %zu, \"n_atiles\": %zu, "
+         "\"short_list\": %d, \"groups\": %d, \"fold_finalize\": %d, \"lstm_ahead\": %d, \"keep\": %d, \"keep_off\": %d, \"keep_line\": %d, \"backwards\": %d, "
+         "\"strip_ordinary\": %d, \"off_grid_nt\": %d, \"atile_runs\": [",
+         (unsigned long long)pl.ws_floats, lopt::table_bytes(pl), pl.tiles.size(), pl.rcitems.size(), pl.rcshort.size(), pl.rctiles.size(),
+         pl.atiles.size(), pl.short_list, pl.groups, pl.fold_finalize, pl.oLstmZ != 0, pl.keep, pl.keep_off, pl.keep_line, pl.backwards,
+         pl.strip_ordinary, pl.off_grid_nt);
   const char* sep = "";
   for (const auto& h : runs) { printf("%s[%d, %lld]", sep, h.first, h.second); sep = ", "; }
   printf("], \"tensors\": [");

@@ -121,6 +121,13 @@ def test_which_tiles_the_statistics_pass_leaves_in_the_cache(kind, hidden):
     assert r["short_list"] == 0 and r["backwards"] == velo and r["keep"] == (r["n_tiles"] * 10 // 64 if velo else 0)
 
 
+def test_lists_that_fold_the_finalize_have_one_kind_of_strip_load():
+    # their launch has no instantiation with ordinary loads: the plan says so
+    for shapes, folds in (([(256, 256), (256,), (64, 256)], 1), ([(1000, 1000)], 1), ([(1200, 1200)], 1), ([(1700, 1400)], 0)):
+        r = plan(shapes)
+        assert (r["fold_finalize"], r["strip_ordinary"]) == (folds, 1 - folds)
+
+
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_lists_of_many_tiles_of_few_rows_are_no_short_lists(kind):
     short = lambda shapes: plan(shapes, kind=kind)["short_list"]
