@@ -136,10 +136,10 @@ struct Launch {
   bool short_list;        // the statistics pass finishes the row and column means itself (Plan::short_list)
   int keep, keep_off;     // tiles below these numbers are read by the statistics pass with ordinary loads: rows on the 128-byte grid,
                           // rows off the 16-byte grid (Plan::keep)
-  bool keep_line;         // the same for all tiles of rows on the 16-byte but off the 128-byte grid
+  bool keep_line;         // short lists: rows on the 16-byte but off the 128-byte grid are read as rows off the 16-byte grid
   bool backwards;         // the statistics pass takes its tiles from the last to the first
-  bool strip_ordinary;    // the strip kernel reads with ordinary loads, the narrow and the VeLO kernel access rows off the 16-byte
-  bool off_grid_nt;       // grid nontemporally (Plan)
+  bool strip_ordinary;    // the strip kernel reads with ordinary loads (Plan; never where it folds the finalize)
+  bool off_grid_nt;       // the narrow and the VeLO kernel access rows off the 16-byte grid nontemporally (Plan)
 };
 
 // kernels (lopt_kernels.hip / lopt_apply_mfma.hip)

@@ -162,11 +162,19 @@ inline void choose_loads(const PlanOptions& o, uint64_t total, Plan* pl) {
   pl->keep_line = pl->short_list && (velo || (total >= (3u << 19) && total < (13u << 20)));
   pl->keep_off = velo && (!pl->short_list || total >= (13u << 20)) ? cached : all;
   // The apply pass. Width 32 reads 128 bytes of a row at a time; off the 128-byte grid these share their lines with the neighbours, which
-  // nontemporal loads fetch again. us a step, nontemporal / ordinary: 3.2 M elements of 901 columns 92 / 87, 6 M of 1225 144 / 141, 8.2 M of
-  // 1531 179.4 / 181.6, 9 M of 1501 191 / 191, 12 M of 1733 253 / 252, 20 M of 2237 409 / 402, 24 M of 2451 499 / 486, 44 M of 3301 1004 /
-  // 823, 108 M of 6001 2554 / 1989; 4 M of 1000 103 / 99.5, 17 M of 2052 371 / 344, 128 M of 8004 2842 / 2270. On the grid it is the cache
-  // that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 /
-  // 322, ViT-B/16 shapes 1464 / 1482.
+  // nontemporal loads fetch again: ordinary ones, except between 7 M and 13 M elements (M: 2^20). There the next step's statistics
+  // pass still finds in the 256 MB Infinity Cache what this pass has stored, as long as this pass's loads have not taken the room
+  // (nontemporal / ordinary, this pass and the statistics pass: 3701x3701, 13.1 M, 188 / 180 and 54 / 64 us; six of 1500x1500, 12.9 M, 186 /
+  // 181 and 57 / 65). Below, both fit; above, neither does (four of 2004x2004, 15.3 M, 258 / 209 and 64 / 65). us a step, nontemporal /
+  // ordinary, one to thirteen matrices of so many columns: below, 3.8 M of 1000 101 / 96.5, 4.3 M of 1500 114 / 105.5, 4.8 M of 1301 130.6 /
+  // 124.5, 5.7 M of 2001 149.6 / 146.7, 6.4 M of 1501 157 / 157; between, 6.7 M of 1000 162 / 163.5, 7.6 M 170.5 / 173, 8.6 M of 1500 and 1501
+  // 193 / 195 and 194.6 / 196, 8.9 M of 1531 200 / 200, 9.5 M of 2001 217.7 / 222, 10.3 M of 1801 238.6 / 245, 10.7 M of 1501 237.5 / 240, 11.4 M
+  // of 1000 249 / 259.5, 11.5 M of 2004 and 6001 252 / 262 and 254 / 254, 12.6 M of 2201 287 / 301, 12.9 M of 1301 296 / 295; above, 13.2 M of
+  // 2300 294 / 291 (but 13.4 M of 2801 295 / 311), 14.3 M of 1000 311 / 310, 15.3 M of 2001 and 2004 327.5 / 330 and 340 / 320.5, 17.2 M of 1501
+  // 376 / 369.5, 24 M of 2451 499 / 486, 44 M of 3301 1004 / 823, 108 M of 6001 2554 / 1989, 128 M of 8004 2842 / 2270. On the grid it is the cache
+  // alone that decides: 1.6 M of 640 46.1 / 45.5, 2.4 M of 768 67.8 / 65.5, 5.3 M of 1152 122 / 120, 6.6 M of 1280 143 / 148, 17 M of 2048 306 /
+  // 322, ViT-B/16 shapes 1464 / 1482. (All these rules count a list's elements of every kind, and a list is what its larger part is; they were
+  // measured on lists of one kind.)
   // Lists that fold the finalize read nontemporally, the shorter of them either way to 5 %: 0.08 M elements in three tensors 17.0 / 16.6,
   // two of 300x300 19.3 / 19.9, 512x512 20.3 / 21.3, 777x1200 32.9 / 34.6, 901x901 33.6 / 34.0, 1000x1000 34.6 / 35.6, 1100x1024 40.1 / 38.4,
   // 1200x1200 43.6 / 44.6.
