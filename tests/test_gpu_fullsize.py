@@ -182,8 +182,8 @@ def test_tallest_tensor_matches_its_periodic_base_pattern(capsys):
 
 @pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
 def test_maximum_size_tensor_with_unaligned_rows(kind, capsys):
-    # 32768 x 65535 = 2,147,450,880 elements, rows of 65535 floats (not a multiple of 4): the scalar-access
-    # instantiations of every pass at byte offsets beyond 2^32; base pattern 4 x 3
+    # 32768 x 65535 = 2,147,450,880 elements, rows of 65535 floats (not a multiple of 4): quads off the
+    # 16-byte grid in every pass, the last of a row a ragged one, at byte offsets beyond 2^32; base pattern 4 x 3
     _periodic_tensor_case(kind, 8192, 21845, _progress(capsys), "maximum size, unaligned rows", pr=4, pc=3)
 
 

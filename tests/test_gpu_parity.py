@@ -522,12 +522,43 @@ def test_narrow_rows_several_to_an_access(kind, state_pass, tall):
     assert worst["param"] <= Hn.TOL_PARAM
 
 
-@pytest.mark.parametrize("cols", [1, 9, 63, 65, 127, 129, 255, 257, 258, 259, 515])
-def test_velo_rows_off_the_grid_write_nothing_beside_the_tensor(cols):
+@pytest.mark.parametrize("tall", [[], [(6145, 2)]])
+@pytest.mark.parametrize("kind", ["small_fc_lopt", "velo"])
+def test_narrow_rows_over_several_trips(kind, tall):
+    # tiles of 64 rows: every wavefront of the statistics pass (8 times 64 / n rows a trip, all four together) and, from 21 columns on, of VeLO's apply pass
+    # (twice as many) makes more than one trip, the last tile of a tensor a ragged one. The columns of one element only make the list long enough
+    # for such tiles.
+    lstm = {} if kind == "small_fc_lopt" else dict(lstm_hidden=32, n_bank=8)
+    wide = [(777, 9), (775, 13), (773, 21), (771, 27), (769, 33), (770, 61), (771, 64), (773, 65), (775, 101)]
+    shapes = wide + [(6100, 1)] * 21 + tall
+    r = plan(shapes, kind=kind, **lstm)
+    assert r["short_list"] == (not tall)
+    for (m, n), t in zip(wide, r["tensors"]):
+        step = 8 * (64 // n if n <= 64 else 1) // (1 if n <= 64 else 2)
+        assert t["TR"] == 64 > step and m % 64 and (n < 21 or 64 > 2 * step)
+    cfg = Hn.make_cfg(kind, **lstm)
+    worst = Hn.run_free(Hn.Case(137, _specs(shapes), "gauss_logscale"), cfg, Hn.random_weights(cfg, seed=39), 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("hidden", [16, 32])
+def test_rows_on_the_16_byte_grid_read_with_ordinary_loads_by_the_statistics_of_short_lists(hidden):
+    # small_fc_lopt from 1.5 M elements on (VeLO at every size)
+    shapes = [(1301, 1300), (65, 260), (7,)]
+    assert plan(shapes, hidden=hidden)["keep_line"] == 1 and plan(shapes[1:], hidden=hidden)["keep_line"] == 0
+    cfg = Hn.make_cfg("small_fc_lopt", hidden=hidden)
+    worst = Hn.run_free(Hn.Case(138, _specs(shapes), "gauss_logscale"), cfg, Hn.random_weights(cfg, seed=40), 2, lr_fn=lambda t: 0.5, wd=0.01)
+    assert worst["param"] <= Hn.TOL_PARAM
+
+
+@pytest.mark.parametrize("rows,cols", [(13, n) for n in (1, 9, 63, 65, 127, 129, 255, 257, 258, 259, 515)] + [(2500, 2557)])
+def test_velo_rows_off_the_grid_write_nothing_beside_the_tensor(rows, cols):
     # parameters and gradients between guard values: the last access of a row ends with the row, that of a tensor with the tensor
     import torch
     import paper_2506_10315_amd as P
-    rows, cfg = 13, Hn.make_cfg("velo", lstm_hidden=32, n_bank=8)
+    # (the last list is long enough for nontemporal accesses)
+    cfg = Hn.make_cfg("velo", lstm_hidden=32, n_bank=8)
+    assert plan([(rows, cols)], kind="velo", lstm_hidden=32, n_bank=8)["off_grid_nt"] == (rows > 13)
     n = rows * cols
     gen = torch.Generator(device="cuda:0").manual_seed(cols)
     flat = torch.randn(n + 128, device="cuda:0", generator=gen) * 0.02
@@ -546,6 +577,8 @@ def test_rows_off_the_grid_with_either_kind_of_access_in_the_apply_pass(kind, hi
     # on, width 32 from 7 to 13 M); shorter ones, with ordinary accesses, are everywhere above
     cfg = Hn.make_cfg(kind, hidden=hidden) if kind == "small_fc_lopt" else Hn.make_cfg(kind, lstm_hidden=32, n_bank=8)
     shapes = [(2700, 2731), (65, 258), (7,)]
+    r = plan(shapes, kind=kind, hidden=hidden, lstm_hidden=32, n_bank=8)
+    assert r["strip_ordinary"] == 0 if hidden == 32 else r["off_grid_nt"] == 1
     worst = Hn.run_free(Hn.Case(135, _specs(shapes), "gauss_logscale"), cfg, Hn.random_weights(cfg, seed=35), 1, lr_fn=lambda t: 0.5, wd=0.01)
     assert worst["param"] <= Hn.TOL_PARAM
 

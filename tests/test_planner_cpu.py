@@ -88,7 +88,7 @@ def test_the_narrow_width_list_reaches_full_tiles_and_second_tiles_of_a_workgrou
 def test_the_unaligned_list_reaches_tiles_of_ordinary_height_and_every_number_of_segments():
     r = plan(UNALIGNED, kind="velo", lstm_hidden=32, n_bank=8)
     assert [t["TR"] for t in r["tensors"]] == [320, 64, 64, 64, 64, 64, 64, 320]
-    # 64-column segments of a tensor's last tile; the wavefronts that share one take 4 rows each, 16 or 8 a round
+    # 64-column segments of a tensor's last tile
     seg = {-(-(n - 256 * ((n - 1) // 256)) // 64) for _, n in UNALIGNED}
     assert seg == {1, 2, 3, 4} and all(m % 16 and n % 4 for m, n in UNALIGNED)
 
@@ -119,6 +119,41 @@ def test_which_tiles_the_statistics_pass_leaves_in_the_cache(kind, hidden):
     assert [plan([(1024, 1025)] * count, kind=kind, hidden=hidden)["backwards"] for count in (10, 11, 14)] == [0, 1, 1]
     r = plan([(1024, 1024)] * 64, kind=kind, hidden=hidden)
     assert r["short_list"] == 0 and r["backwards"] == velo and r["keep"] == (r["n_tiles"] * 10 // 64 if velo else 0)
+
+
+M = 1 << 20
+
+
+@pytest.mark.parametrize("kind,hidden", [("small_fc_lopt", 32), ("small_fc_lopt", 16), ("velo", 4)])
+@pytest.mark.parametrize("cols", [1024, 1000, 1025])
+def test_which_loads_the_passes_take_by_size(kind, hidden, cols):
+    # matrices, and a vector that brings the list to one element below each line or onto it. Strip kernel, off the 128-byte grid:
+    # ordinary loads but from 7 to 13 M, on it up to 5.5 M. Other apply kernels, rows off the 16-byte grid: nontemporal from 6 (7) to 21
+    # (18) M. Statistics of short lists, rows on the 16-byte but off the 128-byte grid: ordinary under VeLO and otherwise from 1.5 to 13 M.
+    velo = kind == "velo"
+    for line in (3 * M // 2, 11 * M // 2, 6 * M, 7 * M, 13 * M, 18 * M, 21 * M):
+        for above in (0, 1):
+            total = line - 1 + above
+            rows, rest = divmod(total, cols)
+            shapes = [s for s in [(1024, cols)] * (rows // 1024) + [(rows % 1024, cols), (1, rest)] if 0 not in s]
+            assert sum(a * b for a, b in shapes) == total
+            r = plan(shapes, kind=kind, hidden=hidden)
+            assert r["short_list"] == 1 and r["n_rcitems"] == 0 and r["n_rcshort"] > 0
+            assert r["keep_line"] == (velo or 3 * M // 2 <= total < 13 * M)
+            assert r["off_grid_nt"] == ((6 if velo else 7) * M <= total < (21 if velo else 18) * M)
+            if kind == "small_fc_lopt" and hidden == 32:
+                ordinary = total < 7 * M or total >= 13 * M if cols != 1024 else total < 11 * M // 2
+                assert r["strip_ordinary"] == (ordinary and not r["fold_finalize"])
+
+
+def test_loads_of_long_lists_and_of_mixed_ones():
+    big, odd = (8192, 8192), (8191, 6001)
+    for kind in ("small_fc_lopt", "velo"):
+        r = plan([big, odd], kind=kind)
+        assert (r["short_list"], r["keep_line"], r["off_grid_nt"]) == (0, 0, 0)
+        assert r["keep_off"] < r["n_tiles"] if kind == "velo" else r["keep_off"] == 2 ** 31 - 1
+    # the strip kernel's loads go by the larger part of the list
+    assert [plan(s)["strip_ordinary"] for s in ([big, odd], [big, odd, odd], [odd], [big])] == [0, 1, 1, 0]
 
 
 def test_lists_that_fold_the_finalize_have_one_kind_of_strip_load():
