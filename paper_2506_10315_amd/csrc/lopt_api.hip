@@ -285,7 +285,7 @@ StepFeats make_feats(int64_t step, float loss) {
   return f;
 }
 
-StepArgs make_args(const lopt_ctx* ctx, int64_t step, float lr, float wd, int n_tensors) {
+StepArgs make_args(const lopt_ctx* ctx, float lr, float wd, int n_tensors) {
   StepArgs A{};
   const lopt_config& c = ctx->cfg;
   for (int i = 0; i < 3; ++i) { A.mom_decay[i] = c.mom_decay[i]; A.fac_decay[i] = c.fac_decay[i]; }
@@ -293,11 +293,9 @@ StepArgs make_args(const lopt_ctx* ctx, int64_t step, float lr, float wd, int n_
   A.eps_acc = c.eps_acc; A.eps_norm = c.eps_norm;
   A.exp_mult = c.exp_mult; A.step_mult = c.step_mult;
   A.lr = lr; A.wd = wd;
-  A.step = (long long)step;
   A.kind = (int)c.kind; A.H = (int)c.hidden; A.HP = ctx->HP; A.F = ctx->F;
   A.HL = (int)c.lstm_hidden; A.K = (int)c.n_bank; A.P = ctx->P;
   A.n_tensors = n_tensors;
-  A.loss = ctx->loss;
   return A;
 }
 
@@ -569,7 +567,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   const TableStore& tb = ctx->heap;
   Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
            (int)ctx->plan.rc_blocks().size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false, false, false, false};
-  StepArgs A = make_args(ctx, 0, 0.f, 0.f, (int)n);
+  StepArgs A = make_args(ctx, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
   return LOPT_OK;
@@ -629,7 +627,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   // workspace base rounded up to 256 bytes (lopt_state_bytes adds the slack)
   float* ws = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   const bool profiling = ctx->profiling && !use_static;   // per-pass timing creates events: not on the static path
-  StepArgs A = make_args(ctx, step, lr, weight_decay, (int)n);
+  StepArgs A = make_args(ctx, lr, weight_decay, (int)n);
   float* lstm_z = pl.oLstmZ ? ws + pl.oLstmZ : nullptr;
   const bool mfma_ok = apply_mfma_available(A);
   // the strip-form kernel addresses a row pair with 32-bit byte offsets from the tile's first column: 4 (127 + cols)

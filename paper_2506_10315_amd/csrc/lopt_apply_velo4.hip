@@ -200,7 +200,6 @@ __device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const Til
   const int n = T.n;
   const NarrowWalk w(n, 4);
   const unsigned cc = (unsigned)min(w.col, n - 1);   // lanes without a column compute on the last one and store nothing
-  const unsigned lane_off = w.col_ok ? w.off : kNoColumn;
   const float* __restrict__ prep = ws + T.oPrep;
   const float* __restrict__ W2 = prep + (kVF + 1) * kVH;
   const float* __restrict__ B2 = W2 + kVH * kVH;
@@ -250,11 +249,11 @@ __device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const Til
     unsigned off[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      off[e] = w.col_ok ? lane_off + 4u * (unsigned)(e * w.rows * n) : kNoColumn;
-      e_in[e][0] = load_one<false>(T.g + ro, off[e], bytes);
-      e_in[e][1] = load_one<false>(T.p + ro, off[e], bytes);
+      off[e] = w.col_ok ? w.off + 4u * (unsigned)(e * w.rows * n) : kNoColumn;
+      e_in[e][0] = load_one(T.g + ro, off[e], bytes);
+      e_in[e][1] = load_one(T.p + ro, off[e], bytes);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) e_in[e][2 + k] = load_one<false>(T.st + k * pN + ro, off[e], bytes);
+      for (int k = 0; k < 4; ++k) e_in[e][2 + k] = load_one(T.st + k * pN + ro, off[e], bytes);
     }
     float x[4][kVE];
     f32x4 h[4];
@@ -285,10 +284,10 @@ __device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const Til
         q2 = __builtin_fmaf(bm2, q2, am2 * g);
         q3 = __builtin_fmaf(bm3, q3, am3 * g);
         v = __builtin_fmaf(bv, v, av * (g * g));
-        store_one<false>(T.st + ro, off[e], bytes, q1);
-        store_one<false>(T.st + pN + ro, off[e], bytes, q2);
-        store_one<false>(T.st + 2 * pN + ro, off[e], bytes, q3);
-        store_one<false>(T.st + 3 * pN + ro, off[e], bytes, v);
+        store_one(T.st + ro, off[e], bytes, q1);
+        store_one(T.st + pN + ro, off[e], bytes, q2);
+        store_one(T.st + 2 * pN + ro, off[e], bytes, q3);
+        store_one(T.st + 3 * pN + ro, off[e], bytes, v);
       }
       const float rs = RAW_RSQ ? __builtin_amdgcn_rsqf(v + eps) : rsqrtf(v + eps);
       const float f0 = rr[0] * rc[0], f1 = rr[1] * rc[1], f2 = rr[2] * rc[2];
@@ -324,7 +323,7 @@ __device__ __forceinline__ void apply_velo4_narrow(const TensorDev& T, const Til
     for (int e = 0; e < 4; ++e) {
       const float delta = o[e][0] * __expf(o[e][1] * A.exp_mult) * A.step_mult;
       const float p = e_in[e][1];
-      store_one<false>(T.p + ro, off[e], bytes, p - lr * (delta + wd * p));
+      store_one(T.p + ro, off[e], bytes, p - lr * (delta + wd * p));
     }
   }
 }

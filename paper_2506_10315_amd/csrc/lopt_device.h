@@ -68,13 +68,11 @@ template <bool NT>
 __device__ __forceinline__ f32x4v load_quad(const float* seg, unsigned off, unsigned bytes) {
   return __builtin_bit_cast(f32x4v, __builtin_amdgcn_raw_buffer_load_b128(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>));
 }
-template <bool NT>
 __device__ __forceinline__ float load_one(const float* seg, unsigned off, unsigned bytes) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>));
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<false>));
 }
-template <bool NT>
 __device__ __forceinline__ void store_one(float* seg, unsigned off, unsigned bytes, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<NT>);
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), segment_rsrc(seg, bytes), (int)off, 0, kBufferAux<false>);
 }
 template <bool NT>
 __device__ __forceinline__ void store_quad(float* seg, unsigned off, unsigned bytes, f32x4v v) {

@@ -55,8 +55,8 @@ struct FinLds {
 };
 
 // s_f and scale of feature f < 32 from the tensor's 32 sums. tot: 0..16 statistics; 17..19 sum r, 20..22 sum r^2, 23..25
-// sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps). One division for all features: a branch per kind of feature, each with a division
-// in double of its own, was a third of the kernel's time on a short list.
+// sum 1/(r+eps); 26..28 sum c^2, 29..31 sum 1/(c+eps). The kinds of feature differ in what they select, not in a branch: a branch per
+// kind, each with a division in double of its own, was a third of the kernel's time on a short list.
 __device__ __forceinline__ void feature_scale(const TensorDev& T, const StepArgs& A, const double* tot, int f, float& sf, float& scale) {
   const double m = (double)T.m, n = (double)T.n;
   const bool fac = (f >= 10 && f < 13) || (f >= 25 && f < 28), clip = f == 28;

@@ -89,11 +89,9 @@ struct StepArgs {
   float eps_acc, eps_norm;
   float exp_mult, step_mult;
   float lr, wd;
-  long long step;             // number of updates already applied (time features tanh(step/x))
   int kind, H, HP, F;         // F = number of normalized per-element features (28 or 29)
   int HL, K, P;               // VeLO: LSTM width, bank rows, floats per per-tensor MLP
   int n_tensors;
-  float loss;                 // VeLO: loss value that goes with this step's gradients
 };
 
 // Time features tanh(step / x) and VeLO's loss features tanh(psi / x), psi = sign(loss) ln(1 + |loss|), formed in double by the host: on the

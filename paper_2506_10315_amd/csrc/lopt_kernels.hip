@@ -770,7 +770,7 @@ __device__ __forceinline__ void accum_tile(const TensorDev& T, const TileDev& ti
 
 // Narrow tensors: one column a lane (NarrowWalk), the same sums. A row past the tile adds nothing: its values read as 0.
 constexpr int kNarrowTrip = 2;   // accesses in flight
-template <bool RAW_RSQ, bool WRITE, bool FUSE, bool NT>
+template <bool RAW_RSQ, bool WRITE, bool FUSE>
 __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& tile, float* __restrict__ ws, const StepArgs& A,
                                              float (&acc)[kNStat], FuseLds* L) {
   if (FUSE) fuse_means(T, tile, ws, A, *L);
@@ -792,10 +792,10 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
 #pragma unroll
     for (int e = 0; e < kNarrowTrip; ++e) {
       const unsigned off = w.off + 4u * (unsigned)(e * w.rows * n);
-      in[e][0] = load_one<NT>(T.g + ro, off, bytes);
-      in[e][1] = load_one<NT>(T.p + ro, off, bytes);
+      in[e][0] = load_one(T.g + ro, off, bytes);
+      in[e][1] = load_one(T.p + ro, off, bytes);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) in[e][2 + k] = load_one<NT>(T.st + k * pN + ro, off, bytes);
+      for (int k = 0; k < 4; ++k) in[e][2 + k] = load_one(T.st + k * pN + ro, off, bytes);
       const unsigned row = min(r + e * w.rows + w.sub, r1 - 1);
 #pragma unroll
       for (int k = 0; k < 3; ++k) rr[e][k] = FUSE ? L->rr[k][row - r0] : ws[T.oRR + (size_t)k * T.padm + row];
@@ -812,10 +812,10 @@ __device__ __forceinline__ void accum_narrow(const TensorDev& T, const TileDev& 
       add_squares(acc, g, g2, p, {nm1, nm2, nm3}, nv, rs, {rr[e][0] * rc[0], rr[e][1] * rc[1], rr[e][2] * rc[2]});
       if (WRITE) {
         const unsigned off = w.off + 4u * (unsigned)(e * w.rows * n);
-        store_one<false>(T.st + ro, off, bytes, nm1);
-        store_one<false>(T.st + pN + ro, off, bytes, nm2);
-        store_one<false>(T.st + 2 * pN + ro, off, bytes, nm3);
-        store_one<false>(T.st + 3 * pN + ro, off, bytes, nv);
+        store_one(T.st + ro, off, bytes, nm1);
+        store_one(T.st + pN + ro, off, bytes, nm2);
+        store_one(T.st + 2 * pN + ro, off, bytes, nm3);
+        store_one(T.st + 3 * pN + ro, off, bytes, nv);
       }
     }
   }
@@ -858,7 +858,7 @@ __global__ void __launch_bounds__(kBlock, FUSE ? 1 : WRITE ? 7 : 8) k_accum_stat
   float acc[kNStat];
 #pragma unroll
   for (int q = 0; q < kNStat; ++q) acc[q] = 0.f;
-  if (T.n <= kNarrowCols) accum_narrow<RAW_RSQ, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
+  if (T.n <= kNarrowCols) accum_narrow<RAW_RSQ, WRITE, FUSE>(T, tile, ws, A, acc, L);
   // (written so that it costs no register: one more and the pass no longer fits beside the apply kernel)
   else if (T.vec == 2 ? idx < keep : (T.vec == 0 || (FUSE && keep_line)) && idx < keep_off) accum_tile<RAW_RSQ, WRITE, FUSE, false>(T, tile, ws, A, acc, L);
   else accum_tile<RAW_RSQ, WRITE, FUSE, true>(T, tile, ws, A, acc, L);
