@@ -299,6 +299,26 @@ StepArgs make_args(const lopt_ctx* ctx, float lr, float wd, int n_tensors) {
   return A;
 }
 
+// The tables of the planned list and the plan's decisions. ws: null where no pass of the launch uses it.
+Launch make_launch(const lopt_ctx* ctx, const TableStore& tb, float* ws) {
+  const Plan& pl = ctx->plan;
+  Launch L{};
+  L.tensors = tb.d_tensors; L.n_tensors = (int)pl.tensors.size();
+  L.tiles = tb.d_tiles; L.n_tiles = (int)pl.tiles.size();
+  L.rcitems = tb.d_rcitems; L.n_rcitems = (int)pl.rc_blocks().size();
+  L.rctiles = tb.d_rctiles; L.n_rctiles = (int)pl.rctiles.size();
+  L.atiles = tb.d_atiles; L.n_atiles = (int)pl.atiles.size();
+  L.ws = ws;
+  L.apply_counter = ws ? (int*)(ws + pl.oCounters) : nullptr;
+  L.resident_wgs = 2 * ctx->n_cu;
+  L.short_list = pl.short_list;
+  L.keep = pl.keep; L.keep_off = pl.keep_off; L.keep_line = pl.keep_line;
+  L.backwards = pl.backwards;
+  L.strip_ordinary = pl.strip_ordinary;
+  L.off_grid_nt = pl.off_grid_nt;
+  return L;
+}
+
 }  // namespace
 
 extern "C" {
@@ -565,8 +585,7 @@ lopt_status lopt_init_state(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* des
   st = upload_tables(ctx, ctx->heap, stream);
   if (st != LOPT_OK) return st;
   const TableStore& tb = ctx->heap;
-  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, nullptr, (int)n, (int)ctx->plan.tiles.size(),
-           (int)ctx->plan.rc_blocks().size(), tb.d_atiles, (int)ctx->plan.atiles.size(), 0, nullptr, 0, 0, nullptr, 0, false, 0, 0, false, false, false, false};
+  const Launch L = make_launch(ctx, tb, nullptr);
   StepArgs A = make_args(ctx, 0.f, 0.f, (int)n);
   launch_fill_zero(L, A, stream);
   HIP_TRY(ctx, hipGetLastError());
@@ -638,9 +657,7 @@ static lopt_status step_impl(lopt_ctx* ctx, size_t n, const lopt_tensor_desc* de
   const bool rows_ok = pl.max_rows <= 0x7fffffff - 63;
   bool strip_ok = rows_ok && mfma_ok && (ctx->apply_variant == LOPT_APPLY_AUTO || ctx->apply_variant == LOPT_APPLY_MFMA_F16S);
   for (size_t i = 0; strip_ok && i < n; ++i) strip_ok = descs[i].rows == 1 || descs[i].cols <= (1 << 30) - 256;
-  Launch L{tb.d_tensors, tb.d_tiles, tb.d_rcitems, ws, (int)n, (int)pl.tiles.size(), (int)pl.rc_blocks().size(),
-           tb.d_atiles, (int)pl.atiles.size(), 0, (int*)(ws + pl.oCounters), 2 * ctx->n_cu, 0,
-           tb.d_rctiles, (int)pl.rctiles.size(), pl.short_list, pl.keep, pl.keep_off, pl.keep_line, pl.backwards, pl.strip_ordinary, pl.off_grid_nt};
+  const Launch L = make_launch(ctx, tb, ws);
   // With the default apply kernels the momentum / second-moment accumulators are written by the apply pass and the
   // statistics pass only reads them: 24 + 44 instead of 40 + 28 bytes per element (configuration field state_pass).
   // The read-only statistics stream runs at 83 % of the HBM rate against 67 % for the read-write one; the strip-form

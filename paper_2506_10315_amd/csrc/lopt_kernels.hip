@@ -452,6 +452,25 @@ __device__ __forceinline__ double strided_sum_coop(const float* __restrict__ par
 // more than 512 in all (decided by the shapes alone, so a given tensor list always takes the same path).
 __device__ __forceinline__ bool rc_sum_coop(int count, int valid) { return count > 512 && count >= 64 * valid; }
 
+__device__ __forceinline__ float new_factor(const StepArgs& A, int k, float old, float mean) {
+  return A.fac_decay[k] * old + (1.0f - A.fac_decay[k]) * mean;
+}
+
+// One row or column: writes its three accumulators and their reciprocal roots, and leaves the nine values that its block sums.
+template <typename V>
+__device__ __forceinline__ void finish_factors(const StepArgs& A, const float (&old)[3], float mean, float* acc3, float* inv3, size_t pd,
+                                               V (&v)[9]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float r = new_factor(A, k, old[k], mean), rr = rsqrtf(r + A.eps_acc);
+    acc3[(size_t)k * pd] = r;
+    inv3[(size_t)k * pd] = rr;
+    v[k] = r;   // (the columns' plain sum is not used)
+    v[3 + k] = (V)r * r;
+    v[6 + k] = (V)rr * rr;
+  }
+}
+
 // Workgroup = a block of 256 rows (or columns) of one tensor; the first 256 threads finish one row each. On short lists it
 // has 1024 threads, which sum each row's partials as four interleaved quarters that meet in LDS in a fixed order: the
 // kernel is a chain of load latencies (125 partials a column, 1000x1000: 7.2 -> 5.5 us with one batch of loads, not eight).
@@ -502,20 +521,7 @@ __global__ void __launch_bounds__(kRcMaxThreads) k_rc_update(const TensorDev* __
       if (quarter == 0) acc = (tree[i] + tree[kBlock + i]) + (tree[2 * kBlock + i] + tree[3 * kBlock + i]);
     }
   }
-  if (mine) {
-    const float mean = (float)(acc / (double)(it.is_col ? T.m : T.n));
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float b = A.fac_decay[k];
-      const float r = b * old[k] + (1.0f - b) * mean;
-      acc3[(size_t)k * pd] = r;
-      const float rr = rsqrtf(r + A.eps_acc);
-      inv3[(size_t)k * pd] = rr;
-      v[k] = r;   // (the columns' plain sum is not used)
-      v[3 + k] = r * r;
-      v[6 + k] = rr * rr;
-    }
-  }
+  if (mine) finish_factors(A, old, (float)(acc / (double)(it.is_col ? T.m : T.n)), acc3, inv3, pd, v);
   const int slot = it.is_col ? T.nrpart + it.blk : it.blk;
   block_sum<9>(v, red, ws + T.oRcPart + (size_t)slot * kRcStride);
 }
@@ -552,9 +558,6 @@ __device__ __forceinline__ double short_row_sum(const TensorDev& T, const float*
 __device__ __forceinline__ double short_col_sum(const TensorDev& T, const float* __restrict__ ws, const StepArgs& A, int c) {
   const int sr = short_rows(T.m, A.kind == LOPT_VELO);
   return strided_sum(short_colpart(T, ws) + c, (T.m + sr - 1) / sr, (size_t)T.n);
-}
-__device__ __forceinline__ float new_factor(const StepArgs& A, int k, float old, float mean) {
-  return A.fac_decay[k] * old + (1.0f - A.fac_decay[k]) * mean;
 }
 
 union ShortLds {
@@ -611,16 +614,7 @@ __device__ __forceinline__ void short_rc_block(const TensorDev& T, const RcItemD
 #pragma unroll
     for (int k = 0; k < 3; ++k) old[k] = acc3[(size_t)k * pd];
     const double sum = it.is_col ? short_col_sum(T, ws, A, idx) : short_row_sum(T, ws, idx);
-    const float mean = (float)(sum / (double)(it.is_col ? T.m : T.n));
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float r = new_factor(A, k, old[k], mean), rr = rsqrtf(r + A.eps_acc);
-      acc3[(size_t)k * pd] = r;
-      inv3[(size_t)k * pd] = rr;
-      v[k] = r;   // (the columns' plain sum is not used)
-      v[3 + k] = (double)r * r;
-      v[6 + k] = (double)rr * rr;
-    }
+    finish_factors(A, old, (float)(sum / (double)(it.is_col ? T.m : T.n)), acc3, inv3, pd, v);
   }
   const int t = threadIdx.x;
 #pragma unroll
