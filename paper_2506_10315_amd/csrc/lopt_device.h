@@ -122,18 +122,6 @@ __device__ __forceinline__ float4 load4(const float* __restrict__ row, int col, 
   return v;
 }
 
-template <bool VEC>
-__device__ __forceinline__ void store4(float* __restrict__ row, int col, int n, float4 v) {
-  if (VEC) {
-    if (col < n) *reinterpret_cast<float4*>(row + col) = v;
-    return;
-  }
-  if (col < n) row[col] = v.x;
-  if (col + 1 < n) row[col + 1] = v.y;
-  if (col + 2 < n) row[col + 2] = v.z;
-  if (col + 3 < n) row[col + 3] = v.w;
-}
-
 // The same for the big streamed arrays (g, p, M, V): every element is touched once per pass and the
 // working set is far larger than the caches, so the accesses are marked nontemporal (measured +5 % on a
 // 6-read/4-write stream).
